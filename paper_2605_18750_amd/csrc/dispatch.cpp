@@ -6,6 +6,7 @@ namespace rrfp {
 
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
   if (g.act != ACT_NONE) return gemm_act_supported(g) ? launch_gemm_mfma(g, s) : hipErrorInvalidValue;
+  if (g.in_dtype == F32 && g.out_dtype == F32) return launch_gemm_f32(g, s);
   return gemm_mfma_supports(g) ? launch_gemm_mfma(g, s) : launch_gemm_simt(g, s);
 }
 hipError_t launch_attn_fwd(const AttnArgs& a, hipStream_t s) {

@@ -1,0 +1,278 @@
+// fp32 GEMM on the fp32 matrix instruction v_mfma_f32_32x32x2_f32: C[M,N] = A(m,k) B(k,n) (+ bias) (+ R), the
+// GEMM of the fp32 path for every operand orientation, size and alignment.
+//
+// Why MFMA: without packed arithmetic the vector pipes reach half of the chip's fp32 rate (157 TFLOP/s), and an
+// fp32-FMA kernel needs an LDS read for every few FMAs; one 32x32x2 MFMA takes two registers and keeps the matrix
+// pipe busy for 64 cycles, so neither LDS nor issue slots limit anything here.  Products and sums stay fp32.
+//
+// Two kernels, chosen by the size of the output alone (see launch_gemm_f32):
+//   gemm_f32_tile_kernel   tiles of 64 x 64, eight wavefronts, 32-deep k steps through two LDS buffers (global loads two
+//     steps ahead, one barrier per step).  1024 x 1024 x 5504: 112 us = 103 TFLOP/s; the fp32-FMA kernel that was here
+//     before: 385 us on 517 rows of it, now 111.  (128 x 128 tiles: 5 % faster at 4096^3, two to four times slower on
+//     outputs of up to 1024 rows.)
+//   gemm_f32_small_kernel  tiles of 32 x 32 whose eight wavefronts split the contraction and read their
+//     fragments straight from global memory (L2): for outputs with too few tiles to fill the chip the time is the
+//     latency of the serial k loop, and this cuts the loop and takes the barriers out of it (128 x 256 x 688: 95 -> 8 us).
+//
+// The contraction index is free to be permuted as long as both operands agree: in a chunk of 8 k the half h of a
+// wavefront holds k = 4h + i for the i-th of four MFMAs, so a K-contiguous operand is read 16 bytes at a time.
+// Every output element is summed in one fixed order (k chunks ascending inside a wavefront, the ranges of
+// the wavefronts added in order), so a call always gives the same bits.
+#include <algorithm>
+
+#include "kernels.h"
+#include "numeric.h"
+
+namespace rrfp {
+namespace {
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4v __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
+
+// Four consecutive values at p[0..3], of which the first n (<= 0: none) exist.  VEC: they exist together and p is
+// 16-byte aligned.
+template <bool VEC>
+__device__ __forceinline__ f32x4v load4(const float* __restrict__ p, int n) {
+  f32x4v v = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (VEC) {
+    if (n > 0) v = *reinterpret_cast<const f32x4v*>(p);
+  } else {
+    if (n > 0) v.x = p[0];
+    if (n > 1) v.y = p[1];
+    if (n > 2) v.z = p[2];
+    if (n > 3) v.w = p[3];
+  }
+  return v;
+}
+
+constexpr int FK = 32;       // k per step of the tile kernel (64 measured the same at K >= 1024, 6 to 15 % slower in the weight-gradient form)
+constexpr int KC_PITCH = FK + 4;   // floats per row of a K-contiguous tile: 16 rows of a b128 read fall into 16 bank groups
+
+// One operand tile of ROWS rows x FK k, moved by NT threads.  KC: stored [rows][K] in memory and [rows][KC_PITCH] in LDS; else stored
+// [K][rows] and [FK][ROWS + 8] in LDS (the two halves of a wavefront read k rows 4 apart: 4 * pitch = 32 mod 64).
+template <bool KC, int ROWS, bool VEC, int NT>
+struct F32Tile {
+  static constexpr int N4 = ROWS * FK / 4 / NT;                // float4 per thread
+  static constexpr int KS_PITCH = ROWS + 8;
+  static constexpr int FLOATS = KC ? ROWS * KC_PITCH : FK * KS_PITCH;
+  __device__ static __forceinline__ void load(f32x4v (&r)[N4], const float* __restrict__ p, int ld, int row0, int n_rows, int k0, int K) {
+#pragma unroll
+    for (int i = 0; i < N4; ++i) {
+      const int q = i * NT + threadIdx.x;
+      if constexpr (KC) {
+        const int row = row0 + (q / (FK / 4)), k = k0 + (q % (FK / 4)) * 4;
+        r[i] = load4<VEC>(p + (size_t)row * ld + k, row < n_rows ? K - k : 0);
+      } else {
+        const int k = k0 + q / (ROWS / 4), row = row0 + (q % (ROWS / 4)) * 4;
+        r[i] = load4<VEC>(p + (size_t)k * ld + row, k < K ? n_rows - row : 0);
+      }
+    }
+  }
+  __device__ static __forceinline__ void store(const f32x4v (&r)[N4], float* lds) {
+#pragma unroll
+    for (int i = 0; i < N4; ++i) {
+      const int q = i * NT + threadIdx.x;
+      if constexpr (KC) *reinterpret_cast<f32x4v*>(lds + (q / (FK / 4)) * KC_PITCH + (q % (FK / 4)) * 4) = r[i];
+      else *reinterpret_cast<f32x4v*>(lds + (q / (ROWS / 4)) * KS_PITCH + (q % (ROWS / 4)) * 4) = r[i];
+    }
+  }
+  // Operand of the four MFMAs of k chunk s (8 k) for the 32 rows at row0: lane l has row l & 31, k = 8s + 4 (l >> 5) + i.
+  __device__ static __forceinline__ f32x4v frag(const float* lds, int row0, int s, int lane) {
+    const int row = row0 + (lane & 31), k = s * 8 + (lane >> 5) * 4;
+    if constexpr (KC) {
+      return *reinterpret_cast<const f32x4v*>(lds + row * KC_PITCH + k);
+    } else {
+      const float* p = lds + k * KS_PITCH + row;
+      return f32x4v{p[0], p[KS_PITCH], p[2 * KS_PITCH], p[3 * KS_PITCH]};
+    }
+  }
+};
+
+// Accumulator value r of a 32x32 block: row 8 (r / 4) + 4 (lane >> 5) + r % 4, column lane & 31: a store instruction
+// writes 128 contiguous bytes of two rows.
+__device__ __forceinline__ void put_f32(float v, float* __restrict__ C, const float* __restrict__ R, const float* __restrict__ bias,
+                                        int m, int n, int ldc, int ldr) {
+  if (bias) v += bias[n];
+  if (R) v += R[(size_t)m * ldr + n];
+  C[(size_t)m * ldc + n] = v;
+}
+
+// Tile of 64 x 64, eight wavefronts: two groups of 2 x 2 (32 x 32 of C each), each group contracting one half of every
+// step's k; the groups' sums are added at the end, group 0 first.  Eight instead of four wavefronts because a grid of
+// about one tile per CU would otherwise leave a single wavefront per SIMD to cover its own LDS reads and barriers.
+constexpr int KG = 2, TILE_THREADS = 256 * KG;
+template <bool TA, bool TB, bool VEC>
+__global__ __launch_bounds__(TILE_THREADS) void gemm_f32_tile_kernel(const float* __restrict__ A, const float* __restrict__ B,
+                                                                     float* __restrict__ C, const float* __restrict__ R,
+                                                                     const float* __restrict__ bias, int M, int N, int K, int lda, int ldb,
+                                                                     int ldc, int ldr) {
+  using TileA = F32Tile<!TA, 64, VEC, TILE_THREADS>;
+  using TileB = F32Tile<TB, 64, VEC, TILE_THREADS>;
+  constexpr int CHUNKS = FK / 8 / KG;                 // 8-deep k chunks of a step per wavefront
+  constexpr int BUF = TileA::FLOATS + TileB::FLOATS;
+  static_assert(2 * BUF >= 4 * 1024, "the second group's sums reuse the tile buffers");
+  __shared__ __attribute__((aligned(16))) float pool[2 * BUF];
+  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
+  const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) & 3, group = threadIdx.x >> 8;
+  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+  f32x16 acc;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+
+  // Global loads run two steps ahead of their use: step t + 2 is requested when step t starts and goes to LDS at the end
+  // of step t + 1.  One step ahead, a tile on every CU waited for memory a third of its time (N = M = K = 1024: 28 us
+  // with four wavefronts and one step ahead, 24 us this way = 89 TFLOP/s).
+  f32x4v ra[2][TileA::N4], rb[2][TileB::N4];
+  const int steps = (K + FK - 1) / FK;
+  auto fetch = [&](int set, int t) {
+    TileA::load(ra[set], A, lda, m0, M, t * FK, K);
+    TileB::load(rb[set], B, ldb, n0, N, t * FK, K);
+  };
+  auto put = [&](int set, int buf) {
+    TileA::store(ra[set], pool + buf * BUF);
+    TileB::store(rb[set], pool + buf * BUF + TileA::FLOATS);
+  };
+  auto step = [&](int t, int cur) {                  // cur = t & 1, a constant at every call
+    if (t + 2 < steps) fetch(cur, t + 2);
+#pragma unroll
+    for (int c8 = 0; c8 < CHUNKS; ++c8) {
+      const f32x4v fa = TileA::frag(pool + cur * BUF, wm, group * CHUNKS + c8, lane);
+      const f32x4v fb = TileB::frag(pool + cur * BUF + TileA::FLOATS, wn, group * CHUNKS + c8, lane);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc = mfma_f32(fa[c], fb[c], acc);
+    }
+    if (t + 1 < steps) put(cur ^ 1, cur ^ 1);
+    __syncthreads();
+  };
+  fetch(0, 0);
+  if (steps > 1) fetch(1, 1);
+  put(0, 0);
+  __syncthreads();
+  for (int t = 0; t < steps; t += 2) {
+    step(t, 0);
+    if (t + 1 < steps) step(t + 1, 1);
+  }
+  if (group > 0)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) pool[wave * 1024 + e * 64 + lane] = acc[e];
+  __syncthreads();
+  if (group > 0) return;
+  const int n = n0 + wn + (lane & 31);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int m = m0 + wm + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
+    if (m < M && n < N) put_f32(acc[r] + pool[wave * 1024 + r * 64 + lane], C, R, bias, m, n, ldc, ldr);
+  }
+}
+
+constexpr int SMALL_WAVES = 8, SMALL_CHUNKS = 4;     // k ranges of a tile, one per wavefront; chunks of 8 k in flight together
+
+// Fragment of 8 k at k0 for rows row0 .. row0+31 straight from memory (rows past the end repeat the last one: their
+// results are never stored; k past the end reads as zero).
+template <bool KC, bool VEC>
+__device__ __forceinline__ f32x4v small_frag(const float* __restrict__ p, int ld, int row, int k, int K) {
+  if constexpr (KC) return load4<VEC>(p + (size_t)row * ld + k, K - k);
+  f32x4v v;
+  v.x = k < K ? p[(size_t)k * ld + row] : 0.f;
+  v.y = k + 1 < K ? p[(size_t)(k + 1) * ld + row] : 0.f;
+  v.z = k + 2 < K ? p[(size_t)(k + 2) * ld + row] : 0.f;
+  v.w = k + 3 < K ? p[(size_t)(k + 3) * ld + row] : 0.f;
+  return v;
+}
+
+template <bool TA, bool TB, bool VEC>
+__global__ __launch_bounds__(64 * SMALL_WAVES) void gemm_f32_small_kernel(const float* __restrict__ A, const float* __restrict__ B,
+                                                                          float* __restrict__ C, const float* __restrict__ R,
+                                                                          const float* __restrict__ bias, int M, int N, int K, int lda,
+                                                                          int ldb, int ldc, int ldr) {
+  __shared__ float red[SMALL_WAVES][32 * 32];
+  const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int m = min(m0 + (lane & 31), M - 1), n = min(n0 + (lane & 31), N - 1);
+  const int chunks = (K + 7) / 8, per = (chunks + SMALL_WAVES - 1) / SMALL_WAVES;
+  const int k_end = min(K, (wave + 1) * per * 8);
+  f32x16 acc;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+  f32x4v fa[2][SMALL_CHUNKS], fb[2][SMALL_CHUNKS];
+  auto fetch = [&](f32x4v (&a)[SMALL_CHUNKS], f32x4v (&b)[SMALL_CHUNKS], int k0) {
+#pragma unroll
+    for (int c = 0; c < SMALL_CHUNKS; ++c) {
+      const int k = k0 + c * 8 + (lane >> 5) * 4;
+      a[c] = small_frag<!TA, VEC>(A, lda, m, k, k_end);
+      b[c] = small_frag<TB, VEC>(B, ldb, n, k, k_end);
+    }
+  };
+  auto multiply = [&](const f32x4v (&a)[SMALL_CHUNKS], const f32x4v (&b)[SMALL_CHUNKS]) {
+#pragma unroll
+    for (int c = 0; c < SMALL_CHUNKS; ++c) {
+      acc = mfma_f32(a[c].x, b[c].x, acc);
+      acc = mfma_f32(a[c].y, b[c].y, acc);
+      acc = mfma_f32(a[c].z, b[c].z, acc);
+      acc = mfma_f32(a[c].w, b[c].w, acc);
+    }
+  };
+  constexpr int KB = SMALL_CHUNKS * 8;
+  int k0 = wave * per * 8;
+  if (k0 < k_end) {
+    fetch(fa[0], fb[0], k0);
+    for (; k0 < k_end; k0 += 2 * KB) {
+      if (k0 + KB < k_end) fetch(fa[1], fb[1], k0 + KB);
+      multiply(fa[0], fb[0]);
+      if (k0 + KB < k_end) {
+        if (k0 + 2 * KB < k_end) fetch(fa[0], fb[0], k0 + 2 * KB);
+        multiply(fa[1], fb[1]);
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) red[wave][((r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) * 32 + (lane & 31)] = acc[r];
+  __syncthreads();
+  for (int q = threadIdx.x; q < 32 * 32; q += 64 * SMALL_WAVES) {
+    float v = red[0][q];
+#pragma unroll
+    for (int w = 1; w < SMALL_WAVES; ++w) v += red[w][q];
+    const int mo = m0 + (q >> 5), no = n0 + (q & 31);
+    if (mo < M && no < N) put_f32(v, C, R, bias, mo, no, ldc, ldr);
+  }
+}
+
+// Which kernel: fewer than 128 tiles of 64 x 64 leave over half of the chip idle, and the small kernel's 32 x 32 tiles
+// then win (128 x 256 x 1376: 15 against 30 us; at 144 tiles, 517 x 1024 x 1024, it is 29 against 24 us).
+// Sixteen k ranges instead of eight change nothing: the operand rows then bound it through the L1.
+template <bool TA, bool TB, bool VEC>
+hipError_t launch_f32(const GemmArgs& g, hipStream_t s) {
+  const float *A = (const float*)g.A, *B = (const float*)g.B, *bias = (const float*)g.bias;
+  float* C = (float*)g.C;
+  const bool small = (long long)((g.M + 63) / 64) * ((g.N + 63) / 64) < 128;
+  const int t = small ? 32 : 64;
+  const dim3 grid((g.N + t - 1) / t, (g.M + t - 1) / t);
+#define RRFP_GO(KERNEL, THREADS) \
+  hipLaunchKernelGGL((KERNEL), grid, dim3(THREADS), 0, s, A, B, C, g.R, bias, g.M, g.N, g.K, g.lda, g.ldb, g.ldc, g.ldr)
+  if (!small) RRFP_GO((gemm_f32_tile_kernel<TA, TB, VEC>), TILE_THREADS);
+  else RRFP_GO((gemm_f32_small_kernel<TA, TB, VEC>), 64 * SMALL_WAVES);
+#undef RRFP_GO
+  return hipGetLastError();
+}
+
+template <bool TA, bool TB>
+hipError_t launch_f32_aligned(const GemmArgs& g, hipStream_t s) {
+  // 16-byte loads need aligned rows and a contiguous extent of whole float4s (M or N when K-strided, K when K-contiguous)
+  const bool vec = !((g.lda | g.ldb) & 3) && !((uintptr_t)g.A & 15) && !((uintptr_t)g.B & 15) && !((TA ? g.M : g.K) & 3) &&
+                   !((TB ? g.K : g.N) & 3);
+  return vec ? launch_f32<TA, TB, true>(g, s) : launch_f32<TA, TB, false>(g, s);
+}
+
+}  // namespace
+
+hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t s) {
+  if (g.M <= 0 || g.N <= 0 || g.K <= 0 || g.in_dtype != F32 || g.out_dtype != F32) return hipErrorInvalidValue;
+  if (!g.transA && !g.transB) return launch_f32_aligned<false, false>(g, s);
+  if (!g.transA) return launch_f32_aligned<false, true>(g, s);
+  if (!g.transB) return launch_f32_aligned<true, false>(g, s);
+  return launch_f32_aligned<true, true>(g, s);
+}
+
+}  // namespace rrfp

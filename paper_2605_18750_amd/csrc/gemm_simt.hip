@@ -1,5 +1,5 @@
-// Plain LDS-tiled fp32-FMA GEMM for any shape, stride and operand orientation.  It is the
-// GEMM of the fp32 path and of bf16 shapes the MFMA kernels do not take.  The k loop runs
+// Plain LDS-tiled fp32-FMA GEMM for any shape, type, stride and operand orientation.  It is the
+// GEMM of bf16 shapes the MFMA kernels do not take and the one an explicit RRFP_GEMM_SIMT asks for.  The k loop runs
 // in ascending order in one thread per output element: one fixed summation order.
 #include "kernels.h"
 #include "numeric.h"

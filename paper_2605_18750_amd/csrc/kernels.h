@@ -52,7 +52,8 @@ struct GemmArgs {
 };
 bool gemm_act_supported(const GemmArgs& g);   // true if launch_gemm can run g.act fused for this shape
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);       // picks the kernel family
-hipError_t launch_gemm_simt(const GemmArgs& g, hipStream_t s);  // fp32-FMA tiles, any shape
+hipError_t launch_gemm_simt(const GemmArgs& g, hipStream_t s);  // fp32-FMA tiles, any shape and type
+hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t s);   // fp32 MFMA tiles, any fp32 shape
 hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s);  // bf16 MFMA kernels (256-wide tiles)
 bool gemm_mfma_supports(const GemmArgs& g);                     // alignment / divisibility rules
 // Launch plan of launch_gemm_mfma for a shape (pure host logic): kernel 0 = refused, 1 = direct-to-LDS,

@@ -1,0 +1,41 @@
+"""The fp32 matrix-instruction kernels at the edges of their tiles, against fp64 definitions."""
+import numpy as np
+import pytest
+
+import stage_inputs as SI
+from tests import helpers as Hp
+
+pytestmark = pytest.mark.gpu
+
+# (M, N, K): one element; one short of, at and past a 32- and a 64-tile; K below, at and past a chunk of 8 and a step of
+# 32; outputs of 127 and 128+ tiles of 64 x 64 (the last size of the small kernel, the first of the tile kernel)
+GEMM_SHAPES = [(1, 1, 1), (31, 33, 7), (32, 64, 8), (63, 65, 33), (70, 45, 31), (8 * 64 + 1, 14 * 64, 40), (8 * 64, 15 * 64 + 63, 9),
+               (8 * 64, 16 * 64, 32), (8 * 64 + 7, 16 * 64 + 3, 70), (1025, 516, 129)]
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("pad", [0, 3])
+def test_f32_gemm_tile_edges(ta, tb, pad):
+    """pad = 3: leading dimensions and start addresses that no 16-byte load could take.  Bound per element: K products and
+    K sums, each within 2^-24 of its exact value."""
+    import torch
+    import paper_2605_18750_amd as R
+    from paper_2605_18750_amd import harness as Hn
+    for M, N, K in GEMM_SHAPES:
+        print(f"[f32 gemm] M{M} N{N} K{K} ta{ta} tb{tb} pad{pad}", flush=True)
+        shp = [(K, M) if ta else (M, K), (N, K) if tb else (K, N), (M, N)]
+        A, B, Rr = [SI.make_tensor(7, f"f32{M}.{N}.{K}{n}", s, 1.0, "fp32") for n, s in zip("ABR", shp)]
+        ref = (A.f64.T if ta else A.f64) @ (B.f64.T if tb else B.f64) + Rr.f64
+        mag = np.abs(A.f64.T if ta else A.f64) @ np.abs(B.f64.T if tb else B.f64) + np.abs(Rr.f64)
+        dev = []
+        for t, s in zip((A, B, Rr), shp):
+            buf = torch.full((s[0] * (s[1] + pad) + pad,), float("nan"), dtype=torch.float32, device="cuda:0")
+            v = buf[pad:].view(s[0], s[1] + pad)[:, :s[1]]
+            v.copy_(Hn.to_device(t.storage, "fp32"))
+            dev.append(v)
+        C = torch.full((M, N + pad), float("nan"), dtype=torch.float32, device="cuda:0")
+        R.rrfp_gemm(dev[0], dev[1], C, dev[2], M, N, K, shp[0][1] + pad, shp[1][1] + pad, N + pad, N + pad, ta, tb, 0, 0)
+        torch.cuda.synchronize()
+        got = C.cpu().to(torch.float64).numpy()
+        assert np.isnan(got[:, N:]).all(), "columns past N written"
+        assert (np.abs(got[:, :N] - ref) <= (2 * K + 2) * 2.0 ** -24 * mag).all(), (M, N, K)
