@@ -88,8 +88,9 @@ struct AttnArgs {
   void* ds;                 // MFMA path: scratch of attn_ds_bytes(...) bytes.  The dK/dV kernel leaves dS there (IEEE halves,
                             // one 4 KB block per 32 keys x 64 queries of a head) and the dQ kernel contracts it with K
   int ds_rows, ds_nqs;      // its shape: 32-key block rows per head, 64-query steps per block row
-  float* dkv_part;          // MFMA path with grouped query heads (nq > nkv): attn_dkv_part_bytes(...) bytes for the partial dK / dV
-                            // planes of the head subsets (see attn_dkv_subsets); null = one workgroup walks the whole group
+  float* dkv_part;          // grouped query heads (nq > nkv): attn_dkv_part_bytes(...) bytes for the partial dK / dV planes of the
+                            // head subsets (see attn_dkv_subsets; fp32: of every query head); MFMA path: null = one workgroup
+                            // walks the whole group
 };
 // Shape of the dS scratch for up to T tokens in up to n_seg segments, and its size for nq query heads.
 inline int attn_ds_rows(int T, int n_seg) { return (T + 31) / 32 + n_seg; }
@@ -111,15 +112,16 @@ inline int attn_dkv_subsets(int nq, int nkv, int n_kv_tiles, int n_cu) {
   }
   return best;
 }
-// Bytes of AttnArgs::dkv_part for up to T tokens: room for the most subsets the rule above can pick; 0 without grouped heads.
-inline size_t attn_dkv_part_bytes(int T, int nq, int nkv, int d) {
+// Bytes of AttnArgs::dkv_part for up to T tokens: room for the most subsets the rule above can pick (fp32: one plane per query
+// head of a group); 0 without grouped heads.
+inline size_t attn_dkv_part_bytes(int T, int nq, int nkv, int d, int dtype) {
   if (nq == nkv) return 0;
-  return (size_t)2 * attn_dkv_subsets(nq, nkv, 1, 1 << 30) * T * nkv * d * 4;
+  return (size_t)2 * (dtype == F32 ? nq / nkv : attn_dkv_subsets(nq, nkv, 1, 1 << 30)) * T * nkv * d * 4;
 }
 hipError_t launch_attn_fwd(const AttnArgs& a, hipStream_t s);
 hipError_t launch_attn_bwd(const AttnArgs& a, hipStream_t s);
-hipError_t launch_attn_fwd_simt(const AttnArgs& a, hipStream_t s);
-hipError_t launch_attn_bwd_simt(const AttnArgs& a, hipStream_t s);
+hipError_t launch_attn_fwd_f32(const AttnArgs& a, hipStream_t s);
+hipError_t launch_attn_bwd_f32(const AttnArgs& a, hipStream_t s);
 hipError_t launch_attn_fwd_mfma(const AttnArgs& a, hipStream_t s);
 hipError_t launch_attn_bwd_mfma(const AttnArgs& a, hipStream_t s);
 bool attn_mfma_supports(const AttnArgs& a);

@@ -172,8 +172,8 @@ int make_plan(const stage_config* c, Plan* p) {
     p->ds_rows = attn_ds_rows((int)T, c->max_segments);
     p->ds_nqs = attn_ds_nqs((int)T);
     p->t_ds = attn_mfma_supports(probe) ? take(attn_ds_bytes((int)T, c->max_segments, (int)nq)) : 0;
-    const size_t part = attn_dkv_part_bytes((int)T, (int)nq, (int)nkv, (int)d);
-    p->t_dkvp = (attn_mfma_supports(probe) && part) ? take(part) : 0;
+    const size_t part = attn_dkv_part_bytes((int)T, (int)nq, (int)nkv, (int)d, c->dtype);
+    p->t_dkvp = part ? take(part) : 0;
   }
   p->mb_bytes = o;
   p->slots_off = p->mb_bytes * (size_t)c->n_microbatches;

@@ -39,3 +39,16 @@ def test_f32_gemm_tile_edges(ta, tb, pad):
         got = C.cpu().to(torch.float64).numpy()
         assert np.isnan(got[:, N:]).all(), "columns past N written"
         assert (np.abs(got[:, :N] - ref) <= (2 * K + 2) * 2.0 ** -24 * mag).all(), (M, N, K)
+
+
+@pytest.mark.parametrize("d,causal,nq,nkv", [(16, True, 4, 2), (32, False, 2, 2), (48, True, 3, 1), (64, True, 2, 2), (80, False, 4, 1),
+                                             (96, True, 2, 1), (112, False, 2, 2), (128, True, 2, 1)])
+def test_f32_attention_tile_edges(d, causal, nq, nkv):
+    """Every head dimension, with and without grouped heads; segments around the 16 rows of a wavefront, the 32 of a step,
+    the 64 of a workgroup and the 128 / 256 of the host's tiles."""
+    shape = SI.StageShape(f"f32attn{d}", 1, 32, nq, nkv, d, 32, 2, dtype="fp32", x_std=1.0, dy_std=1.0, w_std=0.15, causal=causal)
+    lengths = [[1, 15, 16, 17, 31, 32, 33, 63, 64, 65], [127, 129, 257]]
+    w = Hp.Workload(shape, [[0] + [int(v) for v in np.cumsum(n)] for n in lengths])
+    print(f"[f32 attention] d{d} causal{causal} heads {nq}/{nkv}", flush=True)
+    worst = Hp.compare(Hp.run_gpu(w), Hp.run_oracle(w), Hp.TOL["fp32"], f"d{d}")
+    print(f"[f32 attention] d{d}: worst {worst:.2e}", flush=True)
