@@ -941,10 +941,145 @@ inline int splitk_factor(int t, int K, int n_cu) {
   return std::max(1, std::min(std::min(n_cu / t, steps / 16), 16));
 }
 
-// Launch of the direct-to-LDS kernel for the forms with A K-contiguous, per the cut above.
+// Finish of a split-K launch of a form with A K-contiguous: adds the S partial planes [M, N] in range order and applies what
+// the unsplit kernel's epilogue applies (bias, activation or residual, scale, rounding), on the same fp32 values.  A
+// thread owns 8 columns (of SwiGLU forward: 8 features, gate and up).
+template <typename TO, bool HAS_R, int ACT>
+__global__ __launch_bounds__(256) void splitk_finish_kernel(const float* __restrict__ ws, int S, int M, int N, TO* __restrict__ C, int ldc,
+                                                            const float* __restrict__ R, int ldr, bf16_t* __restrict__ E, int lde,
+                                                            const bf16_t* __restrict__ bias, const float* __restrict__ out_scale) {
+  const int width = ACT == ACT_SWIGLU_FWD ? N >> 1 : N, w8 = width >> 3;
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= (size_t)M * w8) return;
+  const int m = (int)(i / w8), n = (int)(i - (size_t)m * w8) * 8;
+  const size_t plane = (size_t)M * N;
+  const float* row = ws + (size_t)m * N + n;
+  auto sum_planes = [&](const float* p, float (&v)[8]) {
+    load_f32x8(p, v);
+#pragma unroll 4
+    for (int y = 1; y < S; ++y) {
+      float t[8];
+      load_f32x8(p + y * plane, t);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] += t[e];
+    }
+  };
+  auto add_bias = [&](int at, float (&v)[8]) {
+    if (!bias) return;
+    float b[8];
+    load_vec<bf16_t>(bias + at, b);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] += b[e];
+  };
+  float v[8];
+  sum_planes(row, v);
+  add_bias(n, v);
+  if constexpr (HAS_R) {
+    float r[8];
+    load_f32x8(R + (size_t)m * ldr + n, r);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] += r[e];
+  }
+  if constexpr (ACT == ACT_SWIGLU_FWD) {
+    float up[8], mm[8];
+    sum_planes(row + width, up);
+    add_bias(width + n, up);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) mm[e] = v[e] * sigmoid_f(v[e]) * up[e];
+    bf16_t* crow = (bf16_t*)C + (size_t)m * ldc + n;
+    store_vec<bf16_t>(crow, v);
+    store_vec<bf16_t>(crow + width, up);
+    store_vec<bf16_t>(E + (size_t)m * lde + n, mm);
+  } else if constexpr (ACT == ACT_GELU_FWD) {
+    float mm[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) mm[e] = gelu_f(v[e]);
+    store_vec<bf16_t>((bf16_t*)C + (size_t)m * ldc + n, v);
+    store_vec<bf16_t>(E + (size_t)m * lde + n, mm);
+  } else if constexpr (ACT == ACT_GELU_BWD) {
+    float u[8];
+    load_vec<bf16_t>(E + (size_t)m * lde + n, u);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] *= gelu_grad_f(u[e]);
+    store_vec<bf16_t>((bf16_t*)C + (size_t)m * ldc + n, v);
+  } else if constexpr (ACT == ACT_SWIGLU_BWD) {
+    float gt[8], up[8], dg[8], du[8];
+    load_vec<bf16_t>(E + (size_t)m * lde + n, gt);
+    load_vec<bf16_t>(E + (size_t)m * lde + N + n, up);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float sg = sigmoid_f(gt[e]);
+      dg[e] = v[e] * up[e] * sg * (1.0f + gt[e] * (1.0f - sg));
+      du[e] = v[e] * gt[e] * sg;
+    }
+    store_vec<bf16_t>((bf16_t*)C + (size_t)m * ldc + n, dg);
+    store_vec<bf16_t>((bf16_t*)C + (size_t)m * ldc + N + n, du);
+  } else {
+    if constexpr (!HAS_R && sizeof(TO) == 2) {
+      const float sc = out_scale ? *out_scale : 1.0f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] *= sc;
+    }
+    store_vec<TO>(C + (size_t)m * ldc + n, v);
+    if constexpr (sizeof(TO) == 4) store_vec<TO>(C + (size_t)m * ldc + n + 4, v + 4);
+  }
+}
+
+// Cut along K of a form with A K-contiguous: ranges > 1 means tiles of tile_rows x 256, each contracted in `ranges` pieces whose
+// fp32 planes go to the scratch and are added by splitk_finish_kernel; ranges == 1 the launches of full_tile_columns.
+// A pure function of the shape, the device and the scratch.
+//
+// A workgroup takes 0.75 us per 32-deep step with 256-row tiles and 0.55 us with 128-row ones, whether it shares the chip
+// with 31 or 255 others (operands from HBM), so a grid of t tiles leaves the rest of the chip idle for K / 32 of those
+// steps.  The rule compares rounds x steps x that time, plus, for a split, the planes' write and read at 8 TB/s (they mostly stay in the
+// caches) and 4 us for the finishing launch.  Measured (us, unsplit -> split): 512 x 4096 x 22016 366 -> 103 (8 ranges), x 4096 68 -> 35
+// (128 rows, 4), 1093 x 4096 x 22016 374 -> 178 (3), 2048 x 4096 x 22016 383 -> 303 (2), 6272 x 1280 x 5120 94 -> 86 (2),
+// 512 x 12288 x 4096 74 -> 60 (2);
+// 2048 x 4096 x 4096 would go 70 -> 78 and stays unsplit.
+struct KSplit { int tile_rows, ranges; };
+inline KSplit a_kc_split(int M, int N, int K, int n_cu, size_t ws_bytes) {
+  constexpr float US_256 = 0.75f, US_128 = 0.55f, FINISH_US = 4.0f, PLANE_BYTES_PER_US = 8.0e6f;
+  constexpr int MAX_RANGES = 12, MIN_STEPS = 8;
+  const int steps = (K + DBK - 1) / DBK;
+  const long long tn = (N + BN - 1) / BN, t256 = (M + 255) / 256 * tn, t128 = (M + 127) / 128 * tn;
+  auto rounds = [&](long long wgs) { return (float)((wgs + n_cu - 1) / n_cu); };
+  KSplit best{256, 1};
+  if (steps < 2 * MIN_STEPS || ws_bytes == 0 || t256 > n_cu) return best;   // several rounds of full tiles: nothing is idle for long
+  float cost = (2 * t256 <= n_cu ? rounds(t128) * US_128 : US_256) * steps;
+  const float mn = (float)M * (float)N;
+  for (int S = 2; S <= MAX_RANGES && steps / S >= MIN_STEPS; ++S) {
+    const int per = (steps + S - 1) / S, s_eff = (steps + per - 1) / per;
+    if (s_eff != S) continue;
+    if ((size_t)S * M * N * 4 > ws_bytes) break;
+    const float finish = FINISH_US + mn * (8 * S + 6) / PLANE_BYTES_PER_US;
+    const float c256 = rounds(t256 * S) * per * US_256 + finish, c128 = rounds(t128 * S) * per * US_128 + finish;
+    if (c256 < cost) { cost = c256; best = KSplit{256, S}; }
+    if (c128 < cost) { cost = c128; best = KSplit{128, S}; }
+  }
+  return best;
+}
+
+// Launch of the direct-to-LDS kernel for the forms with A K-contiguous, per the cuts above.
 template <bool B_KC, typename TO, bool HAS_R, int ACT, bool F16IN = false>
 hipError_t launch_a_kc(const GemmArgs& g, hipStream_t s) {
   constexpr int WMv = dl_wm(true, B_KC), WNv = dl_wn(true, B_KC);
+  const KSplit ks = a_kc_split(g.M, g.N, g.K, cu_count(), g.ws && !((uintptr_t)g.ws & 15) ? g.ws_bytes : 0);
+  if (ks.ranges > 1) {
+    const int steps = (g.K + DBK - 1) / DBK, k_split = (steps + ks.ranges - 1) / ks.ranges * DBK, S = (g.K + k_split - 1) / k_split;
+    const int tm = (g.M + ks.tile_rows - 1) / ks.tile_rows, tn = (g.N + BN - 1) / BN;
+    auto planes = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(tm * tn, S), dim3(WMv * WNv * 64), 0, s, (const bf16_t*)g.A, (const bf16_t*)g.B, (float*)g.ws,
+                         (const float*)nullptr, g.M, g.N, g.K, g.lda, g.ldb, g.N, 0, tm, tn, (bf16_t*)nullptr, 0, 0, k_split,
+                         (const bf16_t*)nullptr, (const float*)nullptr);
+    };
+    if (ks.tile_rows == 256) planes(gemm_mfma_dl_kernel<true, B_KC, float, false, WMv, WNv, ACT_NONE, 256, F16IN>);
+    else planes(gemm_mfma_dl_kernel<true, B_KC, float, false, WMv, WNv, ACT_NONE, 128, F16IN>);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    const size_t threads = (size_t)g.M * ((ACT == ACT_SWIGLU_FWD ? g.N / 2 : g.N) / 8);
+    hipLaunchKernelGGL((splitk_finish_kernel<TO, HAS_R, ACT>), dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, (const float*)g.ws,
+                       S, g.M, g.N, (TO*)g.C, g.ldc, g.R, g.ldr, (bf16_t*)g.E, g.lde, (const bf16_t*)g.bias, g.out_scale);
+    return hipGetLastError();
+  }
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
   const int cn = full_tile_columns(tiles_m, tiles_n, cu_count());
   if (cn > 0)
@@ -1061,6 +1196,14 @@ GemmPlan gemm_mfma_plan(const GemmArgs& g, int n_cu, bool have_scratch) {
   }
   p.kernel = 1;
   if (a_kc) {
+    const KSplit ks = a_kc_split(g.M, g.N, g.K, n_cu, have_scratch ? ~(size_t)0 : 0);
+    if (ks.ranges > 1) {
+      const int wgs = (g.M + ks.tile_rows - 1) / ks.tile_rows * tiles_n;
+      p.main_workgroups = ks.tile_rows == 256 ? wgs : 0;
+      p.short_workgroups = ks.tile_rows == 256 ? 0 : wgs;
+      p.split_k = ks.ranges;
+      return p;
+    }
     const int cn = full_tile_columns(tiles_m, tiles_n, n_cu);
     p.main_workgroups = tiles_m * cn;
     p.short_workgroups = ((g.M + 127) / 128) * (tiles_n - cn);

@@ -51,7 +51,10 @@ struct Plan {
   int64_t p_shape[STAGE_P_COUNT][2];
   size_t param_elems;
   std::vector<LayerStash> layer;
-  size_t t_dm, t_dh, t_do, t_delta, t_dgp, t_dbp, t_qtiles, t_kvtiles;  // per-microbatch temporaries
+  size_t t_dh, t_do, t_delta, t_dgp, t_dbp, t_qtiles, t_kvtiles;  // per-microbatch temporaries
+  // GEMM scratch of a microbatch (split-K planes of F, B and W): t_dm, B's fp32 temporary of an unfused activation backward,
+  // and directly behind it t_ds.  Both are idle outside the one kernel or the two attention kernels of B that use them.
+  size_t t_dm, ws_bytes;
   size_t t_ds;               // dS scratch of the MFMA attention backward (0 when that path cannot run)
   int ds_rows, ds_nqs;
   size_t t_dkvp;             // partial dK / dV planes of its head subsets (0 without grouped query heads)
@@ -145,7 +148,6 @@ int make_plan(const stage_config* c, Plan* p) {
     s.h1_16 = c->dtype == STAGE_DTYPE_BF16 ? take(T * H * 2) : 0;
     s.o16 = c->dtype == STAGE_DTYPE_BF16 ? take(T * nq * d * 2) : 0;
   }
-  p->t_dm = take(T * F * 4);     // fp32: GEMM outputs that only an elementwise kernel consumes are not rounded
   p->t_dh = take(T * H * 4);
   p->t_do = take(T * nq * d * e);
   p->t_delta = take(nq * T * 4);
@@ -171,7 +173,9 @@ int make_plan(const stage_config* c, Plan* p) {
     probe.dtype = c->dtype; probe.d = c->head_dim; probe.n_q_tiles = 1;
     p->ds_rows = attn_ds_rows((int)T, c->max_segments);
     p->ds_nqs = attn_ds_nqs((int)T);
+    p->t_dm = take(T * F * 4);     // fp32: GEMM outputs that only an elementwise kernel consumes are not rounded
     p->t_ds = attn_mfma_supports(probe) ? take(attn_ds_bytes((int)T, c->max_segments, (int)nq)) : 0;
+    p->ws_bytes = o - p->t_dm;
     const size_t part = attn_dkv_part_bytes((int)T, (int)nq, (int)nkv, (int)d, c->dtype);
     p->t_dkvp = part ? take(part) : 0;
   }
@@ -474,6 +478,7 @@ int stage_F(stage_t* st, int mb, const void* x_dev, const int32_t* cu, int n_seg
                                      half_path ? base + L.h1_16 : nullptr));
     GemmArgs g{};
     g.in_dtype = dt; g.out_dtype = dt; g.transA = false; g.transB = false; g.M = T;
+    g.ws = base + P.t_dm; g.ws_bytes = P.ws_bytes;
     g.A = base + L.h1; g.lda = H; g.B = param_ptr(st, l, STAGE_P_WQKV); g.ldb = P.n_qkv;
     if (half_path) { g.in_dtype = F16; g.out_dtype = F16; g.A = base + L.h1_16; g.B = st->arena + P.w16_off[l]; }
     g.C = base + L.qkv; g.ldc = P.n_qkv; g.R = nullptr; g.N = P.n_qkv; g.K = H;
@@ -592,6 +597,7 @@ int stage_B(stage_t* st, int mb, const void* dy_dev, void* dx_dev, void* stream)
     float* dx_out32 = (l == 0) ? nullptr : (float*)(base + P.layer[l - 1].dy32);
     GemmArgs g{};
     g.in_dtype = dt; g.out_dtype = dt; g.transA = false; g.transB = true; g.M = T; g.R = nullptr;
+    g.ws = base + P.t_dm; g.ws_bytes = P.ws_bytes;
     // dm = dy Wd^T
     g.A = base + L.dy; g.lda = H; g.B = param_ptr(st, l, STAGE_P_WD); g.ldb = H;
     // dm = dy Wd^T feeds only the activation backward: fused into the epilogue when the shape allows it
@@ -603,7 +609,9 @@ int stage_B(stage_t* st, int mb, const void* dy_dev, void* dx_dev, void* stream)
     } else {
       g.act = ACT_NONE; g.E = nullptr;
       g.C = base + P.t_dm; g.ldc = F; g.out_dtype = F32;
+      g.ws = nullptr;                        // the output itself lies there
       HIP_TRY(st, launch_gemm(g, s));
+      g.ws = base + P.t_dm;
       if (c.mlp_kind == STAGE_MLP_SWIGLU) HIP_TRY(st, launch_swiglu_bwd((const float*)(base + P.t_dm), base + L.up, base + L.dup, T, F, dt, s));
       else HIP_TRY(st, launch_gelu_bwd((const float*)(base + P.t_dm), base + L.up, base + L.dup, T, F, dt, s));
     }
@@ -689,7 +697,7 @@ int stage_W(stage_t* st, int mb, void* stream) {
     const LayerStash& L = P.layer[l];
     GemmArgs g{};
     g.in_dtype = dt; g.out_dtype = F32; g.transA = true; g.transB = false; g.K = T; g.R = nullptr;
-    g.ws = base + P.t_dm; g.ws_bytes = (size_t)c.max_tokens * F * 4;   // B's fp32 temporary is idle during W
+    g.ws = base + P.t_dm; g.ws_bytes = P.ws_bytes;
     g.A = base + L.h1; g.lda = H; g.B = base + L.dqkv; g.ldb = P.n_qkv;
     g.C = slot + P.p_off[l][STAGE_P_WQKV]; g.ldc = P.n_qkv; g.M = H; g.N = P.n_qkv;
     HIP_TRY(st, launch_gemm(g, s));

@@ -175,6 +175,12 @@ def test_gemm_launch_plan_is_a_pure_function_of_shape_and_cu_count():
     assert R.rrfp_gemm_plan(1000, 2048, 1280, 0, 0, BF) == dict(kernel=1, wavefronts=8, main_workgroups=0, short_workgroups=64, split_k=1)
     # the CU count is an input: with 32 CUs the same 32 tiles are one full round of 256-row tiles
     assert R.rrfp_gemm_plan(1000, 2048, 1280, 0, 0, BF, n_cu=32) == dict(kernel=1, wavefronts=8, main_workgroups=32, short_workgroups=0, split_k=1)
+    # with scratch, a form with A K-contiguous whose tiles leave the chip idle is contracted in ranges (tiles x ranges near the CU
+    # count); whole rounds and short contractions are not
+    assert R.rrfp_gemm_plan(512, H, F2, 0, 1, F32, have_scratch=True) == dict(kernel=1, wavefronts=8, main_workgroups=32, short_workgroups=0, split_k=8)
+    assert R.rrfp_gemm_plan(512, H, H, 0, 0, BF, have_scratch=True) == dict(kernel=1, wavefronts=8, main_workgroups=0, short_workgroups=64, split_k=4)
+    for shp in ((T, H, F2), (T, F2, H), (1024, 512, 480)):
+        assert R.rrfp_gemm_plan(*shp, 0, 0, F32, have_scratch=True) == R.rrfp_gemm_plan(*shp, 0, 0, F32, have_scratch=False)
     # K not a multiple of 32 with a K-contiguous operand: register-staged kernel; N not a multiple of 8: refused
     assert R.rrfp_gemm_plan(264, 520, 200, 0, 0, BF)["kernel"] == 2
     assert R.rrfp_gemm_plan(264, 516, 256, 0, 0, BF)["kernel"] == 0

@@ -1,0 +1,54 @@
+"""The bf16 GEMM forms with A K-contiguous, contracted in ranges: partial planes in the workspace, finished by one kernel."""
+import numpy as np
+import pytest
+
+import stage_inputs as SI
+from tests import helpers as Hp
+
+pytestmark = pytest.mark.gpu
+
+
+# (M, N, K, trans_b): one row; a ragged last tile row and column; ranges of unequal depth; 128- and 256-row tiles; few and
+# many ranges; the smallest contraction that is split
+@pytest.mark.parametrize("M,N,K,tb", [(1, 512, 4096, 0), (300, 2056, 4128, 0), (513, 4104, 12320, 1), (129, 264, 3072, 1), (2048, 4096, 11008, 0),
+                                      (256, 8192, 4096, 1), (77, 72, 1024, 0)])
+@pytest.mark.parametrize("out_fp32,with_r", [(1, 0), (1, 1), (0, 0)])
+def test_split_contraction_matches_fp64(M, N, K, tb, out_fp32, with_r):
+    """fp32 sums of exact products: error within sqrt(K) 2^-24 of the largest sum of magnitudes, bf16 output 2^-8 more."""
+    import torch
+    import paper_2605_18750_amd as R
+    from paper_2605_18750_amd import harness as Hn
+    plan = R.rrfp_gemm_plan(M, N, K, 0, tb, R.STAGE_DTYPE_FP32 if out_fp32 else R.STAGE_DTYPE_BF16, have_scratch=True)
+    print(f"[splitk] M{M} N{N} K{K} tb{tb} f32{out_fp32} r{with_r}: {plan}", flush=True)
+    assert plan["split_k"] > 1
+    g = torch.Generator().manual_seed(M + N + K)
+    A, B = torch.randn((M, K), generator=g).bfloat16().cuda(), torch.randn((N, K) if tb else (K, N), generator=g).bfloat16().cuda()
+    Rr = torch.randn((M, N), generator=g).cuda() if with_r else None
+    ref = A.double() @ (B.double().t().contiguous() if tb else B.double())
+    if with_r:
+        ref = ref + Rr.double()
+    nbytes = plan["split_k"] * M * N * 4
+    outs = []
+    for size in (nbytes, nbytes, nbytes - 256):          # the same call twice; a workspace one range too small
+        ws = torch.full((nbytes + 256,), 0xFF, dtype=torch.uint8, device="cuda:0")       # NaN planes, and a guard behind them
+        C = torch.full((M + 1, N), float("nan"), dtype=torch.float32 if out_fp32 else torch.bfloat16, device="cuda:0")
+        R.rrfp_gemm(A, B, C, Rr, M, N, K, K, B.shape[1], N, N, 0, tb, 1, 0 if out_fp32 else 1, R.RRFP_GEMM_MFMA, workspace=ws, workspace_bytes=size)
+        torch.cuda.synchronize()
+        assert bool((ws[size:] == 0xFF).all()), "written past the workspace"
+        assert bool(torch.isnan(C[M:]).all()), "rows past M were written"
+        err = float((C[:M].double() - ref).abs().max() / ref.abs().max())
+        assert err <= (2e-5 if out_fp32 else 1e-2), (size, err)
+        outs.append(C[:M].clone())
+    assert torch.equal(outs[0], outs[1]), "two calls differ"
+
+
+@pytest.mark.parametrize("mlp,bias,norm", [("swiglu", False, "rms"), ("swiglu", True, "rms"), ("gelu", True, "layer"), ("gelu", False, "rms")])
+def test_stage_with_split_contractions_matches_oracle(mlp, bias, norm):
+    """Every fused epilogue behind the planes: activations forward and backward, biases, residuals, half outputs and the scale
+    of dO.  Hidden 2048 at up to 150 tokens: all the products of F and B are split."""
+    shape = SI.StageShape(f"splitk_{mlp}{bias}{norm}", 1, 2048, 16, 8, 128, 2048, 2, w_std=0.02, mlp_kind=mlp, bias=bias, norm_kind=norm)
+    w = Hp.Workload(shape, [[0, 60, 150], [0, 1]])
+    got = Hp.run_gpu(w, keep_raw=True)
+    worst = Hp.compare(got, Hp.run_oracle(w), Hp.TOL["bf16"], "splitk stage")
+    print(f"[splitk] stage {mlp} bias{bias} {norm}: worst {worst:.2e}", flush=True)
+    Hp.assert_bit_identical(got, Hp.run_gpu(w, order=SI.ready_order(w.M, 5), n_streams=3, keep_raw=True))
