@@ -48,8 +48,8 @@ int rrfp_gemm_ws(const void* A, const void* B, void* C, const void* R, int M, in
  * (no GPU call, no pointers; operands are taken as 16-byte aligned).  The cut is a pure function of the
  * shape and n_cu, which is what keeps the summation order of a call fixed (the bit-exactness requirement
  * behind readiness-driven reordering, paper Section 7.1).  out[0] = kernel (0 the MFMA family refuses the
- * shape, 1 direct-to-LDS, 2 register-staged), out[1] = wavefronts per workgroup, out[2] = workgroups of
- * the 256-row-tile launch, out[3] = workgroups of the second launch that finishes a grid whose last round
+ * shape, 1 direct-to-LDS, 2 register-staged, 3 the 64 x 64 tiles of small outputs, with scratch only), out[1] = wavefronts per workgroup, out[2] = workgroups of
+ * the 256-row-tile (kernel 3: only) launch, out[3] = workgroups of the second launch that finishes a grid whose last round
  * would be nearly empty (128-row tiles when A is K-contiguous; for the weight-gradient form with scratch the
  * trailing tile columns split along K into out[4] ranges), out[4] = split-K ranges (weight-gradient form with
  * scratch: of the whole grid when out[3] = 0, of the tail launch otherwise; A K-contiguous with scratch: of the

@@ -1,6 +1,6 @@
 // bf16 MFMA GEMM for gfx950: C[M,N] = A(m,k) B(k,n) (+R), fp32 accumulation, bf16 or fp32 out.
 //
-// Two kernels share the tile geometry (a workgroup owns a 256-wide tile of C):
+// Two kernels share the tile geometry (a workgroup owns a 256-wide tile of C); a third takes small outputs:
 //
 //   gemm_mfma_dl_kernel  the main kernel.  8 wavefronts (2 x 4, 128 x 64 of C each), accumulators of
 //     v_mfma_f32_16x16x32_bf16.  K advances in 32-deep steps through a ring of five LDS buffers that
@@ -11,6 +11,7 @@
 //     128-row tile variant and a split-K mode for grids that do not fill the CUs.
 //   gemm_mfma_kernel     the fallback for K-contiguous operands whose K is not a multiple of 32: four
 //     wavefronts, v_mfma_f32_32x32x16_bf16, 64-deep steps, two LDS stages filled through registers.
+//   gemm_mfma_small_kernel  64 x 64 tiles, the contraction dealt to the wavefronts of a workgroup.
 //
 // Operand tiles sit in LDS in their memory orientation, so every global load is a coalesced
 // 16-byte access:
@@ -941,9 +942,70 @@ inline int splitk_factor(int t, int K, int n_cu) {
   return std::max(1, std::min(std::min(n_cu / t, steps / 16), 16));
 }
 
+// What the tile epilogue does to 8 consecutive columns n.. of row m, for kernels that hold them in one thread: v (SwiGLU forward:
+// v the gate, up the other half) are the fp32 sums, already with their bias.
+template <typename TO, bool HAS_R, int ACT>
+__device__ __forceinline__ void finish8(float (&v)[8], float (&up)[8], int m, int n, int N, TO* __restrict__ C, int ldc, const float* __restrict__ R,
+                                        int ldr, bf16_t* __restrict__ E, int lde, const float* __restrict__ out_scale) {
+  if constexpr (HAS_R) {
+    float r[8];
+    load_f32x8(R + (size_t)m * ldr + n, r);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] += r[e];
+  }
+  TO* crow = C + (size_t)m * ldc + n;
+  if constexpr (ACT == ACT_SWIGLU_FWD) {
+    float mm[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) mm[e] = v[e] * sigmoid_f(v[e]) * up[e];
+    store_vec<TO>(crow, v);
+    store_vec<TO>(crow + (N >> 1), up);
+    store_vec<bf16_t>(E + (size_t)m * lde + n, mm);
+  } else if constexpr (ACT == ACT_GELU_FWD) {
+    float mm[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) mm[e] = gelu_f(v[e]);
+    store_vec<TO>(crow, v);
+    store_vec<bf16_t>(E + (size_t)m * lde + n, mm);
+  } else if constexpr (ACT == ACT_GELU_BWD) {
+    float u[8];
+    load_vec<bf16_t>(E + (size_t)m * lde + n, u);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] *= gelu_grad_f(u[e]);
+    store_vec<TO>(crow, v);
+  } else if constexpr (ACT == ACT_SWIGLU_BWD) {
+    float gt[8], ut[8], dg[8], du[8];
+    load_vec<bf16_t>(E + (size_t)m * lde + n, gt);
+    load_vec<bf16_t>(E + (size_t)m * lde + N + n, ut);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float sg = sigmoid_f(gt[e]);
+      dg[e] = v[e] * ut[e] * sg * (1.0f + gt[e] * (1.0f - sg));
+      du[e] = v[e] * gt[e] * sg;
+    }
+    store_vec<TO>(crow, dg);
+    store_vec<TO>(crow + N, du);
+  } else {
+    if constexpr (!HAS_R && sizeof(TO) == 2) {
+      const float sc = out_scale ? *out_scale : 1.0f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] *= sc;
+    }
+    store_vec<TO>(crow, v);
+    if constexpr (sizeof(TO) == 4) store_vec<TO>(crow + 4, v + 4);
+  }
+}
+__device__ __forceinline__ void add_bias8(const bf16_t* __restrict__ bias, int n, float (&v)[8]) {
+  if (!bias) return;
+  float b[8];
+  load_vec<bf16_t>(bias + n, b);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] += b[e];
+}
+
 // Finish of a split-K launch of a form with A K-contiguous: adds the S partial planes [M, N] in range order and applies what
-// the unsplit kernel's epilogue applies (bias, activation or residual, scale, rounding), on the same fp32 values.  A
-// thread owns 8 columns (of SwiGLU forward: 8 features, gate and up).
+// the unsplit kernel's epilogue applies, on the same fp32 values.  A thread owns 8 columns (of SwiGLU forward: 8
+// features, gate and up).
 template <typename TO, bool HAS_R, int ACT>
 __global__ __launch_bounds__(256) void splitk_finish_kernel(const float* __restrict__ ws, int S, int M, int N, TO* __restrict__ C, int ldc,
                                                             const float* __restrict__ R, int ldr, bf16_t* __restrict__ E, int lde,
@@ -964,69 +1026,194 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(const float* __restr
       for (int e = 0; e < 8; ++e) v[e] += t[e];
     }
   };
-  auto add_bias = [&](int at, float (&v)[8]) {
-    if (!bias) return;
-    float b[8];
-    load_vec<bf16_t>(bias + at, b);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] += b[e];
-  };
-  float v[8];
+  float v[8], up[8];
   sum_planes(row, v);
-  add_bias(n, v);
-  if constexpr (HAS_R) {
-    float r[8];
-    load_f32x8(R + (size_t)m * ldr + n, r);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] += r[e];
-  }
+  add_bias8(bias, n, v);
   if constexpr (ACT == ACT_SWIGLU_FWD) {
-    float up[8], mm[8];
     sum_planes(row + width, up);
-    add_bias(width + n, up);
+    add_bias8(bias, width + n, up);
+  }
+  finish8<TO, HAS_R, ACT>(v, up, m, n, N, C, ldc, R, ldr, E, lde, out_scale);
+}
+
+// ------------------------------------------------------------------------------------------
+// Small outputs.  Tiles of 64 x 64 whose NW wavefronts each contract a range of k on their own (64 accumulator registers of
+// v_mfma_f32_16x16x32, no barrier before the end); their sums meet in LDS and are added in range order, and every fused
+// epilogue of the tile kernel runs on them.  What bounds an output of a few tiles is latency: a 256- or 128-row tile is one
+// workgroup's serial walk over K plus the store of a large tile by one CU (11 us for 512 x 512 x 100); this spreads
+// both over 4 to 8 times the CUs and cuts the walk by NW.
+//   K-contiguous operand: a lane's 16 bytes of a fragment come straight from memory.
+//   K-strided operand: rows of 128 bytes go through registers to a wavefront-private LDS tile [32 k][64 columns] and come back
+//     by the LDS transpose read; chunk c of row k sits at c ^ swz(k), so that the 8 k-rows of a pass meet 8 bank groups.
+// Operands of k at or past K read as zero, rows and columns past the end repeat the last ones and are not stored.
+// ------------------------------------------------------------------------------------------
+constexpr int ST = 64, ST_TILE = 32 * ST * 2;         // tile edge; bytes of one K-strided operand tile of one step
+
+__device__ __forceinline__ int st_swz(int k) { return ((((k >> 1) & 1) | (((k >> 3) & 1) << 1)) << 1); }
+
+// One operand of a wavefront: 32-deep steps of four loads.  (64-deep ones, which fetch whole 128-byte lines of a K-contiguous
+// operand at once, measured the same and spilled in the SwiGLU form.)
+template <bool KC>
+struct SmallOperand {
+  const bf16_t* p[4];     // KC: row of fragment i at this lane's k offset; else: this lane's chunk of k row (lane >> 3) + 8 i
+  int k_lane[4], step;    // k of the lane's element in step 0; elements per step
+  int lds_w, lds_r;
+  // SwiGLU forward: tile columns 0..31 are gate, 32..63 the up columns of the same features (pair_f = ffn)
+  __device__ __forceinline__ void init(const bf16_t* base, int ld, int outer0, int outer_n, int lane, int pair_f) {
+    step = KC ? 32 : 32 * ld;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) mm[e] = v[e] * sigmoid_f(v[e]) * up[e];
-    bf16_t* crow = (bf16_t*)C + (size_t)m * ldc + n;
-    store_vec<bf16_t>(crow, v);
-    store_vec<bf16_t>(crow + width, up);
-    store_vec<bf16_t>(E + (size_t)m * lde + n, mm);
-  } else if constexpr (ACT == ACT_GELU_FWD) {
-    float mm[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) mm[e] = gelu_f(v[e]);
-    store_vec<bf16_t>((bf16_t*)C + (size_t)m * ldc + n, v);
-    store_vec<bf16_t>(E + (size_t)m * lde + n, mm);
-  } else if constexpr (ACT == ACT_GELU_BWD) {
-    float u[8];
-    load_vec<bf16_t>(E + (size_t)m * lde + n, u);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] *= gelu_grad_f(u[e]);
-    store_vec<bf16_t>((bf16_t*)C + (size_t)m * ldc + n, v);
-  } else if constexpr (ACT == ACT_SWIGLU_BWD) {
-    float gt[8], up[8], dg[8], du[8];
-    load_vec<bf16_t>(E + (size_t)m * lde + n, gt);
-    load_vec<bf16_t>(E + (size_t)m * lde + N + n, up);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float sg = sigmoid_f(gt[e]);
-      dg[e] = v[e] * up[e] * sg * (1.0f + gt[e] * (1.0f - sg));
-      du[e] = v[e] * gt[e] * sg;
+    for (int i = 0; i < 4; ++i) {
+      if constexpr (KC) {
+        k_lane[i] = (lane >> 4) * 8;
+        p[i] = base + (size_t)min(outer0 + i * 16 + (lane & 15), outer_n - 1) * ld + k_lane[i];
+      } else {
+        const int c = (lane & 7) * 8;
+        const int col = pair_f > 0 ? (c >> 5) * pair_f + (outer0 >> 1) + (c & 31) : min(outer0 + c, outer_n - 8);
+        k_lane[i] = (lane >> 3) + i * 8;
+        p[i] = base + (size_t)k_lane[i] * ld + col;
+      }
     }
-    store_vec<bf16_t>((bf16_t*)C + (size_t)m * ldc + n, dg);
-    store_vec<bf16_t>((bf16_t*)C + (size_t)m * ldc + N + n, du);
-  } else {
-    if constexpr (!HAS_R && sizeof(TO) == 2) {
-      const float sc = out_scale ? *out_scale : 1.0f;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] *= sc;
+    if constexpr (!KC) {
+      // k rows of load i are (lane >> 3) + 8 i: bits 0..2 from the lane, bit 3 from i (an XOR of 64 bytes below)
+      lds_w = (lane >> 3) * 128 + (((lane & 7) ^ st_swz(lane >> 3)) << 4);
+      const int kb = (lane >> 4) * 8 + ((lane & 15) >> 2);
+      lds_r = kb * 128 + ((((lane & 3) >> 1) ^ st_swz(kb)) << 4) + (lane & 1) * 8;
     }
-    store_vec<TO>(C + (size_t)m * ldc + n, v);
-    if constexpr (sizeof(TO) == 4) store_vec<TO>(C + (size_t)m * ldc + n + 4, v + 4);
+  }
+  __device__ __forceinline__ void fetch(uint4 (&r)[4], int t, int k_end) const {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      r[i] = make_uint4(0, 0, 0, 0);
+      if (t * 32 + k_lane[i] < k_end) r[i] = *reinterpret_cast<const uint4*>(p[i] + (size_t)t * step);
+    }
+  }
+  __device__ __forceinline__ void put(const uint4 (&r)[4], char* tile) const {
+    if constexpr (!KC) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) *reinterpret_cast<uint4*>(tile + i * 1024 + (lds_w ^ ((i & 1) << 6))) = r[i];
+    }
+  }
+  __device__ __forceinline__ bf16x8 frag(const uint4 (&r)[4], const char* tile, int i) const {
+    if constexpr (KC) return __builtin_bit_cast(bf16x8, r[i]);
+    // block i: chunks 2i, 2i + 1; the second read, 4 k rows on, changes neither swizzle bit
+    const lds_char_ptr q = (lds_char_ptr)tile + (lds_r ^ (i << 5));
+    union { short4v h[2]; bf16x8 v; } u;
+    u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)q);
+    u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(q + 512));
+    return u.v;
+  }
+};
+
+constexpr int SMALL_NW = 8;                            // four wavefronts, two workgroups per CU: 5 to 40 % slower
+template <bool A_KC, bool B_KC, typename TO, bool HAS_R, int ACT, bool F16IN>
+__global__ __launch_bounds__(SMALL_NW * 64) void gemm_mfma_small_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, TO* __restrict__ C,
+                                                                  const float* __restrict__ R, int M, int N, int K, int lda, int ldb, int ldc,
+                                                                  int ldr, int tiles_m, int tiles_n, bf16_t* __restrict__ E, int lde,
+                                                                  const bf16_t* __restrict__ bias, const float* __restrict__ out_scale) {
+  constexpr int NW = SMALL_NW, PITCH = ST + 4;         // floats per row of a wavefront's sums
+  constexpr int RED = ST * PITCH * 4, STAGE = (A_KC ? 0 : ST_TILE) + (B_KC ? 0 : ST_TILE);
+  static_assert(STAGE <= RED, "the staging tiles live inside the wavefront's part of the sums");
+  __shared__ __attribute__((aligned(1024))) char pool[NW * RED];
+  int tm, tn;
+  tile_coords(tiles_m, tiles_n, tm, tn);
+  const int m0 = tm * ST, n0 = tn * ST;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  char* mine = pool + wave * RED;
+  SmallOperand<A_KC> oa;
+  SmallOperand<B_KC> ob;
+  oa.init(A, lda, m0, M, lane, 0);
+  ob.init(B, ldb, n0, N, lane, ACT == ACT_SWIGLU_FWD ? N >> 1 : 0);
+  floatx4 acc[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  const int steps = (K + 31) / 32, per = (steps + NW - 1) / NW;
+  const int t0 = wave * per, t1 = min(steps, t0 + per), k_end = min(K, t1 * 32);
+  auto wave_sync = [] {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  uint4 ra[2][4], rb[2][4];
+  auto multiply = [&](int set) {                      // set: a constant at every call
+    char* tile_b = mine + (A_KC ? 0 : ST_TILE);
+    oa.put(ra[set], mine);
+    ob.put(rb[set], tile_b);
+    if constexpr (!A_KC || !B_KC) wave_sync();
+    bf16x8 fa[4], fb[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { fa[i] = oa.frag(ra[set], mine, i); fb[i] = ob.frag(rb[set], tile_b, i); }
+    mfma_blocks<4, 4, 4, F16IN>(acc, fa, fb, 0);
+    if constexpr (!A_KC || !B_KC) wave_sync();
+  };
+  if (t0 < t1) {
+    oa.fetch(ra[0], t0, k_end);
+    ob.fetch(rb[0], t0, k_end);
+    for (int t = t0; t < t1; t += 2) {                // loads run one step ahead; past the range they give zeros without a memory access
+      oa.fetch(ra[1], t + 1, k_end);
+      ob.fetch(rb[1], t + 1, k_end);
+      multiply(0);
+      if (t + 1 < t1) {
+        oa.fetch(ra[0], t + 2, k_end);
+        ob.fetch(rb[0], t + 2, k_end);
+        multiply(1);
+      }
+    }
+  }
+  // block (i, j): row 16 i + (lane & 15), columns 16 j + 4 (lane >> 4) ..+3
+  float* red = reinterpret_cast<float*>(mine);
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) *reinterpret_cast<floatx4*>(red + (i * 16 + (lane & 15)) * PITCH + j * 16 + (lane >> 4) * 4) = acc[i][j];
+  __syncthreads();
+  constexpr int CH = ACT == ACT_SWIGLU_FWD ? 4 : 8;   // 8-column chunks per row (SwiGLU forward: of features)
+  for (int q = threadIdx.x; q < ST * CH; q += NW * 64) {
+    const int row = q / CH, c = (q % CH) * 8, m = m0 + row;
+    const int n = ACT == ACT_SWIGLU_FWD ? (n0 >> 1) + c : n0 + c;
+    if (m >= M || n >= (ACT == ACT_SWIGLU_FWD ? N >> 1 : N)) continue;
+    auto sum_waves = [&](int at, float (&v)[8]) {
+      const float* p = reinterpret_cast<const float*>(pool) + row * PITCH + at;
+      load_f32x8(p, v);
+#pragma unroll
+      for (int w = 1; w < NW; ++w) {
+        float x[8];
+        load_f32x8(p + w * (RED / 4), x);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] += x[e];
+      }
+    };
+    float v[8], up[8];
+    sum_waves(c, v);
+    add_bias8(bias, n, v);
+    if constexpr (ACT == ACT_SWIGLU_FWD) {
+      sum_waves(32 + c, up);
+      add_bias8(bias, (N >> 1) + n, up);
+    }
+    finish8<TO, HAS_R, ACT>(v, up, m, n, N, C, ldc, R, ldr, E, lde, out_scale);
   }
 }
 
-// Cut along K of a form with A K-contiguous: ranges > 1 means tiles of tile_rows x 256, each contracted in `ranges` pieces whose
-// fp32 planes go to the scratch and are added by splitk_finish_kernel; ranges == 1 the launches of full_tile_columns.
+template <bool A_KC, bool B_KC, typename TO, bool HAS_R, int ACT, bool F16IN>
+hipError_t launch_small(const GemmArgs& g, hipStream_t s) {
+  const int tiles_m = (g.M + ST - 1) / ST, tiles_n = (g.N + ST - 1) / ST;
+  hipLaunchKernelGGL((gemm_mfma_small_kernel<A_KC, B_KC, TO, HAS_R, ACT, F16IN>), dim3(tiles_m * tiles_n), dim3(SMALL_NW * 64), 0, s,
+                     (const bf16_t*)g.A, (const bf16_t*)g.B, (TO*)g.C, g.R, g.M, g.N, g.K, g.lda, g.ldb, g.ldc, g.ldr, tiles_m, tiles_n,
+                     (bf16_t*)g.E, g.lde, (const bf16_t*)g.bias, g.out_scale);
+  return hipGetLastError();
+}
+
+// Estimated time (us) of the small-output kernel: rounds of its 64 x 64 tiles, each bound by what one CU can have in flight
+// from memory (128 rows of K at 35 GB/s) plus 1.5 us of start and store.  Measured: 512 x 512 x 777 7.5, 512 x 3072 x
+// 777 14.6 (the split 256-row tiles: 23.8), 129 x 512 x 512 6.7 (10.3), 1000 x 8192 x 1024 66 (23).
+inline float small_us(int M, int N, int K, int n_cu) {
+  const long long t = (long long)((M + ST - 1) / ST) * ((N + ST - 1) / ST);
+  return 2.0f + (float)((t + n_cu - 1) / n_cu) * (1.5f + 0.0072f * K);
+}
+
+// Cut along K of a form with A K-contiguous: ranges == 0 means the small-output kernel, ranges > 1 tiles of tile_rows x 256, each contracted in `ranges` pieces whose
+// fp32 planes go to the scratch and are added by splitk_finish_kernel, ranges == 1 the launches of full_tile_columns.
 // A pure function of the shape, the device and the scratch.
 //
 // A workgroup takes 0.75 us per 32-deep step with 256-row tiles and 0.55 us with 128-row ones, whether it shares the chip
@@ -1038,13 +1225,13 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(const float* __restr
 // 2048 x 4096 x 4096 would go 70 -> 78 and stays unsplit.
 struct KSplit { int tile_rows, ranges; };
 inline KSplit a_kc_split(int M, int N, int K, int n_cu, size_t ws_bytes) {
-  constexpr float US_256 = 0.75f, US_128 = 0.55f, FINISH_US = 4.0f, PLANE_BYTES_PER_US = 8.0e6f;
+  constexpr float US_256 = 0.75f, US_128 = 0.55f, BASE_US = 4.0f, FINISH_US = 4.0f, PLANE_BYTES_PER_US = 8.0e6f;
   constexpr int MAX_RANGES = 12, MIN_STEPS = 8;
   const int steps = (K + DBK - 1) / DBK;
   const long long tn = (N + BN - 1) / BN, t256 = (M + 255) / 256 * tn, t128 = (M + 127) / 128 * tn;
   auto rounds = [&](long long wgs) { return (float)((wgs + n_cu - 1) / n_cu); };
   KSplit best{256, 1};
-  if (steps < 2 * MIN_STEPS || ws_bytes == 0 || t256 > n_cu) return best;   // several rounds of full tiles: nothing is idle for long
+  if (ws_bytes == 0 || t256 > n_cu) return best;   // without scratch, or several rounds of full tiles
   float cost = (2 * t256 <= n_cu ? rounds(t128) * US_128 : US_256) * steps;
   const float mn = (float)M * (float)N;
   for (int S = 2; S <= MAX_RANGES && steps / S >= MIN_STEPS; ++S) {
@@ -1056,7 +1243,18 @@ inline KSplit a_kc_split(int M, int N, int K, int n_cu, size_t ws_bytes) {
     if (c256 < cost) { cost = c256; best = KSplit{256, S}; }
     if (c128 < cost) { cost = c128; best = KSplit{128, S}; }
   }
+  if (small_us(M, N, K, n_cu) < cost + BASE_US) best = KSplit{ST, 0};
   return best;
+}
+
+// The weight-gradient form takes the small-output kernel when that is estimated a tenth faster than its 256-row tiles (which
+// need about 8 us beyond their k steps, most of it one CU storing 256 KB of fp32).
+inline bool wgrad_small(int M, int N, int K, int n_cu) {
+  const int t = (M + 255) / 256 * ((N + BN - 1) / BN);
+  if (t > n_cu) return false;
+  const int S = splitk_factor(t, K, n_cu), steps = (K + DBK - 1) / DBK, per = (steps + S - 1) / S;
+  const float tile_us = 8.0f + 0.75f * per + (S > 1 ? 4.0f + (float)M * (float)N * (8 * S + 6) / 8.0e6f : 0.0f);
+  return small_us(M, N, K, n_cu) < 0.9f * tile_us;
 }
 
 // Launch of the direct-to-LDS kernel for the forms with A K-contiguous, per the cuts above.
@@ -1064,6 +1262,7 @@ template <bool B_KC, typename TO, bool HAS_R, int ACT, bool F16IN = false>
 hipError_t launch_a_kc(const GemmArgs& g, hipStream_t s) {
   constexpr int WMv = dl_wm(true, B_KC), WNv = dl_wn(true, B_KC);
   const KSplit ks = a_kc_split(g.M, g.N, g.K, cu_count(), g.ws && !((uintptr_t)g.ws & 15) ? g.ws_bytes : 0);
+  if (ks.ranges == 0) return launch_small<true, B_KC, TO, HAS_R, ACT, F16IN>(g, s);
   if (ks.ranges > 1) {
     const int steps = (g.K + DBK - 1) / DBK, k_split = (steps + ks.ranges - 1) / ks.ranges * DBK, S = (g.K + k_split - 1) / k_split;
     const int tm = (g.M + ks.tile_rows - 1) / ks.tile_rows, tn = (g.N + BN - 1) / BN;
@@ -1104,6 +1303,7 @@ hipError_t launch_one(const GemmArgs& g, hipStream_t s) {
     // few tiles to fill the CUs, the contraction is split into S ranges, every range writes its own
     // partial plane into the scratch, and the planes are summed in range order (one fixed order).
     if constexpr (!A_KC && !B_KC && !HAS_R && sizeof(TO) == 4) {
+      if (g.ws && wgrad_small(g.M, g.N, g.K, cu_count())) return launch_small<false, false, float, false, ACT_NONE, false>(g, s);
       const int S = splitk_factor(tiles_m * tiles_n, g.K, cu_count());
       if (S > 1 && g.ws && g.ldc == g.N && (size_t)S * g.M * g.N * 4 <= g.ws_bytes && ((size_t)g.M * g.N) % 4 == 0) {
         const int steps = (g.K + DBK - 1) / DBK, k_split = (steps + S - 1) / S * DBK;
@@ -1195,8 +1395,15 @@ GemmPlan gemm_mfma_plan(const GemmArgs& g, int n_cu, bool have_scratch) {
     return p;
   }
   p.kernel = 1;
+  auto small_plan = [&] {
+    p.kernel = 3;
+    p.wavefronts = SMALL_NW;
+    p.main_workgroups = (g.M + ST - 1) / ST * ((g.N + ST - 1) / ST);
+    return p;
+  };
   if (a_kc) {
     const KSplit ks = a_kc_split(g.M, g.N, g.K, n_cu, have_scratch ? ~(size_t)0 : 0);
+    if (ks.ranges == 0) return small_plan();
     if (ks.ranges > 1) {
       const int wgs = (g.M + ks.tile_rows - 1) / ks.tile_rows * tiles_n;
       p.main_workgroups = ks.tile_rows == 256 ? wgs : 0;
@@ -1211,6 +1418,7 @@ GemmPlan gemm_mfma_plan(const GemmArgs& g, int n_cu, bool have_scratch) {
   }
   p.main_workgroups = tiles_m * tiles_n;
   if (!b_kc && !g.R && g.out_dtype == F32 && have_scratch) {
+    if (wgrad_small(g.M, g.N, g.K, n_cu)) return small_plan();
     const int S = (g.ldc == g.N && ((size_t)g.M * g.N) % 4 == 0) ? splitk_factor(tiles_m * tiles_n, g.K, n_cu) : 1;
     if (S > 1) {
       const int steps = (g.K + DBK - 1) / DBK, k_split = (steps + S - 1) / S * DBK;

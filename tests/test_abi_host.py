@@ -179,8 +179,12 @@ def test_gemm_launch_plan_is_a_pure_function_of_shape_and_cu_count():
     # count); whole rounds and short contractions are not
     assert R.rrfp_gemm_plan(512, H, F2, 0, 1, F32, have_scratch=True) == dict(kernel=1, wavefronts=8, main_workgroups=32, short_workgroups=0, split_k=8)
     assert R.rrfp_gemm_plan(512, H, H, 0, 0, BF, have_scratch=True) == dict(kernel=1, wavefronts=8, main_workgroups=0, short_workgroups=64, split_k=4)
-    for shp in ((T, H, F2), (T, F2, H), (1024, 512, 480)):
+    for shp in ((T, H, F2), (T, F2, H), (1024, 8192, 480)):
         assert R.rrfp_gemm_plan(*shp, 0, 0, F32, have_scratch=True) == R.rrfp_gemm_plan(*shp, 0, 0, F32, have_scratch=False)
+    # outputs of few tiles and short contractions: 64 x 64 tiles, with scratch only
+    assert R.rrfp_gemm_plan(512, 3072, 777, 1, 0, F32, have_scratch=True) == dict(kernel=3, wavefronts=8, main_workgroups=384, short_workgroups=0, split_k=1)
+    assert R.rrfp_gemm_plan(777, 1024, 512, 0, 0, BF, have_scratch=True)["kernel"] == 3
+    assert R.rrfp_gemm_plan(777, 1024, 512, 0, 0, BF)["kernel"] == 1
     # K not a multiple of 32 with a K-contiguous operand: register-staged kernel; N not a multiple of 8: refused
     assert R.rrfp_gemm_plan(264, 520, 200, 0, 0, BF)["kernel"] == 2
     assert R.rrfp_gemm_plan(264, 516, 256, 0, 0, BF)["kernel"] == 0

@@ -9,9 +9,9 @@ pytestmark = pytest.mark.gpu
 
 
 # (M, N, K, trans_b): one row; a ragged last tile row and column; ranges of unequal depth; 128- and 256-row tiles; few and
-# many ranges; the smallest contraction that is split
+# many ranges; one tile
 @pytest.mark.parametrize("M,N,K,tb", [(1, 512, 4096, 0), (300, 2056, 4128, 0), (513, 4104, 12320, 1), (129, 264, 3072, 1), (2048, 4096, 11008, 0),
-                                      (256, 8192, 4096, 1), (77, 72, 1024, 0)])
+                                      (256, 8192, 4096, 1), (77, 72, 4096, 0)])
 @pytest.mark.parametrize("out_fp32,with_r", [(1, 0), (1, 1), (0, 0)])
 def test_split_contraction_matches_fp64(M, N, K, tb, out_fp32, with_r):
     """fp32 sums of exact products: error within sqrt(K) 2^-24 of the largest sum of magnitudes, bf16 output 2^-8 more."""
@@ -40,6 +40,43 @@ def test_split_contraction_matches_fp64(M, N, K, tb, out_fp32, with_r):
         assert err <= (2e-5 if out_fp32 else 1e-2), (size, err)
         outs.append(C[:M].clone())
     assert torch.equal(outs[0], outs[1]), "two calls differ"
+
+
+# one row or column block; K of one step, one more, fewer steps than wavefronts, a ragged last step; M and N around the tile
+@pytest.mark.parametrize("M,N,K", [(8, 8, 1), (8, 64, 32), (64, 72, 33), (72, 56, 200), (136, 64, 256), (56, 136, 257), (1536, 512, 777)])
+def test_small_weight_gradient_matches_fp64(M, N, K):
+    _small(M, N, K, 1, 0, 1, 0)
+
+
+@pytest.mark.parametrize("M,N,K,tb", [(1, 8, 32, 0), (63, 64, 64, 1), (65, 72, 288, 0), (129, 512, 512, 1), (777, 1024, 512, 0), (200, 56, 1056, 1)])
+@pytest.mark.parametrize("out_fp32,with_r", [(1, 0), (1, 1), (0, 0)])
+def test_small_outputs_match_fp64(M, N, K, tb, out_fp32, with_r):
+    _small(M, N, K, 0, tb, out_fp32, with_r)
+
+
+def _small(M, N, K, ta, tb, out_fp32, with_r):
+    """Operands end in NaN rows that must not be read into a result; error bounds as above."""
+    import torch
+    import paper_2605_18750_amd as R
+    plan = R.rrfp_gemm_plan(M, N, K, ta, tb, R.STAGE_DTYPE_FP32 if out_fp32 else R.STAGE_DTYPE_BF16, have_scratch=True)
+    print(f"[small gemm] M{M} N{N} K{K} ta{ta} tb{tb} f32{out_fp32} r{with_r}: {plan}", flush=True)
+    assert plan["kernel"] == 3
+    g = torch.Generator().manual_seed(M + N + K)
+    full = [torch.randn((r + 64, c), generator=g).bfloat16().cuda() for r, c in ((K, M) if ta else (M, K), (N, K) if tb else (K, N))]
+    for t in full:
+        t[-64:] = float("nan")
+    A, B = full[0][:-64], full[1][:-64]
+    Rr = torch.randn((M, N), generator=g).cuda() if with_r else None
+    ref = (A.double().t().contiguous() if ta else A.double()) @ (B.double().t().contiguous() if tb else B.double())
+    if with_r:
+        ref = ref + Rr.double()
+    ws = torch.zeros(256, dtype=torch.uint8, device="cuda:0")
+    C = torch.full((M + 1, N), float("nan"), dtype=torch.float32 if out_fp32 else torch.bfloat16, device="cuda:0")
+    R.rrfp_gemm(A, B, C, Rr, M, N, K, A.shape[1], B.shape[1], N, N, ta, tb, 1, 0 if out_fp32 else 1, R.RRFP_GEMM_MFMA, workspace=ws, workspace_bytes=256)
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(C[M:]).all()), "rows past M were written"
+    err = float((C[:M].double() - ref).abs().max() / ref.abs().max())
+    assert err <= (2e-5 if out_fp32 else 1e-2), err
 
 
 @pytest.mark.parametrize("mlp,bias,norm", [("swiglu", False, "rms"), ("swiglu", True, "rms"), ("gelu", True, "layer"), ("gelu", False, "rms")])
