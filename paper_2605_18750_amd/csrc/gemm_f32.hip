@@ -5,12 +5,12 @@
 // fp32-FMA kernel needs an LDS read for every few FMAs; one 32x32x2 MFMA takes two registers and keeps the matrix
 // pipe busy for 64 cycles, so neither LDS nor issue slots limit anything here.  Products and sums stay fp32.
 //
-// Two kernels, chosen by the size of the output alone (see launch_gemm_f32):
-//   gemm_f32_tile_kernel   tiles of 64 x 64, eight wavefronts, 32-deep k steps through two LDS buffers (global loads two
+// Two tile routines, chosen by the size of the output alone (see launch_f32):
+//   f32_tile   tiles of 64 x 64, eight wavefronts, 32-deep k steps through two LDS buffers (global loads two
 //     steps ahead, one barrier per step).  1024 x 1024 x 5504: 112 us = 103 TFLOP/s; the fp32-FMA kernel that was here
 //     before: 385 us on 517 rows of it, now 111.  (128 x 128 tiles: 5 % faster at 4096^3, two to four times slower on
 //     outputs of up to 1024 rows.)
-//   gemm_f32_small_kernel  tiles of 32 x 32 whose eight wavefronts split the contraction and read their
+//   f32_small  tiles of 32 x 32 whose eight wavefronts split the contraction and read their
 //     fragments straight from global memory (L2): for outputs with too few tiles to fill the chip the time is the
 //     latency of the serial k loop, and this cuts the loop and takes the barriers out of it (128 x 256 x 688: 95 -> 8 us).
 //
@@ -104,17 +104,15 @@ __device__ __forceinline__ void put_f32(float v, float* __restrict__ C, const fl
 // about one tile per CU would otherwise leave a single wavefront per SIMD to cover its own LDS reads and barriers.
 constexpr int KG = 2, TILE_THREADS = 256 * KG;
 template <bool TA, bool TB, bool VEC>
-__global__ __launch_bounds__(TILE_THREADS) void gemm_f32_tile_kernel(const float* __restrict__ A, const float* __restrict__ B,
-                                                                     float* __restrict__ C, const float* __restrict__ R,
-                                                                     const float* __restrict__ bias, int M, int N, int K, int lda, int ldb,
-                                                                     int ldc, int ldr) {
+__device__ __forceinline__ void f32_tile(const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ C,
+                                      const float* __restrict__ R, const float* __restrict__ bias, int M, int N, int K, int lda, int ldb,
+                                      int ldc, int ldr, int m0, int n0) {
   using TileA = F32Tile<!TA, 64, VEC, TILE_THREADS>;
   using TileB = F32Tile<TB, 64, VEC, TILE_THREADS>;
   constexpr int CHUNKS = FK / 8 / KG;                 // 8-deep k chunks of a step per wavefront
   constexpr int BUF = TileA::FLOATS + TileB::FLOATS;
   static_assert(2 * BUF >= 4 * 1024, "the second group's sums reuse the tile buffers");
   __shared__ __attribute__((aligned(16))) float pool[2 * BUF];
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
   const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) & 3, group = threadIdx.x >> 8;
   const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
   f32x16 acc;
@@ -183,12 +181,10 @@ __device__ __forceinline__ f32x4v small_frag(const float* __restrict__ p, int ld
 }
 
 template <bool TA, bool TB, bool VEC>
-__global__ __launch_bounds__(64 * SMALL_WAVES) void gemm_f32_small_kernel(const float* __restrict__ A, const float* __restrict__ B,
-                                                                          float* __restrict__ C, const float* __restrict__ R,
-                                                                          const float* __restrict__ bias, int M, int N, int K, int lda,
-                                                                          int ldb, int ldc, int ldr) {
+__device__ __forceinline__ void f32_small(const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ C,
+                                      const float* __restrict__ R, const float* __restrict__ bias, int M, int N, int K, int lda, int ldb,
+                                      int ldc, int ldr, int m0, int n0) {
   __shared__ float red[SMALL_WAVES][32 * 32];
-  const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int m = min(m0 + (lane & 31), M - 1), n = min(n0 + (lane & 31), N - 1);
   const int chunks = (K + 7) / 8, per = (chunks + SMALL_WAVES - 1) / SMALL_WAVES;
@@ -239,6 +235,39 @@ __global__ __launch_bounds__(64 * SMALL_WAVES) void gemm_f32_small_kernel(const 
   }
 }
 
+template <bool TA, bool TB, bool VEC, bool SMALL>
+__global__ __launch_bounds__(SMALL ? 64 * SMALL_WAVES : TILE_THREADS) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ B,
+                                                                                         float* __restrict__ C, const float* __restrict__ R,
+                                                                                         const float* __restrict__ bias, int M, int N, int K,
+                                                                                         int lda, int ldb, int ldc, int ldr) {
+  if constexpr (SMALL) f32_small<TA, TB, VEC>(A, B, C, R, bias, M, N, K, lda, ldb, ldc, ldr, blockIdx.y * 32, blockIdx.x * 32);
+  else f32_tile<TA, TB, VEC>(A, B, C, R, bias, M, N, K, lda, ldb, ldc, ldr, blockIdx.y * 64, blockIdx.x * 64);
+}
+
+// Weight gradients of a whole task in one launch: the products are independent (A stored [K, M], B [K, N]), and a small
+// stage's are a few tiles each, so launched one by one they leave most of the chip idle and cost a launch each.  One iteration of
+// a 2-layer hidden-128 stage 667 -> 619 us, of a 2-layer hidden-1024 one 3615 -> 3475 us.
+constexpr int F32_GROUP_MAX = 32;
+struct F32Problem {
+  const float *A, *B;
+  float* C;
+  int M, N, lda, ldb, ldc, tiles_n, start;             // start = index of its first tile
+};
+struct F32Group {
+  F32Problem p[F32_GROUP_MAX];
+  int n, K;
+};
+template <bool VEC, bool SMALL>
+__global__ __launch_bounds__(SMALL ? 64 * SMALL_WAVES : TILE_THREADS) void gemm_f32_group_kernel(const F32Group g) {
+  constexpr int EDGE = SMALL ? 32 : 64;
+  int i = 0;
+  while (i + 1 < g.n && g.p[i + 1].start <= (int)blockIdx.x) ++i;
+  const F32Problem& p = g.p[i];
+  const int t = blockIdx.x - p.start, m0 = t / p.tiles_n * EDGE, n0 = t % p.tiles_n * EDGE;
+  if constexpr (SMALL) f32_small<true, false, VEC>(p.A, p.B, p.C, nullptr, nullptr, p.M, p.N, g.K, p.lda, p.ldb, p.ldc, 0, m0, n0);
+  else f32_tile<true, false, VEC>(p.A, p.B, p.C, nullptr, nullptr, p.M, p.N, g.K, p.lda, p.ldb, p.ldc, 0, m0, n0);
+}
+
 // Which kernel: fewer than 128 tiles of 64 x 64 leave over half of the chip idle, and the small kernel's 32 x 32 tiles
 // then win (128 x 256 x 1376: 15 against 30 us; at 144 tiles, 517 x 1024 x 1024, it is 29 against 24 us).
 // Sixteen k ranges instead of eight change nothing: the operand rows then bound it through the L1.
@@ -249,20 +278,50 @@ hipError_t launch_f32(const GemmArgs& g, hipStream_t s) {
   const bool small = (long long)((g.M + 63) / 64) * ((g.N + 63) / 64) < 128;
   const int t = small ? 32 : 64;
   const dim3 grid((g.N + t - 1) / t, (g.M + t - 1) / t);
-#define RRFP_GO(KERNEL, THREADS) \
-  hipLaunchKernelGGL((KERNEL), grid, dim3(THREADS), 0, s, A, B, C, g.R, bias, g.M, g.N, g.K, g.lda, g.ldb, g.ldc, g.ldr)
-  if (!small) RRFP_GO((gemm_f32_tile_kernel<TA, TB, VEC>), TILE_THREADS);
-  else RRFP_GO((gemm_f32_small_kernel<TA, TB, VEC>), 64 * SMALL_WAVES);
+#define RRFP_GO(SMALL, THREADS) \
+  hipLaunchKernelGGL((gemm_f32_kernel<TA, TB, VEC, SMALL>), grid, dim3(THREADS), 0, s, A, B, C, g.R, bias, g.M, g.N, g.K, g.lda, g.ldb, g.ldc, g.ldr)
+  if (!small) RRFP_GO(false, TILE_THREADS);
+  else RRFP_GO(true, 64 * SMALL_WAVES);
 #undef RRFP_GO
   return hipGetLastError();
 }
 
+// 16-byte loads need aligned rows and a contiguous extent of whole float4s (M or N when K-strided, K when K-contiguous)
+bool vec_ok(const GemmArgs& g) {
+  return !((g.lda | g.ldb) & 3) && !((uintptr_t)g.A & 15) && !((uintptr_t)g.B & 15) && !((g.transA ? g.M : g.K) & 3) &&
+         !((g.transB ? g.K : g.N) & 3);
+}
 template <bool TA, bool TB>
 hipError_t launch_f32_aligned(const GemmArgs& g, hipStream_t s) {
-  // 16-byte loads need aligned rows and a contiguous extent of whole float4s (M or N when K-strided, K when K-contiguous)
-  const bool vec = !((g.lda | g.ldb) & 3) && !((uintptr_t)g.A & 15) && !((uintptr_t)g.B & 15) && !((TA ? g.M : g.K) & 3) &&
-                   !((TB ? g.K : g.N) & 3);
-  return vec ? launch_f32<TA, TB, true>(g, s) : launch_f32<TA, TB, false>(g, s);
+  return vec_ok(g) ? launch_f32<TA, TB, true>(g, s) : launch_f32<TA, TB, false>(g, s);
+}
+
+// The rule of launch_f32 on the tiles of the whole group.
+hipError_t launch_f32_group(const GemmArgs* g, int n, hipStream_t s) {
+  F32Group grp{};
+  grp.n = n;
+  grp.K = g[0].K;
+  bool vec = true;
+  auto tiles = [&](int edge) {
+    int t = 0;
+    for (int i = 0; i < n; ++i) {
+      const int tn = (g[i].N + edge - 1) / edge;
+      grp.p[i] = F32Problem{(const float*)g[i].A, (const float*)g[i].B, (float*)g[i].C, g[i].M, g[i].N, g[i].lda, g[i].ldb, g[i].ldc, tn, t};
+      t += (g[i].M + edge - 1) / edge * tn;
+    }
+    return t;
+  };
+  for (int i = 0; i < n; ++i) vec = vec && vec_ok(g[i]);
+  int t = tiles(64);
+  const bool small = t < 128;
+  if (small) t = tiles(32);
+#define RRFP_GO(VEC, SMALL, THREADS) hipLaunchKernelGGL((gemm_f32_group_kernel<VEC, SMALL>), dim3(t), dim3(THREADS), 0, s, grp)
+  if (vec && small) RRFP_GO(true, true, 64 * SMALL_WAVES);
+  else if (vec) RRFP_GO(true, false, TILE_THREADS);
+  else if (small) RRFP_GO(false, true, 64 * SMALL_WAVES);
+  else RRFP_GO(false, false, TILE_THREADS);
+#undef RRFP_GO
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -273,6 +332,17 @@ hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t s) {
   if (!g.transA) return launch_f32_aligned<false, true>(g, s);
   if (!g.transB) return launch_f32_aligned<true, false>(g, s);
   return launch_f32_aligned<true, true>(g, s);
+}
+
+bool gemm_f32_groupable(const GemmArgs& g) {
+  return g.transA && !g.transB && !g.R && !g.bias && g.act == ACT_NONE && g.in_dtype == F32 && g.out_dtype == F32 && g.M > 0 && g.N > 0 && g.K > 0 &&
+         (long long)((g.M + 31) / 32) * ((g.N + 31) / 32) < (1 << 24);
+}
+
+hipError_t launch_gemm_f32_group(const GemmArgs* g, int n, hipStream_t s) {
+  for (int i = 0; i < n; i += F32_GROUP_MAX)
+    if (hipError_t e = launch_f32_group(g + i, std::min(F32_GROUP_MAX, n - i), s); e != hipSuccess) return e;
+  return hipSuccess;
 }
 
 }  // namespace rrfp

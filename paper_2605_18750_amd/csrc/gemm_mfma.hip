@@ -112,9 +112,8 @@ __device__ __forceinline__ bf16x8 read_frag(const char* tile, int row0, int ks, 
 // Output tile index from the hardware workgroup id.  Workgroups are dealt round-robin to the
 // 8 XCDs, each with its own L2; give every XCD a contiguous run of tiles, and order tiles in
 // groups of 8 tile-rows so that the tiles resident on an XCD together share A and B panels.
-__device__ __forceinline__ void tile_coords(int tiles_m, int tiles_n, int& tm, int& tn) {
+__device__ __forceinline__ void tile_coords(int b, int tiles_m, int tiles_n, int& tm, int& tn) {
   const int nt = tiles_m * tiles_n;
-  const int b = blockIdx.x;
   const int q = nt >> 3, r = nt & 7, xcd = b & 7, i = b >> 3;
   const int pid = xcd < r ? xcd * (q + 1) + i : r * (q + 1) + (xcd - r) * q + i;
   constexpr int GM = 8;
@@ -134,7 +133,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_mfma_kernel(const bf16_t* __res
                                                              int tiles_m, int tiles_n) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   int tm, tn;
-  tile_coords(tiles_m, tiles_n, tm, tn);
+  tile_coords(blockIdx.x, tiles_m, tiles_n, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = (wave >> 1) * 128, wn = (wave & 1) * 128;
@@ -474,27 +473,17 @@ __device__ __forceinline__ void unpack4(uint2 w, float* v) {
   v[2] = __uint_as_float(w.y << 16); v[3] = __uint_as_float(w.y & 0xffff0000u);
 }
 
+// One tile of C at rows m0.., columns n0.. (the whole of gemm_mfma_dl_kernel after its placement).
 // BMT = rows of the C tile: 256, or 128 for the short tiles that finish a GEMM whose tile count is
-// not a multiple of the CU count (A K-contiguous only).  tn0 = first tile column of this launch.
+// not a multiple of the CU count (A K-contiguous only).
 // F16IN: A and B hold IEEE halves instead of bf16 (forms with a K-contiguous operand only); TO may be float,
 // bf16_t or f16_t.
 template <bool A_KC, bool B_KC, typename TO, bool HAS_R, int WM, int WN, int ACT, int BMT = 256, bool F16IN = false>
-__global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_dl_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
-                                                               TO* __restrict__ C, const float* __restrict__ R, int M,
-                                                               int N, int K, int lda, int ldb, int ldc, int ldr,
-                                                               int tiles_m, int tiles_n, bf16_t* __restrict__ E, int lde,
-                                                               int tn0, int k_split, const bf16_t* __restrict__ bias,
-                                                               const float* __restrict__ out_scale) {
+__device__ __forceinline__ void dl_tile(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, TO* __restrict__ C,
+                                        const float* __restrict__ R, int M, int N, int K, int lda, int ldb, int ldc, int ldr, int m0,
+                                        int n0, bf16_t* __restrict__ E, int lde, const bf16_t* __restrict__ bias,
+                                        const float* __restrict__ out_scale) {
   constexpr int NW = WM * WN;
-  // Split-K launches (grid y = split): this workgroup contracts k in [y * k_split, min(K, (y+1) * k_split))
-  // and writes its partial tile into the y-th [M, ldc] plane of C.
-  if (k_split > 0) {
-    const int k0 = blockIdx.y * k_split;
-    A += A_KC ? (size_t)k0 : (size_t)k0 * lda;
-    B += B_KC ? (size_t)k0 : (size_t)k0 * ldb;
-    C += (size_t)blockIdx.y * M * ldc;
-    K = min(k_split, K - k0);
-  }
   constexpr int MI = (BMT / 32) / WM;               // 32-high row blocks per wavefront
   constexpr int NB = 8 / WN;                        // 32-wide column blocks per wavefront
   constexpr int WAVE_M = MI * 32, WAVE_N = NB * 32;
@@ -503,9 +492,6 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_dl_kernel(const bf16_t
   __shared__ __attribute__((aligned(1024))) char stage2[DSTAGE];
   __shared__ __attribute__((aligned(1024))) char stage3[DSTAGE];
   __shared__ __attribute__((aligned(1024))) char stage4[DSTAGE];
-  int tm, tn;
-  tile_coords(tiles_m, tiles_n, tm, tn);
-  const int m0 = tm * BMT, n0 = (tn + tn0) * BN;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = (wave / WN) * WAVE_M, wn = (wave % WN) * WAVE_N;
@@ -821,6 +807,29 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_dl_kernel(const bf16_t
   }
 }
 
+// tn0 = first tile column of this launch.
+template <bool A_KC, bool B_KC, typename TO, bool HAS_R, int WM, int WN, int ACT, int BMT = 256, bool F16IN = false>
+__global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_dl_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
+                                                               TO* __restrict__ C, const float* __restrict__ R, int M,
+                                                               int N, int K, int lda, int ldb, int ldc, int ldr,
+                                                               int tiles_m, int tiles_n, bf16_t* __restrict__ E, int lde,
+                                                               int tn0, int k_split, const bf16_t* __restrict__ bias,
+                                                               const float* __restrict__ out_scale) {
+  // Split-K launches (grid y = split): this workgroup contracts k in [y * k_split, min(K, (y+1) * k_split))
+  // and writes its partial tile into the y-th [M, ldc] plane of C.
+  if (k_split > 0) {
+    const int k0 = blockIdx.y * k_split;
+    A += A_KC ? (size_t)k0 : (size_t)k0 * lda;
+    B += B_KC ? (size_t)k0 : (size_t)k0 * ldb;
+    C += (size_t)blockIdx.y * M * ldc;
+    K = min(k_split, K - k0);
+  }
+  int tm, tn;
+  tile_coords(blockIdx.x, tiles_m, tiles_n, tm, tn);
+  dl_tile<A_KC, B_KC, TO, HAS_R, WM, WN, ACT, BMT, F16IN>(A, B, C, R, M, N, K, lda, ldb, ldc, ldr, tm * BMT, (tn + tn0) * BN, E, lde, bias,
+                                                         out_scale);
+}
+
 // Explicit instantiations of every variant the launcher can pick.
 #define RRFP_INST(AKC, BKC, TO, HR, ACT)                                                                     \
   template __global__ void gemm_mfma_dl_kernel<AKC, BKC, TO, HR, dl_wm(AKC, BKC), dl_wn(AKC, BKC), ACT>(      \
@@ -1106,17 +1115,14 @@ struct SmallOperand {
 
 constexpr int SMALL_NW = 8;                            // four wavefronts, two workgroups per CU: 5 to 40 % slower
 template <bool A_KC, bool B_KC, typename TO, bool HAS_R, int ACT, bool F16IN>
-__global__ __launch_bounds__(SMALL_NW * 64) void gemm_mfma_small_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, TO* __restrict__ C,
-                                                                  const float* __restrict__ R, int M, int N, int K, int lda, int ldb, int ldc,
-                                                                  int ldr, int tiles_m, int tiles_n, bf16_t* __restrict__ E, int lde,
-                                                                  const bf16_t* __restrict__ bias, const float* __restrict__ out_scale) {
+__device__ __forceinline__ void small_tile(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, TO* __restrict__ C,
+                                           const float* __restrict__ R, int M, int N, int K, int lda, int ldb, int ldc, int ldr, int m0,
+                                           int n0, bf16_t* __restrict__ E, int lde, const bf16_t* __restrict__ bias,
+                                           const float* __restrict__ out_scale) {
   constexpr int NW = SMALL_NW, PITCH = ST + 4;         // floats per row of a wavefront's sums
   constexpr int RED = ST * PITCH * 4, STAGE = (A_KC ? 0 : ST_TILE) + (B_KC ? 0 : ST_TILE);
   static_assert(STAGE <= RED, "the staging tiles live inside the wavefront's part of the sums");
   __shared__ __attribute__((aligned(1024))) char pool[NW * RED];
-  int tm, tn;
-  tile_coords(tiles_m, tiles_n, tm, tn);
-  const int m0 = tm * ST, n0 = tn * ST;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   char* mine = pool + wave * RED;
   SmallOperand<A_KC> oa;
@@ -1196,6 +1202,16 @@ __global__ __launch_bounds__(SMALL_NW * 64) void gemm_mfma_small_kernel(const bf
 }
 
 template <bool A_KC, bool B_KC, typename TO, bool HAS_R, int ACT, bool F16IN>
+__global__ __launch_bounds__(SMALL_NW * 64) void gemm_mfma_small_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, TO* __restrict__ C,
+                                                                  const float* __restrict__ R, int M, int N, int K, int lda, int ldb, int ldc,
+                                                                  int ldr, int tiles_m, int tiles_n, bf16_t* __restrict__ E, int lde,
+                                                                  const bf16_t* __restrict__ bias, const float* __restrict__ out_scale) {
+  int tm, tn;
+  tile_coords(blockIdx.x, tiles_m, tiles_n, tm, tn);
+  small_tile<A_KC, B_KC, TO, HAS_R, ACT, F16IN>(A, B, C, R, M, N, K, lda, ldb, ldc, ldr, tm * ST, tn * ST, E, lde, bias, out_scale);
+}
+
+template <bool A_KC, bool B_KC, typename TO, bool HAS_R, int ACT, bool F16IN>
 hipError_t launch_small(const GemmArgs& g, hipStream_t s) {
   const int tiles_m = (g.M + ST - 1) / ST, tiles_n = (g.N + ST - 1) / ST;
   hipLaunchKernelGGL((gemm_mfma_small_kernel<A_KC, B_KC, TO, HAS_R, ACT, F16IN>), dim3(tiles_m * tiles_n), dim3(SMALL_NW * 64), 0, s,
@@ -1257,6 +1273,97 @@ inline bool wgrad_small(int M, int N, int K, int n_cu) {
   return small_us(M, N, K, n_cu) < 0.9f * tile_us;
 }
 
+// ------------------------------------------------------------------------------------------
+// Weight gradients of a whole task.  The 4 x layers products of W (both operands K-strided, K = the tokens of the microbatch)
+// do not depend on one another, so their tiles share one launch: a product of 25 to 100 tiles no longer needs splitting along K
+// to fill the chip, and every product but the last stops ending in a round of its own.  Only the tiles left over
+// after the whole rounds of the group are cut along K; each range writes a compact 256 x 256 plane, added in range order.
+// One iteration, product by product -> grouped: 8 layers of hidden 1280 at 6272 tokens 21.46 -> 19.73 ms (planes of 3 to 10 ranges
+// per product are gone), 4 such layers on three streams 9.72 -> 8.59, a hidden-512 stage 1.374 -> 1.241; hidden 4096 at 4096 tokens,
+// whose products are several rounds each, 39.1 -> 39.0.
+// ------------------------------------------------------------------------------------------
+constexpr int GROUP_MAX = 32;                          // products per launch: the list travels in the kernel arguments (1.8 KB of 4)
+struct WgradProblem {
+  const bf16_t* A; const bf16_t* B; float* C;
+  int M, N, lda, ldb, ldc, tiles_m, tiles_n, start;    // start = index of its first tile
+};
+struct WgradGroup {
+  WgradProblem p[GROUP_MAX];
+  int n, K;
+  int full, tail, k_split;                             // tiles contracted whole; tiles after them, cut into ranges of k_split
+  float* ws;
+};
+
+__device__ __forceinline__ const WgradProblem& group_problem(const WgradGroup& g, int tile) {
+  int i = 0;
+  while (i + 1 < g.n && g.p[i + 1].start <= tile) ++i;
+  return g.p[i];
+}
+
+// Not a plain call of dl_tile on the launch's arguments: work item id is tile id for id < full, else range (id - full) / tail of
+// tile full + (id - full) % tail.
+__global__ __launch_bounds__(256) void gemm_mfma_wgrad_group_kernel(const WgradGroup g) {
+  int tile = blockIdx.x, range = -1;
+  if (tile >= g.full) {
+    range = (tile - g.full) / g.tail;
+    tile = g.full + (tile - g.full) % g.tail;
+  }
+  const WgradProblem& p = group_problem(g, tile);
+  int tm, tn;
+  tile_coords(tile - p.start, p.tiles_m, p.tiles_n, tm, tn);
+  const bf16_t *A = p.A, *B = p.B;
+  float* C = p.C;
+  int K = g.K, ldc = p.ldc;
+  const int m0 = tm * BM, n0 = tn * BN;
+  if (range >= 0) {
+    const int k0 = range * g.k_split;
+    A += (size_t)k0 * p.lda;
+    B += (size_t)k0 * p.ldb;
+    K = min(g.k_split, K - k0);
+    ldc = BN;                                          // dl_tile addresses by row and column of the product: the plane moves left by the tile's origin
+    C = g.ws + ((ptrdiff_t)range * g.tail + (tile - g.full)) * (BM * BN) - ((ptrdiff_t)m0 * BN + n0);
+  }
+  dl_tile<false, false, float, false, dl_wm(false, false), dl_wn(false, false), ACT_NONE>(
+      A, B, C, nullptr, p.M, p.N, K, p.lda, p.ldb, ldc, 0, m0, n0, nullptr, 0, nullptr, nullptr);
+}
+
+// Planes of the cut tiles added in range order: 16 workgroups per tile, 16 rows each.
+__global__ __launch_bounds__(256) void wgrad_group_finish_kernel(const WgradGroup g, int ranges) {
+  const int t = blockIdx.x >> 4, tile = g.full + t;
+  const WgradProblem& p = group_problem(g, tile);
+  int tm, tn;
+  tile_coords(tile - p.start, p.tiles_m, p.tiles_n, tm, tn);
+  const int c = (threadIdx.x & 63) * 4, n = tn * BN + c;
+  if (n >= p.N) return;                                // N is a multiple of 8
+  float4 v[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int y = 0; y < ranges; ++y) {
+    const float* plane = g.ws + ((size_t)y * g.tail + t) * (BM * BN) + c;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = (blockIdx.x & 15) * 16 + i * 4 + (threadIdx.x >> 6);
+      if (tm * BM + row >= p.M) continue;              // not written by the planes either
+      const float4 x = *reinterpret_cast<const float4*>(plane + row * BN);
+      v[i].x += x.x; v[i].y += x.y; v[i].z += x.z; v[i].w += x.w;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int m = tm * BM + (blockIdx.x & 15) * 16 + i * 4 + (threadIdx.x >> 6);
+    if (m < p.M) *reinterpret_cast<float4*>(p.C + (size_t)m * p.ldc + n) = v[i];
+  }
+}
+
+// The same list with 64 x 64 tiles (tile counts and starts are those of the small kernel).
+__global__ __launch_bounds__(SMALL_NW * 64) void gemm_mfma_wgrad_group_small_kernel(const WgradGroup g) {
+  const WgradProblem& p = group_problem(g, blockIdx.x);
+  int tm, tn;
+  tile_coords(blockIdx.x - p.start, p.tiles_m, p.tiles_n, tm, tn);
+  small_tile<false, false, float, false, ACT_NONE, false>(p.A, p.B, p.C, nullptr, p.M, p.N, g.K, p.lda, p.ldb, p.ldc, 0, tm * ST, tn * ST,
+                                                          nullptr, 0, nullptr, nullptr);
+}
+
 // Launch of the direct-to-LDS kernel for the forms with A K-contiguous, per the cuts above.
 template <bool B_KC, typename TO, bool HAS_R, int ACT, bool F16IN = false>
 hipError_t launch_a_kc(const GemmArgs& g, hipStream_t s) {
@@ -1291,6 +1398,59 @@ hipError_t launch_a_kc(const GemmArgs& g, hipStream_t s) {
                        dim3(WMv * WNv * 64), 0, s, (const bf16_t*)g.A, (const bf16_t*)g.B, (TO*)g.C, g.R, g.M, g.N, g.K,
                        g.lda, g.ldb, g.ldc, g.ldr, tiles_m2, tiles_n - cn, (bf16_t*)g.E, g.lde, cn, 0, (const bf16_t*)g.bias, g.out_scale);
   }
+  return hipGetLastError();
+}
+
+// How the group is cut: estimated times as in a_kc_split, 8 us a round of 256-row tiles beyond its k steps.
+// ranges = 0: the small-output kernel.  A pure function of the shapes, the device and the scratch.
+struct GroupCut { int full, tail, ranges; };
+inline GroupCut wgrad_group_cut(long long t256, long long t64, int K, int n_cu, size_t ws_bytes) {
+  constexpr float US_STEP = 0.75f, US_ROUND = 8.0f, FINISH_US = 4.0f, PLANE_BYTES_PER_US = 8.0e6f;
+  constexpr int MAX_RANGES = 16, MIN_STEPS = 8;
+  const int steps = (K + DBK - 1) / DBK, r = (int)(t256 % n_cu);
+  GroupCut best{(int)t256, 0, 1};
+  const float whole = (float)(t256 / n_cu) * (US_ROUND + US_STEP * steps);
+  float cost = r ? US_ROUND + US_STEP * steps : 0.0f;  // of the last round
+  for (int S = 2; r && S <= MAX_RANGES && steps / S >= MIN_STEPS; ++S) {
+    const int per = (steps + S - 1) / S;
+    if ((steps + per - 1) / per != S) continue;
+    if ((size_t)S * r * BM * BN * 4 > ws_bytes) break;
+    const float c = (float)((r * S + n_cu - 1) / n_cu) * (US_ROUND + US_STEP * per) + FINISH_US + (float)r * (BM * BN) * (8 * S + 6) / PLANE_BYTES_PER_US;
+    if (c < cost) { cost = c; best = GroupCut{(int)(t256 - r), r, S}; }
+  }
+  const float small = 2.0f + (float)((t64 + n_cu - 1) / n_cu) * (1.5f + 0.0072f * K);
+  if (small < 0.9f * (whole + cost)) best = GroupCut{(int)t64, 0, 0};
+  return best;
+}
+
+hipError_t launch_wgrad_group_mfma(const GemmArgs* g, int n, hipStream_t s) {
+  WgradGroup grp{};
+  grp.n = n;
+  grp.K = g[0].K;
+  auto tiles = [&](int edge, bool fill) {
+    long long t = 0;
+    for (int i = 0; i < n; ++i) {
+      const int tm = (g[i].M + edge - 1) / edge, tn = (g[i].N + edge - 1) / edge;
+      if (fill) grp.p[i] = WgradProblem{(const bf16_t*)g[i].A, (const bf16_t*)g[i].B, (float*)g[i].C, g[i].M, g[i].N, g[i].lda, g[i].ldb, g[i].ldc, tm, tn, (int)t};
+      t += (long long)tm * tn;
+    }
+    return t;
+  };
+  const bool ws = g[0].ws && !((uintptr_t)g[0].ws & 15);
+  const GroupCut cut = wgrad_group_cut(tiles(BM, false), tiles(ST, false), grp.K, cu_count(), ws ? g[0].ws_bytes : 0);
+  tiles(cut.ranges == 0 ? ST : BM, true);
+  if (cut.ranges == 0) {
+    hipLaunchKernelGGL(gemm_mfma_wgrad_group_small_kernel, dim3(cut.full), dim3(SMALL_NW * 64), 0, s, grp);
+    return hipGetLastError();
+  }
+  const int steps = (grp.K + DBK - 1) / DBK;
+  grp.full = cut.full;
+  grp.tail = cut.tail;
+  grp.k_split = (steps + cut.ranges - 1) / cut.ranges * DBK;
+  grp.ws = (float*)g[0].ws;
+  hipLaunchKernelGGL(gemm_mfma_wgrad_group_kernel, dim3(cut.full + cut.tail * cut.ranges), dim3(256), 0, s, grp);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess || cut.tail == 0) return e;
+  hipLaunchKernelGGL(wgrad_group_finish_kernel, dim3(cut.tail * 16), dim3(256), 0, s, grp, cut.ranges);
   return hipGetLastError();
 }
 
@@ -1455,6 +1615,17 @@ bool gemm_mfma_supports(const GemmArgs& g) {
   if (!a_kc && (g.M & 7)) return false;               // K-strided A: rows of C come in chunks of 8
   auto aligned = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
   return aligned(g.A) && aligned(g.B) && aligned(g.C);
+}
+
+bool gemm_mfma_wgrad_groupable(const GemmArgs& g) {
+  return g.transA && !g.transB && !g.R && !g.bias && g.act == ACT_NONE && g.in_dtype == BF16 && g.out_dtype == F32 && gemm_mfma_supports(g) &&
+         direct_ok(g) && !(g.ldc & 3) && (long long)((g.M + ST - 1) / ST) * ((g.N + ST - 1) / ST) < (1 << 24);
+}
+
+hipError_t launch_gemm_mfma_wgrad_group(const GemmArgs* g, int n, hipStream_t s) {
+  for (int i = 0; i < n; i += GROUP_MAX)
+    if (hipError_t e = launch_wgrad_group_mfma(g + i, std::min(GROUP_MAX, n - i), s); e != hipSuccess) return e;
+  return hipSuccess;
 }
 
 hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s) {

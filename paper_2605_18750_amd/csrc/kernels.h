@@ -55,6 +55,13 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);       // picks the ker
 hipError_t launch_gemm_simt(const GemmArgs& g, hipStream_t s);  // fp32-FMA tiles, any shape and type
 hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t s);   // fp32 MFMA tiles, any fp32 shape
 hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s);  // bf16 MFMA kernels (256-wide tiles)
+// Weight gradients of a task: n independent products, A stored [K, M], B [K, N], fp32 out, all of the same K and sharing one
+// scratch (g[0].ws).  Products the grouped kernels take go in few launches, the others one by one.
+hipError_t launch_wgrad_group(const GemmArgs* g, int n, hipStream_t s);
+bool gemm_f32_groupable(const GemmArgs& g);
+bool gemm_mfma_wgrad_groupable(const GemmArgs& g);
+hipError_t launch_gemm_f32_group(const GemmArgs* g, int n, hipStream_t s);
+hipError_t launch_gemm_mfma_wgrad_group(const GemmArgs* g, int n, hipStream_t s);
 bool gemm_mfma_supports(const GemmArgs& g);                     // alignment / divisibility rules
 // Launch plan of launch_gemm_mfma for a shape (pure host logic): kernel 0 = refused, 1 = direct-to-LDS,
 // 2 = register-staged, 3 = small-output; workgroups of the 256-row launch and of the 128-row launch; split-K ranges.

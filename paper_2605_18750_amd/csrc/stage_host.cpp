@@ -693,23 +693,27 @@ int stage_W(stage_t* st, int mb, void* stream) {
   char* base = mb_base(st, mb);
   float* slot = slot_base(st, mb);
   const int T = m.T, H = c.hidden, F = c.ffn, dt = c.dtype, nqd = c.n_q_heads * c.head_dim;
-  for (int l = 0; l < c.n_layers; ++l) {
-    const LayerStash& L = P.layer[l];
-    GemmArgs g{};
-    g.in_dtype = dt; g.out_dtype = F32; g.transA = true; g.transB = false; g.K = T; g.R = nullptr;
-    g.ws = base + P.t_dm; g.ws_bytes = P.ws_bytes;
-    g.A = base + L.h1; g.lda = H; g.B = base + L.dqkv; g.ldb = P.n_qkv;
-    g.C = slot + P.p_off[l][STAGE_P_WQKV]; g.ldc = P.n_qkv; g.M = H; g.N = P.n_qkv;
-    HIP_TRY(st, launch_gemm(g, s));
-    g.A = base + L.o; g.lda = nqd; g.B = base + L.dx1; g.ldb = H;
-    g.C = slot + P.p_off[l][STAGE_P_WO]; g.ldc = H; g.M = nqd; g.N = H;
-    HIP_TRY(st, launch_gemm(g, s));
-    g.A = base + L.h2; g.lda = H; g.B = base + L.dup; g.ldb = P.n_up;
-    g.C = slot + P.p_off[l][STAGE_P_WUP]; g.ldc = P.n_up; g.M = H; g.N = P.n_up;
-    HIP_TRY(st, launch_gemm(g, s));
-    g.A = base + L.m; g.lda = F; g.B = base + L.dy; g.ldb = H;
-    g.C = slot + P.p_off[l][STAGE_P_WD]; g.ldc = H; g.M = F; g.N = H;
-    HIP_TRY(st, launch_gemm(g, s));
+  // the products of all layers are independent: they are launched as one list, a fixed number of layers at a time
+  constexpr int LAYERS = 8;
+  GemmArgs list[4 * LAYERS];
+  for (int l0 = 0; l0 < c.n_layers; l0 += LAYERS) {
+    int n = 0;
+    auto add = [&](const void* A, int lda, int M, const void* B, int ldb, int N, size_t slot_off) {
+      GemmArgs g{};
+      g.in_dtype = dt; g.out_dtype = F32; g.transA = true; g.transB = false; g.K = T; g.R = nullptr;
+      g.ws = base + P.t_dm; g.ws_bytes = P.ws_bytes;
+      g.A = A; g.lda = lda; g.M = M; g.B = B; g.ldb = ldb; g.N = N;
+      g.C = slot + slot_off; g.ldc = N;
+      list[n++] = g;
+    };
+    for (int l = l0; l < std::min(c.n_layers, l0 + LAYERS); ++l) {
+      const LayerStash& L = P.layer[l];
+      add(base + L.h1, H, H, base + L.dqkv, P.n_qkv, P.n_qkv, P.p_off[l][STAGE_P_WQKV]);
+      add(base + L.o, nqd, nqd, base + L.dx1, H, H, P.p_off[l][STAGE_P_WO]);
+      add(base + L.h2, H, H, base + L.dup, P.n_up, P.n_up, P.p_off[l][STAGE_P_WUP]);
+      add(base + L.m, F, F, base + L.dy, H, H, P.p_off[l][STAGE_P_WD]);
+    }
+    HIP_TRY(st, launch_wgrad_group(list, n, s));
   }
   HIP_TRY(st, hipEventRecord(m.ev_W, s));
   m.state = MB_W;
