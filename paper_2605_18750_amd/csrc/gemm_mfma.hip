@@ -460,9 +460,34 @@ __device__ __forceinline__ void interleave_ds_vm_mfma() {
 
 // WM x WN wavefronts tile the 256x256 block; each owns (256/WM) x (256/WN).
 __device__ __forceinline__ float sigmoid_f(float z) { return 1.0f / (1.0f + __expf(-z)); }
-__device__ __forceinline__ float gelu_f(float u) { return 0.5f * u * (1.0f + erff(u * 0.70710678118654752f)); }
+// Normal distribution function of u and e = exp(-u^2/2): the lower tail Phi(-|u|) = e w, w = erfcx(|u| / sqrt 2) / 2 = 1/2 + s R(s)
+// with s = 1 / (1 + 0.3 |u| / sqrt 2) - 1 and R the degree-8 polynomial whose relative error in w is least (1.7e-8 for |u| < 13;
+// reweighted least squares against 64-bit erfcx).  The epilogues of the GELU forms are bound by this: the library's erff is
+// two expansions, both run by a wavefront whose lanes differ.  Against 64 bits (2-norm, u in -3..0 / 0..9 / -9..-3): u Phi 8e-8 / 2e-8 /
+// 4e-7, the derivative 5e-8 / 4e-8 / 2e-7; by 1 + erff 1e-7 / 2e-8 / 4e-5 and 5e-8 / 4e-8 / 3e-6 (1 + erff cancels in the lower tail).
+__device__ __forceinline__ float normal_cdf(float u, float& e) {
+  const float x = fminf(fabsf(u), 1e30f) * 0.212132034f, t = __builtin_amdgcn_rcpf(1.0f + x), s = -(x * t);
+  e = __expf(-0.5f * u * u);
+  float r = -0.0615883172f;
+  r = fmaf(r, s, -0.329083174f);
+  r = fmaf(r, s, -0.629304707f);
+  r = fmaf(r, s, -0.148489118f);
+  r = fmaf(r, s, 1.6587162f);
+  r = fmaf(r, s, 3.8503294f);
+  r = fmaf(r, s, 4.69918823f);
+  r = fmaf(r, s, 3.67486835f);
+  r = fmaf(r, s, 1.88063073f);
+  const float q = fmaf(r, s, 0.5f) * e;
+  return u < 0.0f ? q : 1.0f - q;
+}
+__device__ __forceinline__ float gelu_f(float u) {
+  float e;
+  return u * normal_cdf(u, e);
+}
 __device__ __forceinline__ float gelu_grad_f(float u) {
-  return 0.5f * (1.0f + erff(u * 0.70710678118654752f)) + u * 0.39894228040143268f * __expf(-0.5f * u * u);
+  float e;
+  const float phi = normal_cdf(u, e);
+  return fmaf(u * 0.39894228040143268f, e, phi);
 }
 __device__ __forceinline__ void load_f32x8(const float* p, float* v) {
   const float4 a = *reinterpret_cast<const float4*>(p), b = *reinterpret_cast<const float4*>(p + 4);
