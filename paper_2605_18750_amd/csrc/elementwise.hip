@@ -262,28 +262,26 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_gain_kernel(const float* __re
 }
 
 // ---------------------------------------------------------------- RMSNorm backward, fused
-// Rows and gain partials in one pass over dh and x.  A workgroup owns FUSED_ROWS consecutive rows, two
-// per wavefront; every lane keeps the running sums of dh * xhat of its own columns (NV vectors of
-// Vec<T>::N columns) in registers, the four wavefronts are added in wavefront order through LDS, and
+// Rows and gain partials in one pass over dh and x.  A workgroup owns `rows` consecutive rows (norm_bwd_rows), dealt to up to
+// four wavefronts; every lane keeps the running sums of dh * xhat of its own columns (NV vectors of
+// Vec<T>::N columns) in registers, the wavefronts are added in wavefront order through LDS, and
 // the workgroup writes one partial row.  H <= NV * 64 * Vec<T>::N and H % Vec<T>::N == 0.
-constexpr int FUSED_ROWS = 8;
-
 template <typename T, int NV>
 __global__ __launch_bounds__(256) void rmsnorm_bwd_fused_kernel(const float* __restrict__ dh, const float* __restrict__ x,
                                                                 const float* __restrict__ r, const T* __restrict__ g,
                                                                 const float* __restrict__ add_in, float* __restrict__ out32,
                                                                 T* __restrict__ out_t, float* __restrict__ partial,
-                                                                int Tn, int H) {
+                                                                int Tn, int H, int rows) {
   constexpr int V = Vec<T>::N;
-  extern __shared__ float red[];                 // [4][H]
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  extern __shared__ float red[];                 // [wavefronts][H]
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, waves = blockDim.x >> 6, per = rows / waves;
   float gsum[NV][V];
 #pragma unroll
   for (int v = 0; v < NV; ++v)
 #pragma unroll
     for (int i = 0; i < V; ++i) gsum[v][i] = 0.f;
-  for (int rr_ = 0; rr_ < FUSED_ROWS / 4; ++rr_) {
-    const int row = blockIdx.x * FUSED_ROWS + wave * (FUSED_ROWS / 4) + rr_;
+  for (int rr_ = 0; rr_ < per; ++rr_) {
+    const int row = blockIdx.x * rows + wave * per + rr_;
     if (row >= Tn) break;
     const size_t off = (size_t)row * H;
     const float rr = r[row];
@@ -371,8 +369,11 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_fused_kernel(const float* __r
     if (c < H) store_f32<V>(red + (size_t)wave * H + c, gsum[v]);
   }
   __syncthreads();
-  for (int c = threadIdx.x; c < H; c += 256)
-    partial[(size_t)blockIdx.x * H + c] = ((red[c] + red[H + c]) + red[2 * H + c]) + red[3 * H + c];
+  for (int c = threadIdx.x; c < H; c += blockDim.x) {
+    float t = red[c];
+    for (int w = 1; w < waves; ++w) t += red[(size_t)w * H + c];
+    partial[(size_t)blockIdx.x * H + c] = t;
+  }
 }
 
 // Column sums of `partial` [n_partial][H] in one fixed order: 16 contiguous slices of the rows are
@@ -770,31 +771,48 @@ hipError_t launch_rmsnorm_fwd(const float* x, const void* g, void* h, float* r_o
 
 template <typename T, int NV>
 hipError_t launch_bwd_fused(const float* dh, const float* x, const float* r, const void* g, const float* add_in,
-                            float* out32, void* out_t, float* dg_partial, int Tn, int H, hipStream_t s) {
+                            float* out32, void* out_t, float* dg_partial, int Tn, int H, int rows, hipStream_t s) {
   auto kern = rmsnorm_bwd_fused_kernel<T, NV>;
-  const size_t smem = (size_t)4 * H * sizeof(float);
+  const int waves = std::min(rows, 4);
+  const size_t smem = (size_t)waves * H * sizeof(float);
   static std::once_flag once;
   static hipError_t once_status = hipSuccess;
   if (hipError_t e = set_max_dynamic_lds_once(once, once_status, (const void*)kern, 4 * NV * WAVE * Vec<T>::N * 4); e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((Tn + FUSED_ROWS - 1) / FUSED_ROWS), dim3(256), smem, s, dh, x, r, (const T*)g, add_in, out32,
-                     (T*)out_t, dg_partial, Tn, H);
+  hipLaunchKernelGGL(kern, dim3((Tn + rows - 1) / rows), dim3(waves * WAVE), smem, s, dh, x, r, (const T*)g, add_in, out32,
+                     (T*)out_t, dg_partial, Tn, H, rows);
   return hipGetLastError();
 }
 
-int norm_bwd_partials(int Tn, int H, int dtype) {
+static bool norm_bwd_fused(int H, int dtype) {
   const int V = dtype == F32 ? 4 : 8;
-  const bool fused = (H % V) == 0 && H <= 16 * WAVE * V && (dtype != F32 || H <= 8 * WAVE * V);
-  return fused ? (Tn + FUSED_ROWS - 1) / FUSED_ROWS : (Tn + NORM_BWD_ROWS - 1) / NORM_BWD_ROWS;
+  return (H % V) == 0 && H <= 16 * WAVE * V && (dtype != F32 || H <= 8 * WAVE * V);
+}
+
+int norm_bwd_partials(int Tn, int H, int dtype, int rows) {
+  const int per = norm_bwd_fused(H, dtype) ? rows : NORM_BWD_ROWS;
+  return (Tn + per - 1) / per;
+}
+
+// A row of 4096 costs 74 KB of traffic, and one CU moves about 35 KB a microsecond: workgroups of 8 rows that do not reach every CU leave
+// the time to the few that work.  So below one workgroup per CU the rows per workgroup are halved, down to 2.  Measured, one B
+// task of 4 layers of hidden 4096 with 256 to 675 tokens, 8 rows -> this rule: 1400 -> 1336 us.  The line: 4 workgroups per CU
+// instead of one adds partial rows for nothing (4096 tokens 7.43 -> 7.52 ms a task, 3272 tokens of hidden 2048 1109 -> 1130 us); rows
+// below 1024 values are too short to matter (hidden 512: 658 against 660).
+int norm_bwd_rows(int Tn, int H, int dtype, size_t scratch_bytes) {
+  int rows = NORM_BWD_FUSED_ROWS;
+  if (H < 1024 || !norm_bwd_fused(H, dtype)) return rows;
+  while (rows > 2 && (Tn + rows - 1) / rows < device_cu_count() && (size_t)((Tn + rows / 2 - 1) / (rows / 2)) * H * 4 <= scratch_bytes) rows /= 2;
+  return rows;
 }
 
 hipError_t launch_rmsnorm_bwd(const float* dh, const float* x, const float* r, const void* g, const float* add_in,
-                              float* out32, void* out_t, float* dg_partial, int Tn, int H, int dtype, hipStream_t s) {
+                              float* out32, void* out_t, float* dg_partial, int Tn, int H, int dtype, hipStream_t s, int rows) {
   const int V = dtype == F32 ? 4 : 8;
-  if (norm_bwd_partials(Tn, H, dtype) == (Tn + FUSED_ROWS - 1) / FUSED_ROWS && (H % V) == 0) {
+  if (norm_bwd_fused(H, dtype)) {
     const int nv = (H + WAVE * V - 1) / (WAVE * V);
 #define RRFP_FUSED(NVV)                                                                                         \
   if (nv <= NVV) {                                                                                              \
-    DISPATCH_T(dtype, return (launch_bwd_fused<T, NVV>(dh, x, r, g, add_in, out32, out_t, dg_partial, Tn, H, s))); \
+    DISPATCH_T(dtype, return (launch_bwd_fused<T, NVV>(dh, x, r, g, add_in, out32, out_t, dg_partial, Tn, H, rows, s))); \
   }
     RRFP_FUSED(1) RRFP_FUSED(2) RRFP_FUSED(3) RRFP_FUSED(4) RRFP_FUSED(6) RRFP_FUSED(8)
     if (dtype != F32) { RRFP_FUSED(16) }

@@ -1551,6 +1551,8 @@ hipError_t launch_act(const GemmArgs& g, hipStream_t s) {
   return launch_a_kc<B_KC, bf16_t, false, ACT>(g, s);
 }
 
+int device_cu_count() { return cu_count(); }
+
 bool gemm_act_supported(const GemmArgs& g) {
   if (g.act == ACT_NONE) return true;
   if (!gemm_mfma_supports(g) || !direct_ok(g) || g.R || g.out_dtype != BF16 || !g.E || (g.lde & 7) ||

@@ -155,15 +155,19 @@ hipError_t launch_bf16_to_f16(const void* src, void* dst, size_t n, hipStream_t 
 
 constexpr int NORM_BWD_ROWS = 64;  // rows per partial of the gain-gradient column sum (unfused kernels)
 // Number of partial rows launch_rmsnorm_bwd writes for this shape (a pure function of shape and dtype:
-// the fused kernel writes one per 8 rows, the unfused pair one per 64).
-int norm_bwd_partials(int T, int H, int dtype);
+// the fused kernel writes one per `rows` rows, the unfused pair one per 64).
+constexpr int NORM_BWD_FUSED_ROWS = 8;
+int norm_bwd_partials(int T, int H, int dtype, int rows = NORM_BWD_FUSED_ROWS);
+// Rows per workgroup and partial row of the fused kernel (1, 2, 4 or 8) for a caller with scratch_bytes for the partial rows.
+int norm_bwd_rows(int T, int H, int dtype, size_t scratch_bytes);
+int device_cu_count();   // compute units of the current device
 // dx = add_in + r * (w - xhat * mean(w * xhat)), w = dh * g, xhat = x * r; dh, x and add_in fp32.
 // dx is written to out32 (fp32) and/or out_t (storage type); either may be null.
-// dg_partial [norm_bwd_partials(T, H, dtype), H] fp32 receives per-row-chunk sums of dh * xhat;
+// dg_partial [norm_bwd_partials(T, H, dtype, rows), H] fp32 receives per-row-chunk sums of dh * xhat;
 // launch_colsum then adds the partials in chunk order into dg [H].
 hipError_t launch_rmsnorm_bwd(const float* dh, const float* x, const float* r, const void* g,
                               const float* add_in, float* out32, void* out_t, float* dg_partial,
-                              int T, int H, int dtype, hipStream_t s);
+                              int T, int H, int dtype, hipStream_t s, int rows = NORM_BWD_FUSED_ROWS);
 hipError_t launch_colsum(const float* partial, int n_partial, int H, float* out, hipStream_t s);
 // LayerNorm (model-fidelity variant): forward saves r and mu per row; backward writes dx (+ add_in) and
 // the per-chunk partial sums of the gain and bias gradients ([colsum_chunks(T), H] each, for launch_colsum).

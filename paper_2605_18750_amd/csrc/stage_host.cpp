@@ -557,7 +557,9 @@ int stage_B(stage_t* st, int mb, const void* dy_dev, void* dx_dev, void* stream)
   char* base = mb_base(st, mb);
   float* slot = slot_base(st, mb);
   const int T = m.T, H = c.hidden, F = c.ffn, dt = c.dtype, nqd = c.n_q_heads * c.head_dim;
-  const int n_part = norm_bwd_partials(T, H, dt);
+  // RMSNorm backward: with few rows the gain partials outgrow their own array and go to the GEMM scratch, idle at that point
+  const int n_rows = norm_bwd_rows(T, H, dt, P.ws_bytes), n_part = norm_bwd_partials(T, H, dt, n_rows);
+  float* const g_part = (float*)(base + (n_rows == NORM_BWD_FUSED_ROWS ? P.t_dgp : P.t_dm));
   // one pass over dy: the fp32 head of the residual-gradient chain and the library's own copy for the GEMMs and W
   HIP_TRY(st, launch_widen(dy_dev, (float*)(base + P.layer[c.n_layers - 1].dy32), (size_t)T * H, dt, s,
                            base + P.layer[c.n_layers - 1].dy));
@@ -585,8 +587,8 @@ int stage_B(stage_t* st, int mb, const void* dy_dev, void* dx_dev, void* stream)
       HIP_TRY(st, launch_colsum((const float*)(base + P.t_dgp), n_chunk, H, slot + P.p_off[l][pg], s));
       HIP_TRY(st, launch_colsum((const float*)(base + P.t_dbp), n_chunk, H, slot + P.p_off[l][pb], s));
     } else {
-      HIP_TRY(st, launch_rmsnorm_bwd(dh, x, r, param_ptr(st, l, pg), add_in, out32, out_t, (float*)(base + P.t_dgp), T, H, dt, s));
-      HIP_TRY(st, launch_colsum((const float*)(base + P.t_dgp), n_part, H, slot + P.p_off[l][pg], s));
+      HIP_TRY(st, launch_rmsnorm_bwd(dh, x, r, param_ptr(st, l, pg), add_in, out32, out_t, g_part, T, H, dt, s, n_rows));
+      HIP_TRY(st, launch_colsum(g_part, n_part, H, slot + P.p_off[l][pg], s));
     }
     return STAGE_OK;
   };
