@@ -547,6 +547,128 @@ __global__ __launch_bounds__(256) void layernorm_bwd_rows_kernel(const float* __
   }
 }
 
+// The same for rows of whole vectors: dh and x are read once, 32 bytes per lane and every load issued before the first use, and
+// stay in registers between the sums and the result.  H <= NV * 64 * Vec<T>::N and H % Vec<T>::N == 0.
+template <typename T, int NV>
+__global__ __launch_bounds__(256) void layernorm_bwd_rows_vec_kernel(const float* __restrict__ dh, const float* __restrict__ x,
+                                                                     const float* __restrict__ r, const float* __restrict__ mu,
+                                                                     const T* __restrict__ g, const float* __restrict__ add_in,
+                                                                     float* __restrict__ out32, T* __restrict__ out_t, int Tn, int H) {
+  constexpr int V = Vec<T>::N;
+  const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (row >= Tn) return;
+  const size_t off = (size_t)row * H;
+  const float rr = r[row], m = mu[row];
+  float w[NV][V], xh[NV][V];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const int c = (v * WAVE + lane) * V;
+    if (c < H) {
+      load_f32<V>(dh + off + c, w[v]);
+      load_f32<V>(x + off + c, xh[v]);
+    }
+  }
+  float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const int c = (v * WAVE + lane) * V;
+    if (c < H) {
+      float gv[V];
+      load_vec<T>(g + c, gv);
+#pragma unroll
+      for (int i = 0; i < V; ++i) {
+        w[v][i] *= gv[i];
+        xh[v][i] = (xh[v][i] - m) * rr;
+        s1 += w[v][i];
+        s2 += w[v][i] * xh[v][i];
+      }
+    }
+  }
+  s1 = wave_sum(s1) / (float)H;
+  s2 = wave_sum(s2) / (float)H;
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const int c = (v * WAVE + lane) * V;
+    if (c < H) {
+      float o[V];
+      load_f32<V>(add_in + off + c, o);
+#pragma unroll
+      for (int i = 0; i < V; ++i) o[i] += rr * (w[v][i] - s1 - xh[v][i] * s2);
+      if (out32) store_f32<V>(out32 + off + c, o);
+      if (out_t) store_vec<T>(out_t + off + c, o);
+    }
+  }
+}
+
+// Column sums over chunks of NORM_BWD_ROWS rows, one chunk of 32 column vectors per workgroup.  One thread per column, walking its 64
+// rows, is bound by the latency of a load at a time; here eight groups of threads take eight rows each with all loads in
+// flight, and the groups are added in row order through LDS.  With the vector kernel above, one iteration of 4 layers of hidden 1280
+// with LayerNorm and biases, 2641 + 2120 tokens: 6455 -> 5518 us.
+constexpr int CS_GROUPS = 8, CS_ROWS = NORM_BWD_ROWS / CS_GROUPS, CS_VECS = 256 / CS_GROUPS;
+template <int V>
+__device__ __forceinline__ void colsum_groups(float (&acc)[V], float (*red)[CS_VECS * V], float* __restrict__ out, int c0, int n) {
+  const int cv = threadIdx.x % CS_VECS, grp = threadIdx.x / CS_VECS;
+#pragma unroll
+  for (int i = 0; i < V; ++i) red[grp][cv * V + i] = acc[i];
+  __syncthreads();
+  if (threadIdx.x < CS_VECS * V && c0 + (int)threadIdx.x < n) {
+    float t = red[0][threadIdx.x];
+#pragma unroll
+    for (int q = 1; q < CS_GROUPS; ++q) t += red[q][threadIdx.x];
+    out[c0 + threadIdx.x] = t;
+  }
+  __syncthreads();
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void colsum_rows_vec_kernel(const T* __restrict__ src, int ld, float* __restrict__ partial, int Tn, int N) {
+  constexpr int V = Vec<T>::N;
+  __shared__ float red[CS_GROUPS][CS_VECS * V];
+  const int c0 = blockIdx.x * CS_VECS * V, c = c0 + (threadIdx.x % CS_VECS) * V;
+  const int r0 = blockIdx.y * NORM_BWD_ROWS + threadIdx.x / CS_VECS * CS_ROWS;
+  float acc[V] = {}, v[CS_ROWS][V] = {};
+  if (c < N) {
+#pragma unroll
+    for (int i = 0; i < CS_ROWS; ++i)
+      if (r0 + i < Tn) load_vec<T>(src + (size_t)(r0 + i) * ld + c, v[i]);
+  }
+#pragma unroll
+  for (int i = 0; i < CS_ROWS; ++i)
+#pragma unroll
+    for (int k = 0; k < V; ++k) acc[k] += v[i][k];
+  colsum_groups<V>(acc, red, partial + (size_t)blockIdx.y * N, c0, N);
+}
+
+__global__ __launch_bounds__(256) void layernorm_bwd_partials_vec_kernel(const float* __restrict__ dh, const float* __restrict__ x,
+                                                                         const float* __restrict__ r, const float* __restrict__ mu,
+                                                                         float* __restrict__ partial_g, float* __restrict__ partial_b,
+                                                                         int Tn, int H) {
+  constexpr int V = 4;
+  __shared__ float red[CS_GROUPS][CS_VECS * V];
+  const int c0 = blockIdx.x * CS_VECS * V, c = c0 + (threadIdx.x % CS_VECS) * V;
+  const int r0 = blockIdx.y * NORM_BWD_ROWS + threadIdx.x / CS_VECS * CS_ROWS;
+  float sg[V] = {}, sb[V] = {}, d[CS_ROWS][V] = {}, xv[CS_ROWS][V] = {}, m[CS_ROWS] = {}, rr[CS_ROWS] = {};
+  if (c < H) {
+#pragma unroll
+    for (int i = 0; i < CS_ROWS; ++i)
+      if (r0 + i < Tn) {
+        load_f32<V>(dh + (size_t)(r0 + i) * H + c, d[i]);
+        load_f32<V>(x + (size_t)(r0 + i) * H + c, xv[i]);
+        m[i] = mu[r0 + i];
+        rr[i] = r[r0 + i];
+      }
+  }
+#pragma unroll
+  for (int i = 0; i < CS_ROWS; ++i)
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+      sg[k] += d[i][k] * ((xv[i][k] - m[i]) * rr[i]);
+      sb[k] += d[i][k];
+    }
+  colsum_groups<V>(sg, red, partial_g + (size_t)blockIdx.y * H, c0, H);
+  colsum_groups<V>(sb, red, partial_b + (size_t)blockIdx.y * H, c0, H);
+}
+
 // Per-chunk partial sums for the LayerNorm gain and bias gradients: partial_g[chunk][c] = sum over the
 // chunk's rows (ascending) of dh * xhat, partial_b[chunk][c] = sum of dh.  One thread per column.
 __global__ __launch_bounds__(256) void layernorm_bwd_partials_kernel(const float* __restrict__ dh, const float* __restrict__ x,
@@ -873,14 +995,35 @@ hipError_t launch_layernorm_fwd(const float* x, const void* g, const void* b, vo
 hipError_t launch_layernorm_bwd(const float* dh, const float* x, const float* r, const float* mu, const void* g,
                                 const float* add_in, float* out32, void* out_t, float* partial_g, float* partial_b,
                                 int Tn, int H, int dtype, hipStream_t s) {
-  hipLaunchKernelGGL(layernorm_bwd_partials_kernel, dim3((H + 255) / 256, colsum_chunks(Tn)), dim3(256), 0, s, dh, x, r, mu,
-                     partial_g, partial_b, Tn, H);
+  if ((H & 3) == 0)
+    hipLaunchKernelGGL(layernorm_bwd_partials_vec_kernel, dim3((H + CS_VECS * 4 - 1) / (CS_VECS * 4), colsum_chunks(Tn)), dim3(256), 0, s, dh, x,
+                       r, mu, partial_g, partial_b, Tn, H);
+  else
+    hipLaunchKernelGGL(layernorm_bwd_partials_kernel, dim3((H + 255) / 256, colsum_chunks(Tn)), dim3(256), 0, s, dh, x, r, mu,
+                       partial_g, partial_b, Tn, H);
+  // rows of whole vectors up to 4096 values (fp32 2048) stay in registers; longer and odd ones take the scalar kernel
+  const int V = dtype == F32 ? 4 : 8, nv = (H + WAVE * V - 1) / (WAVE * V);
+  auto aligned = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
+#define RRFP_LN(NVV)                                                                                                        \
+  if (nv <= NVV) {                                                                                                          \
+    DISPATCH_T(dtype, hipLaunchKernelGGL((layernorm_bwd_rows_vec_kernel<T, NVV>), dim3((Tn + 3) / 4), dim3(256), 0, s, dh, x, r, mu, \
+                                         (const T*)g, add_in, out32, (T*)out_t, Tn, H));                                    \
+    return hipGetLastError();                                                                                               \
+  }
+  if (H % V == 0 && aligned(out_t) && aligned(out32) && aligned(g)) { RRFP_LN(1) RRFP_LN(3) RRFP_LN(8) }
+#undef RRFP_LN
   DISPATCH_T(dtype, hipLaunchKernelGGL(layernorm_bwd_rows_kernel<T>, dim3((Tn + 3) / 4), dim3(256), 0, s, dh, x, r, mu,
                                        (const T*)g, add_in, out32, (T*)out_t, Tn, H));
   return hipGetLastError();
 }
 
 hipError_t launch_colsum_rows(const void* src, int ld, float* partial, int Tn, int N, int dtype, hipStream_t s) {
+  const int V = dtype == F32 ? 4 : 8;
+  if (N % V == 0 && ld % V == 0 && ((uintptr_t)src & 15) == 0) {
+    DISPATCH_T(dtype, hipLaunchKernelGGL(colsum_rows_vec_kernel<T>, dim3((N + CS_VECS * V - 1) / (CS_VECS * V), colsum_chunks(Tn)), dim3(256), 0, s,
+                                         (const T*)src, ld, partial, Tn, N));
+    return hipGetLastError();
+  }
   DISPATCH_T(dtype, hipLaunchKernelGGL(colsum_rows_kernel<T>, dim3((N + 255) / 256, colsum_chunks(Tn)), dim3(256), 0, s,
                                        (const T*)src, ld, partial, Tn, N));
   return hipGetLastError();
