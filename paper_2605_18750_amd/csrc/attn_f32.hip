@@ -12,7 +12,9 @@
 // A workgroup has four wavefronts of 16 rows (queries in the forward and dQ kernels, keys in the dK/dV kernel); the
 // other side streams through LDS in steps of 32 rows, double buffered, the next step's global loads in flight under
 // the current one's MFMAs.  The grid has one workgroup per 64-row sub-tile of the host's tiles, so that small stages
-// still spread over the chip.  Bound by the fp32 matrix rate (157 TFLOP/s) once the sequences are long enough, by the
+// still spread over the chip: heads in grid x (sub-tiles there and heads in y were 2.5 % slower on an iteration of the shape
+// below), sub-tiles in y and, past 65535 of them (many segments of a few tokens), in z.  Bound by the fp32 matrix rate (157
+// TFLOP/s) once the sequences are long enough, by the
 // latency of the key loop before that.  16 query / 4 KV heads of 64, T = 1024 in segments of 300 and 724 (average with a
 // second microbatch of 517): forward 42 us, dQ 49, dK/dV 62 + 5 for the planes; the fp32-FMA kernels that were here before:
 // 2050, 3235 and 10281 us (one LDS read per FMA, and one workgroup per 128 keys of a KV head for the whole group).
@@ -102,19 +104,21 @@ __device__ __forceinline__ void cols_times_scores(f32x4v (&out)[F32Cfg<D>::NS], 
 
 struct SubTile { int r0, r1, s0, s1; };
 // Sub-tile of SUB rows; r0 >= r1: nothing to do.
-__device__ __forceinline__ SubTile sub_tile(const AttnTile* __restrict__ tiles, int per_tile) {
-  const AttnTile t = tiles[blockIdx.y / per_tile];
-  const int r0 = t.r0 + (int)(blockIdx.y % per_tile) * SUB;
+__device__ __forceinline__ SubTile sub_tile(const AttnTile* __restrict__ tiles, int n_tiles, int per_tile) {
+  const int i = (int)(blockIdx.z * gridDim.y + blockIdx.y);
+  if (i >= n_tiles * per_tile) return SubTile{0, 0, 0, 0};
+  const AttnTile t = tiles[i / per_tile];
+  const int r0 = t.r0 + i % per_tile * SUB;
   return SubTile{r0, min(r0 + SUB, t.r1), t.s0, t.s1};
 }
 
 // ------------------------------------------------------------------------- forward
 template <int D>
 __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(const float* __restrict__ qkv, float* __restrict__ o, float* __restrict__ lse,
-                                                           const AttnTile* __restrict__ tiles, int Tn, int nq, int nkv, int causal) {
+                                                           const AttnTile* __restrict__ tiles, int n_tiles, int Tn, int nq, int nkv, int causal) {
   constexpr int NS = F32Cfg<D>::NS;
   __shared__ __attribute__((aligned(16))) float sk[2][STEP * F32Cfg<D>::PITCH], sv[2][STEP * F32Cfg<D>::PITCH];
-  const SubTile tl = sub_tile(tiles, ATTN_TILE_Q / SUB);
+  const SubTile tl = sub_tile(tiles, n_tiles, ATTN_TILE_Q / SUB);
   if (tl.r0 >= tl.r1) return;
   const int a = blockIdx.x, b = a / (nq / nkv);
   const int ld = (nq + 2 * nkv) * D;
@@ -214,11 +218,11 @@ __global__ __launch_bounds__(256) void attn_delta_f32_kernel(const float* __rest
 template <int D>
 __global__ __launch_bounds__(256) void attn_dq_f32_kernel(const float* __restrict__ qkv, const float* __restrict__ d_o,
                                                           const float* __restrict__ lse, const float* __restrict__ delta,
-                                                          float* __restrict__ dqkv, const AttnTile* __restrict__ tiles, int Tn, int nq,
+                                                          float* __restrict__ dqkv, const AttnTile* __restrict__ tiles, int n_tiles, int Tn, int nq,
                                                           int nkv, int causal) {
   constexpr int NS = F32Cfg<D>::NS;
   __shared__ __attribute__((aligned(16))) float sk[2][STEP * F32Cfg<D>::PITCH], sv[2][STEP * F32Cfg<D>::PITCH];
-  const SubTile tl = sub_tile(tiles, ATTN_TILE_Q / SUB);
+  const SubTile tl = sub_tile(tiles, n_tiles, ATTN_TILE_Q / SUB);
   if (tl.r0 >= tl.r1) return;
   const int a = blockIdx.x, b = a / (nq / nkv);
   const int ld = (nq + 2 * nkv) * D;
@@ -280,12 +284,12 @@ __global__ __launch_bounds__(256) void attn_dq_f32_kernel(const float* __restric
 template <int D>
 __global__ __launch_bounds__(256) void attn_dkv_f32_kernel(const float* __restrict__ qkv, const float* __restrict__ d_o,
                                                            const float* __restrict__ lse, const float* __restrict__ delta,
-                                                           float* __restrict__ dqkv, const AttnTile* __restrict__ tiles, int Tn, int nq,
+                                                           float* __restrict__ dqkv, const AttnTile* __restrict__ tiles, int n_tiles, int Tn, int nq,
                                                            int nkv, int causal, float* __restrict__ part) {
   constexpr int NS = F32Cfg<D>::NS;
   __shared__ __attribute__((aligned(16))) float sq[2][STEP * F32Cfg<D>::PITCH], sd[2][STEP * F32Cfg<D>::PITCH];
   __shared__ __attribute__((aligned(16))) float stat[2][2 * STEP];      // lse, delta of the step's rows
-  const SubTile tl = sub_tile(tiles, ATTN_TILE_KV / SUB);
+  const SubTile tl = sub_tile(tiles, n_tiles, ATTN_TILE_KV / SUB);
   if (tl.r0 >= tl.r1) return;
   const int a = blockIdx.x, G = nq / nkv, b = a / G;
   const int ld = (nq + 2 * nkv) * D;
@@ -373,10 +377,15 @@ __global__ __launch_bounds__(256) void dkv_combine_f32_kernel(const float* __res
   }
 }
 
+dim3 sub_tile_grid(int nq, int n) {
+  const int z = (n + 65534) / 65535;
+  return dim3(nq, (n + z - 1) / z, z);
+}
+
 template <int D>
 hipError_t fwd_launch(const AttnArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(attn_fwd_f32_kernel<D>, dim3(a.nq, a.n_q_tiles * (ATTN_TILE_Q / SUB)), dim3(256), 0, s, (const float*)a.qkv, (float*)a.o,
-                     a.lse, a.q_tiles, a.T, a.nq, a.nkv, a.causal);
+  hipLaunchKernelGGL(attn_fwd_f32_kernel<D>, sub_tile_grid(a.nq, a.n_q_tiles * (ATTN_TILE_Q / SUB)), dim3(256), 0, s, (const float*)a.qkv, (float*)a.o,
+                     a.lse, a.q_tiles, a.n_q_tiles, a.T, a.nq, a.nkv, a.causal);
   return hipGetLastError();
 }
 
@@ -385,13 +394,13 @@ hipError_t bwd_launch(const AttnArgs& a, hipStream_t s) {
   float* part = a.nq > a.nkv ? a.dkv_part : nullptr;
   hipLaunchKernelGGL(attn_delta_f32_kernel, dim3((a.T * a.nq + 15) / 16), dim3(256), 0, s, (const float*)a.o, (const float*)a.d_o, a.delta, a.T,
                      a.nq, a.d);
-  hipLaunchKernelGGL(attn_dkv_f32_kernel<D>, dim3(a.nq, a.n_kv_tiles * (ATTN_TILE_KV / SUB)), dim3(256), 0, s, (const float*)a.qkv,
-                     (const float*)a.d_o, a.lse, a.delta, (float*)a.dqkv, a.kv_tiles, a.T, a.nq, a.nkv, a.causal, part);
+  hipLaunchKernelGGL(attn_dkv_f32_kernel<D>, sub_tile_grid(a.nq, a.n_kv_tiles * (ATTN_TILE_KV / SUB)), dim3(256), 0, s, (const float*)a.qkv,
+                     (const float*)a.d_o, a.lse, a.delta, (float*)a.dqkv, a.kv_tiles, a.n_kv_tiles, a.T, a.nq, a.nkv, a.causal, part);
   if (part)
     hipLaunchKernelGGL(dkv_combine_f32_kernel, dim3((unsigned)(((size_t)a.T * a.nkv * D / 4 + 255) / 256)), dim3(256), 0, s, part,
                        (float*)a.dqkv, a.T, a.nq, a.nkv, D, 1.0f / sqrtf((float)D));
-  hipLaunchKernelGGL(attn_dq_f32_kernel<D>, dim3(a.nq, a.n_q_tiles * (ATTN_TILE_Q / SUB)), dim3(256), 0, s, (const float*)a.qkv,
-                     (const float*)a.d_o, a.lse, a.delta, (float*)a.dqkv, a.q_tiles, a.T, a.nq, a.nkv, a.causal);
+  hipLaunchKernelGGL(attn_dq_f32_kernel<D>, sub_tile_grid(a.nq, a.n_q_tiles * (ATTN_TILE_Q / SUB)), dim3(256), 0, s, (const float*)a.qkv,
+                     (const float*)a.d_o, a.lse, a.delta, (float*)a.dqkv, a.q_tiles, a.n_q_tiles, a.T, a.nq, a.nkv, a.causal);
   return hipGetLastError();
 }
 

@@ -52,3 +52,13 @@ def test_f32_attention_tile_edges(d, causal, nq, nkv):
     print(f"[f32 attention] d{d} causal{causal} heads {nq}/{nkv}", flush=True)
     worst = Hp.compare(Hp.run_gpu(w), Hp.run_oracle(w), Hp.TOL["fp32"], f"d{d}")
     print(f"[f32 attention] d{d}: worst {worst:.2e}", flush=True)
+
+
+def test_f32_attention_many_segments():
+    """33 000 segments of one or two tokens: 132 000 sub-tiles of queries and 66 000 of keys, more than the 65 535 workgroups a
+    grid takes in y."""
+    shape = SI.StageShape("f32manysegments", 1, 32, 2, 1, 16, 32, 1, dtype="fp32", x_std=1.0, dy_std=1.0, w_std=0.15)
+    w = Hp.Workload(shape, [[0] + [int(v) for v in np.cumsum(1 + np.arange(33000) % 2)]])
+    print(f"[f32 attention] {len(w.cus[0]) - 1} segments, {w.cus[0][-1]} tokens", flush=True)
+    worst = Hp.compare(Hp.run_gpu(w), Hp.run_oracle(w), Hp.TOL["fp32"], "many segments")
+    print(f"[f32 attention] many segments: worst {worst:.2e}", flush=True)
