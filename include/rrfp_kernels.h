@@ -33,30 +33,43 @@ int rrfp_gemm(const void* A, const void* B, void* C, const void* R, int M, int N
               int ldb, int ldc, int ldr, int trans_a, int trans_b, int in_dtype, int out_dtype,
               int family, void* stream);
 
-/* rrfp_gemm with a caller-owned device workspace (256-byte aligned, contents undefined afterwards), as the W task
- * calls it: with a workspace the weight-gradient form (bf16 inputs, trans_a = 1, trans_b = 0, fp32 output, no
- * residual) may split the contraction into ranges that write partial planes into the workspace and are added in
- * range order (rrfp_gemm_plan with have_scratch = 1 tells which shapes do); so may the forms with A K-contiguous when
- * their tiles would leave the chip idle.  A workspace too small for a shape's
- * split simply disables the split.  The result is bit-identical from call to call for a given shape, workspace
- * size class and device. */
+/* rrfp_gemm with a caller-owned device workspace (256-byte aligned, contents undefined afterwards), as the F and B tasks
+ * call it: with a workspace the forms with A K-contiguous may split the contraction into ranges that write partial planes
+ * into the workspace and are added in range order, or run in 64 x 64 tiles, when their tiles would leave the chip idle; so
+ * may the weight-gradient form (bf16 inputs, trans_a = 1, trans_b = 0, fp32 output, no residual).  Without a workspace a call
+ * keeps the cut and the bits of the unsplit tiles.  A workspace too small for the ranges a shape would take gives fewer
+ * ranges, 64 x 64 tiles or no split (rrfp_gemm_plan_ws tells which).  The result is bit-identical from call to call for a
+ * given shape, plan and device. */
 int rrfp_gemm_ws(const void* A, const void* B, void* C, const void* R, int M, int N, int K, int lda, int ldb,
                  int ldc, int ldr, int trans_a, int trans_b, int in_dtype, int out_dtype, int family,
                  void* workspace, size_t workspace_bytes, void* stream);
 
 /* How the bf16 MFMA GEMM cuts a shape into launches on a device with n_cu compute units: host logic only
- * (no GPU call, no pointers; operands are taken as 16-byte aligned).  The cut is a pure function of the
+ * (no GPU call, no pointers; operands are taken as 16-byte aligned; have_scratch: with as much workspace as it
+ * would use).  The cut is a pure function of the
  * shape and n_cu, which is what keeps the summation order of a call fixed (the bit-exactness requirement
  * behind readiness-driven reordering, paper Section 7.1).  out[0] = kernel (0 the MFMA family refuses the
- * shape, 1 direct-to-LDS, 2 register-staged, 3 the 64 x 64 tiles of small outputs, with scratch only), out[1] = wavefronts per workgroup, out[2] = workgroups of
- * the 256-row-tile (kernel 3: only) launch, out[3] = workgroups of the second launch that finishes a grid whose last round
- * would be nearly empty (128-row tiles when A is K-contiguous; for the weight-gradient form with scratch the
+ * shape, 1 direct-to-LDS, 2 register-staged, 3 the 64 x 64 tiles of small outputs, with scratch only), out[1] =
+ * wavefronts per workgroup, out[2] = workgroups of the 256-row-tile (kernel 3: only) launch, out[3] = workgroups of
+ * the second launch that finishes a grid whose last round would be nearly empty (128-row tiles when A is K-contiguous; for the weight-gradient form with scratch the
  * trailing tile columns split along K into out[4] ranges), out[4] = split-K ranges (weight-gradient form with
  * scratch: of the whole grid when out[3] = 0, of the tail launch otherwise; A K-contiguous with scratch: of the
  * whole grid, whose tiles are counted in out[2] or, with 128 rows, in out[3]; 1 = none).
  * Returns STAGE_OK or STAGE_EINVAL. */
 int rrfp_gemm_plan(int M, int N, int K, int lda, int ldb, int ldc, int trans_a, int trans_b, int out_dtype,
                    int have_scratch, int n_cu, int32_t out[5]);
+
+/* rrfp_gemm_plan for a call with workspace_bytes of workspace (0 = none): what rrfp_gemm_ws does with that many bytes. */
+int rrfp_gemm_plan_ws(int M, int N, int K, int lda, int ldb, int ldc, int trans_a, int trans_b, int out_dtype,
+                      size_t workspace_bytes, int n_cu, int32_t out[5]);
+
+/* How the weight gradients of a W task (paper Section 7.1) are cut: n products (at most 32) of M[i] x N[i], contracted over the
+ * same K tokens, in one launch.  Pure host logic.  out[0] = tiles of 256 x 256 contracted whole, out[1] = tiles after them
+ * that are cut along K, out[2] = the ranges they are cut into (1: none, 0: the whole list runs in 64 x 64 tiles, out[0] of
+ * them).  Each range writes a 256 x 256 fp32 plane per tile into the workspace; ranges that do not fit are not made.
+ * STAGE_EINVAL for NULL or non-positive arguments and for a product the grouped kernel does not take (M or N not a
+ * multiple of 8, operands of 2 GiB). */
+int rrfp_wgrad_group_plan(int n, const int32_t* M, const int32_t* N, int K, size_t workspace_bytes, int n_cu, int32_t out[3]);
 
 /* Launch plan of the attention backward's dK/dV kernel, pure host logic (no HIP call): the number of workgroups that
  * share the query heads of one KV head.  A workgroup of that kernel owns 128 keys of a KV head; with grouped query

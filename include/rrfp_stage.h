@@ -130,6 +130,10 @@ int stage_query(const stage_config* cfg /*host*/, size_t* param_bytes /*host*/,
 int stage_param_layout(const stage_config* cfg /*host*/, int layer, int which,
                        size_t* offset_elems /*host*/, int64_t shape[2] /*host*/);
 
+/* Bytes of the matrix-product scratch every microbatch has in the arena (what rrfp_gemm_plan_ws and rrfp_wgrad_group_plan of
+ * rrfp_kernels.h take as workspace_bytes to tell how the stage's products are cut).  Pure host. */
+int stage_scratch_bytes(const stage_config* cfg /*host*/, size_t* bytes /*host*/);
+
 /* Creates a stage.  params_dev: device, param_bytes, caller-owned, read-only to the library
  * and must stay valid and unchanged while tasks are in flight.  arena_dev: device, at least
  * arena_bytes (STAGE_ENOMEM otherwise), 256-byte aligned, caller-owned, contents managed by

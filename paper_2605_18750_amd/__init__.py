@@ -61,6 +61,12 @@ def lib() -> C.CDLL:
         L.rrfp_gemm_ws.restype = C.c_int
         L.rrfp_gemm_plan.argtypes = [C.c_int] * 11 + [C.POINTER(C.c_int32)]
         L.rrfp_gemm_plan.restype = C.c_int
+        L.rrfp_gemm_plan_ws.argtypes = [C.c_int] * 9 + [sz, C.c_int, C.POINTER(C.c_int32)]
+        L.rrfp_gemm_plan_ws.restype = C.c_int
+        L.rrfp_wgrad_group_plan.argtypes = [C.c_int] + [C.POINTER(C.c_int32)] * 2 + [C.c_int, sz, C.c_int, C.POINTER(C.c_int32)]
+        L.rrfp_wgrad_group_plan.restype = C.c_int
+        L.stage_scratch_bytes.argtypes = [cfgp, C.POINTER(sz)]
+        L.stage_scratch_bytes.restype = C.c_int
         L.rrfp_attn_dkv_subsets.argtypes = [C.c_int] * 4
         L.rrfp_attn_dkv_subsets.restype = C.c_int
         L.rrfp_rmsnorm_fwd.argtypes = [vp, vp, vp, vp, C.c_int, C.c_int, C.c_float, C.c_int, vp]
@@ -113,6 +119,13 @@ def stage_query(cfg: stage_config):
     a, b, c = C.c_size_t(), C.c_size_t(), C.c_size_t()
     _check(lib().stage_query(C.byref(cfg), C.byref(a), C.byref(b), C.byref(c)))
     return a.value, b.value, c.value
+
+
+def stage_scratch_bytes(cfg: stage_config) -> int:
+    """Bytes of the matrix-product scratch of one microbatch."""
+    n = C.c_size_t()
+    _check(lib().stage_scratch_bytes(C.byref(cfg), C.byref(n)))
+    return n.value
 
 
 def stage_param_layout(cfg: stage_config, layer: int, which: int):
@@ -193,17 +206,31 @@ def rrfp_attn_dkv_subsets(n_q_heads, n_kv_heads, n_kv_tiles, n_cu=256):
     return rc
 
 
-def rrfp_gemm_plan(M, N, K, trans_a, trans_b, out_dtype, n_cu=256, have_scratch=False, lda=None, ldb=None, ldc=None):
+def rrfp_gemm_plan(M, N, K, trans_a, trans_b, out_dtype, n_cu=256, have_scratch=False, lda=None, ldb=None, ldc=None, workspace_bytes=None):
     """Launch plan of the bf16 MFMA GEMM for a shape (host logic only, no GPU): dict with kernel
-    (0 refused, 1 direct-to-LDS, 2 register-staged), wavefronts, main_workgroups, short_workgroups, split_k."""
+    (0 refused, 1 direct-to-LDS, 2 register-staged), wavefronts, main_workgroups, short_workgroups, split_k.  workspace_bytes given: the plan with that much scratch, else with none or (have_scratch) any amount."""
     lda = (M if trans_a else K) if lda is None else lda
     ldb = (K if trans_b else N) if ldb is None else ldb
     ldc = N if ldc is None else ldc
     out = (C.c_int32 * 5)()
-    rc = lib().rrfp_gemm_plan(M, N, K, lda, ldb, ldc, int(trans_a), int(trans_b), out_dtype, int(have_scratch), n_cu, out)
+    if workspace_bytes is None:
+        rc = lib().rrfp_gemm_plan(M, N, K, lda, ldb, ldc, int(trans_a), int(trans_b), out_dtype, int(have_scratch), n_cu, out)
+    else:
+        rc = lib().rrfp_gemm_plan_ws(M, N, K, lda, ldb, ldc, int(trans_a), int(trans_b), out_dtype, workspace_bytes, n_cu, out)
     if rc != STAGE_OK:
         raise StageError(rc, "rrfp_gemm_plan rejected its arguments")
     return dict(zip(("kernel", "wavefronts", "main_workgroups", "short_workgroups", "split_k"), (int(v) for v in out)))
+
+
+def rrfp_wgrad_group_plan(products, K, workspace_bytes=1 << 62, n_cu=256):
+    """Cut of the weight gradients [(M, N), ...] over K tokens in one launch: dict with full, tail, ranges."""
+    n = len(products)
+    Ms, Ns = (C.c_int32 * n)(*[p[0] for p in products]), (C.c_int32 * n)(*[p[1] for p in products])
+    out = (C.c_int32 * 3)()
+    rc = lib().rrfp_wgrad_group_plan(n, Ms, Ns, K, workspace_bytes, n_cu, out)
+    if rc != STAGE_OK:
+        raise StageError(rc, "rrfp_wgrad_group_plan rejected its arguments")
+    return dict(zip(("full", "tail", "ranges"), (int(v) for v in out)))
 
 
 def _kcheck(rc: int, name: str):

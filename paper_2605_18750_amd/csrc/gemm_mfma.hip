@@ -1307,7 +1307,7 @@ inline bool wgrad_small(int M, int N, int K, int n_cu) {
 // per product are gone), 4 such layers on three streams 9.72 -> 8.59, a hidden-512 stage 1.374 -> 1.241; hidden 4096 at 4096 tokens,
 // whose products are several rounds each, 39.1 -> 39.0.
 // ------------------------------------------------------------------------------------------
-constexpr int GROUP_MAX = 32;                          // products per launch: the list travels in the kernel arguments (1.8 KB of 4)
+constexpr int GROUP_MAX = WGRAD_GROUP_MAX;             // the list travels in the kernel arguments (1.8 KB of 4)
 struct WgradProblem {
   const bf16_t* A; const bf16_t* B; float* C;
   int M, N, lda, ldb, ldc, tiles_m, tiles_n, start;    // start = index of its first tile
@@ -1448,22 +1448,23 @@ inline GroupCut wgrad_group_cut(long long t256, long long t64, int K, int n_cu, 
   return best;
 }
 
+// Tiles of edge x edge of all products of a group.
+inline long long group_tiles(const GemmArgs* g, int n, int edge) {
+  long long t = 0;
+  for (int i = 0; i < n; ++i) t += (long long)((g[i].M + edge - 1) / edge) * ((g[i].N + edge - 1) / edge);
+  return t;
+}
+
 hipError_t launch_wgrad_group_mfma(const GemmArgs* g, int n, hipStream_t s) {
   WgradGroup grp{};
   grp.n = n;
   grp.K = g[0].K;
-  auto tiles = [&](int edge, bool fill) {
-    long long t = 0;
-    for (int i = 0; i < n; ++i) {
-      const int tm = (g[i].M + edge - 1) / edge, tn = (g[i].N + edge - 1) / edge;
-      if (fill) grp.p[i] = WgradProblem{(const bf16_t*)g[i].A, (const bf16_t*)g[i].B, (float*)g[i].C, g[i].M, g[i].N, g[i].lda, g[i].ldb, g[i].ldc, tm, tn, (int)t};
-      t += (long long)tm * tn;
-    }
-    return t;
-  };
   const bool ws = g[0].ws && !((uintptr_t)g[0].ws & 15);
-  const GroupCut cut = wgrad_group_cut(tiles(BM, false), tiles(ST, false), grp.K, cu_count(), ws ? g[0].ws_bytes : 0);
-  tiles(cut.ranges == 0 ? ST : BM, true);
+  const GroupCut cut = wgrad_group_cut(group_tiles(g, n, BM), group_tiles(g, n, ST), grp.K, cu_count(), ws ? g[0].ws_bytes : 0);
+  const int edge = cut.ranges == 0 ? ST : BM;
+  for (int i = 0; i < n; ++i)
+    grp.p[i] = WgradProblem{(const bf16_t*)g[i].A, (const bf16_t*)g[i].B, (float*)g[i].C, g[i].M, g[i].N, g[i].lda, g[i].ldb, g[i].ldc,
+                            (g[i].M + edge - 1) / edge, (g[i].N + edge - 1) / edge, (int)group_tiles(g, i, edge)};
   if (cut.ranges == 0) {
     hipLaunchKernelGGL(gemm_mfma_wgrad_group_small_kernel, dim3(cut.full), dim3(SMALL_NW * 64), 0, s, grp);
     return hipGetLastError();
@@ -1567,9 +1568,9 @@ bool gemm_act_supported(const GemmArgs& g) {
   }
 }
 
-// How launch_gemm_mfma would cut g (without an activation) on a device with n_cu compute units: the same
-// decisions as the launchers above, without touching the device.
-GemmPlan gemm_mfma_plan(const GemmArgs& g, int n_cu, bool have_scratch) {
+// How launch_gemm_mfma would cut g (without an activation) on a device with n_cu compute units and ws_bytes of scratch: the
+// same decisions as the launchers above, without touching the device.
+GemmPlan gemm_mfma_plan(const GemmArgs& g, int n_cu, size_t ws_bytes) {
   GemmPlan p{};
   if (!gemm_mfma_supports(g)) return p;
   const bool a_kc = !g.transA, b_kc = g.transB;
@@ -1589,7 +1590,7 @@ GemmPlan gemm_mfma_plan(const GemmArgs& g, int n_cu, bool have_scratch) {
     return p;
   };
   if (a_kc) {
-    const KSplit ks = a_kc_split(g.M, g.N, g.K, n_cu, have_scratch ? ~(size_t)0 : 0);
+    const KSplit ks = a_kc_split(g.M, g.N, g.K, n_cu, ws_bytes);
     if (ks.ranges == 0) return small_plan();
     if (ks.ranges > 1) {
       const int wgs = (g.M + ks.tile_rows - 1) / ks.tile_rows * tiles_n;
@@ -1604,15 +1605,15 @@ GemmPlan gemm_mfma_plan(const GemmArgs& g, int n_cu, bool have_scratch) {
     return p;
   }
   p.main_workgroups = tiles_m * tiles_n;
-  if (!b_kc && !g.R && g.out_dtype == F32 && have_scratch) {
+  if (!b_kc && !g.R && g.out_dtype == F32 && ws_bytes > 0) {
     if (wgrad_small(g.M, g.N, g.K, n_cu)) return small_plan();
     const int S = (g.ldc == g.N && ((size_t)g.M * g.N) % 4 == 0) ? splitk_factor(tiles_m * tiles_n, g.K, n_cu) : 1;
-    if (S > 1) {
+    if (S > 1 && (size_t)S * g.M * g.N * 4 <= ws_bytes) {
       const int steps = (g.K + DBK - 1) / DBK, k_split = (steps + S - 1) / S * DBK;
       p.split_k = (g.K + k_split - 1) / k_split;
     } else {
       const int cn = wgrad_full_tile_columns(g, tiles_m, tiles_n, n_cu, true);
-      if (cn < tiles_n) {   // plain launch over cn tile columns + a tail launch split along K
+      if (cn < tiles_n && wgrad_tail_scratch_bytes(g, cn) <= ws_bytes) {   // plain launch over cn tile columns + a tail launch split along K
         p.main_workgroups = tiles_m * cn;
         p.short_workgroups = tiles_m * (tiles_n - cn) * TAIL_SPLIT;
         p.split_k = TAIL_SPLIT;
@@ -1647,6 +1648,11 @@ bool gemm_mfma_supports(const GemmArgs& g) {
 bool gemm_mfma_wgrad_groupable(const GemmArgs& g) {
   return g.transA && !g.transB && !g.R && !g.bias && g.act == ACT_NONE && g.in_dtype == BF16 && g.out_dtype == F32 && gemm_mfma_supports(g) &&
          direct_ok(g) && !(g.ldc & 3) && (long long)((g.M + ST - 1) / ST) * ((g.N + ST - 1) / ST) < (1 << 24);
+}
+
+WgradGroupPlan gemm_mfma_wgrad_group_plan(const GemmArgs* g, int n, int n_cu, size_t ws_bytes) {
+  const GroupCut cut = wgrad_group_cut(group_tiles(g, n, BM), group_tiles(g, n, ST), g[0].K, n_cu, ws_bytes);
+  return WgradGroupPlan{cut.full, cut.tail, cut.ranges, cut.ranges > 1 ? (size_t)cut.ranges * cut.tail * BM * BN * 4 : 0};
 }
 
 hipError_t launch_gemm_mfma_wgrad_group(const GemmArgs* g, int n, hipStream_t s) {

@@ -37,13 +37,31 @@ extern "C" int rrfp_gemm_ws(const void* A, const void* B, void* C, const void* R
 
 extern "C" int rrfp_gemm_plan(int M, int N, int K, int lda, int ldb, int ldc, int trans_a, int trans_b, int out_dtype,
                               int have_scratch, int n_cu, int32_t out[5]) {
+  return rrfp_gemm_plan_ws(M, N, K, lda, ldb, ldc, trans_a, trans_b, out_dtype, have_scratch ? ~(size_t)0 : 0, n_cu, out);
+}
+
+extern "C" int rrfp_gemm_plan_ws(int M, int N, int K, int lda, int ldb, int ldc, int trans_a, int trans_b, int out_dtype,
+                                 size_t workspace_bytes, int n_cu, int32_t out[5]) {
   if (!out || M < 1 || N < 1 || K < 1 || n_cu < 1) return STAGE_EINVAL;
   if (out_dtype != F32 && out_dtype != BF16) return STAGE_EINVAL;
   GemmArgs g{};
   g.M = M; g.N = N; g.K = K; g.lda = lda; g.ldb = ldb; g.ldc = ldc; g.ldr = ldc;
   g.transA = trans_a != 0; g.transB = trans_b != 0; g.in_dtype = BF16; g.out_dtype = out_dtype;
-  const GemmPlan p = gemm_mfma_plan(g, n_cu, have_scratch != 0);
+  const GemmPlan p = gemm_mfma_plan(g, n_cu, workspace_bytes);
   out[0] = p.kernel; out[1] = p.wavefronts; out[2] = p.main_workgroups; out[3] = p.short_workgroups; out[4] = p.split_k;
+  return STAGE_OK;
+}
+
+extern "C" int rrfp_wgrad_group_plan(int n, const int32_t* M, const int32_t* N, int K, size_t workspace_bytes, int n_cu, int32_t out[3]) {
+  if (!M || !N || !out || n < 1 || n > WGRAD_GROUP_MAX || K < 1 || n_cu < 1) return STAGE_EINVAL;
+  GemmArgs g[WGRAD_GROUP_MAX] = {};
+  for (int i = 0; i < n; ++i) {
+    g[i].M = M[i]; g[i].N = N[i]; g[i].K = K; g[i].lda = M[i]; g[i].ldb = g[i].ldc = N[i];
+    g[i].transA = true; g[i].in_dtype = BF16; g[i].out_dtype = F32;
+    if (!gemm_mfma_wgrad_groupable(g[i])) return STAGE_EINVAL;
+  }
+  const WgradGroupPlan p = gemm_mfma_wgrad_group_plan(g, n, n_cu, workspace_bytes);
+  out[0] = p.full; out[1] = p.tail; out[2] = p.ranges;
   return STAGE_OK;
 }
 

@@ -66,7 +66,12 @@ bool gemm_mfma_supports(const GemmArgs& g);                     // alignment / d
 // Launch plan of launch_gemm_mfma for a shape (pure host logic): kernel 0 = refused, 1 = direct-to-LDS,
 // 2 = register-staged, 3 = small-output; workgroups of the 256-row launch and of the 128-row launch; split-K ranges.
 struct GemmPlan { int kernel, wavefronts, main_workgroups, short_workgroups, split_k; };
-GemmPlan gemm_mfma_plan(const GemmArgs& g, int n_cu, bool have_scratch);
+GemmPlan gemm_mfma_plan(const GemmArgs& g, int n_cu, size_t ws_bytes);
+// The same for a list of weight gradients that go in one launch: tiles contracted whole, tiles after them that are cut along K
+// and into how many ranges (1 = none; 0: the whole list in 64 x 64 tiles), bytes of their partial planes.
+constexpr int WGRAD_GROUP_MAX = 32;   // products per launch
+struct WgradGroupPlan { int full, tail, ranges; size_t plane_bytes; };
+WgradGroupPlan gemm_mfma_wgrad_group_plan(const GemmArgs* g, int n, int n_cu, size_t ws_bytes);
 
 // One attention work item: a tile of rows [r0, r1) inside the segment [s0, s1).  kb0 = number of 32-key blocks in
 // the segments before this one (each segment rounded up): the segment's first block row in the dS scratch.

@@ -321,6 +321,15 @@ int stage_param_layout(const stage_config* cfg, int layer, int which, size_t* of
   return STAGE_OK;
 }
 
+int stage_scratch_bytes(const stage_config* cfg, size_t* bytes) {
+  Plan p;
+  int rc = make_plan(cfg, &p);
+  if (rc) return rc;
+  if (!bytes) { set_tls_error("bytes is NULL"); return STAGE_EINVAL; }
+  *bytes = p.ws_bytes;
+  return STAGE_OK;
+}
+
 int stage_create_dry(const stage_config* cfg, stage_t** out) {
   stage_t* st = nullptr;
   int rc = create_common(cfg, out, &st);

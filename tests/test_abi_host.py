@@ -203,3 +203,43 @@ def test_dkv_head_subsets_are_a_pure_function_of_shape():
     assert R.rrfp_attn_dkv_subsets(6, 2, 1) == 3 and R.rrfp_attn_dkv_subsets(16, 2, 1) == 4 and R.rrfp_attn_dkv_subsets(10, 2, 1) == 1
     assert R.rrfp_attn_dkv_subsets(64, 8, 32, n_cu=128) == 1
     _expect(R.STAGE_EINVAL, R.rrfp_attn_dkv_subsets, 6, 4, 1)
+
+
+def _task_products(H, nq, nkv, d, F, layers, swiglu=True):
+    """(M, N) of the weight gradients of a W task, in the order the stage lists them."""
+    return [(H, (nq + 2 * nkv) * d), (nq * d, H), (H, (2 if swiglu else 1) * F), (F, H)] * layers
+
+
+def test_wgrad_group_plan():
+    """The cut of all weight gradients of a W task: a pure function of the shapes, the tokens, the CU count and (only where the
+    planes do not fit) the workspace."""
+    language = _task_products(4096, 32, 32, 128, 11008, 4)
+    # 12352 tiles = 48 rounds + 64 tiles, which four ranges spread over all CUs; short contractions are not worth planes
+    assert R.rrfp_wgrad_group_plan(language, 4096) == dict(full=12288, tail=64, ranges=4)
+    assert R.rrfp_wgrad_group_plan(language, 512) == dict(full=12352, tail=0, ranges=1)
+    # 8 layers of hidden 1280: 2400 tiles = 9 rounds + 96
+    assert R.rrfp_wgrad_group_plan(_task_products(1280, 16, 16, 80, 5120, 8, swiglu=False), 6272) == dict(full=2304, tail=96, ranges=2)
+    # less than a round: everything is cut; small outputs: 64 x 64 tiles
+    assert R.rrfp_wgrad_group_plan(_task_products(832, 13, 1, 64, 1600, 1), 2100) == dict(full=0, tail=112, ranges=2)
+    assert R.rrfp_wgrad_group_plan(_task_products(64, 1, 1, 64, 64, 8), 33) == dict(full=56, tail=0, ranges=0)
+    # a plane is 256 KB: one byte less than four of 64 tiles leaves three
+    assert R.rrfp_wgrad_group_plan(language, 4096, workspace_bytes=4 * 64 * 262144)["ranges"] == 4
+    assert R.rrfp_wgrad_group_plan(language, 4096, workspace_bytes=4 * 64 * 262144 - 1)["ranges"] == 3
+    assert R.rrfp_wgrad_group_plan(language, 4096, workspace_bytes=0) == dict(full=12352, tail=0, ranges=1)
+    assert R.rrfp_wgrad_group_plan(language, 4096, n_cu=64) == dict(full=12352, tail=0, ranges=1)       # whole rounds
+    for bad in ([(60, 64)], [(64, 60)], [(0, 64)], [(64, 64)] * 33):
+        _expect(R.STAGE_EINVAL, R.rrfp_wgrad_group_plan, bad, 100)
+
+
+def test_gemm_plan_with_a_limited_workspace():
+    """A workspace too small for a split leaves fewer ranges, the 64 x 64 tiles (which need no bytes of it) or the unsplit launch."""
+    F32 = R.STAGE_DTYPE_FP32
+    plan = lambda ws: R.rrfp_gemm_plan(512, 4096, 22016, 0, 1, F32, workspace_bytes=ws)
+    plane = 512 * 4096 * 4
+    assert plan(8 * plane) == R.rrfp_gemm_plan(512, 4096, 22016, 0, 1, F32, have_scratch=True) and plan(8 * plane)["split_k"] == 8
+    assert 1 < plan(8 * plane - 1)["split_k"] < 8
+    assert plan(2 * plane - 1)["kernel"] == 3 and plan(0) == R.rrfp_gemm_plan(512, 4096, 22016, 0, 1, F32)
+    assert R.rrfp_gemm_plan(777, 1024, 512, 0, 0, F32, workspace_bytes=1)["kernel"] == 3
+    # weight-gradient form: no planes, no split of a 25-tile grid; no room for the tail's planes, no tail
+    assert R.rrfp_gemm_plan(1280, 1280, 6272, 1, 0, F32, workspace_bytes=1 << 20)["split_k"] == 1
+    assert R.rrfp_gemm_plan(4096, 22016, 4096, 1, 0, F32, workspace_bytes=1 << 20) == R.rrfp_gemm_plan(4096, 22016, 4096, 1, 0, F32)
