@@ -91,6 +91,11 @@ int rrfp_attn_dkv_subsets(int n_q_heads, int n_kv_heads, int n_kv_tiles, int n_c
 int rrfp_rmsnorm_fwd(const float* x, const void* g, void* h, float* r_out, int T, int H, float eps, int dtype,
                      void* stream);
 
+/* Rows of [T,H] a workgroup of the RMSNorm backward takes inside a B task (each workgroup leaves one partial gain row, added in
+ * order: a pure function of shape and n_cu): 8, or 4 or 2 where 8 would not give every CU a workgroup.  STAGE_EINVAL for
+ * non-positive arguments or an unknown dtype.  rrfp_rmsnorm_bwd below always takes 8. */
+int rrfp_rmsnorm_bwd_rows(int T, int H, int dtype, int n_cu);
+
 /* Bytes of workspace rrfp_rmsnorm_bwd needs for this shape (partial gain-gradient rows); pure host. */
 size_t rrfp_rmsnorm_bwd_workspace(int T, int H, int dtype);
 

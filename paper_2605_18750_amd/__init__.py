@@ -71,6 +71,8 @@ def lib() -> C.CDLL:
         L.rrfp_attn_dkv_subsets.restype = C.c_int
         L.rrfp_rmsnorm_fwd.argtypes = [vp, vp, vp, vp, C.c_int, C.c_int, C.c_float, C.c_int, vp]
         L.rrfp_rmsnorm_fwd.restype = C.c_int
+        L.rrfp_rmsnorm_bwd_rows.argtypes = [C.c_int] * 4
+        L.rrfp_rmsnorm_bwd_rows.restype = C.c_int
         L.rrfp_rmsnorm_bwd_workspace.argtypes = [C.c_int, C.c_int, C.c_int]
         L.rrfp_rmsnorm_bwd_workspace.restype = sz
         L.rrfp_rmsnorm_bwd.argtypes = [vp] * 9 + [sz, C.c_int, C.c_int, C.c_int, vp]
@@ -240,6 +242,14 @@ def _kcheck(rc: int, name: str):
 
 def rrfp_rmsnorm_fwd(x, g, h, r_out, T: int, H: int, eps: float, dtype: int, stream=None):
     _kcheck(lib().rrfp_rmsnorm_fwd(_ptr(x), _ptr(g), _ptr(h), _ptr(r_out), T, H, eps, dtype, _stream(stream)), "rrfp_rmsnorm_fwd")
+
+
+def rrfp_rmsnorm_bwd_rows(T: int, H: int, dtype: int, n_cu: int = 256) -> int:
+    """Rows per workgroup of the RMSNorm backward of a stage (pure host logic)."""
+    rows = lib().rrfp_rmsnorm_bwd_rows(T, H, dtype, n_cu)
+    if rows < 1:
+        raise StageError(rows, "rrfp_rmsnorm_bwd_rows rejected its arguments")
+    return rows
 
 
 def rrfp_rmsnorm_bwd_workspace(T: int, H: int, dtype: int) -> int:

@@ -969,11 +969,16 @@ int norm_bwd_partials(int Tn, int H, int dtype, int rows) {
 // task of 4 layers of hidden 4096 with 256 to 675 tokens, 8 rows -> this rule: 1400 -> 1336 us.  The line: 4 workgroups per CU
 // instead of one adds partial rows for nothing (4096 tokens 7.43 -> 7.52 ms a task, 3272 tokens of hidden 2048 1109 -> 1130 us); rows
 // below 1024 values are too short to matter (hidden 512: 658 against 660).
-int norm_bwd_rows(int Tn, int H, int dtype, size_t scratch_bytes) {
+constexpr int NORM_BWD_MAX_CUS = 256;   // of the chip: bounds the partial rows
+int norm_bwd_rows(int Tn, int H, int dtype, int n_cu) {
   int rows = NORM_BWD_FUSED_ROWS;
   if (H < 1024 || !norm_bwd_fused(H, dtype)) return rows;
-  while (rows > 2 && (Tn + rows - 1) / rows < device_cu_count() && (size_t)((Tn + rows / 2 - 1) / (rows / 2)) * H * 4 <= scratch_bytes) rows /= 2;
+  while (rows > 2 && (Tn + rows - 1) / rows < std::min(n_cu, NORM_BWD_MAX_CUS)) rows /= 2;
   return rows;
+}
+size_t norm_bwd_few_rows_bytes(int Tn, int H, int dtype) {
+  if (H < 1024 || !norm_bwd_fused(H, dtype)) return 0;
+  return (size_t)std::min((Tn + 1) / 2, 2 * NORM_BWD_MAX_CUS) * H * 4;   // halving less than a workgroup per CU gives less than two
 }
 
 hipError_t launch_rmsnorm_bwd(const float* dh, const float* x, const float* r, const void* g, const float* add_in,

@@ -1253,9 +1253,11 @@ inline float small_us(int M, int N, int K, int n_cu) {
   return 2.0f + (float)((t + n_cu - 1) / n_cu) * (1.5f + 0.0072f * K);
 }
 
-// Cut along K of a form with A K-contiguous: ranges == 0 means the small-output kernel, ranges > 1 tiles of tile_rows x 256, each contracted in `ranges` pieces whose
-// fp32 planes go to the scratch and are added by splitk_finish_kernel, ranges == 1 the launches of full_tile_columns.
-// A pure function of the shape, the device and the scratch.
+// Cut along K of a form with A K-contiguous: ranges == 0 means the small-output kernel, ranges > 1 tiles of tile_rows x 256,
+// each contracted in `ranges` pieces whose fp32 planes go to the scratch and are added by splitk_finish_kernel, ranges == 1 the
+// launches of full_tile_columns.  A pure function of the shape and the device for a caller whose scratch holds the planes (a
+// stage's always does: gemm_mfma_plane_bytes); a smaller one gives the best cut that fits.  A call without scratch keeps the
+// unsplit tiles and their bits, also where the small-output kernel, which needs none, would be faster.  tiles_only: without that kernel.
 //
 // A workgroup takes 0.75 us per 32-deep step with 256-row tiles and 0.55 us with 128-row ones, whether it shares the chip
 // with 31 or 255 others (operands from HBM), so a grid of t tiles leaves the rest of the chip idle for K / 32 of those
@@ -1265,26 +1267,27 @@ inline float small_us(int M, int N, int K, int n_cu) {
 // 512 x 12288 x 4096 74 -> 60 (2);
 // 2048 x 4096 x 4096 would go 70 -> 78 and stays unsplit.
 struct KSplit { int tile_rows, ranges; };
-inline KSplit a_kc_split(int M, int N, int K, int n_cu, size_t ws_bytes) {
+inline KSplit a_kc_split(int M, int N, int K, int n_cu, size_t ws_bytes, bool tiles_only = false) {
   constexpr float US_256 = 0.75f, US_128 = 0.55f, BASE_US = 4.0f, FINISH_US = 4.0f, PLANE_BYTES_PER_US = 8.0e6f;
   constexpr int MAX_RANGES = 12, MIN_STEPS = 8;
   const int steps = (K + DBK - 1) / DBK;
-  const long long tn = (N + BN - 1) / BN, t256 = (M + 255) / 256 * tn, t128 = (M + 127) / 128 * tn;
-  auto rounds = [&](long long wgs) { return (float)((wgs + n_cu - 1) / n_cu); };
+  const long long tn = (N + BN - 1) / BN;
   KSplit best{256, 1};
-  if (ws_bytes == 0 || t256 > n_cu) return best;   // without scratch, or several rounds of full tiles
-  float cost = (2 * t256 <= n_cu ? rounds(t128) * US_128 : US_256) * steps;
+  if (ws_bytes == 0 || (M + 255) / 256 * tn > n_cu) return best;   // without scratch, or several rounds of full tiles
+  const unsigned t256 = (unsigned)((M + 255) / 256 * tn), t128 = (unsigned)((M + 127) / 128 * tn), cus = (unsigned)n_cu;
+  auto rounds = [&](unsigned wgs) { return (float)((wgs + cus - 1) / cus); };
+  float cost = (2 * t256 <= cus ? rounds(t128) * US_128 : US_256) * steps;
   const float mn = (float)M * (float)N;
   for (int S = 2; S <= MAX_RANGES && steps / S >= MIN_STEPS; ++S) {
-    const int per = (steps + S - 1) / S, s_eff = (steps + per - 1) / per;
-    if (s_eff != S) continue;
+    const int per = (steps + S - 1) / S;
+    if (per * (S - 1) >= steps) continue;            // fewer ranges of that depth hold all steps
     if ((size_t)S * M * N * 4 > ws_bytes) break;
     const float finish = FINISH_US + mn * (8 * S + 6) / PLANE_BYTES_PER_US;
     const float c256 = rounds(t256 * S) * per * US_256 + finish, c128 = rounds(t128 * S) * per * US_128 + finish;
     if (c256 < cost) { cost = c256; best = KSplit{256, S}; }
     if (c128 < cost) { cost = c128; best = KSplit{128, S}; }
   }
-  if (small_us(M, N, K, n_cu) < cost + BASE_US) best = KSplit{ST, 0};
+  if (!tiles_only && small_us(M, N, K, n_cu) < cost + BASE_US) best = KSplit{ST, 0};
   return best;
 }
 
@@ -1438,9 +1441,9 @@ inline GroupCut wgrad_group_cut(long long t256, long long t64, int K, int n_cu, 
   float cost = r ? US_ROUND + US_STEP * steps : 0.0f;  // of the last round
   for (int S = 2; r && S <= MAX_RANGES && steps / S >= MIN_STEPS; ++S) {
     const int per = (steps + S - 1) / S;
-    if ((steps + per - 1) / per != S) continue;
+    if (per * (S - 1) >= steps) continue;            // fewer ranges of that depth hold all steps
     if ((size_t)S * r * BM * BN * 4 > ws_bytes) break;
-    const float c = (float)((r * S + n_cu - 1) / n_cu) * (US_ROUND + US_STEP * per) + FINISH_US + (float)r * (BM * BN) * (8 * S + 6) / PLANE_BYTES_PER_US;
+    const float c = (float)((unsigned)(r * S + n_cu - 1) / (unsigned)n_cu) * (US_ROUND + US_STEP * per) + FINISH_US + (float)r * (BM * BN) * (8 * S + 6) / PLANE_BYTES_PER_US;
     if (c < cost) { cost = c; best = GroupCut{(int)(t256 - r), r, S}; }
   }
   const float small = 2.0f + (float)((t64 + n_cu - 1) / n_cu) * (1.5f + 0.0072f * K);
@@ -1648,6 +1651,28 @@ bool gemm_mfma_supports(const GemmArgs& g) {
 bool gemm_mfma_wgrad_groupable(const GemmArgs& g) {
   return g.transA && !g.transB && !g.R && !g.bias && g.act == ACT_NONE && g.in_dtype == BF16 && g.out_dtype == F32 && gemm_mfma_supports(g) &&
          direct_ok(g) && !(g.ldc & 3) && (long long)((g.M + ST - 1) / ST) * ((g.N + ST - 1) / ST) < (1 << 24);
+}
+
+// The rows enter the cut through the counts of 128- and 256-row tiles and, smoothly, through the cost of adding the planes,
+// which only speaks for fewer ranges as the rows grow: within 128 rows the first one takes the most ranges.
+size_t gemm_mfma_plane_bytes(int max_M, int N, int K, int n_cu) {
+  size_t most = 0;
+  for (int M = 1; M <= max_M && (long long)((M + 255) / 256) * ((N + BN - 1) / BN) <= n_cu; M += 128) {
+    const KSplit ks = a_kc_split(M, N, K, n_cu, ~(size_t)0, true);
+    if (ks.ranges > 1) most = std::max(most, (size_t)ks.ranges * std::min(M + 127, max_M) * N * 4);
+  }
+  return most;
+}
+
+// Of the lengths of one 32-deep step the longest is the last to go to the 64 x 64 tiles; else the cut is that of the step.
+size_t gemm_mfma_wgrad_plane_bytes(const GemmArgs* g, int n, int min_K, int max_K, int n_cu) {
+  const long long t256 = group_tiles(g, n, BM), t64 = group_tiles(g, n, ST);
+  size_t most = 0;
+  for (int step = (min_K - 1) / DBK; step * DBK < max_K; ++step) {
+    const GroupCut cut = wgrad_group_cut(t256, t64, std::min((step + 1) * DBK, max_K), n_cu, ~(size_t)0);
+    if (cut.ranges > 1) most = std::max(most, (size_t)cut.ranges * cut.tail * BM * BN * 4);
+  }
+  return most;
 }
 
 WgradGroupPlan gemm_mfma_wgrad_group_plan(const GemmArgs* g, int n, int n_cu, size_t ws_bytes) {

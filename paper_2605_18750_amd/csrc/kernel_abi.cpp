@@ -77,6 +77,11 @@ extern "C" int rrfp_attn_dkv_subsets(int n_q_heads, int n_kv_heads, int n_kv_til
   return attn_dkv_subsets(n_q_heads, n_kv_heads, n_kv_tiles, n_cu);
 }
 
+extern "C" int rrfp_rmsnorm_bwd_rows(int T, int H, int dtype, int n_cu) {
+  if (T < 1 || H < 1 || n_cu < 1 || (dtype != F32 && dtype != BF16)) return STAGE_EINVAL;
+  return norm_bwd_rows(T, H, dtype, n_cu);
+}
+
 extern "C" size_t rrfp_rmsnorm_bwd_workspace(int T, int H, int dtype) {
   if (T < 1 || H < 1 || (dtype != F32 && dtype != BF16)) return 0;
   return (size_t)norm_bwd_partials(T, H, dtype) * (size_t)H * sizeof(float);

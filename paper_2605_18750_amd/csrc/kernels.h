@@ -65,12 +65,18 @@ hipError_t launch_gemm_mfma_wgrad_group(const GemmArgs* g, int n, hipStream_t s)
 bool gemm_mfma_supports(const GemmArgs& g);                     // alignment / divisibility rules
 // Launch plan of launch_gemm_mfma for a shape (pure host logic): kernel 0 = refused, 1 = direct-to-LDS,
 // 2 = register-staged, 3 = small-output; workgroups of the 256-row launch and of the 128-row launch; split-K ranges.
+// Bytes of partial planes that the cut of a form with A K-contiguous asks for at any M up to max_M, at most.
+size_t gemm_mfma_plane_bytes(int max_M, int N, int K, int n_cu);
 struct GemmPlan { int kernel, wavefronts, main_workgroups, short_workgroups, split_k; };
 GemmPlan gemm_mfma_plan(const GemmArgs& g, int n_cu, size_t ws_bytes);
 // The same for a list of weight gradients that go in one launch: tiles contracted whole, tiles after them that are cut along K
 // and into how many ranges (1 = none; 0: the whole list in 64 x 64 tiles), bytes of their partial planes.
 constexpr int WGRAD_GROUP_MAX = 32;   // products per launch
 struct WgradGroupPlan { int full, tail, ranges; size_t plane_bytes; };
+// The same over every K up to max_K, and over n_counts CU counts, for a list as launch_wgrad_group takes it (K of its products is
+// overwritten).
+size_t wgrad_group_plane_bytes(GemmArgs* g, int n, int max_K, const int* n_cu, int n_counts);
+size_t gemm_mfma_wgrad_plane_bytes(const GemmArgs* g, int n, int min_K, int max_K, int n_cu);   // one launch of that list
 WgradGroupPlan gemm_mfma_wgrad_group_plan(const GemmArgs* g, int n, int n_cu, size_t ws_bytes);
 
 // One attention work item: a tile of rows [r0, r1) inside the segment [s0, s1).  kb0 = number of 32-key blocks in
@@ -163,8 +169,10 @@ constexpr int NORM_BWD_ROWS = 64;  // rows per partial of the gain-gradient colu
 // the fused kernel writes one per `rows` rows, the unfused pair one per 64).
 constexpr int NORM_BWD_FUSED_ROWS = 8;
 int norm_bwd_partials(int T, int H, int dtype, int rows = NORM_BWD_FUSED_ROWS);
-// Rows per workgroup and partial row of the fused kernel (1, 2, 4 or 8) for a caller with scratch_bytes for the partial rows.
-int norm_bwd_rows(int T, int H, int dtype, size_t scratch_bytes);
+// Rows per workgroup and partial row of the fused kernel inside a B task (2, 4 or 8), and the bytes of the partial rows that
+// 2 and 4 rows give at any T up to this one (8 rows: norm_bwd_partials).
+int norm_bwd_rows(int T, int H, int dtype, int n_cu);
+size_t norm_bwd_few_rows_bytes(int T, int H, int dtype);
 int device_cu_count();   // compute units of the current device
 // dx = add_in + r * (w - xhat * mean(w * xhat)), w = dh * g, xhat = x * r; dh, x and add_in fp32.
 // dx is written to out32 (fp32) and/or out_t (storage type); either may be null.

@@ -11,6 +11,7 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <utility>
 #include <vector>
 
 using namespace rrfp;
@@ -52,8 +53,9 @@ struct Plan {
   size_t param_elems;
   std::vector<LayerStash> layer;
   size_t t_dh, t_do, t_delta, t_dgp, t_dbp, t_qtiles, t_kvtiles;  // per-microbatch temporaries
-  // GEMM scratch of a microbatch (split-K planes of F, B and W): t_dm, B's fp32 temporary of an unfused activation backward,
-  // and directly behind it t_ds.  Both are idle outside the one kernel or the two attention kernels of B that use them.
+  // GEMM scratch of a microbatch (split-K planes of F, B and W, partial gain rows of B): t_dm, B's fp32 temporary of an unfused
+  // activation backward, directly behind it t_ds, both idle outside the one kernel or the two attention kernels of B that use
+  // them, and as much more as scratch_need asks for.
   size_t t_dm, ws_bytes;
   size_t t_ds;               // dS scratch of the MFMA attention backward (0 when that path cannot run)
   int ds_rows, ds_nqs;
@@ -68,6 +70,21 @@ struct Plan {
   size_t w16o_off[64];              // the same for Wo
   size_t arena_bytes;
 };
+
+// The weight gradients of `layers` layers in the order W lists them: sizes, types and leading dimensions, no pointers and no K.
+constexpr int W_LAYERS = 8;       // layers per list
+int wgrad_list(const Plan& p, int layers, GemmArgs* list) {
+  const int H = p.c.hidden, F = p.c.ffn, nqd = p.c.n_q_heads * p.c.head_dim;
+  const int shapes[4][2] = {{H, p.n_qkv}, {nqd, H}, {H, p.n_up}, {F, H}};
+  for (int i = 0; i < 4 * layers; ++i) {
+    GemmArgs g{};
+    g.in_dtype = p.c.dtype; g.out_dtype = F32; g.transA = true;
+    g.M = g.lda = shapes[i & 3][0];
+    g.N = g.ldb = g.ldc = shapes[i & 3][1];
+    list[i] = g;
+  }
+  return 4 * layers;
+}
 
 int check_config(const stage_config* c) {
   if (!c) { set_tls_error("config is NULL"); return STAGE_EINVAL; }
@@ -102,7 +119,28 @@ int check_config(const stage_config* c) {
   return STAGE_OK;
 }
 
-int make_plan(const stage_config* c, Plan* p) {
+// Scratch with which every cut of every microbatch of up to max_tokens tokens is the one its own shape asks for: the planes
+// of the products of F, B and W and the partial rows of the RMSNorm backward.  Without it the cut, and so the summation
+// order, of a microbatch would hang on max_tokens and max_segments.  The chip whole and in its equal partitions.
+size_t scratch_need(const stage_config* c, const Plan* p) {
+  const int T = c->max_tokens, H = c->hidden, F = c->ffn, nqd = c->n_q_heads * c->head_dim;
+  size_t need = c->norm_kind == 0 ? norm_bwd_few_rows_bytes(T, H, c->dtype) : 0;
+  if (c->dtype != STAGE_DTYPE_BF16) return need;
+  std::pair<int, int> forms[8] = {{p->n_qkv, H}, {H, nqd}, {p->n_up, H}, {H, F}, {F, H}, {H, p->n_up}, {nqd, H}, {H, p->n_qkv}};   // N, K
+  std::sort(forms, forms + 8);
+  const auto* const end = std::unique(forms, forms + 8);
+  constexpr int cus[4] = {256, 128, 64, 32};
+  for (int n_cu : cus)
+    for (const auto* f = forms; f != end; ++f) need = std::max(need, gemm_mfma_plane_bytes(T, f->first, f->second, n_cu));
+  GemmArgs list[4 * W_LAYERS];
+  const int lists[2] = {std::min(c->n_layers, W_LAYERS), c->n_layers > W_LAYERS ? c->n_layers % W_LAYERS : 0};   // layers of the full and of the last one
+  for (int layers : lists)
+    if (layers) need = std::max(need, wgrad_group_plane_bytes(list, wgrad_list(*p, layers, list), T, cus, 4));
+  return need;
+}
+
+// layout_only: the parameter layout, without the arena.
+int make_plan(const stage_config* c, Plan* p, bool layout_only = false) {
   int rc = check_config(c);
   if (rc) return rc;
   p->c = *c;
@@ -127,6 +165,7 @@ int make_plan(const stage_config* c, Plan* p) {
     }
   p->param_elems = off;
   p->slot_floats = off;
+  if (layout_only) return STAGE_OK;
 
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t r = o; o += align_up(bytes); return r; };
@@ -175,6 +214,8 @@ int make_plan(const stage_config* c, Plan* p) {
     p->ds_nqs = attn_ds_nqs((int)T);
     p->t_dm = take(T * F * 4);     // fp32: GEMM outputs that only an elementwise kernel consumes are not rounded
     p->t_ds = attn_mfma_supports(probe) ? take(attn_ds_bytes((int)T, c->max_segments, (int)nq)) : 0;
+    const size_t need = scratch_need(c, p);
+    if (o - p->t_dm < need) take(need - (o - p->t_dm));
     p->ws_bytes = o - p->t_dm;
     const size_t part = attn_dkv_part_bytes((int)T, (int)nq, (int)nkv, (int)d, c->dtype);
     p->t_dkvp = part ? take(part) : 0;
@@ -310,7 +351,7 @@ int stage_query(const stage_config* cfg, size_t* param_bytes, size_t* grad_bytes
 
 int stage_param_layout(const stage_config* cfg, int layer, int which, size_t* offset_elems, int64_t shape[2]) {
   Plan p;
-  int rc = make_plan(cfg, &p);
+  int rc = make_plan(cfg, &p, true);
   if (rc) return rc;
   if (layer < 0 || layer >= cfg->n_layers || which < 0 || which >= STAGE_P_COUNT) {
     set_tls_error("layer %d / tensor %d out of range", layer, which);
@@ -567,7 +608,7 @@ int stage_B(stage_t* st, int mb, const void* dy_dev, void* dx_dev, void* stream)
   float* slot = slot_base(st, mb);
   const int T = m.T, H = c.hidden, F = c.ffn, dt = c.dtype, nqd = c.n_q_heads * c.head_dim;
   // RMSNorm backward: with few rows the gain partials outgrow their own array and go to the GEMM scratch, idle at that point
-  const int n_rows = norm_bwd_rows(T, H, dt, P.ws_bytes), n_part = norm_bwd_partials(T, H, dt, n_rows);
+  const int n_rows = norm_bwd_rows(T, H, dt, device_cu_count()), n_part = norm_bwd_partials(T, H, dt, n_rows);
   float* const g_part = (float*)(base + (n_rows == NORM_BWD_FUSED_ROWS ? P.t_dgp : P.t_dm));
   // one pass over dy: the fp32 head of the residual-gradient chain and the library's own copy for the GEMMs and W
   HIP_TRY(st, launch_widen(dy_dev, (float*)(base + P.layer[c.n_layers - 1].dy32), (size_t)T * H, dt, s,
@@ -703,26 +744,21 @@ int stage_W(stage_t* st, int mb, void* stream) {
   HIP_TRY(st, hipStreamWaitEvent(s, m.ev_B, 0));
   char* base = mb_base(st, mb);
   float* slot = slot_base(st, mb);
-  const int T = m.T, H = c.hidden, F = c.ffn, dt = c.dtype, nqd = c.n_q_heads * c.head_dim;
   // the products of all layers are independent: they are launched as one list, a fixed number of layers at a time
-  constexpr int LAYERS = 8;
-  GemmArgs list[4 * LAYERS];
-  for (int l0 = 0; l0 < c.n_layers; l0 += LAYERS) {
-    int n = 0;
-    auto add = [&](const void* A, int lda, int M, const void* B, int ldb, int N, size_t slot_off) {
-      GemmArgs g{};
-      g.in_dtype = dt; g.out_dtype = F32; g.transA = true; g.transB = false; g.K = T; g.R = nullptr;
-      g.ws = base + P.t_dm; g.ws_bytes = P.ws_bytes;
-      g.A = A; g.lda = lda; g.M = M; g.B = B; g.ldb = ldb; g.N = N;
-      g.C = slot + slot_off; g.ldc = N;
-      list[n++] = g;
-    };
-    for (int l = l0; l < std::min(c.n_layers, l0 + LAYERS); ++l) {
+  GemmArgs list[4 * W_LAYERS];
+  for (int l0 = 0; l0 < c.n_layers; l0 += W_LAYERS) {
+    const int n = wgrad_list(P, std::min(W_LAYERS, c.n_layers - l0), list);
+    for (int i = 0; i < n; ++i) {
+      const int l = l0 + i / 4;
       const LayerStash& L = P.layer[l];
-      add(base + L.h1, H, H, base + L.dqkv, P.n_qkv, P.n_qkv, P.p_off[l][STAGE_P_WQKV]);
-      add(base + L.o, nqd, nqd, base + L.dx1, H, H, P.p_off[l][STAGE_P_WO]);
-      add(base + L.h2, H, H, base + L.dup, P.n_up, P.n_up, P.p_off[l][STAGE_P_WUP]);
-      add(base + L.m, F, F, base + L.dy, H, H, P.p_off[l][STAGE_P_WD]);
+      const size_t A[4] = {L.h1, L.o, L.h2, L.m}, B[4] = {L.dqkv, L.dx1, L.dup, L.dy};
+      constexpr int param[4] = {STAGE_P_WQKV, STAGE_P_WO, STAGE_P_WUP, STAGE_P_WD};
+      list[i].A = base + A[i & 3];
+      list[i].B = base + B[i & 3];
+      list[i].C = slot + P.p_off[l][param[i & 3]];
+      list[i].K = m.T;
+      list[i].ws = base + P.t_dm;
+      list[i].ws_bytes = P.ws_bytes;
     }
     HIP_TRY(st, launch_wgrad_group(list, n, s));
   }

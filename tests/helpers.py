@@ -71,7 +71,7 @@ def canonical_order(M: int):
     return [("F", j) for j in range(M)] + [("B", j) for j in range(M)] + [("W", j) for j in range(M)]
 
 
-def run_gpu(w: Workload, order=None, n_streams: int = 1, max_tokens=None, keep_raw: bool = False):
+def run_gpu(w: Workload, order=None, n_streams: int = 1, max_tokens=None, keep_raw: bool = False, max_segments=None):
     """Runs the workload through the HIP library in the given task order (default canonical),
     round-robin over n_streams streams.  Returns the same dict as run_oracle (fp64 numpy), plus
     raw bit-level copies when keep_raw is set."""
@@ -81,7 +81,7 @@ def run_gpu(w: Workload, order=None, n_streams: int = 1, max_tokens=None, keep_r
 
     shape = w.shape
     T_max = max(int(c[-1]) for c in w.cus) if max_tokens is None else max_tokens
-    cfg = Hn.make_config(shape, T_max, max(len(c) - 1 for c in w.cus), n_microbatches=w.M)
+    cfg = Hn.make_config(shape, T_max, max_segments or max(len(c) - 1 for c in w.cus), n_microbatches=w.M)
     stage = Hn.Stage(cfg, Hn.pack_params(cfg, w.layers))
     tdt = torch.float32 if shape.dtype == "fp32" else torch.bfloat16
     xs = [Hn.to_device(t.storage, shape.dtype) for t in w.x]

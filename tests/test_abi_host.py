@@ -2,6 +2,7 @@
 declares; configuration validation; parameter layout; the per-microbatch dependency state
 machine (paper Section 3.1 / 4.1 / 7.1 ordering rules) through stage_create_dry."""
 import os
+import random
 import re
 import ctypes
 
@@ -229,6 +230,47 @@ def test_wgrad_group_plan():
     assert R.rrfp_wgrad_group_plan(language, 4096, n_cu=64) == dict(full=12352, tail=0, ranges=1)       # whole rounds
     for bad in ([(60, 64)], [(64, 60)], [(0, 64)], [(64, 64)] * 33):
         _expect(R.STAGE_EINVAL, R.rrfp_wgrad_group_plan, bad, 100)
+
+
+@pytest.mark.parametrize("H,nq,nkv,d,F,layers,swiglu,max_tokens", [
+    (4096, 32, 32, 128, 11008, 4, True, 512), (4096, 32, 8, 128, 11008, 2, True, 6136), (512, 8, 2, 64, 1536, 2, True, 777),
+    (1280, 16, 16, 80, 5120, 8, False, 6272), (8192, 64, 8, 128, 28672, 2, True, 2100), (2048, 16, 8, 128, 64, 11, True, 150),
+    (64, 1, 1, 64, 64, 1, False, 5000)])
+def test_stage_scratch_never_limits_a_cut(H, nq, nkv, d, F, layers, swiglu, max_tokens):
+    """The scratch of a stage holds the planes of every cut that any microbatch of up to max_tokens would take, so that the
+    bits of a microbatch hang on its own shape and not on max_tokens, max_segments or an unrelated width."""
+    F32, BF = R.STAGE_DTYPE_FP32, R.STAGE_DTYPE_BF16
+    base = dict(n_layers=layers, hidden=H, n_q_heads=nq, n_kv_heads=nkv, head_dim=d, ffn=F, dtype=1, mlp_kind=0 if swiglu else 1,
+                max_tokens=max_tokens, max_segments=1)
+    cfg = lambda **kw: _cfg(**{**base, **kw})
+    ws = R.stage_scratch_bytes(cfg())
+    assert R.stage_scratch_bytes(cfg(max_segments=64)) >= ws and R.stage_scratch_bytes(cfg(max_tokens=max_tokens + 1000)) >= ws
+    n_qkv, n_up = (nq + 2 * nkv) * d, (2 if swiglu else 1) * F
+    forms = [(n_qkv, H, 0, BF), (H, nq * d, 0, F32), (n_up, H, 0, BF), (H, F, 0, F32), (F, H, 1, BF), (H, n_up, 1, F32), (nq * d, H, 1, BF),
+             (H, n_qkv, 1, F32)]
+    rng = random.Random(H + max_tokens)
+    tokens = set(rng.sample(range(1, max_tokens + 1), 100)) | {t + e for t in range(0, max_tokens + 1, 128) for e in (-1, 0, 1)} | {max_tokens}
+    for n_cu in (256, 64):
+        for T in (t for t in tokens if 1 <= t <= max_tokens):
+            for N, K, tb, out in forms:
+                full = R.rrfp_gemm_plan(T, N, K, 0, tb, out, n_cu=n_cu, have_scratch=True)
+                assert R.rrfp_gemm_plan(T, N, K, 0, tb, out, n_cu=n_cu, workspace_bytes=ws) == full, (T, N, K)
+            for first in range(0, layers, 8):
+                products = _task_products(H, nq, nkv, d, F, min(8, layers - first), swiglu)
+                assert R.rrfp_wgrad_group_plan(products, T, workspace_bytes=ws, n_cu=n_cu) == R.rrfp_wgrad_group_plan(products, T, n_cu=n_cu), T
+            for dtype in (BF, F32):
+                rows = R.rrfp_rmsnorm_bwd_rows(T, H, dtype, n_cu)
+                need = 0 if rows == 8 else -(-T // rows) * H * 4
+                assert need <= (ws if dtype == BF else R.stage_scratch_bytes(cfg(dtype=0)))
+
+
+def test_rmsnorm_backward_rows():
+    """Rows per workgroup: 8, halved down to 2 while the workgroups do not reach every CU; rows below 1024 values always 8."""
+    BF, F32 = R.STAGE_DTYPE_BF16, R.STAGE_DTYPE_FP32
+    for H, dtype in ((1024, BF), (4096, BF), (1024, F32), (2048, F32)):
+        assert [R.rrfp_rmsnorm_bwd_rows(T, H, dtype) for T in (1, 1020, 1021, 2040, 2041, 1 << 20)] == [2, 2, 4, 4, 8, 8]
+    assert R.rrfp_rmsnorm_bwd_rows(1, 1016, BF) == 8 and R.rrfp_rmsnorm_bwd_rows(1, 2052, F32) == 8 and R.rrfp_rmsnorm_bwd_rows(1, 1025, F32) == 8
+    assert [R.rrfp_rmsnorm_bwd_rows(T, 1024, BF, n_cu=16) for T in (60, 61, 120, 121)] == [2, 4, 4, 8]
 
 
 def test_gemm_plan_with_a_limited_workspace():

@@ -89,3 +89,14 @@ def test_stage_with_split_contractions_matches_oracle(mlp, bias, norm):
     worst = Hp.compare(got, Hp.run_oracle(w), Hp.TOL["bf16"], "splitk stage")
     print(f"[splitk] stage {mlp} bias{bias} {norm}: worst {worst:.2e}", flush=True)
     Hp.assert_bit_identical(got, Hp.run_gpu(w, order=SI.ready_order(w.M, 5), n_streams=3, keep_raw=True))
+
+
+def test_bits_do_not_hang_on_the_limits_of_the_stage():
+    """The same microbatches through stages made for more tokens and more segments: the same bits, ranges and planes of the
+    products and partial rows of the norm backward included."""
+    shape = SI.StageShape("splitk_limits", 1, 2048, 16, 8, 128, 1024, 2, w_std=0.02)
+    w = Hp.Workload(shape, [[0, 60, 150], [0, 1]])
+    print("[splitk] limits of the stage", flush=True)
+    first = Hp.run_gpu(w, keep_raw=True)
+    for more in (dict(max_tokens=4096), dict(max_segments=40)):
+        Hp.assert_bit_identical(first, Hp.run_gpu(w, keep_raw=True, **more))
