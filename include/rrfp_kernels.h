@@ -71,6 +71,13 @@ int rrfp_gemm_plan_ws(int M, int N, int K, int lda, int ldb, int ldc, int trans_
  * multiple of 8, operands of 2 GiB). */
 int rrfp_wgrad_group_plan(int n, const int32_t* M, const int32_t* N, int K, size_t workspace_bytes, int n_cu, int32_t out[3]);
 
+/* The weight gradients of a W task as it launches them: C[i] = A[i]^T B[i] for n (at most 32) independent products over the same
+ * K tokens.  A[i]: device [K, M[i]], B[i]: device [K, N[i]], both of type in_dtype, C[i]: device fp32 [M[i], N[i]], written, all
+ * contiguous; the arrays themselves are host memory, read during the call.  Products that the grouped kernel of the type
+ * does not take run one by one.  workspace: as in rrfp_gemm_ws, may be NULL. */
+int rrfp_wgrad_group(int n, const void* const* A, const void* const* B, void* const* C, const int32_t* M, const int32_t* N, int K,
+                     int in_dtype, void* workspace, size_t workspace_bytes, void* stream);
+
 /* Launch plan of the attention backward's dK/dV kernel, pure host logic (no HIP call): the number of workgroups that
  * share the query heads of one KV head.  A workgroup of that kernel owns 128 keys of a KV head; with grouped query
  * heads (n_q_heads > n_kv_heads) and few KV heads the grid n_kv_heads x n_kv_tiles under-fills the chip and, under a

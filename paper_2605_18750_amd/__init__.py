@@ -65,6 +65,8 @@ def lib() -> C.CDLL:
         L.rrfp_gemm_plan_ws.restype = C.c_int
         L.rrfp_wgrad_group_plan.argtypes = [C.c_int] + [C.POINTER(C.c_int32)] * 2 + [C.c_int, sz, C.c_int, C.POINTER(C.c_int32)]
         L.rrfp_wgrad_group_plan.restype = C.c_int
+        L.rrfp_wgrad_group.argtypes = [C.c_int] + [C.POINTER(vp)] * 3 + [C.POINTER(C.c_int32)] * 2 + [C.c_int, C.c_int, vp, sz, vp]
+        L.rrfp_wgrad_group.restype = C.c_int
         L.stage_scratch_bytes.argtypes = [cfgp, C.POINTER(sz)]
         L.stage_scratch_bytes.restype = C.c_int
         L.rrfp_attn_dkv_subsets.argtypes = [C.c_int] * 4
@@ -222,6 +224,16 @@ def rrfp_gemm_plan(M, N, K, trans_a, trans_b, out_dtype, n_cu=256, have_scratch=
     if rc != STAGE_OK:
         raise StageError(rc, "rrfp_gemm_plan rejected its arguments")
     return dict(zip(("kernel", "wavefronts", "main_workgroups", "short_workgroups", "split_k"), (int(v) for v in out)))
+
+
+def rrfp_wgrad_group(A, B, Cout, products, K, in_dtype, stream=None, workspace=None, workspace_bytes=0):
+    """Cout[i] = A[i]^T B[i], products [(M, N), ...] over K tokens, launched as the W task does."""
+    n = len(products)
+    ptrs = [(C.c_void_p * n)(*[_ptr(t) for t in ts]) for ts in (A, B, Cout)]
+    Ms, Ns = (C.c_int32 * n)(*[p[0] for p in products]), (C.c_int32 * n)(*[p[1] for p in products])
+    rc = lib().rrfp_wgrad_group(n, *ptrs, Ms, Ns, K, in_dtype, _ptr(workspace), workspace_bytes, _stream(stream))
+    if rc != STAGE_OK:
+        raise StageError(rc, "rrfp_wgrad_group rejected its arguments" if rc == STAGE_EINVAL else "HIP launch failed")
 
 
 def rrfp_wgrad_group_plan(products, K, workspace_bytes=1 << 62, n_cu=256):

@@ -65,6 +65,22 @@ extern "C" int rrfp_wgrad_group_plan(int n, const int32_t* M, const int32_t* N, 
   return STAGE_OK;
 }
 
+extern "C" int rrfp_wgrad_group(int n, const void* const* A, const void* const* B, void* const* C, const int32_t* M, const int32_t* N, int K,
+                                int in_dtype, void* workspace, size_t workspace_bytes, void* stream) {
+  if (!A || !B || !C || !M || !N || n < 1 || n > WGRAD_GROUP_MAX || K < 1) return STAGE_EINVAL;
+  if (in_dtype != F32 && in_dtype != BF16) return STAGE_EINVAL;
+  if (workspace && ((uintptr_t)workspace & 255)) return STAGE_EINVAL;
+  GemmArgs g[WGRAD_GROUP_MAX] = {};
+  for (int i = 0; i < n; ++i) {
+    if (!A[i] || !B[i] || !C[i] || M[i] < 1 || N[i] < 1) return STAGE_EINVAL;
+    g[i].A = A[i]; g[i].B = B[i]; g[i].C = C[i];
+    g[i].M = M[i]; g[i].N = N[i]; g[i].K = K; g[i].lda = M[i]; g[i].ldb = g[i].ldc = N[i];
+    g[i].transA = true; g[i].in_dtype = in_dtype; g[i].out_dtype = F32;
+    g[i].ws = workspace; g[i].ws_bytes = workspace ? workspace_bytes : 0;
+  }
+  return launch_wgrad_group(g, n, (hipStream_t)stream) == hipSuccess ? STAGE_OK : STAGE_EHIP;
+}
+
 extern "C" int rrfp_rmsnorm_fwd(const float* x, const void* g, void* h, float* r_out, int T, int H, float eps, int dtype,
                                 void* stream) {
   if (!x || !g || !h || !r_out || T < 1 || H < 1 || !(eps >= 0.0f)) return STAGE_EINVAL;
