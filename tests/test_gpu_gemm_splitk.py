@@ -82,9 +82,16 @@ def _small(M, N, K, ta, tb, out_fp32, with_r):
 @pytest.mark.parametrize("mlp,bias,norm", [("swiglu", False, "rms"), ("swiglu", True, "rms"), ("gelu", True, "layer"), ("gelu", False, "rms")])
 def test_stage_with_split_contractions_matches_oracle(mlp, bias, norm):
     """Every fused epilogue behind the planes: activations forward and backward, biases, residuals, half outputs and the scale
-    of dO.  Hidden 2048 at up to 150 tokens: all the products of F and B are split."""
+    of dO.  Hidden 2048 at 150 tokens and at one: all the products of F and B are split (150: two tile rows, the second ragged)."""
+    import paper_2605_18750_amd as R
+    from paper_2605_18750_amd import harness as Hn
     shape = SI.StageShape(f"splitk_{mlp}{bias}{norm}", 1, 2048, 16, 8, 128, 2048, 2, w_std=0.02, mlp_kind=mlp, bias=bias, norm_kind=norm)
     w = Hp.Workload(shape, [[0, 60, 150], [0, 1]])
+    scratch = R.stage_scratch_bytes(Hn.make_config(shape, 150, 2, n_microbatches=2))
+    F32, BF, n_up = R.STAGE_DTYPE_FP32, R.STAGE_DTYPE_BF16, 4096 if mlp == "swiglu" else 2048
+    for T in (150, 1):
+        for N, K, tb, out in ((4096, 2048, 0, BF), (2048, 2048, 0, F32), (n_up, 2048, 0, BF), (2048, 2048, 1, BF), (2048, n_up, 1, F32), (2048, 4096, 1, F32)):
+            assert R.rrfp_gemm_plan(T, N, K, 0, tb, out, workspace_bytes=scratch)["split_k"] > 1, (T, N, K)
     got = Hp.run_gpu(w, keep_raw=True)
     worst = Hp.compare(got, Hp.run_oracle(w), Hp.TOL["bf16"], "splitk stage")
     print(f"[splitk] stage {mlp} bias{bias} {norm}: worst {worst:.2e}", flush=True)
