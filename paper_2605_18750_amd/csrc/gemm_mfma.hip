@@ -461,8 +461,9 @@ __device__ __forceinline__ void interleave_ds_vm_mfma() {
 // WM x WN wavefronts tile the 256x256 block; each owns (256/WM) x (256/WN).
 __device__ __forceinline__ float sigmoid_f(float z) { return 1.0f / (1.0f + __expf(-z)); }
 // Normal distribution function of u and e = exp(-u^2/2): the lower tail Phi(-|u|) = e w, w = erfcx(|u| / sqrt 2) / 2 = 1/2 + s R(s)
-// with s = 1 / (1 + 0.3 |u| / sqrt 2) - 1 and R the degree-8 polynomial whose relative error in w is least (1.7e-8 for |u| < 13;
-// reweighted least squares against 64-bit erfcx).  The epilogues of the GELU forms are bound by this: the library's erff is
+// with s = 1 / (1 + 0.3 |u| / sqrt 2) - 1 and R a degree-8 polynomial fitted to the relative error in w (reweighted least squares
+// against 64-bit erfcx).  With its coefficients in fp32 that error is 5e-8 for |u| < 1, 2e-7 to 3, 5e-7 to 6 and 1.7e-6 to 13
+// (unrounded the fit reaches 1.7e-8: the terms cancel as w falls).  The epilogues of the GELU forms are bound by this: the library's erff is
 // two expansions, both run by a wavefront whose lanes differ.  Against 64 bits (2-norm, u in -3..0 / 0..9 / -9..-3): u Phi 8e-8 / 2e-8 /
 // 4e-7, the derivative 5e-8 / 4e-8 / 2e-7; by 1 + erff 1e-7 / 2e-8 / 4e-5 and 5e-8 / 4e-8 / 3e-6 (1 + erff cancels in the lower tail).
 __device__ __forceinline__ float normal_cdf(float u, float& e) {
