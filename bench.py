@@ -9,9 +9,9 @@ the stage plus stage_grad_reduce, inputs resident in HBM.  Prints ONE JSON line.
 value     = algorithmic TFLOP of the step / wall time (GEMM 2*T*P per layer per task kind,
             attention forward 4*d*n_q*pairs with pairs = s^2/2 causal or s^2 bidirectional,
             attention backward counted as twice the forward, no recompute, no elementwise flops).
-roofline  = the kernel with the largest share of the step time in the form the step launches it (the
-            bf16 MFMA GEMM in its weight-gradient form on the up projection, fp32 output: one call of the
-            W task), timed alone with HIP events on its stream, against the dense bf16 MFMA peak of
+roofline  = the kernel with the largest share of the step time as the step launches it (the grouped bf16 MFMA
+            GEMM: all weight gradients of a W task in one launch, fp32 output, with the scratch the stage
+            gives it), timed alone with HIP events on its stream, against the dense bf16 MFMA peak of
             2.5 PFLOP/s.
 hbm_kernels = the HBM-bound kernels of the step timed alone through their own entry points (RMSNorm
             forward and backward at [T, hidden], the gradient reduction), algorithmic bytes per call
@@ -81,15 +81,41 @@ def cpu_baseline(shape, T_sample: int):
                       f"{dt:.1f} s wall"}
 
 
+def wgrad_group(shape, T, gen):
+    """The weight gradients of one W task of T tokens as the stage launches them: products, operands of N(0, 1), outputs."""
+    import torch
+    H, F, nqd = shape.hidden, shape.ffn, shape.n_q_heads * shape.head_dim
+    n_qkv, n_up = (shape.n_q_heads + 2 * shape.n_kv_heads) * shape.head_dim, (2 if shape.mlp_kind == "swiglu" else 1) * F
+    products = [(H, n_qkv), (nqd, H), (H, n_up), (F, H)] * min(shape.n_layers, 8)
+    normal = lambda w: torch.empty((T, w), dtype=torch.bfloat16, device="cuda:0").normal_(0.0, 1.0, generator=gen)
+    return products, [normal(m) for m, _ in products], [normal(n) for _, n in products], \
+        [torch.empty((m, n), dtype=torch.float32, device="cuda:0") for m, n in products]
+
+
 def gemm_roofline(shape, T, Bw, s, gen, n_launch=40, form="nn"):
-    """The bf16 MFMA GEMM of the up projection alone, HIP events on the launch stream.  form "nn": the
-    forward [T, hidden] x [hidden, N_up] (the roofline kernel of the step bench); "nt": its input
-    gradient [T, N_up] x [hidden, N_up]^T -> fp32 [T, hidden]; "tn": its weight gradient
-    [T, hidden]^T x [T, N_up] -> fp32 [hidden, N_up] (for counter runs of the other operand orientations)."""
+    """A bf16 MFMA GEMM alone, HIP events on the launch stream.  form "w": all weight gradients of a W task in the
+    one launch the step makes (the roofline kernel of the step bench).  The others are the GEMM of the up projection, for
+    counter runs of single operand orientations: "nn" the forward [T, hidden] x [hidden, N_up]; "nt" its input
+    gradient [T, N_up] x [hidden, N_up]^T -> fp32 [T, hidden]; "tn" its weight gradient [T, hidden]^T x [T, N_up] -> fp32
+    [hidden, N_up] as a single call with a workspace (rrfp_gemm_ws), which no task makes."""
     import torch
     import paper_2605_18750_amd as R
     N_up = (2 if shape.mlp_kind == "swiglu" else 1) * shape.ffn
     H = shape.hidden
+    if form == "w":
+        from paper_2605_18750_amd import harness as Hn
+        products, As, Bs, Cs = wgrad_group(shape, T, gen)
+        ws_bytes = R.stage_scratch_bytes(Hn.make_config(shape, T, 1))
+        ws = torch.empty(ws_bytes, dtype=torch.uint8, device="cuda:0")
+        cut = R.rrfp_wgrad_group_plan(products, T, workspace_bytes=ws_bytes,
+                                      n_cu=torch.cuda.get_device_properties(0).multi_processor_count)
+
+        def launch():
+            R.rrfp_wgrad_group(As, Bs, Cs, products, T, R.STAGE_DTYPE_BF16, s, workspace=ws, workspace_bytes=ws_bytes)
+        key = f"w:{len(products)}x{H}x{shape.ffn}x{T}"
+        label = f"gemm_mfma_wgrad_group_kernel, {len(products)} products of {T} tokens bf16 (all weight gradients of a W task, fp32 out; " \
+                f"{cut['full']} tiles" + (f" + {cut['tail']} in {cut['ranges']} ranges of K and the sum of their planes)" if cut["ranges"] > 1 else ")")
+        return _time_gemm(launch, s, n_launch, sum(2.0 * m * n * T for m, n in products), label, key)
     A = torch.empty((T, H), dtype=torch.bfloat16, device=Bw.device).normal_(0.0, 1.0, generator=gen)
     if form == "nn":
         Cc = torch.empty((T, N_up), dtype=torch.bfloat16, device=Bw.device)
@@ -108,14 +134,24 @@ def gemm_roofline(shape, T, Bw, s, gen, n_launch=40, form="nn"):
         else:
             Cc = torch.empty((H, N_up), dtype=torch.float32, device=Bw.device)
             dims = (H, N_up, T)
-            ws_bytes = T * shape.ffn * 4            # the scratch the W task hands to this call (B's idle fp32 temporary)
+            ws_bytes = T * shape.ffn * 4
             ws = torch.empty(ws_bytes, dtype=torch.uint8, device=Bw.device)
 
             def launch():
                 R.rrfp_gemm(A, G, Cc, None, H, N_up, T, H, N_up, N_up, N_up, 1, 0, 1, 0, R.RRFP_GEMM_MFMA, s,
                             workspace=ws, workspace_bytes=ws_bytes)
+    label = {"nn": "(one call: 256-row tiles + 128-row tail launch)", "nt": "(fp32 out)",
+             "tn": "(weight-gradient form, fp32 out; one call: plain launch + split-K tail launch + its reduce)"}[form]
+    shape_text = f"{dims[0]}x{dims[1]}x{dims[2]}"
+    return _time_gemm(launch, s, n_launch, 2.0 * dims[0] * dims[1] * dims[2],
+                      f"gemm_mfma_dl_kernel {form.upper()} {shape_text} bf16 {label}", f"{form}:{shape_text}")
+
+
+def _time_gemm(launch, s, n_launch, g_fl, kernel, key):
+    """Roofline entry of `launch` (g_fl flops a call); key names its recorded traffic."""
+    import torch
     with torch.cuda.stream(s):
-        # the tensors above were just made: the chip has been idle, and its clock takes some tens of launches to
+        # the operands were just made: the chip has been idle, and its clock takes some tens of launches to
         # settle under the GEMM again (the step timed before ran with a settled clock)
         for _ in range(max(3, n_launch)):
             launch()
@@ -126,7 +162,6 @@ def gemm_roofline(shape, T, Bw, s, gen, n_launch=40, form="nn"):
         g1.record(s)
     torch.cuda.synchronize()
     g_ms = g0.elapsed_time(g1) / n_launch
-    g_fl = 2.0 * dims[0] * dims[1] * dims[2]
     ach = g_fl / (g_ms * 1e-3) / 1e12
     # HBM traffic per call: a recorded rocprofv3 counter value (profiles/gemm_mfma_traffic.json names the
     # counter summary it comes from), not a measurement of this run.
@@ -135,13 +170,11 @@ def gemm_roofline(shape, T, Bw, s, gen, n_launch=40, form="nn"):
     if os.path.exists(tpath):
         try:
             rec = json.load(open(tpath))
-            traffic = rec.get(f"{form}:{dims[0]}x{dims[1]}x{dims[2]}")
+            traffic = rec.get(key)
             traffic_source = rec.get("source") if traffic is not None else None
         except Exception:
             traffic = None
-    label = {"nn": "(one call: 256-row tiles + 128-row tail launch)", "nt": "(fp32 out)",
-             "tn": "(weight-gradient form of the W task, fp32 out; one call: plain launch + split-K tail launch + its reduce)"}[form]
-    return {"bound": "mfma", "kernel": f"gemm_mfma_dl_kernel {form.upper()} {dims[0]}x{dims[1]}x{dims[2]} bf16 {label}", "achieved": round(ach, 1),
+    return {"bound": "mfma", "kernel": kernel, "achieved": round(ach, 1),
             "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": round(ach / PEAK_BF16_TFLOPS, 4),
             "flops_per_launch": g_fl, "avg_launch_ms": round(g_ms, 4), "traffic": traffic,
             "traffic_source": traffic_source}
@@ -306,9 +339,9 @@ def main():
     ap.add_argument("--warmup", type=int, default=2)
     ap.add_argument("--workload", default="language")
     ap.add_argument("--streams", type=int, default=1, help="streams the tasks are dealt to (B/F/W order)")
-    ap.add_argument("--gemm-form", default=None, choices=["nn", "nt", "tn"],
-                    help="operand orientation of the roofline GEMM (forward, input-gradient or weight-gradient form of the "
-                         "up projection); default: tn, the form with the largest share of the step")
+    ap.add_argument("--gemm-form", default="w", choices=["w", "nn", "nt", "tn"],
+                    help="roofline GEMM: w, all weight gradients of a W task in one launch (the kernel with the largest share of the "
+                         "step), or one GEMM of the up projection in its forward, input-gradient or weight-gradient orientation")
     ap.add_argument("--only", default="step", choices=["step", "gemm", "gemm_sweep", "copy", "pipeline"],
                     help="gemm: launch only the roofline GEMM (for counter runs); gemm_sweep: time of the GEMM forms against "
                          "K with a full, a half and a quarter round of 256 x 256 tiles (main-loop rate and fixed cost per "
@@ -366,7 +399,7 @@ def main():
         N_up = (2 if shape.mlp_kind == "swiglu" else 1) * shape.ffn
         Bw = torch.empty((shape.hidden, N_up), dtype=torch.bfloat16, device="cuda:0").normal_(0.0, shape.w_std, generator=gen)
         print(json.dumps({"only": "gemm", "roofline": gemm_roofline(shape, T, Bw, torch.cuda.Stream(), gen, n_launch=args.steps,
-                                                                    form=args.gemm_form or "tn")}))
+                                                                    form=args.gemm_form)}))
         return
     M = shape.n_microbatches
     cus = [SI.default_cu_seqlens(shape, j) for j in range(M)]
@@ -471,13 +504,12 @@ def main():
     red_gbs = (M + 1) * gb / (red_ms * 1e-3) / 1e9
     grad_reduce = {"ms": round(red_ms, 4), "GB/s": round(red_gbs, 1), "frac_of_hbm_peak": round(red_gbs / PEAK_HBM_GBS, 4),
                    "bytes": (M + 1) * gb}
-    # Roofline of the dominant kernel: the weight-gradient GEMM of the up projection ([hidden, N_up] with
-    # K = tokens, fp32 out), the single launch with the largest share of the step and the form (both operands
-    # K-strided) that takes the largest share of the step overall; timed alone with HIP events on its stream.
+    # Roofline of the dominant kernel: the launch with the largest share of the step, all weight gradients of a W task,
+    # timed alone with HIP events on its stream.
     roof, hbm = None, None
     if shape.dtype == "bf16":
         off, (r, c) = R.stage_param_layout(cfg, 0, R.STAGE_P_WUP)
-        roof = gemm_roofline(shape, T_max, params[off:off + r * c].view(r, c), streams[0], gen, form=args.gemm_form or "tn")
+        roof = gemm_roofline(shape, T_max, params[off:off + r * c].view(r, c), streams[0], gen, form=args.gemm_form)
 
     torch.cuda.synchronize()
     R.stage_destroy(st)
