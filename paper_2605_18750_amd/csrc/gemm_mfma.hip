@@ -952,7 +952,8 @@ __global__ __launch_bounds__(256) void splitk_tail_reduce_kernel(const float* __
   }
 }
 
-// Weight-gradient form on a grid of more than one round: when the last round would be nearly empty and carving
+// Weight-gradient form as a single call (rrfp_gemm_ws; a W task launches its products together, see wgrad_group_cut) on a grid
+// of more than one round: when the last round would be nearly empty and carving
 // the trailing tile columns off removes it (the rule of full_tile_columns), those columns are a second launch
 // whose tiles are split along K into TAIL_SPLIT ranges (so the tail fills the CUs for half a round instead of a
 // fraction of them for a whole one); each range writes its own compact partial plane into the scratch and the
@@ -1489,7 +1490,7 @@ hipError_t launch_one(const GemmArgs& g, hipStream_t s) {
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
   if (direct_ok(g)) {
     if constexpr (A_KC) return launch_a_kc<B_KC, TO, HAS_R, ACT_NONE>(g, s);
-    // Weight-gradient form (both operands K-strided, fp32 out, K = tokens): when the output has too
+    // Weight-gradient form as a single call (both operands K-strided, fp32 out, K = tokens): when the output has too
     // few tiles to fill the CUs, the contraction is split into S ranges, every range writes its own
     // partial plane into the scratch, and the planes are summed in range order (one fixed order).
     if constexpr (!A_KC && !B_KC && !HAS_R && sizeof(TO) == 4) {

@@ -65,7 +65,7 @@ SMALL = {
     "fp32_layernorm_bias": (SI.StageShape("s_fp32_ln", 2, 100, 4, 2, 16, 36, 2, dtype="fp32", mlp_kind="gelu", x_std=1.0, dy_std=1.0,
                                           w_std=0.1, norm_kind="layer", bias=True),
                             [[0, 37, 150], [0, 70]]),
-    # bf16, many tokens on a narrow stage: the weight-gradient GEMMs (K = tokens) take the split-K path
+    # bf16, many tokens on a narrow stage: the weight gradients (K = tokens) run in 64 x 64 tiles, K dealt to the wavefronts
     "bf16_long_tokens_splitk": (SI.StageShape("s_bf16_e", 1, 128, 4, 2, 64, 192, 2, w_std=0.05),
                                 [[0, 1100], [0, 600, 1163]]),
     # bf16, head_dim 128, GQA 4:1
