@@ -1330,31 +1330,212 @@ __device__ __forceinline__ const WgradProblem& group_problem(const WgradGroup& g
   return g.p[i];
 }
 
-// Not a plain call of dl_tile on the launch's arguments: work item id is tile id for id < full, else range (id - full) / tail of
-// tile full + (id - full) % tail.
-__global__ __launch_bounds__(256) void gemm_mfma_wgrad_group_kernel(const WgradGroup g) {
-  int tile = blockIdx.x, range = -1;
-  if (tile >= g.full) {
-    range = (tile - g.full) / g.tail;
-    tile = g.full + (tile - g.full) % g.tail;
+// Work item id: tile id for id < full, else range (id - full) / tail of tile full + (id - full) % tail.  Pointers are those of the
+// item's first element; rows, cols: how much of the 256 x 256 tile the output has.
+struct WgradItem {
+  const bf16_t *A, *B;
+  float* C;
+  int a_bytes, b_bytes, lda, ldb, ldc, rows, cols, nk;
+};
+__device__ __forceinline__ WgradItem wgrad_item(const WgradGroup& g, int id) {
+  int tile = id, range = -1, k0 = 0, K = g.K;
+  if (id >= g.full) {
+    range = (id - g.full) / g.tail;
+    tile = g.full + (id - g.full) % g.tail;
+    k0 = range * g.k_split;
+    K = min(g.k_split, K - k0);
   }
   const WgradProblem& p = group_problem(g, tile);
   int tm, tn;
   tile_coords(tile - p.start, p.tiles_m, p.tiles_n, tm, tn);
-  const bf16_t *A = p.A, *B = p.B;
-  float* C = p.C;
-  int K = g.K, ldc = p.ldc;
   const int m0 = tm * BM, n0 = tn * BN;
-  if (range >= 0) {
-    const int k0 = range * g.k_split;
-    A += (size_t)k0 * p.lda;
-    B += (size_t)k0 * p.ldb;
-    K = min(g.k_split, K - k0);
-    ldc = BN;                                          // dl_tile addresses by row and column of the product: the plane moves left by the tile's origin
-    C = g.ws + ((ptrdiff_t)range * g.tail + (tile - g.full)) * (BM * BN) - ((ptrdiff_t)m0 * BN + n0);
+  WgradItem w;
+  w.lda = p.lda; w.ldb = p.ldb;
+  w.A = p.A + (size_t)k0 * p.lda + m0;
+  w.B = p.B + (size_t)k0 * p.ldb + n0;
+  w.a_bytes = (int)(((size_t)(K - 1) * p.lda + (p.M - m0)) * 2);
+  w.b_bytes = (int)(((size_t)(K - 1) * p.ldb + (p.N - n0)) * 2);
+  w.rows = min(BM, p.M - m0);
+  w.cols = min(BN, p.N - n0);
+  w.nk = (K + DBK - 1) / DBK;
+  w.ldc = range < 0 ? p.ldc : BN;
+  w.C = range < 0 ? p.C + (size_t)m0 * p.ldc + n0 : g.ws + ((size_t)range * g.tail + (tile - g.full)) * (BM * BN);
+  return w;
+}
+
+// One K-strided operand tile of 32 k x 256 columns, as DirectLoader lays it out for the 32x32x16 reads, for a wavefront of four.
+struct WgradLoader {
+  const bf16_t* base;
+  int bytes, k_stride;
+  int voff[4];
+  __device__ __forceinline__ void init(const bf16_t* p, int n_bytes, int ld, int wave, int lane) {
+    base = p;
+    bytes = n_bytes;
+    k_stride = DBK * ld * 2;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int k = (i * 4 + wave) * 2 + (lane >> 5), cp = lane & 31;
+      const int f = (k & 3) | (((k >> 3) & 1) << 2);
+      voff[i] = (k * ld + ((((cp >> 2) ^ f) << 2) | (cp & 3)) * 8) * 2;
+    }
   }
-  dl_tile<false, false, float, false, dl_wm(false, false), dl_wn(false, false), ACT_NONE>(
-      A, B, C, nullptr, p.M, p.N, K, p.lda, p.ldb, ldc, 0, m0, n0, nullptr, 0, nullptr, nullptr);
+  // The wavefront's four loads of step t; a step that does not exist has no bytes, so they give zeros without a memory access.
+  __device__ __forceinline__ void issue(char* tile, int t, bool exists, int wave) const {
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, exists ? bytes : 0, 0x00020000);
+    const int soff = exists ? t * k_stride : 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_ptr)(tile + (i * 4 + wave) * 1024), 16, voff[i], soff, 0, 0);
+  }
+};
+
+// Groups of four steps of an item, at least two (its first and its last).
+__device__ __forceinline__ int wgrad_groups(int nk) { return max(2, (nk + 3) >> 2); }
+
+// A workgroup per CU walks the items blockIdx.x, + gridDim.x, ...  The steps of all its items form one sequence: the first steps of an item
+// are loaded under the last MFMAs of the one before, and its sums go straight from the accumulators to memory, no LDS between, so that
+// the stores drain under the next item's steps.  Four 32 KB buffers hold a group of four steps; an item's steps are padded to whole
+// groups with steps of zeros.  While step s is contracted the loads of step s + 4 go to its own buffer: A's after the barrier in the
+// middle of the step (when nobody reads that buffer any more), B's in the first half of step s + 1.  They are waited for in the
+// middle of step s + 3: everything but the 16 loads of the two steps after it that were issued later.
+// A is the first operand of the MFMA here: a lane holds one column, and a store instruction writes 128 contiguous bytes of two rows.
+// What bounds it: at K of a few hundred the fp32 output (a CU alone stores a tile in 3.4 us, 256 at once in 11: 6 TB/s) and the operand
+// reads behind the L2s, at K of thousands the matrix pipes at the power limit.  A workgroup per tile, its sums through LDS -> this, inside
+// the stage: 4 layers of hidden 4096 at 256 to 512 tokens 1137 -> 979 us a launch, at 4096 tokens 5368 -> 5191; 8 layers of hidden 1280 at
+// 6272 tokens 1540 -> 1519; 2 layers of hidden 2048 at 3704 tokens 652 -> 616.  Waiting for 16 operations instead of 60 behind the stores
+// of an item (so for nearly all of them) gave half of that; stepping one item in two groups at least (K <= 128 is padded to 256) costs nothing
+// there, where the stores set the time.
+__global__ __launch_bounds__(256) void gemm_mfma_wgrad_group_kernel(const WgradGroup g, int items) {
+  __shared__ __attribute__((aligned(1024))) char stage0[DSTAGE];
+  __shared__ __attribute__((aligned(1024))) char stage1[DSTAGE];
+  __shared__ __attribute__((aligned(1024))) char stage2[DSTAGE];
+  __shared__ __attribute__((aligned(1024))) char stage3[DSTAGE];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = (wave >> 1) * 128, wn = (wave & 1) * 128;
+  // lgkmcnt(0) and at most 16 (60) loads and stores of the wavefront in flight
+  constexpr int VM_16 = 0x0070 | (16 & 15) | ((16 >> 4) << 14), VM_60 = 0x0070 | (60 & 15) | ((60 >> 4) << 14);
+  floatx16 acc[4][4];
+  auto clear = [&] {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  };
+  auto multiply = [&](const Frags32<4, 4>& f) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i], f.b[j], acc[i][j], 0, 0, 0);
+  };
+  int id = blockIdx.x;
+  WgradItem next = wgrad_item(g, id);                  // the item whose steps are being loaded
+  WgradLoader la, lb;
+  la.init(next.A, next.a_bytes, next.lda, wave, lane);
+  lb.init(next.B, next.b_bytes, next.ldb, wave, lane);
+  float* C = next.C;                                   // of the item that is being contracted
+  int ldc = next.ldc, rows = next.rows, cols = next.cols, groups = wgrad_groups(next.nk), t = 0;
+  la.issue(stage0, 0, true, wave);
+  lb.issue(stage0 + DTILE, 0, true, wave);
+  la.issue(stage1, 1, 1 < next.nk, wave);
+  lb.issue(stage1 + DTILE, 1, 1 < next.nk, wave);
+  la.issue(stage2, 2, 2 < next.nk, wave);
+  lb.issue(stage2 + DTILE, 2, 2 < next.nk, wave);
+  la.issue(stage3, 3, 3 < next.nk, wave);
+  lb.issue(stage3 + DTILE, 3, 3 < next.nk, wave);
+  clear();
+  __builtin_amdgcn_s_waitcnt(0x0070);
+  stage_barrier();
+  Frags32<4, 4> fx, fy;
+  load_frags32<4, 4>(fx, stage0, 0, wm, wn, lane);
+  load_frags32<4, 4>(fy, stage0, 1, wm, wn, lane);
+  multiply(fx);
+#define RRFP_W_FIRST(P, VM, b0, b1)                                                                      \
+  __builtin_amdgcn_s_waitcnt(VM);                                                                        \
+  stage_barrier();                                                                                       \
+  la.issue(b0, t + (P), t + (P) < next.nk, wave);                                                        \
+  load_frags32<4, 4>(fx, b1, 0, wm, wn, lane);                                                           \
+  multiply(fy);                                                                                          \
+  interleave_ds_vm_mfma<16, 16, 4>();                                                                    \
+  __builtin_amdgcn_sched_barrier(0);
+#define RRFP_W_SECOND(P, b0, b1)                                                                         \
+  lb.issue(b0 + DTILE, t + (P), t + (P) < next.nk, wave);                                                \
+  load_frags32<4, 4>(fy, b1, 1, wm, wn, lane);                                                           \
+  multiply(fx);                                                                                          \
+  interleave_ds_vm_mfma<16, 16, 4>();                                                                    \
+  __builtin_amdgcn_sched_barrier(0);
+  for (;;) {
+    // first four steps: the loads of the next two were issued before the 256 stores of the item before
+    t = 4;
+    RRFP_W_FIRST(0, VM_60, stage0, stage1)
+    RRFP_W_SECOND(0, stage0, stage1)
+    RRFP_W_FIRST(1, VM_60, stage1, stage2)
+    RRFP_W_SECOND(1, stage1, stage2)
+    RRFP_W_FIRST(2, VM_16, stage2, stage3)
+    RRFP_W_SECOND(2, stage2, stage3)
+    RRFP_W_FIRST(3, VM_16, stage3, stage0)
+    RRFP_W_SECOND(3, stage3, stage0)
+    for (; groups > 2; --groups) {
+      t += 4;
+      RRFP_W_FIRST(0, VM_16, stage0, stage1)
+      RRFP_W_SECOND(0, stage0, stage1)
+      RRFP_W_FIRST(1, VM_16, stage1, stage2)
+      RRFP_W_SECOND(1, stage1, stage2)
+      RRFP_W_FIRST(2, VM_16, stage2, stage3)
+      RRFP_W_SECOND(2, stage2, stage3)
+      RRFP_W_FIRST(3, VM_16, stage3, stage0)
+      RRFP_W_SECOND(3, stage3, stage0)
+    }
+    // last four steps of the item: their loads are the next item's
+    id += gridDim.x;
+    t = 0;
+    next.nk = 0;
+    if (id < items) {
+      next = wgrad_item(g, id);
+      la.init(next.A, next.a_bytes, next.lda, wave, lane);
+      lb.init(next.B, next.b_bytes, next.ldb, wave, lane);
+    }
+    RRFP_W_FIRST(0, VM_16, stage0, stage1)
+    RRFP_W_SECOND(0, stage0, stage1)
+    RRFP_W_FIRST(1, VM_16, stage1, stage2)
+    RRFP_W_SECOND(1, stage1, stage2)
+    RRFP_W_FIRST(2, VM_16, stage2, stage3)
+    RRFP_W_SECOND(2, stage2, stage3)
+    RRFP_W_FIRST(3, VM_16, stage3, stage0)
+    int voff[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int col = wn + j * 32 + (lane & 31);
+      voff[j] = col < cols ? ((lane >> 5) * 4 * ldc + col) * 4 : (int)0x80000000;      // past any buffer: not stored
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int row = wm + i * 32 + q * 8;
+        // M is a multiple of 8; rows past it get a buffer of no bytes (and no offset: the range check subtracts it), so that the
+        // stores are always 256
+        const int pitch = row < rows ? ldc * 4 : 0;
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(C + (size_t)row * ldc, 0, row < rows ? 0x7fffffff : 0, 0x00020000);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[i][j][q * 4 + e]), rsrc, voff[j], e * pitch, 0);
+      }
+    if (id >= items) break;
+    C = next.C;
+    ldc = next.ldc;
+    rows = next.rows;
+    cols = next.cols;
+    groups = wgrad_groups(next.nk);
+    clear();
+    RRFP_W_SECOND(3, stage3, stage0)
+  }
+#undef RRFP_W_FIRST
+#undef RRFP_W_SECOND
+  __builtin_amdgcn_s_waitcnt(0x0070);                  // no load into this workgroup's LDS is left in flight
 }
 
 // Planes of the cut tiles added in range order: 16 workgroups per tile, 16 rows each.
@@ -1479,7 +1660,8 @@ hipError_t launch_wgrad_group_mfma(const GemmArgs* g, int n, hipStream_t s) {
   grp.tail = cut.tail;
   grp.k_split = (steps + cut.ranges - 1) / cut.ranges * DBK;
   grp.ws = (float*)g[0].ws;
-  hipLaunchKernelGGL(gemm_mfma_wgrad_group_kernel, dim3(cut.full + cut.tail * cut.ranges), dim3(256), 0, s, grp);
+  const int items = cut.full + cut.tail * cut.ranges;
+  hipLaunchKernelGGL(gemm_mfma_wgrad_group_kernel, dim3(std::min(items, cu_count())), dim3(256), 0, s, grp, items);
   if (hipError_t e = hipGetLastError(); e != hipSuccess || cut.tail == 0) return e;
   hipLaunchKernelGGL(wgrad_group_finish_kernel, dim3(cut.tail * 16), dim3(256), 0, s, grp, cut.ranges);
   return hipGetLastError();

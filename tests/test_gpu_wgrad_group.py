@@ -51,6 +51,11 @@ LISTS = [
     (_products(2, 1088, 17, 17, 64, 2880), 1100, 18 * 3, dict(full=512, tail=18, ranges=3)),
     (_products(1, 72, 1, 1, 64, 136), 65, None, dict(full=24, tail=0, ranges=0)),
     ([(1032, 2056)], 4129, None, dict(full=0, tail=45, ranges=5)),
+    # workgroups that walk two tiles, of 1, 5, 9 and 12 steps (a workgroup takes them in groups of four, at least two of them)
+    ([(2376, 3176), (4096, 2056), (1032, 6152)], 31, None, dict(full=399, tail=0, ranges=1)),
+    ([(2376, 3176), (4096, 2056), (1032, 6152)], 131, None, dict(full=399, tail=0, ranges=1)),
+    ([(2376, 3176), (4096, 2056), (1032, 6152)], 257, None, dict(full=399, tail=0, ranges=1)),
+    ([(2376, 3176), (4096, 2056), (1032, 6152)], 384, None, dict(full=399, tail=0, ranges=1)),
 ]
 
 
