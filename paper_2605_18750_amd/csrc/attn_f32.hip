@@ -12,12 +12,11 @@
 // A workgroup has four wavefronts of 16 rows (queries in the forward and dQ kernels, keys in the dK/dV kernel); the
 // other side streams through LDS in steps of 32 rows, double buffered, the next step's global loads in flight under
 // the current one's MFMAs.  The grid has one workgroup per 64-row sub-tile of the host's tiles, so that small stages
-// still spread over the chip: heads in grid x (sub-tiles there and heads in y were 2.5 % slower on an iteration of the shape
-// below), sub-tiles in y and, past 65535 of them (many segments of a few tokens), in z.  Bound by the fp32 matrix rate (157
+// still spread over the chip: heads in grid x (sub-tiles there and heads in y were 2.5 % slower on an iteration of a 16-head
+// stage at 1024 tokens), sub-tiles in y and, past 65535 of them (many segments of a few tokens), in z.  Bound by the fp32 matrix rate (157
 // TFLOP/s) once the sequences are long enough, by the
-// latency of the key loop before that.  16 query / 4 KV heads of 64, T = 1024 in segments of 300 and 724 (average with a
-// second microbatch of 517): forward 42 us, dQ 49, dK/dV 62 + 5 for the planes; the fp32-FMA kernels that were here before:
-// 2050, 3235 and 10281 us (one LDS read per FMA, and one workgroup per 128 keys of a KV head for the whole group).
+// latency of the key loop before that, where the split kernels below take over (see split_streams for both at each size).  16 query
+// heads of 64, T = 2048: forward 155 us, dQ 189, dK/dV 248.
 // No atomics: sums run over ascending steps; with grouped heads every query head leaves its own dK, dV plane and the
 // planes are added in head order.
 #include "kernels.h"
@@ -103,13 +102,13 @@ __device__ __forceinline__ void cols_times_scores(f32x4v (&out)[F32Cfg<D>::NS], 
 }
 
 struct SubTile { int r0, r1, s0, s1; };
-// Sub-tile of SUB rows; r0 >= r1: nothing to do.
-__device__ __forceinline__ SubTile sub_tile(const AttnTile* __restrict__ tiles, int n_tiles, int per_tile) {
+// Sub-tile of `rows` rows; r0 >= r1: nothing to do.
+__device__ __forceinline__ SubTile sub_tile(const AttnTile* __restrict__ tiles, int n_tiles, int per_tile, int rows = SUB) {
   const int i = (int)(blockIdx.z * gridDim.y + blockIdx.y);
   if (i >= n_tiles * per_tile) return SubTile{0, 0, 0, 0};
   const AttnTile t = tiles[i / per_tile];
-  const int r0 = t.r0 + i % per_tile * SUB;
-  return SubTile{r0, min(r0 + SUB, t.r1), t.s0, t.s1};
+  const int r0 = t.r0 + i % per_tile * rows;
+  return SubTile{r0, min(r0 + rows, t.r1), t.s0, t.s1};
 }
 
 // ------------------------------------------------------------------------- forward
@@ -361,6 +360,248 @@ __global__ __launch_bounds__(256) void attn_dkv_f32_kernel(const float* __restri
   }
 }
 
+// ------------------------------------------------------------------------- short grids: the streamed side dealt to the wavefronts
+// When 64-row sub-tiles leave CUs idle, the time of the kernels above is one wavefront's serial walk over the other side (2.2 us per
+// 32 rows).  Here a workgroup owns 16 rows and its eight wavefronts take the 16-row blocks of the other side in turn, straight from
+// memory (no LDS, no barrier in the walk); their sums meet in LDS and are added in wavefront order.
+constexpr int SPLIT = 8, ROWS = 16;                     // wavefronts of a workgroup; rows it owns
+
+// Block of 16 rows at row0 of a [*, ld] tensor, rows at or past row_end repeat row_end - 1.  Rows: lane l has row l & 15, the values
+// 16 s + 4 (l >> 4) .. + 3 of slice s.  Columns: lane l has value 16 db + (l & 15) of row 4 (l >> 4) + r.
+template <int D>
+__device__ __forceinline__ void block_rows(f32x4v (&f)[F32Cfg<D>::NS], const float* __restrict__ p, int ld, int row0, int row_end, int lane) {
+  const float* row = p + (size_t)min(row0 + (lane & 15), row_end - 1) * ld + (lane >> 4) * 4;
+#pragma unroll
+  for (int s = 0; s < F32Cfg<D>::NS; ++s) f[s] = *reinterpret_cast<const f32x4v*>(row + s * 16);
+}
+template <int D>
+__device__ __forceinline__ void block_cols(f32x4v (&f)[F32Cfg<D>::NS], const float* __restrict__ p, int ld, int row0, int row_end, int lane) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const float* row = p + (size_t)min(row0 + (lane >> 4) * 4 + r, row_end - 1) * ld + (lane & 15);
+#pragma unroll
+    for (int db = 0; db < F32Cfg<D>::NS; ++db) f[db][r] = row[db * 16];
+  }
+}
+// a (16 rows) x b's fragments over the head dimension, in two chains
+template <int D>
+__device__ __forceinline__ f32x4v block_scores(const f32x4v (&a)[F32Cfg<D>::NS], const f32x4v (&b)[F32Cfg<D>::NS]) {
+  f32x4v acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+  for (int s = 0; s < F32Cfg<D>::NS; ++s)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[c & 1] = mfma4(a[s][c], b[s][c], acc[c & 1]);
+  return acc[0] + acc[1];
+}
+// out[db] += columns x weights w in the score layout
+template <int D>
+__device__ __forceinline__ void block_outer(f32x4v (&out)[F32Cfg<D>::NS], const f32x4v (&cols)[F32Cfg<D>::NS], const f32x4v& w) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int db = 0; db < F32Cfg<D>::NS; ++db) out[db] = mfma4(cols[db][r], w[r], out[db]);
+}
+// This wavefront's sums to its part of the exchange area [SPLIT][ROWS][D + 4].
+template <int D>
+__device__ __forceinline__ void put_sums(float* area, const f32x4v (&out)[F32Cfg<D>::NS], int wave, int lane) {
+  float* mine = area + (wave * ROWS + (lane & 15)) * F32Cfg<D>::PITCH + (lane >> 4) * 4;
+#pragma unroll
+  for (int db = 0; db < F32Cfg<D>::NS; ++db) *reinterpret_cast<f32x4v*>(mine + db * 16) = out[db];
+}
+// Sum over the wavefronts of four values of a row, each times its factor.
+template <int D>
+__device__ __forceinline__ f32x4v get_sum(const float* area, int row, int c, const float* factor) {
+  f32x4v v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int w = 0; w < SPLIT; ++w) {
+    const f32x4v x = *reinterpret_cast<const f32x4v*>(area + (w * ROWS + row) * F32Cfg<D>::PITCH + c);
+    v += factor ? x * factor[w * ROWS + row] : x;
+  }
+  return v;
+}
+
+template <int D>
+__global__ __launch_bounds__(64 * SPLIT) void attn_fwd_f32_split_kernel(const float* __restrict__ qkv, float* __restrict__ o, float* __restrict__ lse,
+                                                                        const AttnTile* __restrict__ tiles, int n_tiles, int Tn, int nq, int nkv,
+                                                                        int causal) {
+  constexpr int NS = F32Cfg<D>::NS;
+  __shared__ __attribute__((aligned(16))) float area[SPLIT * ROWS * F32Cfg<D>::PITCH];
+  __shared__ float ms[SPLIT * ROWS], ls[SPLIT * ROWS];
+  const SubTile tl = sub_tile(tiles, n_tiles, ATTN_TILE_Q / ROWS, ROWS);
+  if (tl.r0 >= tl.r1) return;
+  const int a = blockIdx.x, b = a / (nq / nkv);
+  const int ld = (nq + 2 * nkv) * D;
+  const float* kp = qkv + (nq + b) * D;
+  const float* vp = qkv + (nq + nkv + b) * D;
+  const float scale = 1.0f / sqrtf((float)D);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int qi = tl.r0 + (lane & 15);                   // this lane's query
+  f32x4v qf[NS], out[NS], kf[NS], vf[NS];
+  float m_run = -INFINITY, l_run = 0.f;
+  block_rows<D>(qf, qkv + a * D, ld, tl.r0, tl.r1, lane);
+#pragma unroll
+  for (int db = 0; db < NS; ++db) out[db] = f32x4v{0.f, 0.f, 0.f, 0.f};
+  const int kv_end = causal ? tl.r1 : tl.s1;
+  int k0 = tl.s0 + wave * 16;
+  if (k0 < kv_end) block_rows<D>(kf, kp, ld, k0, kv_end, lane);
+  for (; k0 < kv_end; k0 += 16 * SPLIT) {
+    block_cols<D>(vf, vp, ld, k0, kv_end, lane);
+    f32x4v s = block_scores<D>(kf, qf);
+    if (k0 + 16 * SPLIT < kv_end) block_rows<D>(kf, kp, ld, k0 + 16 * SPLIT, kv_end, lane);
+    float mx = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int j = k0 + (lane >> 4) * 4 + r;
+      s[r] = (j < kv_end && (!causal || j <= qi)) ? s[r] * scale : -INFINITY;
+      mx = fmaxf(mx, s[r]);
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float m_new = fmaxf(m_run, mx);              // -inf while every key so far is masked
+    const float alpha = m_run == -INFINITY ? 0.f : __expf(m_run - m_new);
+    float ps = 0.f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      s[r] = s[r] == -INFINITY ? 0.f : __expf(s[r] - m_new);
+      ps += s[r];
+    }
+    ps += __shfl_xor(ps, 16, 64);
+    ps += __shfl_xor(ps, 32, 64);
+    l_run = l_run * alpha + ps;
+    m_run = m_new;
+#pragma unroll
+    for (int db = 0; db < NS; ++db) out[db] *= alpha;
+    block_outer<D>(out, vf, s);
+  }
+  put_sums<D>(area, out, wave, lane);
+  if (lane < 16) {
+    ms[wave * ROWS + lane] = m_run;
+    ls[wave * ROWS + lane] = l_run;
+  }
+  __syncthreads();
+  if (threadIdx.x < ROWS) {                            // factors that bring the wavefronts to one reference point, over the row's sum
+    const int row = threadIdx.x;
+    float m = ms[row];
+#pragma unroll
+    for (int w = 1; w < SPLIT; ++w) m = fmaxf(m, ms[w * ROWS + row]);
+    float l = 0.f;
+#pragma unroll
+    for (int w = 0; w < SPLIT; ++w) l += ls[w * ROWS + row] == 0.f ? 0.f : ls[w * ROWS + row] * __expf(ms[w * ROWS + row] - m);
+    const float inv = 1.0f / l;
+#pragma unroll
+    for (int w = 0; w < SPLIT; ++w) ms[w * ROWS + row] = ls[w * ROWS + row] == 0.f ? 0.f : __expf(ms[w * ROWS + row] - m) * inv;
+    if (tl.r0 + row < tl.r1) lse[(size_t)a * Tn + tl.r0 + row] = m + __logf(l);
+  }
+  __syncthreads();
+  for (int q = threadIdx.x; q < ROWS * D / 4; q += 64 * SPLIT) {
+    const int row = q / (D / 4), c = (q - row * (D / 4)) * 4;
+    if (tl.r0 + row < tl.r1) *reinterpret_cast<f32x4v*>(o + (size_t)(tl.r0 + row) * nq * D + a * D + c) = get_sum<D>(area, row, c, ms);
+  }
+}
+
+template <int D>
+__global__ __launch_bounds__(64 * SPLIT) void attn_dq_f32_split_kernel(const float* __restrict__ qkv, const float* __restrict__ d_o,
+                                                                       const float* __restrict__ lse, const float* __restrict__ delta,
+                                                                       float* __restrict__ dqkv, const AttnTile* __restrict__ tiles, int n_tiles,
+                                                                       int Tn, int nq, int nkv, int causal) {
+  constexpr int NS = F32Cfg<D>::NS;
+  __shared__ __attribute__((aligned(16))) float area[SPLIT * ROWS * F32Cfg<D>::PITCH];
+  const SubTile tl = sub_tile(tiles, n_tiles, ATTN_TILE_Q / ROWS, ROWS);
+  if (tl.r0 >= tl.r1) return;
+  const int a = blockIdx.x, b = a / (nq / nkv);
+  const int ld = (nq + 2 * nkv) * D;
+  const float* kp = qkv + (nq + b) * D;
+  const float* vp = qkv + (nq + nkv + b) * D;
+  const float scale = 1.0f / sqrtf((float)D);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int qi = min(tl.r0 + (lane & 15), tl.r1 - 1);   // this lane's query; past the end the last one, not stored
+  f32x4v qf[NS], df[NS], out[NS], kf[NS], vf[NS], kc[NS];
+  block_rows<D>(qf, qkv + a * D, ld, tl.r0, tl.r1, lane);
+  block_rows<D>(df, d_o + a * D, nq * D, tl.r0, tl.r1, lane);
+  const float lse_q = lse[(size_t)a * Tn + qi], delta_q = delta[(size_t)a * Tn + qi];
+#pragma unroll
+  for (int db = 0; db < NS; ++db) out[db] = f32x4v{0.f, 0.f, 0.f, 0.f};
+  const int kv_end = causal ? tl.r1 : tl.s1;
+  for (int k0 = tl.s0 + wave * 16; k0 < kv_end; k0 += 16 * SPLIT) {
+    block_rows<D>(kf, kp, ld, k0, kv_end, lane);
+    block_rows<D>(vf, vp, ld, k0, kv_end, lane);
+    block_cols<D>(kc, kp, ld, k0, kv_end, lane);
+    f32x4v s = block_scores<D>(kf, qf);
+    const f32x4v dp = block_scores<D>(vf, df);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int j = k0 + (lane >> 4) * 4 + r;
+      const float p = (j < kv_end && (!causal || j <= qi)) ? __expf(s[r] * scale - lse_q) : 0.f;
+      s[r] = p * (dp[r] - delta_q);
+    }
+    block_outer<D>(out, kc, s);
+  }
+  put_sums<D>(area, out, wave, lane);
+  __syncthreads();
+  for (int q = threadIdx.x; q < ROWS * D / 4; q += 64 * SPLIT) {
+    const int row = q / (D / 4), c = (q - row * (D / 4)) * 4;
+    if (tl.r0 + row < tl.r1)
+      *reinterpret_cast<f32x4v*>(dqkv + (size_t)(tl.r0 + row) * ld + a * D + c) = get_sum<D>(area, row, c, nullptr) * scale;
+  }
+}
+
+template <int D>
+__global__ __launch_bounds__(64 * SPLIT) void attn_dkv_f32_split_kernel(const float* __restrict__ qkv, const float* __restrict__ d_o,
+                                                                        const float* __restrict__ lse, const float* __restrict__ delta,
+                                                                        float* __restrict__ dqkv, const AttnTile* __restrict__ tiles, int n_tiles,
+                                                                        int Tn, int nq, int nkv, int causal, float* __restrict__ part) {
+  constexpr int NS = F32Cfg<D>::NS;
+  __shared__ __attribute__((aligned(16))) float area[SPLIT * ROWS * F32Cfg<D>::PITCH];
+  const SubTile tl = sub_tile(tiles, n_tiles, ATTN_TILE_KV / ROWS, ROWS);
+  if (tl.r0 >= tl.r1) return;
+  const int a = blockIdx.x, G = nq / nkv, b = a / G;
+  const int ld = (nq + 2 * nkv) * D;
+  const float scale = 1.0f / sqrtf((float)D);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int key = tl.r0 + (lane & 15);                  // of this lane; not stored when past the end
+  f32x4v kf[NS], vf[NS], dk[NS], dv[NS], x[NS], y[NS];
+  block_rows<D>(kf, qkv + (nq + b) * D, ld, tl.r0, tl.r1, lane);
+  block_rows<D>(vf, qkv + (nq + nkv + b) * D, ld, tl.r0, tl.r1, lane);
+#pragma unroll
+  for (int db = 0; db < NS; ++db) { dk[db] = f32x4v{0.f, 0.f, 0.f, 0.f}; dv[db] = dk[db]; }
+  for (int q0 = (causal ? tl.r0 : tl.s0) + wave * 16; q0 < tl.s1; q0 += 16 * SPLIT) {
+    f32x4v l4, d4;
+    block_rows<D>(x, qkv + a * D, ld, q0, tl.s1, lane);
+    block_rows<D>(y, d_o + a * D, nq * D, q0, tl.s1, lane);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const size_t qi = (size_t)a * Tn + min(q0 + (lane >> 4) * 4 + r, tl.s1 - 1);
+      l4[r] = lse[qi];
+      d4[r] = delta[qi];
+    }
+    f32x4v s = block_scores<D>(x, kf), dp = block_scores<D>(y, vf);
+    block_cols<D>(x, qkv + a * D, ld, q0, tl.s1, lane);
+    block_cols<D>(y, d_o + a * D, nq * D, q0, tl.s1, lane);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int qi = q0 + (lane >> 4) * 4 + r;
+      const float p = (qi < tl.s1 && (!causal || key <= qi)) ? __expf(s[r] * scale - l4[r]) : 0.f;
+      s[r] = p;
+      dp[r] = p * (dp[r] - d4[r]);
+    }
+    block_outer<D>(dk, x, dp);
+    block_outer<D>(dv, y, s);
+  }
+#pragma unroll
+  for (int tensor = 0; tensor < 2; ++tensor) {
+    if (tensor) __syncthreads();
+    put_sums<D>(area, tensor ? dv : dk, wave, lane);
+    __syncthreads();
+    for (int q = threadIdx.x; q < ROWS * D / 4; q += 64 * SPLIT) {
+      const int row = q / (D / 4), c = (q - row * (D / 4)) * 4, kj = tl.r0 + row;
+      if (kj >= tl.r1) continue;
+      const f32x4v v = get_sum<D>(area, row, c, nullptr);
+      if (part) *reinterpret_cast<f32x4v*>(part + ((size_t)(tensor * G + a - b * G) * Tn + kj) * nkv * D + b * D + c) = v;
+      else *reinterpret_cast<f32x4v*>(dqkv + (size_t)kj * ld + (nq + tensor * nkv + b) * D + c) = tensor ? v : v * scale;
+    }
+  }
+}
+
 // dK, dV = sum of the G planes of a group in head order.
 __global__ __launch_bounds__(256) void dkv_combine_f32_kernel(const float* __restrict__ part, float* __restrict__ dqkv, int Tn, int nq,
                                                               int nkv, int D, float scale) {
@@ -382,24 +623,37 @@ dim3 sub_tile_grid(int nq, int n) {
   return dim3(nq, (n + z - 1) / z, z);
 }
 
+// Which kernels: below two 64-row sub-tiles of a query head per CU the split ones.  us, 64-row sub-tiles -> split, forward, dK/dV, dQ:
+// 128 rows x 4 heads 12.4 -> 6.7, 15.7 -> 8.2, 12.1 -> 7.0; 517 x 16 35 -> 18, 54 -> 29, 40 -> 21; 1024 x 16 (two segments) 53 -> 31, 75 -> 56,
+// 62 -> 42; 1024 x 8 of 128 105 -> 49, 172 -> 75, 131 -> 62; 2048 x 16 155 -> 121, 248 -> 258, 189 -> 187; 4096 x 16 421 -> 425, 721 -> 935,
+// 543 -> 682 (every block of the other side is read by four times as many workgroups).  32 rows a workgroup: slower up to 1024 x 16.
+bool split_streams(const AttnArgs& a) { return (long long)a.T * a.nq < 2LL * SUB * device_cu_count(); }
+
 template <int D>
 hipError_t fwd_launch(const AttnArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(attn_fwd_f32_kernel<D>, sub_tile_grid(a.nq, a.n_q_tiles * (ATTN_TILE_Q / SUB)), dim3(256), 0, s, (const float*)a.qkv, (float*)a.o,
-                     a.lse, a.q_tiles, a.n_q_tiles, a.T, a.nq, a.nkv, a.causal);
+  const bool split = split_streams(a);
+  const auto kernel = split ? attn_fwd_f32_split_kernel<D> : attn_fwd_f32_kernel<D>;
+  hipLaunchKernelGGL(kernel, sub_tile_grid(a.nq, a.n_q_tiles * (ATTN_TILE_Q / (split ? ROWS : SUB))), dim3(split ? 64 * SPLIT : 256), 0, s,
+                     (const float*)a.qkv, (float*)a.o, a.lse, a.q_tiles, a.n_q_tiles, a.T, a.nq, a.nkv, a.causal);
   return hipGetLastError();
 }
 
 template <int D>
 hipError_t bwd_launch(const AttnArgs& a, hipStream_t s) {
   float* part = a.nq > a.nkv ? a.dkv_part : nullptr;
+  const bool split = split_streams(a);
+  const dim3 threads(split ? 64 * SPLIT : 256);
+  const int rows = split ? ROWS : SUB;
   hipLaunchKernelGGL(attn_delta_f32_kernel, dim3((a.T * a.nq + 15) / 16), dim3(256), 0, s, (const float*)a.o, (const float*)a.d_o, a.delta, a.T,
                      a.nq, a.d);
-  hipLaunchKernelGGL(attn_dkv_f32_kernel<D>, sub_tile_grid(a.nq, a.n_kv_tiles * (ATTN_TILE_KV / SUB)), dim3(256), 0, s, (const float*)a.qkv,
+  const auto dkv = split ? attn_dkv_f32_split_kernel<D> : attn_dkv_f32_kernel<D>;
+  hipLaunchKernelGGL(dkv, sub_tile_grid(a.nq, a.n_kv_tiles * (ATTN_TILE_KV / rows)), threads, 0, s, (const float*)a.qkv,
                      (const float*)a.d_o, a.lse, a.delta, (float*)a.dqkv, a.kv_tiles, a.n_kv_tiles, a.T, a.nq, a.nkv, a.causal, part);
   if (part)
     hipLaunchKernelGGL(dkv_combine_f32_kernel, dim3((unsigned)(((size_t)a.T * a.nkv * D / 4 + 255) / 256)), dim3(256), 0, s, part,
                        (float*)a.dqkv, a.T, a.nq, a.nkv, D, 1.0f / sqrtf((float)D));
-  hipLaunchKernelGGL(attn_dq_f32_kernel<D>, sub_tile_grid(a.nq, a.n_q_tiles * (ATTN_TILE_Q / SUB)), dim3(256), 0, s, (const float*)a.qkv,
+  const auto dq = split ? attn_dq_f32_split_kernel<D> : attn_dq_f32_kernel<D>;
+  hipLaunchKernelGGL(dq, sub_tile_grid(a.nq, a.n_q_tiles * (ATTN_TILE_Q / rows)), threads, 0, s, (const float*)a.qkv,
                      (const float*)a.d_o, a.lse, a.delta, (float*)a.dqkv, a.q_tiles, a.n_q_tiles, a.T, a.nq, a.nkv, a.causal);
   return hipGetLastError();
 }

@@ -11,6 +11,9 @@ pytestmark = pytest.mark.gpu
 # 32; outputs of 127 and 128+ tiles of 64 x 64 (the last size of the small kernel, the first of the tile kernel)
 GEMM_SHAPES = [(1, 1, 1), (31, 33, 7), (32, 64, 8), (63, 65, 33), (70, 45, 31), (8 * 64 + 1, 14 * 64, 40), (8 * 64, 15 * 64 + 63, 9),
                (8 * 64, 16 * 64, 32), (8 * 64 + 7, 16 * 64 + 3, 70), (1025, 516, 129)]
+# one short of, at and past a 16-tile, a chunk of 16 k and the k range of a wavefront; 96 tiles of 32 x 32 (the last size of the 16-tile
+# kernel) and 99, 97
+TINY_SHAPES = [(15, 17, 15), (16, 16, 16), (17, 31, 129), (33, 47, 513), (8 * 32, 12 * 32, 130), (8 * 32 + 1, 11 * 32, 127), (1, 97 * 32, 20)]
 
 
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
@@ -21,7 +24,7 @@ def test_f32_gemm_tile_edges(ta, tb, pad):
     import torch
     import paper_2605_18750_amd as R
     from paper_2605_18750_amd import harness as Hn
-    for M, N, K in GEMM_SHAPES:
+    for M, N, K in GEMM_SHAPES + TINY_SHAPES:
         print(f"[f32 gemm] M{M} N{N} K{K} ta{ta} tb{tb} pad{pad}", flush=True)
         shp = [(K, M) if ta else (M, K), (N, K) if tb else (K, N), (M, N)]
         A, B, Rr = [SI.make_tensor(7, f"f32{M}.{N}.{K}{n}", s, 1.0, "fp32") for n, s in zip("ABR", shp)]
@@ -51,6 +54,22 @@ def test_f32_attention_tile_edges(d, causal, nq, nkv):
     w = Hp.Workload(shape, [[0] + [int(v) for v in np.cumsum(n)] for n in lengths])
     print(f"[f32 attention] d{d} causal{causal} heads {nq}/{nkv}", flush=True)
     worst = Hp.compare(Hp.run_gpu(w), Hp.run_oracle(w), Hp.TOL["fp32"], f"d{d}")
+    print(f"[f32 attention] d{d}: worst {worst:.2e}", flush=True)
+
+
+@pytest.mark.parametrize("d,causal,nkv", [(16, True, 64), (32, False, 8), (48, True, 16), (64, True, 4), (80, False, 16), (96, True, 32),
+                                          (112, False, 16), (128, True, 4)])
+def test_f32_attention_choice_of_kernels(d, causal, nkv):
+    """64 query heads: at 512 tokens (2 x 64 rows a CU on 256 CUs) the 64-row kernels run, at 511 the ones that deal the other side to the
+    wavefronts.  Segments around 16 and 128 rows (one and all blocks of eight wavefronts)."""
+    shape = SI.StageShape(f"f32choice{d}", 1, 32, 64, nkv, d, 32, 2, dtype="fp32", x_std=1.0, dy_std=1.0, w_std=0.15, causal=causal)
+    lengths = [[1, 17, 127, 129, 15, 223], [16, 144, 128, 223]]
+    assert [sum(n) for n in lengths] == [512, 511]
+    w = Hp.Workload(shape, [[0] + [int(v) for v in np.cumsum(n)] for n in lengths])
+    print(f"[f32 attention] d{d} causal{causal} heads 64/{nkv}", flush=True)
+    got = Hp.run_gpu(w, keep_raw=True)
+    worst = Hp.compare(got, Hp.run_oracle(w), Hp.TOL["fp32"], f"d{d}")
+    Hp.assert_bit_identical(got, Hp.run_gpu(w, keep_raw=True))
     print(f"[f32 attention] d{d}: worst {worst:.2e}", flush=True)
 
 
