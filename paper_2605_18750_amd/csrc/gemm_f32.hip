@@ -5,7 +5,7 @@
 // fp32-FMA kernel needs an LDS read for every few FMAs; one 32x32x2 MFMA takes two registers and keeps the matrix
 // pipe busy for 64 cycles, so neither LDS nor issue slots limit anything here.  Products and sums stay fp32.
 //
-// Two tile routines, chosen by the size of the output alone (see launch_f32):
+// Three tile routines, chosen by the size of the output alone (see f32_tile_edge):
 //   f32_tile   tiles of 64 x 64, eight wavefronts, 32-deep k steps through two LDS buffers (global loads two
 //     steps ahead, one barrier per step).  1024 x 1024 x 5504: 112 us = 103 TFLOP/s; the fp32-FMA kernel that was here
 //     before: 385 us on 517 rows of it, now 111.  (128 x 128 tiles: 5 % faster at 4096^3, two to four times slower on
@@ -13,6 +13,7 @@
 //   f32_small  tiles of 32 x 32 whose eight wavefronts split the contraction and read their
 //     fragments straight from global memory (L2): for outputs with too few tiles to fill the chip the time is the
 //     latency of the serial k loop, and this cuts the loop and takes the barriers out of it (128 x 256 x 688: 95 -> 8 us).
+//   f32_tiny   the same with tiles of 16 x 16 for the smallest outputs (128 x 256 x 688: 8 -> 5 us).
 //
 // The contraction index is free to be permuted as long as both operands agree: in a chunk of 8 k the half h of a
 // wavefront holds k = 4h + i for the i-th of four MFMAs, so a K-contiguous operand is read 16 bytes at a time.
@@ -235,12 +236,66 @@ __device__ __forceinline__ void f32_small(const float* __restrict__ A, const flo
   }
 }
 
-template <bool TA, bool TB, bool VEC, bool SMALL>
-__global__ __launch_bounds__(SMALL ? 64 * SMALL_WAVES : TILE_THREADS) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ B,
+// Tiles of 16 x 16 on v_mfma_f32_16x16x4_f32, otherwise as f32_small: four times the workgroups for the smallest outputs.  In a
+// chunk of 16 k lane l holds row l & 15 and k = 4 (l >> 4) + i for the i-th of four MFMAs.
+constexpr int TINY = 16, TINY_CHUNKS = 4;
+__device__ __forceinline__ f32x4v mfma_f32_16(float a, float b, f32x4v c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+template <bool TA, bool TB, bool VEC>
+__device__ __forceinline__ void f32_tiny(const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ C,
+                                         const float* __restrict__ R, const float* __restrict__ bias, int M, int N, int K, int lda, int ldb,
+                                         int ldc, int ldr, int m0, int n0) {
+  __shared__ float red[SMALL_WAVES][TINY * TINY];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int m = min(m0 + (lane & 15), M - 1), n = min(n0 + (lane & 15), N - 1);
+  const int chunks = (K + 15) / 16, per = (chunks + SMALL_WAVES - 1) / SMALL_WAVES;
+  const int k_end = min(K, (wave + 1) * per * 16);
+  f32x4v acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+  f32x4v fa[2][TINY_CHUNKS], fb[2][TINY_CHUNKS];
+  auto fetch = [&](f32x4v (&a)[TINY_CHUNKS], f32x4v (&b)[TINY_CHUNKS], int k0) {
+#pragma unroll
+    for (int c = 0; c < TINY_CHUNKS; ++c) {
+      const int k = k0 + c * 16 + (lane >> 4) * 4;
+      a[c] = small_frag<!TA, VEC>(A, lda, m, k, k_end);
+      b[c] = small_frag<TB, VEC>(B, ldb, n, k, k_end);
+    }
+  };
+  auto multiply = [&](const f32x4v (&a)[TINY_CHUNKS], const f32x4v (&b)[TINY_CHUNKS]) {
+#pragma unroll
+    for (int c = 0; c < TINY_CHUNKS; ++c)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[c & 1] = mfma_f32_16(a[c][i], b[c][i], acc[c & 1]);
+  };
+  constexpr int KB = TINY_CHUNKS * 16;
+  int k0 = wave * per * 16;
+  if (k0 < k_end) {
+    fetch(fa[0], fb[0], k0);
+    for (; k0 < k_end; k0 += 2 * KB) {
+      if (k0 + KB < k_end) fetch(fa[1], fb[1], k0 + KB);
+      multiply(fa[0], fb[0]);
+      if (k0 + KB < k_end) {
+        if (k0 + 2 * KB < k_end) fetch(fa[0], fb[0], k0 + 2 * KB);
+        multiply(fa[1], fb[1]);
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) red[wave][((lane >> 4) * 4 + r) * TINY + (lane & 15)] = acc[0][r] + acc[1][r];
+  __syncthreads();
+  const int q = threadIdx.x, mo = m0 + (q >> 4), no = n0 + (q & 15);
+  if (q >= TINY * TINY || mo >= M || no >= N) return;
+  float v = red[0][q];
+#pragma unroll
+  for (int w = 1; w < SMALL_WAVES; ++w) v += red[w][q];
+  put_f32(v, C, R, bias, mo, no, ldc, ldr);
+}
+
+template <bool TA, bool TB, bool VEC, int EDGE>
+__global__ __launch_bounds__(EDGE < 64 ? 64 * SMALL_WAVES : TILE_THREADS) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ B,
                                                                                          float* __restrict__ C, const float* __restrict__ R,
                                                                                          const float* __restrict__ bias, int M, int N, int K,
                                                                                          int lda, int ldb, int ldc, int ldr) {
-  if constexpr (SMALL) f32_small<TA, TB, VEC>(A, B, C, R, bias, M, N, K, lda, ldb, ldc, ldr, blockIdx.y * 32, blockIdx.x * 32);
+  if constexpr (EDGE == TINY) f32_tiny<TA, TB, VEC>(A, B, C, R, bias, M, N, K, lda, ldb, ldc, ldr, blockIdx.y * TINY, blockIdx.x * TINY);
+  else if constexpr (EDGE == 32) f32_small<TA, TB, VEC>(A, B, C, R, bias, M, N, K, lda, ldb, ldc, ldr, blockIdx.y * 32, blockIdx.x * 32);
   else f32_tile<TA, TB, VEC>(A, B, C, R, bias, M, N, K, lda, ldb, ldc, ldr, blockIdx.y * 64, blockIdx.x * 64);
 }
 
@@ -271,17 +326,24 @@ __global__ __launch_bounds__(SMALL ? 64 * SMALL_WAVES : TILE_THREADS) void gemm_
 // Which kernel: fewer than 128 tiles of 64 x 64 leave over half of the chip idle, and the small kernel's 32 x 32 tiles
 // then win (128 x 256 x 1376: 15 against 30 us; at 144 tiles, 517 x 1024 x 1024, it is 29 against 24 us).
 // Sixteen k ranges instead of eight change nothing: the operand rows then bound it through the L1.
+// So below 97 tiles of 32 x 32 the tiles are 16 x 16, which spreads those rows over four times the CUs (us, 32 -> 16): 128 x 256 x 1376 15.3 ->
+// 7.5, x 256 4.4 -> 3.2, 32 x 1024 x 2752 28.9 -> 12.7, 128 x 768 x 256 (96 tiles) 4.5 -> 4.4; but 128 x 1376 x 256 (172 tiles) 4.9 -> 6.5.
+int f32_tile_edge(int M, int N) {
+  auto tiles = [&](int edge) { return (long long)((M + edge - 1) / edge) * ((N + edge - 1) / edge); };
+  return tiles(64) >= 128 ? 64 : tiles(32) > 96 ? 32 : TINY;
+}
+
 template <bool TA, bool TB, bool VEC>
 hipError_t launch_f32(const GemmArgs& g, hipStream_t s) {
   const float *A = (const float*)g.A, *B = (const float*)g.B, *bias = (const float*)g.bias;
   float* C = (float*)g.C;
-  const bool small = (long long)((g.M + 63) / 64) * ((g.N + 63) / 64) < 128;
-  const int t = small ? 32 : 64;
+  const int t = f32_tile_edge(g.M, g.N);
   const dim3 grid((g.N + t - 1) / t, (g.M + t - 1) / t);
-#define RRFP_GO(SMALL, THREADS) \
-  hipLaunchKernelGGL((gemm_f32_kernel<TA, TB, VEC, SMALL>), grid, dim3(THREADS), 0, s, A, B, C, g.R, bias, g.M, g.N, g.K, g.lda, g.ldb, g.ldc, g.ldr)
-  if (!small) RRFP_GO(false, TILE_THREADS);
-  else RRFP_GO(true, 64 * SMALL_WAVES);
+#define RRFP_GO(EDGE, THREADS) \
+  hipLaunchKernelGGL((gemm_f32_kernel<TA, TB, VEC, EDGE>), grid, dim3(THREADS), 0, s, A, B, C, g.R, bias, g.M, g.N, g.K, g.lda, g.ldb, g.ldc, g.ldr)
+  if (t == 64) RRFP_GO(64, TILE_THREADS);
+  else if (t == 32) RRFP_GO(32, 64 * SMALL_WAVES);
+  else RRFP_GO(TINY, 64 * SMALL_WAVES);
 #undef RRFP_GO
   return hipGetLastError();
 }
