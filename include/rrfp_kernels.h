@@ -38,7 +38,7 @@ int rrfp_gemm(const void* A, const void* B, void* C, const void* R, int M, int N
  * into the workspace and are added in range order, or run in 64 x 64 tiles, when their tiles would leave the chip idle; so
  * may the weight-gradient form (bf16 inputs, trans_a = 1, trans_b = 0, fp32 output, no residual).  Without a workspace a call
  * keeps the cut and the bits of the unsplit tiles.  A workspace too small for the ranges a shape would take gives fewer
- * ranges, 64 x 64 tiles or no split (rrfp_gemm_plan_ws tells which).  The result is bit-identical from call to call for a
+ * ranges, small tiles or no split (rrfp_gemm_plan_ws tells which).  The result is bit-identical from call to call for a
  * given shape, plan and device. */
 int rrfp_gemm_ws(const void* A, const void* B, void* C, const void* R, int M, int N, int K, int lda, int ldb,
                  int ldc, int ldr, int trans_a, int trans_b, int in_dtype, int out_dtype, int family,
@@ -49,7 +49,7 @@ int rrfp_gemm_ws(const void* A, const void* B, void* C, const void* R, int M, in
  * would use).  The cut is a pure function of the
  * shape and n_cu, which is what keeps the summation order of a call fixed (the bit-exactness requirement
  * behind readiness-driven reordering, paper Section 7.1).  out[0] = kernel (0 the MFMA family refuses the
- * shape, 1 direct-to-LDS, 2 register-staged, 3 the 64 x 64 tiles of small outputs, with scratch only), out[1] =
+ * shape, 1 direct-to-LDS, 2 register-staged, 3 the 64 x 64 or 32 x 32 tiles of small outputs, with scratch only), out[1] =
  * wavefronts per workgroup, out[2] = workgroups of the 256-row-tile (kernel 3: only) launch, out[3] = workgroups of
  * the second launch that finishes a grid whose last round would be nearly empty (128-row tiles when A is K-contiguous; for the weight-gradient form with scratch the
  * trailing tile columns split along K into out[4] ranges), out[4] = split-K ranges (weight-gradient form with

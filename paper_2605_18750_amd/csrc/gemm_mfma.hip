@@ -11,7 +11,7 @@
 //     128-row tile variant and a split-K mode for grids that do not fill the CUs.
 //   gemm_mfma_kernel     the fallback for K-contiguous operands whose K is not a multiple of 32: four
 //     wavefronts, v_mfma_f32_32x32x16_bf16, 64-deep steps, two LDS stages filled through registers.
-//   gemm_mfma_small_kernel  64 x 64 tiles, the contraction dealt to the wavefronts of a workgroup.
+//   gemm_mfma_small_kernel  64 x 64 or 32 x 32 tiles, the contraction dealt to the wavefronts of a workgroup.
 //
 // Operand tiles sit in LDS in their memory orientation, so every global load is a coalesced
 // 16-byte access:
@@ -1073,7 +1073,7 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(const float* __restr
 }
 
 // ------------------------------------------------------------------------------------------
-// Small outputs.  Tiles of 64 x 64 whose NW wavefronts each contract a range of k on their own (64 accumulator registers of
+// Small outputs.  Tiles of 64 x 64 (or 32 x 32, see small_edge) whose NW wavefronts each contract a range of k on their own (64 accumulator registers of
 // v_mfma_f32_16x16x32, no barrier before the end); their sums meet in LDS and are added in range order, and every fused
 // epilogue of the tile kernel runs on them.  What bounds an output of a few tiles is latency: a 256- or 128-row tile is one
 // workgroup's serial walk over K plus the store of a large tile by one CU (11 us for 512 x 512 x 100); this spreads
@@ -1083,84 +1083,94 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(const float* __restr
 //     by the LDS transpose read; chunk c of row k sits at c ^ swz(k), so that the 8 k-rows of a pass meet 8 bank groups.
 // Operands of k at or past K read as zero, rows and columns past the end repeat the last ones and are not stored.
 // ------------------------------------------------------------------------------------------
-constexpr int ST = 64, ST_TILE = 32 * ST * 2;         // tile edge; bytes of one K-strided operand tile of one step
+constexpr int ST = 64;                                 // tile edge
 
 __device__ __forceinline__ int st_swz(int k) { return ((((k >> 1) & 1) | (((k >> 3) & 1) << 1)) << 1); }
 
-// One operand of a wavefront: 32-deep steps of four loads.  (64-deep ones, which fetch whole 128-byte lines of a K-contiguous
+// One operand of a wavefront: 32-deep steps of EDGE / 16 loads.  (64-deep ones, which fetch whole 128-byte lines of a K-contiguous
 // operand at once, measured the same and spilled in the SwiGLU form.)
-template <bool KC>
+template <bool KC, int EDGE>
 struct SmallOperand {
-  const bf16_t* p[4];     // KC: row of fragment i at this lane's k offset; else: this lane's chunk of k row (lane >> 3) + 8 i
-  int k_lane[4], step;    // k of the lane's element in step 0; elements per step
+  static constexpr int NB = EDGE / 16;                // 16-row blocks, and loads of a step
+  static constexpr int CPR = EDGE / 8, KPL = 64 / CPR; // K-strided: 16-byte chunks per k row, k rows per load
+  const bf16_t* p[NB];    // KC: row of fragment i at this lane's k offset; else: this lane's chunk of k row lane / CPR + KPL i
+  int k_lane[NB], step;   // k of the lane's element in step 0; elements per step
   int lds_w, lds_r;
-  // SwiGLU forward: tile columns 0..31 are gate, 32..63 the up columns of the same features (pair_f = ffn)
+  // SwiGLU forward: the first half of the tile columns is gate, the second the up columns of the same features (pair_f = ffn)
   __device__ __forceinline__ void init(const bf16_t* base, int ld, int outer0, int outer_n, int lane, int pair_f) {
     step = KC ? 32 : 32 * ld;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < NB; ++i) {
       if constexpr (KC) {
         k_lane[i] = (lane >> 4) * 8;
         p[i] = base + (size_t)min(outer0 + i * 16 + (lane & 15), outer_n - 1) * ld + k_lane[i];
       } else {
-        const int c = (lane & 7) * 8;
-        const int col = pair_f > 0 ? (c >> 5) * pair_f + (outer0 >> 1) + (c & 31) : min(outer0 + c, outer_n - 8);
-        k_lane[i] = (lane >> 3) + i * 8;
+        const int c = lane % CPR * 8;
+        const int col = pair_f > 0 ? (c >= EDGE / 2 ? pair_f : 0) + (outer0 >> 1) + c % (EDGE / 2) : min(outer0 + c, outer_n - 8);
+        k_lane[i] = lane / CPR + i * KPL;
         p[i] = base + (size_t)k_lane[i] * ld + col;
       }
     }
     if constexpr (!KC) {
-      // k rows of load i are (lane >> 3) + 8 i: bits 0..2 from the lane, bit 3 from i (an XOR of 64 bytes below)
-      lds_w = (lane >> 3) * 128 + (((lane & 7) ^ st_swz(lane >> 3)) << 4);
+      // a row of the LDS tile is EDGE * 2 bytes; bits 0..2 (EDGE 32: 0..3) of k come from the lane, bit 3 of EDGE 64 from i (an XOR of
+      // 64 bytes in put)
+      lds_w = lane / CPR * (EDGE * 2) + ((lane % CPR ^ swz(lane / CPR)) << 4);
       const int kb = (lane >> 4) * 8 + ((lane & 15) >> 2);
-      lds_r = kb * 128 + ((((lane & 3) >> 1) ^ st_swz(kb)) << 4) + (lane & 1) * 8;
+      lds_r = kb * (EDGE * 2) + ((((lane & 3) >> 1) ^ swz(kb)) << 4) + (lane & 1) * 8;
     }
   }
-  __device__ __forceinline__ void fetch(uint4 (&r)[4], int t, int k_end) const {
+  // The 8 k rows of a transposed read's pass meet 8 bank groups (EDGE 32: rows of half the length, two chunk pairs)
+  __device__ static __forceinline__ int swz(int k) { return EDGE == 64 ? st_swz(k) : ((k >> 2) & 1) << 1; }
+  __device__ __forceinline__ void fetch(uint4 (&r)[NB], int t, int k_end) const {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < NB; ++i) {
       r[i] = make_uint4(0, 0, 0, 0);
       if (t * 32 + k_lane[i] < k_end) r[i] = *reinterpret_cast<const uint4*>(p[i] + (size_t)t * step);
     }
   }
-  __device__ __forceinline__ void put(const uint4 (&r)[4], char* tile) const {
+  __device__ __forceinline__ void put(const uint4 (&r)[NB], char* tile) const {
     if constexpr (!KC) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) *reinterpret_cast<uint4*>(tile + i * 1024 + (lds_w ^ ((i & 1) << 6))) = r[i];
+      for (int i = 0; i < NB; ++i) *reinterpret_cast<uint4*>(tile + i * 1024 + (EDGE == 64 ? lds_w ^ ((i & 1) << 6) : lds_w)) = r[i];
     }
   }
-  __device__ __forceinline__ bf16x8 frag(const uint4 (&r)[4], const char* tile, int i) const {
+  __device__ __forceinline__ bf16x8 frag(const uint4 (&r)[NB], const char* tile, int i) const {
     if constexpr (KC) return __builtin_bit_cast(bf16x8, r[i]);
-    // block i: chunks 2i, 2i + 1; the second read, 4 k rows on, changes neither swizzle bit
+    // block i: chunks 2i, 2i + 1; the second read is 4 k rows on (EDGE 32: the other swizzle)
     const lds_char_ptr q = (lds_char_ptr)tile + (lds_r ^ (i << 5));
+    const lds_char_ptr q4 = EDGE == 64 ? q + 512 : (lds_char_ptr)tile + ((lds_r + 256) ^ (i << 5) ^ 32);
     union { short4v h[2]; bf16x8 v; } u;
     u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)q);
-    u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(q + 512));
+    u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)q4);
     return u.v;
   }
 };
 
 constexpr int SMALL_NW = 8;                            // four wavefronts, two workgroups per CU: 5 to 40 % slower
-template <bool A_KC, bool B_KC, typename TO, bool HAS_R, int ACT, bool F16IN>
+// EDGE: 64, or 32 for the smallest outputs, whose time is a wavefront's chain of loads and the exchange of the sums: four times
+// the workgroups, a quarter of the exchange, and loads three steps ahead instead of one.
+template <bool A_KC, bool B_KC, typename TO, bool HAS_R, int ACT, bool F16IN, int EDGE>
 __device__ __forceinline__ void small_tile(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, TO* __restrict__ C,
                                            const float* __restrict__ R, int M, int N, int K, int lda, int ldb, int ldc, int ldr, int m0,
                                            int n0, bf16_t* __restrict__ E, int lde, const bf16_t* __restrict__ bias,
                                            const float* __restrict__ out_scale) {
-  constexpr int NW = SMALL_NW, PITCH = ST + 4;         // floats per row of a wavefront's sums
-  constexpr int RED = ST * PITCH * 4, STAGE = (A_KC ? 0 : ST_TILE) + (B_KC ? 0 : ST_TILE);
+  constexpr int NW = SMALL_NW, PITCH = EDGE + 4, NB = EDGE / 16;   // PITCH: floats per row of a wavefront's sums
+  constexpr int TILE = 32 * EDGE * 2;                  // bytes of one K-strided operand tile of one step
+  constexpr int RED = EDGE * PITCH * 4, STAGE = (A_KC ? 0 : TILE) + (B_KC ? 0 : TILE);
+  constexpr int AHEAD = EDGE == 64 ? 2 : 4;            // steps in registers
   static_assert(STAGE <= RED, "the staging tiles live inside the wavefront's part of the sums");
   __shared__ __attribute__((aligned(1024))) char pool[NW * RED];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   char* mine = pool + wave * RED;
-  SmallOperand<A_KC> oa;
-  SmallOperand<B_KC> ob;
+  SmallOperand<A_KC, EDGE> oa;
+  SmallOperand<B_KC, EDGE> ob;
   oa.init(A, lda, m0, M, lane, 0);
   ob.init(B, ldb, n0, N, lane, ACT == ACT_SWIGLU_FWD ? N >> 1 : 0);
-  floatx4 acc[4][4];
+  floatx4 acc[NB][NB];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < NB; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < NB; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
   const int steps = (K + 31) / 32, per = (steps + NW - 1) / NW;
   const int t0 = wave * per, t1 = min(steps, t0 + per), k_end = min(K, t1 * 32);
   auto wave_sync = [] {
@@ -1168,41 +1178,43 @@ __device__ __forceinline__ void small_tile(const bf16_t* __restrict__ A, const b
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   };
-  uint4 ra[2][4], rb[2][4];
+  uint4 ra[AHEAD][NB], rb[AHEAD][NB];
   auto multiply = [&](int set) {                      // set: a constant at every call
-    char* tile_b = mine + (A_KC ? 0 : ST_TILE);
+    char* tile_b = mine + (A_KC ? 0 : TILE);
     oa.put(ra[set], mine);
     ob.put(rb[set], tile_b);
     if constexpr (!A_KC || !B_KC) wave_sync();
-    bf16x8 fa[4], fb[4];
+    bf16x8 fa[NB], fb[NB];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) { fa[i] = oa.frag(ra[set], mine, i); fb[i] = ob.frag(rb[set], tile_b, i); }
-    mfma_blocks<4, 4, 4, F16IN>(acc, fa, fb, 0);
+    for (int i = 0; i < NB; ++i) { fa[i] = oa.frag(ra[set], mine, i); fb[i] = ob.frag(rb[set], tile_b, i); }
+    mfma_blocks<NB, NB, NB, F16IN>(acc, fa, fb, 0);
     if constexpr (!A_KC || !B_KC) wave_sync();
   };
   if (t0 < t1) {
-    oa.fetch(ra[0], t0, k_end);
-    ob.fetch(rb[0], t0, k_end);
-    for (int t = t0; t < t1; t += 2) {                // loads run one step ahead; past the range they give zeros without a memory access
-      oa.fetch(ra[1], t + 1, k_end);
-      ob.fetch(rb[1], t + 1, k_end);
-      multiply(0);
-      if (t + 1 < t1) {
-        oa.fetch(ra[0], t + 2, k_end);
-        ob.fetch(rb[0], t + 2, k_end);
-        multiply(1);
+#pragma unroll
+    for (int i = 0; i < AHEAD - 1; ++i) {
+      oa.fetch(ra[i], t0 + i, k_end);
+      ob.fetch(rb[i], t0 + i, k_end);
+    }
+    for (int t = t0; t < t1; t += AHEAD) {            // loads run AHEAD - 1 steps ahead; past the range they give zeros without a memory access
+#pragma unroll
+      for (int i = 0; i < AHEAD; ++i) {
+        if (i > 0 && t + i >= t1) break;
+        oa.fetch(ra[(i + AHEAD - 1) % AHEAD], t + i + AHEAD - 1, k_end);
+        ob.fetch(rb[(i + AHEAD - 1) % AHEAD], t + i + AHEAD - 1, k_end);
+        multiply(i);
       }
     }
   }
   // block (i, j): row 16 i + (lane & 15), columns 16 j + 4 (lane >> 4) ..+3
   float* red = reinterpret_cast<float*>(mine);
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < NB; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) *reinterpret_cast<floatx4*>(red + (i * 16 + (lane & 15)) * PITCH + j * 16 + (lane >> 4) * 4) = acc[i][j];
+    for (int j = 0; j < NB; ++j) *reinterpret_cast<floatx4*>(red + (i * 16 + (lane & 15)) * PITCH + j * 16 + (lane >> 4) * 4) = acc[i][j];
   __syncthreads();
-  constexpr int CH = ACT == ACT_SWIGLU_FWD ? 4 : 8;   // 8-column chunks per row (SwiGLU forward: of features)
-  for (int q = threadIdx.x; q < ST * CH; q += NW * 64) {
+  constexpr int CH = (ACT == ACT_SWIGLU_FWD ? EDGE / 2 : EDGE) / 8;   // 8-column chunks per row (SwiGLU forward: of features)
+  for (int q = threadIdx.x; q < EDGE * CH; q += NW * 64) {
     const int row = q / CH, c = (q % CH) * 8, m = m0 + row;
     const int n = ACT == ACT_SWIGLU_FWD ? (n0 >> 1) + c : n0 + c;
     if (m >= M || n >= (ACT == ACT_SWIGLU_FWD ? N >> 1 : N)) continue;
@@ -1221,38 +1233,49 @@ __device__ __forceinline__ void small_tile(const bf16_t* __restrict__ A, const b
     sum_waves(c, v);
     add_bias8(bias, n, v);
     if constexpr (ACT == ACT_SWIGLU_FWD) {
-      sum_waves(32 + c, up);
+      sum_waves(EDGE / 2 + c, up);
       add_bias8(bias, (N >> 1) + n, up);
     }
     finish8<TO, HAS_R, ACT>(v, up, m, n, N, C, ldc, R, ldr, E, lde, out_scale);
   }
 }
 
-template <bool A_KC, bool B_KC, typename TO, bool HAS_R, int ACT, bool F16IN>
+template <bool A_KC, bool B_KC, typename TO, bool HAS_R, int ACT, bool F16IN, int EDGE>
 __global__ __launch_bounds__(SMALL_NW * 64) void gemm_mfma_small_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, TO* __restrict__ C,
                                                                   const float* __restrict__ R, int M, int N, int K, int lda, int ldb, int ldc,
                                                                   int ldr, int tiles_m, int tiles_n, bf16_t* __restrict__ E, int lde,
                                                                   const bf16_t* __restrict__ bias, const float* __restrict__ out_scale) {
   int tm, tn;
   tile_coords(blockIdx.x, tiles_m, tiles_n, tm, tn);
-  small_tile<A_KC, B_KC, TO, HAS_R, ACT, F16IN>(A, B, C, R, M, N, K, lda, ldb, ldc, ldr, tm * ST, tn * ST, E, lde, bias, out_scale);
+  small_tile<A_KC, B_KC, TO, HAS_R, ACT, F16IN, EDGE>(A, B, C, R, M, N, K, lda, ldb, ldc, ldr, tm * EDGE, tn * EDGE, E, lde, bias, out_scale);
 }
+
+// Edge of the small-output tiles: 32 while there are at most two of them per CU.  us, 64 -> 32: 129 x 512 x 512 6.2 -> 4.1, x 1536 10.8 -> 6.7,
+// 512 x 512 x 3072 24.7 -> 13.8, 129 x 3072 x 512 (480 tiles of 32) 6.4 -> 5.5; but 777 x 768 x 512 (600) 6.5 -> 7.3, 300 x 3072 x 512 (960) 6.8 -> 9.2.
+inline long long small_tiles(int M, int N, int edge) { return (long long)((M + edge - 1) / edge) * ((N + edge - 1) / edge); }
+// Below 32 rows (a few tokens in all: no training microbatch) the 64 x 64 tiles and with them the choice of split tiles stay, although
+// 1 x 2048 x 2048 would go 10.1 -> 6.9.
+inline int small_edge(int M, int N, int n_cu) { return M >= 32 && small_tiles(M, N, 32) <= 2 * n_cu ? 32 : ST; }
 
 template <bool A_KC, bool B_KC, typename TO, bool HAS_R, int ACT, bool F16IN>
 hipError_t launch_small(const GemmArgs& g, hipStream_t s) {
-  const int tiles_m = (g.M + ST - 1) / ST, tiles_n = (g.N + ST - 1) / ST;
-  hipLaunchKernelGGL((gemm_mfma_small_kernel<A_KC, B_KC, TO, HAS_R, ACT, F16IN>), dim3(tiles_m * tiles_n), dim3(SMALL_NW * 64), 0, s,
+  const int edge = small_edge(g.M, g.N, cu_count()), tiles_m = (g.M + edge - 1) / edge, tiles_n = (g.N + edge - 1) / edge;
+  const auto kernel = edge == 32 ? gemm_mfma_small_kernel<A_KC, B_KC, TO, HAS_R, ACT, F16IN, 32> : gemm_mfma_small_kernel<A_KC, B_KC, TO, HAS_R, ACT, F16IN, ST>;
+  hipLaunchKernelGGL(kernel, dim3(tiles_m * tiles_n), dim3(SMALL_NW * 64), 0, s,
                      (const bf16_t*)g.A, (const bf16_t*)g.B, (TO*)g.C, g.R, g.M, g.N, g.K, g.lda, g.ldb, g.ldc, g.ldr, tiles_m, tiles_n,
                      (bf16_t*)g.E, g.lde, (const bf16_t*)g.bias, g.out_scale);
   return hipGetLastError();
 }
 
-// Estimated time (us) of the small-output kernel: rounds of its 64 x 64 tiles, each bound by what one CU can have in flight
-// from memory (128 rows of K at 35 GB/s) plus 1.5 us of start and store.  Measured: 512 x 512 x 777 7.5, 512 x 3072 x
-// 777 14.6 (the split 256-row tiles: 23.8), 129 x 512 x 512 6.7 (10.3), 1000 x 8192 x 1024 66 (23).
+// Estimated time (us) of the small-output kernel.  64 x 64 tiles: rounds, each bound by what one CU can have in flight
+// from memory (128 rows of K at 35 GB/s) plus 1.5 us of start and store.  Measured: 512 x 3072 x 777 14.6 (the split 256-row tiles:
+// 23.8), 1000 x 8192 x 1024 66 (23).  32 x 32 tiles: a wavefront's chain of loads, twice as long with two tiles on a CU: 512 x 512 x 3072
+// 13.8 (the split tiles: 17.1), 129 x 512 x 3072 13.5 (13.2), 777 x 512 x 1536 11.7.
 inline float small_us(int M, int N, int K, int n_cu) {
-  const long long t = (long long)((M + ST - 1) / ST) * ((N + ST - 1) / ST);
-  return 2.0f + (float)((t + n_cu - 1) / n_cu) * (1.5f + 0.0072f * K);
+  const int edge = small_edge(M, N, n_cu);
+  const long long rounds = (small_tiles(M, N, edge) + n_cu - 1) / n_cu;
+  if (edge == 32) return 2.7f + (rounds > 1 ? 0.0063f : 0.0034f) * K;
+  return 2.0f + (float)rounds * (1.5f + 0.0072f * K);
 }
 
 // Cut along K of a form with A K-contiguous: ranges == 0 means the small-output kernel, ranges > 1 tiles of tile_rows x 256,
@@ -1571,7 +1594,7 @@ __global__ __launch_bounds__(SMALL_NW * 64) void gemm_mfma_wgrad_group_small_ker
   const WgradProblem& p = group_problem(g, blockIdx.x);
   int tm, tn;
   tile_coords(blockIdx.x - p.start, p.tiles_m, p.tiles_n, tm, tn);
-  small_tile<false, false, float, false, ACT_NONE, false>(p.A, p.B, p.C, nullptr, p.M, p.N, g.K, p.lda, p.ldb, p.ldc, 0, tm * ST, tn * ST,
+  small_tile<false, false, float, false, ACT_NONE, false, ST>(p.A, p.B, p.C, nullptr, p.M, p.N, g.K, p.lda, p.ldb, p.ldc, 0, tm * ST, tn * ST,
                                                           nullptr, 0, nullptr, nullptr);
 }
 
@@ -1773,7 +1796,7 @@ GemmPlan gemm_mfma_plan(const GemmArgs& g, int n_cu, size_t ws_bytes) {
   auto small_plan = [&] {
     p.kernel = 3;
     p.wavefronts = SMALL_NW;
-    p.main_workgroups = (g.M + ST - 1) / ST * ((g.N + ST - 1) / ST);
+    p.main_workgroups = (int)small_tiles(g.M, g.N, small_edge(g.M, g.N, n_cu));
     return p;
   };
   if (a_kc) {

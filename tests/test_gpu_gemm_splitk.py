@@ -54,6 +54,16 @@ def test_small_outputs_match_fp64(M, N, K, tb, out_fp32, with_r):
     _small(M, N, K, 0, tb, out_fp32, with_r)
 
 
+# The two tile edges on both sides of the rule (32 while there are at most 512 such tiles on 256 CUs), ragged in every direction, K of a
+# whole number of steps and of 1, 31 and 33 more where the form takes them; steps that do not divide by the wavefronts or the steps ahead
+@pytest.mark.parametrize("M,N,K,ta,tb,tiles", [(512, 1024, 512, 0, 1, 512), (513, 1000, 544, 0, 1, 144), (545, 968, 288, 0, 0, 144), (32, 40, 1312, 0, 0, 2),
+                                               (33, 24, 96, 0, 1, 2), (520, 1032, 257, 1, 0, 153), (40, 16, 1025, 1, 0, 2), (24, 72, 63, 1, 0, 2)])
+def test_small_tile_edges_match_fp64(M, N, K, ta, tb, tiles):
+    import paper_2605_18750_amd as R
+    assert R.rrfp_gemm_plan(M, N, K, ta, tb, R.STAGE_DTYPE_FP32, have_scratch=True)["main_workgroups"] == tiles
+    _small(M, N, K, ta, tb, 1, 0)
+
+
 def _small(M, N, K, ta, tb, out_fp32, with_r):
     """Operands end in NaN rows that must not be read into a result; error bounds as above."""
     import torch
