@@ -376,47 +376,64 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_fused_kernel(const float* __r
   }
 }
 
-// Column sums of `partial` [n_partial][H] in one fixed order: 16 contiguous slices of the rows are
-// summed front to back by 16 thread groups (4 columns per thread), then added in slice order.
-__global__ __launch_bounds__(256) void colsum_kernel(const float* __restrict__ partial, int n_partial, int H,
-                                                     float* __restrict__ out) {
+// Column sums of `partial` [n_partial][width], rows ld apart, in one fixed order: 16 contiguous slices of the rows are
+// summed front to back by 16 thread groups (4 columns per thread), then added in slice order.  64 columns from c0 per workgroup.
+__device__ __forceinline__ void colsum_block(const float* __restrict__ partial, int n_partial, int ld, int width, int c0,
+                                             float* __restrict__ out) {
   __shared__ float red[16][64];
   const int cv = threadIdx.x & 15, grp = threadIdx.x >> 4;
-  const int c = blockIdx.x * 64 + cv * 4;
+  const int c = c0 + cv * 4;
   const int per = (n_partial + 15) / 16;
   const int p0 = grp * per, p1 = min(p0 + per, n_partial);
   float acc[4] = {0.f, 0.f, 0.f, 0.f};
-  if (c + 3 < H && (H & 3) == 0) {
+  if (c + 3 < width && (ld & 3) == 0 && ((uintptr_t)partial & 15) == 0) {
     // eight loads in flight at a time, added in row order (the loop is bound by the latency of its loads)
     int p = p0;
     for (; p + 8 <= p1; p += 8) {
       float4 v[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const float4*>(partial + (size_t)(p + u) * H + c);
+      for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const float4*>(partial + (size_t)(p + u) * ld + c);
 #pragma unroll
       for (int u = 0; u < 8; ++u) { acc[0] += v[u].x; acc[1] += v[u].y; acc[2] += v[u].z; acc[3] += v[u].w; }
     }
     for (; p < p1; ++p) {
-      const float4 v = *reinterpret_cast<const float4*>(partial + (size_t)p * H + c);
+      const float4 v = *reinterpret_cast<const float4*>(partial + (size_t)p * ld + c);
       acc[0] += v.x; acc[1] += v.y; acc[2] += v.z; acc[3] += v.w;
     }
   } else {
     for (int p = p0; p < p1; ++p)
       for (int i = 0; i < 4; ++i)
-        if (c + i < H) acc[i] += partial[(size_t)p * H + c + i];
+        if (c + i < width) acc[i] += partial[(size_t)p * ld + c + i];
   }
 #pragma unroll
   for (int i = 0; i < 4; ++i) red[grp][cv * 4 + i] = acc[i];
   __syncthreads();
   if (threadIdx.x < 64) {
-    const int cc = blockIdx.x * 64 + threadIdx.x;
-    if (cc < H) {
+    const int cc = c0 + threadIdx.x;
+    if (cc < width) {
       float t = red[0][threadIdx.x];
 #pragma unroll
       for (int q = 1; q < 16; ++q) t += red[q][threadIdx.x];
       out[cc] = t;
     }
   }
+}
+__global__ __launch_bounds__(256) void colsum_kernel(const float* __restrict__ partial, int n_partial, int H, float* __restrict__ out) {
+  colsum_block(partial, n_partial, H, H, blockIdx.x * 64, out);
+}
+// The vector gradients of a whole B task: each sum is 2 to 5 us of latency (a few workgroups that walk some hundred rows), so one launch
+// takes up to COLSUM_LIST_MAX of them, workgroup after workgroup.  4 layers with LayerNorm and biases: 32 launches of 4.7 us a task -> 1 (with the
+// chunk sums of the bias gradients below, also one launch).
+struct ColsumList {
+  ColsumJob job[COLSUM_LIST_MAX];
+  int start[COLSUM_LIST_MAX + 1];      // first workgroup of each, and the end
+  int n;
+};
+__global__ __launch_bounds__(256) void colsum_list_kernel(const ColsumList list) {
+  int i = 0;
+  while (i + 1 < list.n && list.start[i + 1] <= (int)blockIdx.x) ++i;
+  const ColsumJob& j = list.job[i];
+  colsum_block(j.partial, j.n_partial, j.ld, j.width, ((int)blockIdx.x - list.start[i]) * 64, j.out);
 }
 
 // ---------------------------------------------------------------- SwiGLU / GELU
@@ -670,10 +687,10 @@ __device__ __forceinline__ void colsum_groups(float (&acc)[V], float (*red)[CS_V
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void colsum_rows_vec_kernel(const T* __restrict__ src, int ld, float* __restrict__ partial, int Tn, int N) {
+__device__ __forceinline__ void colsum_rows_block(const T* __restrict__ src, int ld, float* __restrict__ partial, int Tn, int N, int block) {
   constexpr int V = Vec<T>::N;
   __shared__ float red[CS_GROUPS][CS_VECS * V];
-  const int c0 = blockIdx.x * CS_VECS * V, c = c0 + (threadIdx.x % CS_VECS) * V;
+  const int c0 = block * CS_VECS * V, c = c0 + (threadIdx.x % CS_VECS) * V;
   const int r0 = blockIdx.y * NORM_BWD_ROWS + threadIdx.x / CS_VECS * CS_ROWS;
   float acc[V] = {}, v[CS_ROWS][V] = {};
   if (c < N) {
@@ -686,6 +703,22 @@ __global__ __launch_bounds__(256) void colsum_rows_vec_kernel(const T* __restric
 #pragma unroll
     for (int k = 0; k < V; ++k) acc[k] += v[i][k];
   colsum_groups<V>(acc, red, partial + (size_t)blockIdx.y * N, c0, N);
+}
+template <typename T>
+__global__ __launch_bounds__(256) void colsum_rows_vec_kernel(const T* __restrict__ src, int ld, float* __restrict__ partial, int Tn, int N) {
+  colsum_rows_block<T>(src, ld, partial, Tn, N, blockIdx.x);
+}
+struct ColsumRowsList {
+  ColsumRowsJob job[COLSUM_LIST_MAX];
+  int start[COLSUM_LIST_MAX + 1];
+  int n;
+};
+template <typename T>
+__global__ __launch_bounds__(256) void colsum_rows_list_kernel(const ColsumRowsList list, int Tn) {
+  int i = 0;
+  while (i + 1 < list.n && list.start[i + 1] <= (int)blockIdx.x) ++i;
+  const ColsumRowsJob& j = list.job[i];
+  colsum_rows_block<T>((const T*)j.src, j.N, j.partial, Tn, j.N, (int)blockIdx.x - list.start[i]);
 }
 
 __global__ __launch_bounds__(256) void layernorm_bwd_partials_vec_kernel(const float* __restrict__ dh, const float* __restrict__ x,
@@ -1097,6 +1130,45 @@ hipError_t launch_colsum_rows(const void* src, int ld, float* partial, int Tn, i
 hipError_t launch_colsum(const float* partial, int n_partial, int H, float* out, hipStream_t s) {
   hipLaunchKernelGGL(colsum_kernel, dim3((H + 63) / 64), dim3(256), 0, s, partial, n_partial, H, out);
   return hipGetLastError();
+}
+
+hipError_t launch_colsum_list(const ColsumJob* jobs, int n, hipStream_t s) {
+  for (int i0 = 0; i0 < n; i0 += COLSUM_LIST_MAX) {
+    ColsumList list;
+    list.n = std::min(COLSUM_LIST_MAX, n - i0);
+    list.start[0] = 0;
+    for (int i = 0; i < list.n; ++i) {
+      list.job[i] = jobs[i0 + i];
+      list.start[i + 1] = list.start[i] + (jobs[i0 + i].width + 63) / 64;
+    }
+    hipLaunchKernelGGL(colsum_list_kernel, dim3(list.start[list.n]), dim3(256), 0, s, list);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+hipError_t launch_colsum_rows_list(const ColsumRowsJob* jobs, int n, int Tn, int dtype, hipStream_t s) {
+  const int V = dtype == F32 ? 4 : 8, chunks = colsum_chunks(Tn);
+  ColsumRowsList list;
+  list.n = 0;
+  list.start[0] = 0;
+  auto flush = [&]() -> hipError_t {
+    if (list.n > 0) DISPATCH_T(dtype, hipLaunchKernelGGL(colsum_rows_list_kernel<T>, dim3(list.start[list.n], chunks), dim3(256), 0, s, list, Tn));
+    list.n = 0;
+    return hipGetLastError();
+  };
+  for (int i = 0; i < n; ++i) {
+    const ColsumRowsJob& j = jobs[i];
+    if (j.N % V || ((uintptr_t)j.src & 15)) {          // the kernel of single columns, by itself
+      if (hipError_t e = launch_colsum_rows(j.src, j.N, j.partial, Tn, j.N, dtype, s); e != hipSuccess) return e;
+      continue;
+    }
+    list.job[list.n] = j;
+    list.start[list.n + 1] = list.start[list.n] + (j.N + CS_VECS * V - 1) / (CS_VECS * V);
+    if (++list.n == COLSUM_LIST_MAX)
+      if (hipError_t e = flush(); e != hipSuccess) return e;
+  }
+  return flush();
 }
 
 hipError_t launch_swiglu_fwd(const void* gu, void* m, int Tn, int F, int dtype, hipStream_t s) {

@@ -182,6 +182,10 @@ hipError_t launch_rmsnorm_bwd(const float* dh, const float* x, const float* r, c
                               const float* add_in, float* out32, void* out_t, float* dg_partial,
                               int T, int H, int dtype, hipStream_t s, int rows = NORM_BWD_FUSED_ROWS);
 hipError_t launch_colsum(const float* partial, int n_partial, int H, float* out, hipStream_t s);
+// The same for a list of sums: width columns of n_partial rows ld apart, each to out [width]; no output is another's input.
+struct ColsumJob { const float* partial; float* out; int n_partial, ld, width; };
+constexpr int COLSUM_LIST_MAX = 64;   // per launch (the list travels in the kernel arguments)
+hipError_t launch_colsum_list(const ColsumJob* jobs, int n, hipStream_t s);
 // LayerNorm (model-fidelity variant): forward saves r and mu per row; backward writes dx (+ add_in) and
 // the per-chunk partial sums of the gain and bias gradients ([colsum_chunks(T), H] each, for launch_colsum).
 int colsum_chunks(int T);
@@ -203,6 +207,8 @@ hipError_t launch_headnorm_bwd(void* dy, int ld, int nq, int n_heads, int d, con
                                int xhat_dtype = -1);     // type of the saved xhat when it differs from dtype (F16: forward ran on a half tensor)
 // Per-chunk column sums of a [T, N] tensor of the storage type into partial [colsum_chunks(T), N] (bias gradients).
 hipError_t launch_colsum_rows(const void* src, int ld, float* partial, int T, int N, int dtype, hipStream_t s);
+struct ColsumRowsJob { const void* src; float* partial; int N; };   // [T, N] tensor without gaps
+hipError_t launch_colsum_rows_list(const ColsumRowsJob* jobs, int n, int T, int dtype, hipStream_t s);
 
 // SwiGLU on gu [T, 2F] (gate columns then up columns): m = silu(gate) * up.
 hipError_t launch_swiglu_fwd(const void* gu, void* m, int T, int F, int dtype, hipStream_t s);

@@ -42,6 +42,10 @@ struct LayerStash {
   size_t qk_hat, qk_r;                                // written by F: normalised q, k heads and their 1/rms (QK-norm variant)
   size_t h1_16;                                       // written by F (bf16 path): first norm output as IEEE halves, operand of the QKV projection
   size_t o16;                                         // written by F (bf16 path): attention output as IEEE halves, operand of the output projection
+  // written by B: partial rows of the vector gradients, all summed at its end (zero-sized when their variant is off)
+  size_t p_gain[2], p_beta[2];                        // norm gains, LayerNorm biases; first and second norm
+  size_t p_bias[4];                                   // projection biases: qkv, o, up, d
+  size_t p_gq, p_gk, p_kb;                            // head-norm gains, un-rounded key block of the qkv bias
 };
 
 struct Plan {
@@ -52,7 +56,7 @@ struct Plan {
   int64_t p_shape[STAGE_P_COUNT][2];
   size_t param_elems;
   std::vector<LayerStash> layer;
-  size_t t_dh, t_do, t_delta, t_dgp, t_dbp, t_qtiles, t_kvtiles;  // per-microbatch temporaries
+  size_t t_dh, t_do, t_delta, t_qtiles, t_kvtiles;  // per-microbatch temporaries
   // GEMM scratch of a microbatch (split-K planes of F, B and W, partial gain rows of B): t_dm, B's fp32 temporary of an unfused
   // activation backward, directly behind it t_ds, both idle outside the one kernel or the two attention kernels of B that use
   // them, and as much more as scratch_need asks for.
@@ -120,7 +124,7 @@ int check_config(const stage_config* c) {
 }
 
 // Scratch with which every cut of every microbatch of up to max_tokens tokens is the one its own shape asks for: the planes
-// of the products of F, B and W and the partial rows of the RMSNorm backward.  Without it the cut, and so the summation
+// of the products of F, B and W (and as much as the partial rows of the RMSNorm backward take).  Without it the cut, and so the summation
 // order, of a microbatch would hang on max_tokens and max_segments.  The chip whole and in its equal partitions.
 size_t scratch_need(const stage_config* c, const Plan* p) {
   const int T = c->max_tokens, H = c->hidden, F = c->ffn, nqd = c->n_q_heads * c->head_dim;
@@ -186,18 +190,22 @@ int make_plan(const stage_config* c, Plan* p, bool layout_only = false) {
     s.qk_r = c->qk_norm ? take(T * (nq + nkv) * 4) : 0;
     s.h1_16 = c->dtype == STAGE_DTYPE_BF16 ? take(T * H * 2) : 0;
     s.o16 = c->dtype == STAGE_DTYPE_BF16 ? take(T * nq * d * 2) : 0;
+    const size_t chunk = (size_t)colsum_chunks((int)T) * 4;       // bytes of a column of partial rows
+    const size_t gain = c->norm_kind == 1 ? chunk * H : std::max((size_t)norm_bwd_partials((int)T, (int)H, c->dtype) * H * 4,
+                                                                 norm_bwd_few_rows_bytes((int)T, (int)H, c->dtype));
+    for (int i = 0; i < 2; ++i) {
+      s.p_gain[i] = take(gain);
+      s.p_beta[i] = c->norm_kind == 1 ? take(chunk * H) : 0;
+    }
+    const size_t widths[4] = {(size_t)p->n_qkv, H, (size_t)p->n_up, H};
+    for (int i = 0; i < 4; ++i) s.p_bias[i] = c->bias ? take(chunk * widths[i]) : 0;
+    s.p_gq = c->qk_norm ? take((size_t)headnorm_partials((int)T, (int)nq) * d * 4) : 0;
+    s.p_gk = c->qk_norm ? take((size_t)headnorm_partials((int)T, (int)nkv) * d * 4) : 0;
+    s.p_kb = c->qk_norm && c->bias ? take(chunk * nkv * d) : 0;
   }
   p->t_dh = take(T * H * 4);
   p->t_do = take(T * nq * d * e);
   p->t_delta = take(nq * T * 4);
-  size_t dgp = (size_t)std::max(norm_bwd_partials((int)T, (int)H, c->dtype), colsum_chunks((int)T)) * H * 4;
-  if (c->qk_norm) dgp = std::max(dgp, (size_t)headnorm_partials((int)T, (int)nq) * d * 4);
-  p->t_dgp = take(dgp);
-  // second partial array: LayerNorm bias gradient, and the projection-bias gradients (widest tensor)
-  const size_t wide = std::max((size_t)H, (size_t)std::max(p->n_qkv, p->n_up));
-  size_t dbp = (c->norm_kind == 1 || c->bias) ? (size_t)colsum_chunks((int)T) * wide * 4 : 0;
-  if (c->qk_norm) dbp = std::max(dbp, (size_t)headnorm_partials((int)T, (int)nkv) * d * 4);
-  p->t_dbp = dbp ? take(dbp) : 0;
   p->t_dk32 = (c->qk_norm && c->bias) ? take(T * nkv * d * 4) : 0;
   p->t_gscale = take(256);
   p->t_gpart = take((size_t)grad_scale_partials(T * H) * 4);
@@ -607,9 +615,7 @@ int stage_B(stage_t* st, int mb, const void* dy_dev, void* dx_dev, void* stream)
   char* base = mb_base(st, mb);
   float* slot = slot_base(st, mb);
   const int T = m.T, H = c.hidden, F = c.ffn, dt = c.dtype, nqd = c.n_q_heads * c.head_dim;
-  // RMSNorm backward: with few rows the gain partials outgrow their own array and go to the GEMM scratch, idle at that point
   const int n_rows = norm_bwd_rows(T, H, dt, device_cu_count()), n_part = norm_bwd_partials(T, H, dt, n_rows);
-  float* const g_part = (float*)(base + (n_rows == NORM_BWD_FUSED_ROWS ? P.t_dgp : P.t_dm));
   // one pass over dy: the fp32 head of the residual-gradient chain and the library's own copy for the GEMMs and W
   HIP_TRY(st, launch_widen(dy_dev, (float*)(base + P.layer[c.n_layers - 1].dy32), (size_t)T * H, dt, s,
                            base + P.layer[c.n_layers - 1].dy));
@@ -621,30 +627,36 @@ int stage_B(stage_t* st, int mb, const void* dy_dev, void* dx_dev, void* stream)
     gscale = (const float*)(base + P.t_gscale);
   }
   const int n_chunk = colsum_chunks(T);
-  // bias gradient = column sum of a projection's output-gradient (storage type), in a fixed order
-  auto bias_grad = [&](const void* src, int n, size_t slot_off) -> int {
-    HIP_TRY(st, launch_colsum_rows(src, n, (float*)(base + P.t_dbp), T, n, dt, s));
-    HIP_TRY(st, launch_colsum((const float*)(base + P.t_dbp), n_chunk, n, slot + slot_off, s));
+  // The vector gradients end in sums of partial rows, which nothing in B reads: they are listed and launched together at its end
+  ColsumJob sums[COLSUM_LIST_MAX];
+  int n_sums = 0;
+  auto flush_sums = [&]() -> int {
+    HIP_TRY(st, launch_colsum_list(sums, n_sums, s));
+    n_sums = 0;
     return STAGE_OK;
   };
-  // backward of one norm: dx (+ add_in) and the vector gradients into the slot
+  auto sum_later = [&](size_t partial, int n, int ld, int width, size_t slot_off, int col = 0) -> int {
+    if (n_sums == COLSUM_LIST_MAX)
+      if (int e = flush_sums()) return e;
+    sums[n_sums++] = ColsumJob{(const float*)(base + partial) + col, slot + slot_off + col, n, ld, width};
+    return STAGE_OK;
+  };
+  // backward of one norm: dx (+ add_in) and the partial rows of the vector gradients
   auto norm_bwd = [&](int l, bool first, const float* dh, const float* x, const float* r, const float* mu, const float* add_in,
                       float* out32, void* out_t) -> int {
     const int pg = first ? STAGE_P_G1 : STAGE_P_G2, pb = first ? STAGE_P_B1 : STAGE_P_B2;
+    const size_t gain = P.layer[l].p_gain[first ? 0 : 1], beta = P.layer[l].p_beta[first ? 0 : 1];
     if (c.norm_kind == 1) {
-      HIP_TRY(st, launch_layernorm_bwd(dh, x, r, mu, param_ptr(st, l, pg), add_in, out32, out_t, (float*)(base + P.t_dgp),
-                                       (float*)(base + P.t_dbp), T, H, dt, s));
-      HIP_TRY(st, launch_colsum((const float*)(base + P.t_dgp), n_chunk, H, slot + P.p_off[l][pg], s));
-      HIP_TRY(st, launch_colsum((const float*)(base + P.t_dbp), n_chunk, H, slot + P.p_off[l][pb], s));
-    } else {
-      HIP_TRY(st, launch_rmsnorm_bwd(dh, x, r, param_ptr(st, l, pg), add_in, out32, out_t, g_part, T, H, dt, s, n_rows));
-      HIP_TRY(st, launch_colsum(g_part, n_part, H, slot + P.p_off[l][pg], s));
+      HIP_TRY(st, launch_layernorm_bwd(dh, x, r, mu, param_ptr(st, l, pg), add_in, out32, out_t, (float*)(base + gain), (float*)(base + beta),
+                                       T, H, dt, s));
+      if (int e = sum_later(beta, n_chunk, H, H, P.p_off[l][pb])) return e;
+      return sum_later(gain, n_chunk, H, H, P.p_off[l][pg]);
     }
-    return STAGE_OK;
+    HIP_TRY(st, launch_rmsnorm_bwd(dh, x, r, param_ptr(st, l, pg), add_in, out32, out_t, (float*)(base + gain), T, H, dt, s, n_rows));
+    return sum_later(gain, n_part, H, H, P.p_off[l][pg]);
   };
   for (int l = c.n_layers - 1; l >= 0; --l) {
     const LayerStash& L = P.layer[l];
-    if (c.bias) { rc = bias_grad(base + L.dy, H, P.p_off[l][STAGE_P_BD]); if (rc) return rc; }
     void* dx_out = (l == 0) ? dx_dev : (void*)(base + P.layer[l - 1].dy);
     float* dx_out32 = (l == 0) ? nullptr : (float*)(base + P.layer[l - 1].dy32);
     GemmArgs g{};
@@ -671,11 +683,9 @@ int stage_B(stage_t* st, int mb, const void* dy_dev, void* dx_dev, void* stream)
     g.A = base + L.dup; g.lda = P.n_up; g.B = param_ptr(st, l, STAGE_P_WUP); g.ldb = P.n_up;
     g.C = base + P.t_dh; g.ldc = H; g.N = H; g.K = P.n_up; g.out_dtype = F32;
     HIP_TRY(st, launch_gemm(g, s));
-    if (c.bias) { rc = bias_grad(base + L.dup, P.n_up, P.p_off[l][STAGE_P_BUP]); if (rc) return rc; }
     rc = norm_bwd(l, false, (const float*)(base + P.t_dh), (const float*)(base + L.x1), (const float*)(base + L.r2),
                   (const float*)(base + L.mu2), (const float*)(base + L.dy32), (float*)(base + L.dx1_32), base + L.dx1);
     if (rc) return rc;
-    if (c.bias) { rc = bias_grad(base + L.dx1, H, P.p_off[l][STAGE_P_BO]); if (rc) return rc; }
     // do = dx1 Wo^T
     g.A = base + L.dx1; g.lda = H; g.B = param_ptr(st, l, STAGE_P_WO); g.ldb = H;
     g.C = base + P.t_do; g.ldc = nqd; g.N = nqd; g.K = H;
@@ -700,19 +710,12 @@ int stage_B(stage_t* st, int mb, const void* dy_dev, void* dx_dev, void* stream)
     if (c.qk_norm) {   // gradients w.r.t. the normalised heads -> w.r.t. the projection outputs, gain gradients to the slot
       HIP_TRY(st, launch_headnorm_bwd(base + L.dqkv, P.n_qkv, c.n_q_heads, c.n_q_heads + c.n_kv_heads, c.head_dim,
                                       param_ptr(st, l, STAGE_P_GQ), param_ptr(st, l, STAGE_P_GK), base + L.qk_hat,
-                                      (const float*)(base + L.qk_r), (float*)(base + P.t_dgp), (float*)(base + P.t_dbp), T, dt, s,
+                                      (const float*)(base + L.qk_r), (float*)(base + L.p_gq), (float*)(base + L.p_gk), T, dt, s,
                                       c.bias ? (float*)(base + P.t_dk32) : nullptr, dt == BF16 ? (int)F16 : -1));
-      HIP_TRY(st, launch_colsum((const float*)(base + P.t_dgp), headnorm_partials(T, c.n_q_heads), c.head_dim, slot + P.p_off[l][STAGE_P_GQ], s));
-      HIP_TRY(st, launch_colsum((const float*)(base + P.t_dbp), headnorm_partials(T, c.n_kv_heads), c.head_dim, slot + P.p_off[l][STAGE_P_GK], s));
-    }
-    if (c.bias) {
-      rc = bias_grad(base + L.dqkv, P.n_qkv, P.p_off[l][STAGE_P_BQKV]);
-      if (rc) return rc;
-      if (c.qk_norm) {   // the key block again, from the un-rounded gradients (a sum of cancelling terms)
-        const int nk = c.n_kv_heads * c.head_dim;
-        HIP_TRY(st, launch_colsum_rows(base + P.t_dk32, nk, (float*)(base + P.t_dbp), T, nk, F32, s));
-        HIP_TRY(st, launch_colsum((const float*)(base + P.t_dbp), n_chunk, nk, slot + P.p_off[l][STAGE_P_BQKV] + c.n_q_heads * c.head_dim, s));
-      }
+      if ((rc = sum_later(L.p_gq, headnorm_partials(T, c.n_q_heads), c.head_dim, c.head_dim, P.p_off[l][STAGE_P_GQ])) != 0) return rc;
+      if ((rc = sum_later(L.p_gk, headnorm_partials(T, c.n_kv_heads), c.head_dim, c.head_dim, P.p_off[l][STAGE_P_GK])) != 0) return rc;
+      if (c.bias)      // the key block of the qkv bias, from the un-rounded gradients (a sum of cancelling terms)
+        HIP_TRY(st, launch_colsum_rows(base + P.t_dk32, c.n_kv_heads * c.head_dim, (float*)(base + L.p_kb), T, c.n_kv_heads * c.head_dim, F32, s));
     }
     // dh1 = [dq|dk|dv] Wqkv^T
     g.A = base + L.dqkv; g.lda = P.n_qkv; g.B = param_ptr(st, l, STAGE_P_WQKV); g.ldb = P.n_qkv;
@@ -722,6 +725,35 @@ int stage_B(stage_t* st, int mb, const void* dy_dev, void* dx_dev, void* stream)
                   (const float*)(base + L.mu1), (const float*)(base + L.dx1_32), dx_out32, dx_out);
     if (rc) return rc;
   }
+  if (c.bias) {
+    // bias gradient = column sum of a projection's output-gradient (storage type), in a fixed order
+    const int nk = c.n_kv_heads * c.head_dim;
+    constexpr int param[4] = {STAGE_P_BQKV, STAGE_P_BO, STAGE_P_BUP, STAGE_P_BD};
+    const int width[4] = {P.n_qkv, H, P.n_up, H};
+    for (int l0 = 0; l0 < c.n_layers; l0 += COLSUM_LIST_MAX / 4) {
+      ColsumRowsJob rows[COLSUM_LIST_MAX];
+      int n = 0;
+      for (int l = l0; l < std::min(c.n_layers, l0 + COLSUM_LIST_MAX / 4); ++l) {
+        const LayerStash& L = P.layer[l];
+        const size_t src[4] = {L.dqkv, L.dx1, L.dup, L.dy};
+        for (int i = 0; i < 4; ++i) rows[n++] = ColsumRowsJob{base + src[i], (float*)(base + L.p_bias[i]), width[i]};
+      }
+      HIP_TRY(st, launch_colsum_rows_list(rows, n, T, dt, s));
+    }
+    for (int l = 0; l < c.n_layers; ++l)
+      for (int i = 0; i < 4; ++i) {
+        const LayerStash& L = P.layer[l];
+        const size_t off = P.p_off[l][param[i]];
+        if (i > 0 || !c.qk_norm) {
+          if ((rc = sum_later(L.p_bias[i], n_chunk, width[i], width[i], off)) != 0) return rc;
+        } else {       // behind a head norm the key block has partial rows of its own
+          if ((rc = sum_later(L.p_bias[i], n_chunk, P.n_qkv, nqd, off)) != 0) return rc;
+          if ((rc = sum_later(L.p_kb, n_chunk, nk, nk, off + nqd)) != 0) return rc;
+          if ((rc = sum_later(L.p_bias[i], n_chunk, P.n_qkv, nk, off, nqd + nk)) != 0) return rc;
+        }
+      }
+  }
+  if ((rc = flush_sums()) != 0) return rc;
   HIP_TRY(st, hipEventRecord(m.ev_B, s));
   m.state = MB_B;
   return STAGE_OK;
