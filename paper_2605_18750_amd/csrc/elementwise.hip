@@ -34,40 +34,34 @@ __device__ inline void store_f32(float* p, const float* in) {
 }
 
 // ---------------------------------------------------------------- storage type -> fp32 copy
-// copy, when given, also receives the values unchanged (one read of src serves both outputs).
+// copy, when given, also receives the values unchanged, and partial the largest magnitude each workgroup met (one read of src serves
+// all outputs; a maximum has no summation order, so the result does not depend on how the work was cut).
+// words: as many 32-bit words copied along, from pinned host memory: what a task brings with it costs no launch of its own (two copies of
+// 2.4 us a forward task before).
 template <typename T>
-__global__ __launch_bounds__(256) void widen_kernel(const T* __restrict__ src, float* __restrict__ dst, size_t n,
-                                                    T* __restrict__ copy) {
+__global__ __launch_bounds__(256) void widen_kernel(const T* __restrict__ src, float* __restrict__ dst, size_t n, T* __restrict__ copy,
+                                                    float* __restrict__ partial, const int* __restrict__ words_src, int* __restrict__ words_dst,
+                                                    int words) {
   constexpr int V = Vec<T>::N;
-  const size_t nv = n / V;
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < nv; i += (size_t)gridDim.x * 256) {
+  __shared__ float red[4];
+  const size_t nv = n / V, first = (size_t)blockIdx.x * 256 + threadIdx.x, stride = (size_t)gridDim.x * 256;
+  for (size_t i = first; i < (size_t)words; i += stride) words_dst[i] = words_src[i];
+  float mx = 0.f;
+  for (size_t i = first; i < nv; i += stride) {
     float v[V];
     load_vec<T>(src + i * V, v);
     store_f32<V>(dst + i * V, v);
     if (copy) store_vec<T>(copy + i * V, v);     // widening and rounding back is the identity
-  }
-  for (size_t i = nv * V + (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
-    dst[i] = to_float(src[i]);
-    if (copy) copy[i] = src[i];
-  }
-}
-
-// ---------------------------------------------------------------- gradient scale
-// max |v| over the tensor in two steps (per-workgroup maxima, then one workgroup): a maximum has no summation
-// order, so the result does not depend on how the work was cut.
-template <typename T>
-__global__ __launch_bounds__(256) void absmax_partial_kernel(const T* __restrict__ src, size_t n, float* __restrict__ partial) {
-  constexpr int V = Vec<T>::N;
-  __shared__ float red[4];
-  float mx = 0.f;
-  const size_t nv = n / V;
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < nv; i += (size_t)gridDim.x * 256) {
-    float v[V];
-    load_vec<T>(src + i * V, v);
 #pragma unroll
     for (int e = 0; e < V; ++e) mx = fmaxf(mx, fabsf(v[e]));      // fmaxf drops NaNs: a NaN in dy shows in the results, not here
   }
-  for (size_t i = nv * V + (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) mx = fmaxf(mx, fabsf(to_float(src[i])));
+  for (size_t i = nv * V + first; i < n; i += stride) {
+    const float v = to_float(src[i]);
+    dst[i] = v;
+    if (copy) copy[i] = src[i];
+    mx = fmaxf(mx, fabsf(v));
+  }
+  if (!partial) return;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, WAVE));
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
@@ -75,6 +69,8 @@ __global__ __launch_bounds__(256) void absmax_partial_kernel(const T* __restrict
   if (threadIdx.x == 0) partial[blockIdx.x] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
 }
 
+// ---------------------------------------------------------------- gradient scale
+// from the workgroups' maxima of widen_kernel
 __global__ __launch_bounds__(256) void grad_scale_kernel(const float* __restrict__ partial, int n_partial, float* __restrict__ scale) {
   __shared__ float red[4];
   float mx = 0.f;
@@ -927,17 +923,35 @@ inline int grid_for(size_t n, int cap = 256 * 32) {
   if ((dtype) == F32) { using T = float; __VA_ARGS__; } \
   else { using T = bf16_t; __VA_ARGS__; }
 
-// bf16 -> IEEE half, element by element (exact except below half's normal range; saturating).
-__global__ __launch_bounds__(256) void bf16_to_f16_kernel(const bf16_t* __restrict__ src, f16_t* __restrict__ dst, size_t n8) {
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n8; i += (size_t)gridDim.x * 256) {
-    float v[8];
-    load_vec<bf16_t>(src + i * 8, v);
-    store_vec<f16_t>(dst + i * 8, v);
-  }
+// bf16 -> IEEE half, element by element (exact except below half's normal range; saturating), for a list of tensors: a workgroup converts
+// HALF_COPY_VECS vectors, all its loads in flight.
+constexpr int HALF_COPIES_MAX = 64, HALF_COPY_VECS = 4 * 256;
+struct HalfCopies {
+  HalfCopy c[HALF_COPIES_MAX];
+  int start[HALF_COPIES_MAX + 1];      // first workgroup of each, and the end
+  int n;
+};
+__global__ __launch_bounds__(256) void bf16_to_f16_kernel(const HalfCopies list) {
+  int t = 0;
+  while (t + 1 < list.n && list.start[t + 1] <= (int)blockIdx.x) ++t;
+  const bf16_t* src = (const bf16_t*)list.c[t].src;
+  f16_t* dst = (f16_t*)list.c[t].dst;
+  const size_t n8 = list.c[t].n / 8, i0 = (size_t)((int)blockIdx.x - list.start[t]) * HALF_COPY_VECS + threadIdx.x;
+  float v[4][8];
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    if (i0 + k * 256 < n8) load_vec<bf16_t>(src + (i0 + k * 256) * 8, v[k]);
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    if (i0 + k * 256 < n8) store_vec<f16_t>(dst + (i0 + k * 256) * 8, v[k]);
 }
 
-hipError_t launch_widen(const void* src, float* dst, size_t n, int dtype, hipStream_t s, void* copy) {
-  DISPATCH_T(dtype, hipLaunchKernelGGL(widen_kernel<T>, dim3(grid_for(n / Vec<T>::N + 1)), dim3(256), 0, s, (const T*)src, dst, n, (T*)copy));
+hipError_t launch_widen(const void* src, float* dst, size_t n, int dtype, hipStream_t s, void* copy, float* scale, float* partial,
+                        const void* host, void* device, size_t bytes) {
+  const int blocks = scale ? grad_scale_partials(n) : grid_for(n / (dtype == F32 ? 4 : 8) + 1);
+  DISPATCH_T(dtype, hipLaunchKernelGGL(widen_kernel<T>, dim3(blocks), dim3(256), 0, s, (const T*)src, dst, n, (T*)copy, scale ? partial : nullptr,
+                                       (const int*)host, (int*)device, (int)(bytes / 4)));
+  if (scale) hipLaunchKernelGGL(grad_scale_kernel, dim3(1), dim3(256), 0, s, (const float*)partial, blocks, scale);
   return hipGetLastError();
 }
 
@@ -1209,17 +1223,20 @@ hipError_t launch_gelu_bwd(const float* dm, const void* u, void* du, int Tn, int
 
 int grad_scale_partials(size_t n) { return grid_for(n / 8 + 1, 1024); }
 
-hipError_t launch_grad_scale(const void* dy, size_t n, int dtype, float* partial, float* scale, hipStream_t s) {
-  const int nb = grad_scale_partials(n);
-  DISPATCH_T(dtype, hipLaunchKernelGGL(absmax_partial_kernel<T>, dim3(nb), dim3(256), 0, s, (const T*)dy, n, partial));
-  hipLaunchKernelGGL(grad_scale_kernel, dim3(1), dim3(256), 0, s, (const float*)partial, nb, scale);
-  return hipGetLastError();
-}
-
-hipError_t launch_bf16_to_f16(const void* src, void* dst, size_t n, hipStream_t s) {
-  if (n % 8 || ((uintptr_t)src & 15) || ((uintptr_t)dst & 15)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(bf16_to_f16_kernel, dim3(grid_for(n / 8)), dim3(256), 0, s, (const bf16_t*)src, (f16_t*)dst, n / 8);
-  return hipGetLastError();
+hipError_t launch_bf16_to_f16(const HalfCopy* list, int n, hipStream_t s) {
+  for (int i0 = 0; i0 < n; i0 += HALF_COPIES_MAX) {
+    HalfCopies c;
+    c.n = std::min(HALF_COPIES_MAX, n - i0);
+    c.start[0] = 0;
+    for (int i = 0; i < c.n; ++i) {
+      c.c[i] = list[i0 + i];
+      if (c.c[i].n % 8 || ((uintptr_t)c.c[i].src & 15) || ((uintptr_t)c.c[i].dst & 15)) return hipErrorInvalidValue;
+      c.start[i + 1] = c.start[i] + (int)((c.c[i].n / 8 + HALF_COPY_VECS - 1) / HALF_COPY_VECS);
+    }
+    hipLaunchKernelGGL(bf16_to_f16_kernel, dim3(c.start[c.n]), dim3(256), 0, s, c);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_grad_reduce(const float* slots, size_t slot_stride, int M, float* out, size_t n, hipStream_t s) {

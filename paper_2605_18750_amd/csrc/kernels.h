@@ -146,11 +146,12 @@ bool attn_mfma_supports(const AttnArgs& a);
 
 // dst[i] = (float)src[i]: storage type -> fp32 (entry of the residual stream).
 // copy (optional): also receives src unchanged, in the storage type.
-hipError_t launch_widen(const void* src, float* dst, size_t n, int dtype, hipStream_t s, void* copy = nullptr);
-// Gradient scale of a microbatch from its output gradient dy [n] (storage type): scale[0] = s = 2^-floor(log2 max|dy|)
-// (1 if dy is all zero or not finite), scale[1] = 1/s.  partial: device scratch of grad_scale_partials(n) floats.
+// scale (optional): the gradient scale of a microbatch from its output gradient src: scale[0] = s = 2^-floor(log2 max|src|)
+// (1 if src is all zero or not finite), scale[1] = 1/s.  partial: device scratch of grad_scale_partials(n) floats.
+// bytes (a multiple of 4; optional): as many copied from pinned host memory to device.
 int grad_scale_partials(size_t n);
-hipError_t launch_grad_scale(const void* dy, size_t n, int dtype, float* partial, float* scale, hipStream_t s);
+hipError_t launch_widen(const void* src, float* dst, size_t n, int dtype, hipStream_t s, void* copy = nullptr, float* scale = nullptr,
+                        float* partial = nullptr, const void* host = nullptr, void* device = nullptr, size_t bytes = 0);
 // Rotary embedding, in place, on the first n_heads heads (head_dim d, even) of every row of a [T, ld]
 // tensor: pair (x_i, x_{i+d/2}) turns by sign * pos * base^(-2i/d), pos = row - segment start, rows and
 // segment starts taken from the query tile list (the tiles partition the rows).
@@ -161,8 +162,9 @@ hipError_t launch_rope(void* x, const AttnTile* q_tiles, int n_q_tiles, int n_he
 // h16 (optional, bf16 storage only): the same output rounded to IEEE half instead of bf16, [T, H].
 hipError_t launch_rmsnorm_fwd(const float* x, const void* g, void* h, float* r_out,
                               int T, int H, float eps, int dtype, hipStream_t s, void* h16 = nullptr);
-// dst[i] = (half)src[i] for n bf16 values (n a multiple of 8, 16-byte aligned pointers); saturating.
-hipError_t launch_bf16_to_f16(const void* src, void* dst, size_t n, hipStream_t s);
+// dst[i] = (half)src[i] for n bf16 values (n a multiple of 8, 16-byte aligned pointers), for each of a list; saturating.
+struct HalfCopy { const void* src; void* dst; size_t n; };
+hipError_t launch_bf16_to_f16(const HalfCopy* list, int n, hipStream_t s);
 
 constexpr int NORM_BWD_ROWS = 64;  // rows per partial of the gain-gradient column sum (unfused kernels)
 // Number of partial rows launch_rmsnorm_bwd writes for this shape (a pure function of shape and dtype:

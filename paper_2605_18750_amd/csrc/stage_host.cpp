@@ -56,7 +56,7 @@ struct Plan {
   int64_t p_shape[STAGE_P_COUNT][2];
   size_t param_elems;
   std::vector<LayerStash> layer;
-  size_t t_dh, t_do, t_delta, t_qtiles, t_kvtiles;  // per-microbatch temporaries
+  size_t t_dh, t_do, t_delta, t_tiles;   // per-microbatch temporaries; t_tiles: query tiles, then key tiles
   // GEMM scratch of a microbatch (split-K planes of F, B and W, partial gain rows of B): t_dm, B's fp32 temporary of an unfused
   // activation backward, directly behind it t_ds, both idle outside the one kernel or the two attention kernels of B that use
   // them, and as much more as scratch_need asks for.
@@ -211,8 +211,7 @@ int make_plan(const stage_config* c, Plan* p, bool layout_only = false) {
   p->t_gpart = take((size_t)grad_scale_partials(T * H) * 4);
   const int tile = std::min(ATTN_TILE_Q, ATTN_TILE_KV);
   p->max_tiles = (int)((T + tile - 1) / tile) + c->max_segments;
-  p->t_qtiles = take((size_t)p->max_tiles * sizeof(AttnTile));
-  p->t_kvtiles = take((size_t)p->max_tiles * sizeof(AttnTile));
+  p->t_tiles = take(2 * (size_t)p->max_tiles * sizeof(AttnTile));
   // The MFMA attention backward forms dS once, in the dK/dV kernel, and hands it to the dQ kernel through this
   // scratch (per microbatch: B tasks of different microbatches may run side by side on different streams).
   {
@@ -492,9 +491,8 @@ int stage_F(stage_t* st, int mb, const void* x_dev, const int32_t* cu, int n_seg
   // the previous iteration's kernels of this slot, so in steady state it has long completed.
   if (m.copy_pending) { HIP_TRY(st, hipEventSynchronize(m.ev_copy)); m.copy_pending = false; }
   AttnTile* qt = m.staging;
-  AttnTile* kt = m.staging + P.max_tiles;
   m.n_q_tiles = build_tiles(cu, n_seg, ATTN_TILE_Q, c.causal != 0, false, qt);
-  m.n_kv_tiles = build_tiles(cu, n_seg, ATTN_TILE_KV, c.causal != 0, true, kt);
+  m.n_kv_tiles = build_tiles(cu, n_seg, ATTN_TILE_KV, c.causal != 0, true, qt + m.n_q_tiles);
 
   char* base = mb_base(st, mb);
   if (st->reduce_recorded) HIP_TRY(st, hipStreamWaitEvent(s, st->ev_reduce, 0));
@@ -504,26 +502,26 @@ int stage_F(stage_t* st, int mb, const void* x_dev, const int32_t* cu, int n_seg
     // stream, behind the previous reduce and so behind every earlier reader of the copies; every F waits for
     // that conversion.
     if (!st->w16_valid) {
+      HalfCopy copies[2 * 64];          // layers are capped at 64
       for (int l = 0; l < c.n_layers; ++l) {
-        HIP_TRY(st, launch_bf16_to_f16(param_ptr(st, l, STAGE_P_WQKV), st->arena + P.w16_off[l], (size_t)c.hidden * P.n_qkv, s));
-        HIP_TRY(st, launch_bf16_to_f16(param_ptr(st, l, STAGE_P_WO), st->arena + P.w16o_off[l],
-                                       (size_t)c.n_q_heads * c.head_dim * c.hidden, s));
+        copies[2 * l] = HalfCopy{param_ptr(st, l, STAGE_P_WQKV), st->arena + P.w16_off[l], (size_t)c.hidden * P.n_qkv};
+        copies[2 * l + 1] = HalfCopy{param_ptr(st, l, STAGE_P_WO), st->arena + P.w16o_off[l], (size_t)c.n_q_heads * c.head_dim * c.hidden};
       }
+      HIP_TRY(st, launch_bf16_to_f16(copies, 2 * c.n_layers, s));
       HIP_TRY(st, hipEventRecord(st->ev_w16, s));
       st->w16_valid = true;
     } else {
       HIP_TRY(st, hipStreamWaitEvent(s, st->ev_w16, 0));
     }
   }
-  HIP_TRY(st, hipMemcpyAsync(base + P.t_qtiles, qt, (size_t)m.n_q_tiles * sizeof(AttnTile), hipMemcpyHostToDevice, s));
-  HIP_TRY(st, hipMemcpyAsync(base + P.t_kvtiles, kt, (size_t)m.n_kv_tiles * sizeof(AttnTile), hipMemcpyHostToDevice, s));
-  HIP_TRY(st, hipEventRecord(m.ev_copy, s));
-  m.copy_pending = true;
-
   const int H = c.hidden, F = c.ffn, dt = c.dtype, nqd = c.n_q_heads * c.head_dim;
   const bool half_path = dt == BF16;            // h1 -> QKV projection -> attention run on IEEE halves
   const int qdt = half_path ? (int)F16 : dt;    // element type of the q|k|v stash
-  HIP_TRY(st, launch_widen(x_dev, (float*)(base + P.layer[0].x), (size_t)T * H, dt, s));
+  // x to the fp32 residual stream, and the tile lists (one range, the query tiles first) to the device
+  HIP_TRY(st, launch_widen(x_dev, (float*)(base + P.layer[0].x), (size_t)T * H, dt, s, nullptr, nullptr, nullptr, qt, base + P.t_tiles,
+                           (size_t)(m.n_q_tiles + m.n_kv_tiles) * sizeof(AttnTile)));
+  HIP_TRY(st, hipEventRecord(m.ev_copy, s));
+  m.copy_pending = true;
   for (int l = 0; l < c.n_layers; ++l) {
     const LayerStash& L = P.layer[l];
     const bool last = l == c.n_layers - 1;
@@ -548,14 +546,14 @@ int stage_F(stage_t* st, int mb, const void* x_dev, const int32_t* cu, int n_seg
                                       param_ptr(st, l, STAGE_P_GQ), param_ptr(st, l, STAGE_P_GK), base + L.qk_hat,
                                       (float*)(base + L.qk_r), T, c.norm_eps, qdt, s));
     if (c.rope)   // rotate q and k in place: the stash then holds what the attention (and its backward) reads
-      HIP_TRY(st, launch_rope(base + L.qkv, (const AttnTile*)(base + P.t_qtiles), m.n_q_tiles, c.n_q_heads + c.n_kv_heads,
+      HIP_TRY(st, launch_rope(base + L.qkv, (const AttnTile*)(base + P.t_tiles), m.n_q_tiles, c.n_q_heads + c.n_kv_heads,
                               c.head_dim, P.n_qkv, c.rope_base, 1.0f, qdt, s));
     AttnArgs a{};
     a.qkv = base + L.qkv; a.o = base + L.o; a.lse = (float*)(base + L.lse);
     a.o32 = dt == BF16 ? (float*)(base + L.o32) : nullptr;
     a.o16 = half_path ? base + L.o16 : nullptr;
-    a.q_tiles = (const AttnTile*)(base + P.t_qtiles); a.n_q_tiles = m.n_q_tiles;
-    a.kv_tiles = (const AttnTile*)(base + P.t_kvtiles); a.n_kv_tiles = m.n_kv_tiles;
+    a.q_tiles = (const AttnTile*)(base + P.t_tiles); a.n_q_tiles = m.n_q_tiles;
+    a.kv_tiles = (const AttnTile*)(base + P.t_tiles) + m.n_q_tiles; a.n_kv_tiles = m.n_kv_tiles;
     a.T = T; a.nq = c.n_q_heads; a.nkv = c.n_kv_heads; a.d = c.head_dim; a.causal = c.causal; a.dtype = dt;
     HIP_TRY(st, launch_attn_fwd(a, s));
     g.A = base + L.o; g.lda = nqd; g.B = param_ptr(st, l, STAGE_P_WO); g.ldb = H;
@@ -617,15 +615,11 @@ int stage_B(stage_t* st, int mb, const void* dy_dev, void* dx_dev, void* stream)
   const int T = m.T, H = c.hidden, F = c.ffn, dt = c.dtype, nqd = c.n_q_heads * c.head_dim;
   const int n_rows = norm_bwd_rows(T, H, dt, device_cu_count()), n_part = norm_bwd_partials(T, H, dt, n_rows);
   // one pass over dy: the fp32 head of the residual-gradient chain and the library's own copy for the GEMMs and W
-  HIP_TRY(st, launch_widen(dy_dev, (float*)(base + P.layer[c.n_layers - 1].dy32), (size_t)T * H, dt, s,
-                           base + P.layer[c.n_layers - 1].dy));
   // bf16 path: the attention backward keeps its copy of dO as IEEE halves; s = 2^-floor(log2 max|dy|) brings it
   // into their range whatever the scale of the loss (dO is linear in dy), and dq, dk, dv are multiplied by 1/s
-  const float* gscale = nullptr;
-  if (dt == BF16) {
-    HIP_TRY(st, launch_grad_scale(dy_dev, (size_t)T * H, dt, (float*)(base + P.t_gpart), (float*)(base + P.t_gscale), s));
-    gscale = (const float*)(base + P.t_gscale);
-  }
+  float* gscale = dt == BF16 ? (float*)(base + P.t_gscale) : nullptr;
+  HIP_TRY(st, launch_widen(dy_dev, (float*)(base + P.layer[c.n_layers - 1].dy32), (size_t)T * H, dt, s,
+                           base + P.layer[c.n_layers - 1].dy, gscale, (float*)(base + P.t_gpart)));
   const int n_chunk = colsum_chunks(T);
   // The vector gradients end in sums of partial rows, which nothing in B reads: they are listed and launched together at its end
   ColsumJob sums[COLSUM_LIST_MAX];
@@ -696,8 +690,8 @@ int stage_B(stage_t* st, int mb, const void* dy_dev, void* dx_dev, void* stream)
     AttnArgs a{};
     a.qkv = base + L.qkv; a.o = base + L.o; a.lse = (float*)(base + L.lse);
     a.o32 = dt == BF16 ? (float*)(base + L.o32) : nullptr;
-    a.q_tiles = (const AttnTile*)(base + P.t_qtiles); a.n_q_tiles = m.n_q_tiles;
-    a.kv_tiles = (const AttnTile*)(base + P.t_kvtiles); a.n_kv_tiles = m.n_kv_tiles;
+    a.q_tiles = (const AttnTile*)(base + P.t_tiles); a.n_q_tiles = m.n_q_tiles;
+    a.kv_tiles = (const AttnTile*)(base + P.t_tiles) + m.n_q_tiles; a.n_kv_tiles = m.n_kv_tiles;
     a.T = T; a.nq = c.n_q_heads; a.nkv = c.n_kv_heads; a.d = c.head_dim; a.causal = c.causal; a.dtype = dt;
     a.d_o = base + P.t_do; a.dqkv = base + L.dqkv; a.delta = (float*)(base + P.t_delta);
     a.grad_scale = gscale;
@@ -705,7 +699,7 @@ int stage_B(stage_t* st, int mb, const void* dy_dev, void* dx_dev, void* stream)
     a.dkv_part = P.t_dkvp ? (float*)(base + P.t_dkvp) : nullptr;
     HIP_TRY(st, launch_attn_bwd(a, s));
     if (c.rope)   // gradients w.r.t. the rotated q, k -> w.r.t. the projection outputs (inverse rotation)
-      HIP_TRY(st, launch_rope(base + L.dqkv, (const AttnTile*)(base + P.t_qtiles), m.n_q_tiles, c.n_q_heads + c.n_kv_heads,
+      HIP_TRY(st, launch_rope(base + L.dqkv, (const AttnTile*)(base + P.t_tiles), m.n_q_tiles, c.n_q_heads + c.n_kv_heads,
                               c.head_dim, P.n_qkv, c.rope_base, -1.0f, dt, s));
     if (c.qk_norm) {   // gradients w.r.t. the normalised heads -> w.r.t. the projection outputs, gain gradients to the slot
       HIP_TRY(st, launch_headnorm_bwd(base + L.dqkv, P.n_qkv, c.n_q_heads, c.n_q_heads + c.n_kv_heads, c.head_dim,
