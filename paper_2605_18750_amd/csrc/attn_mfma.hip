@@ -19,6 +19,9 @@
 namespace rrfp {
 
 hipError_t launch_attn_dq_mfma(const AttnArgs& a, hipStream_t s);   // attn_mfma_dq.hip
+hipError_t launch_attn_fwd_split(const AttnArgs& a, hipStream_t s);             // attn_mfma_split.hip
+hipError_t launch_attn_dkv_split(const AttnArgs& a, int n_sub, hipStream_t s);
+hipError_t launch_attn_dq_split(const AttnArgs& a, hipStream_t s);
 
 namespace {
 
@@ -721,6 +724,13 @@ inline int attn_cu_count() {
   return cached[dev];
 }
 
+// Which kernels: up to 64 rows of a query head per CU the ones of attn_mfma_split.hip, dK/dV only for heads of 64 (wider ones need
+// so many registers that a CU holds four wavefronts) and with the query heads of a group dealt as far as the partial planes allow.  us, the
+// kernels here -> split, forward, dK/dV, dQ: 100 rows x 8 heads of 64 7.3 -> 5.4, 9.8 -> 7.0, 4.9 -> 3.6; 777 x 8 15.6 -> 9.2, 18.4 -> 13.4,
+// 11.5 -> 4.6; 2048 x 8 41 -> 30, 47 -> 38, 33 -> 16; 512 x 32 of 128 23.5 -> 19.8, (26.5 -> 30.6), 14.4 -> 9.6; 784 x 16 of 80, bidirectional
+// 25.8 -> 25.7, (40 -> 39), 19.8 -> 13.4; but 1024 x 32 of 128 38 -> 45, 26.4 -> 23.8 and 2352 x 16 of 80 30 -> 61, 23 -> 32.
+bool split_streams(const AttnArgs& a) { return (long long)a.T * a.nq <= 64LL * attn_cu_count(); }
+
 template <int D>
 hipError_t bwd_launch(const AttnArgs& a, hipStream_t s) {
   auto kkv = attn_dkv_mfma_kernel<D>;
@@ -730,8 +740,11 @@ hipError_t bwd_launch(const AttnArgs& a, hipStream_t s) {
   const float scale = 1.0f / sqrtf((float)D);
   hipLaunchKernelGGL(attn_delta_mfma_kernel<D>, dim3((a.T * a.nq + 15) / 16), dim3(256), 0, s, (const bf16_t*)a.o,
                      a.o32, (const el_t*)a.d_o, a.delta, a.T, a.nq);
-  const int n_sub = a.dkv_part ? attn_dkv_subsets(a.nq, a.nkv, a.n_kv_tiles, attn_cu_count()) : 1;
-  hipLaunchKernelGGL(kkv, dim3(a.nkv * n_sub, a.n_kv_tiles), dim3(256), DkvCfg<D>::SMEM, s, (const el_t*)a.qkv,
+  const bool split = split_streams(a), split_dkv = split && D == 64;
+  const int n_sub = a.dkv_part ? attn_dkv_subsets(a.nq, a.nkv, split_dkv ? 1 : a.n_kv_tiles, split_dkv ? 1 << 30 : attn_cu_count()) : 1;
+  if (split_dkv) {
+    if (hipError_t e = launch_attn_dkv_split(a, n_sub, s); e != hipSuccess) return e;
+  } else hipLaunchKernelGGL(kkv, dim3(a.nkv * n_sub, a.n_kv_tiles), dim3(256), DkvCfg<D>::SMEM, s, (const el_t*)a.qkv,
                      (const el_t*)a.d_o, a.lse, a.delta, (bf16_t*)a.dqkv, a.kv_tiles, a.T, a.nq, a.nkv, a.causal, scale, a.grad_scale,
                      (el_t*)a.ds, a.ds_rows, a.ds_nqs, n_sub, a.dkv_part);
   if (n_sub > 1) {
@@ -741,7 +754,7 @@ hipError_t bwd_launch(const AttnArgs& a, hipStream_t s) {
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return launch_attn_dq_mfma(a, s);
+  return split ? launch_attn_dq_split(a, s) : launch_attn_dq_mfma(a, s);
 }
 
 template <int D>
@@ -766,6 +779,7 @@ bool attn_mfma_supports(const AttnArgs& a) {
 
 hipError_t launch_attn_fwd_mfma(const AttnArgs& a, hipStream_t s) {
   if (!attn_mfma_supports(a)) return hipErrorInvalidValue;
+  if (split_streams(a)) return launch_attn_fwd_split(a, s);
   if (a.d == 64) return fwd_launch<64>(a, s);
   if (a.d == 80) return fwd_launch<80>(a, s);
   return fwd_launch<128>(a, s);
