@@ -6,10 +6,11 @@
 // pipe busy for 64 cycles, so neither LDS nor issue slots limit anything here.  Products and sums stay fp32.
 //
 // Three tile routines, chosen by the size of the output alone (see f32_tile_edge):
-//   f32_tile   tiles of 64 x 64, eight wavefronts, 32-deep k steps through two LDS buffers (global loads two
-//     steps ahead, one barrier per step).  1024 x 1024 x 5504: 112 us = 103 TFLOP/s; the fp32-FMA kernel that was here
-//     before: 385 us on 517 rows of it, now 111.  (128 x 128 tiles: 5 % faster at 4096^3, two to four times slower on
-//     outputs of up to 1024 rows.)
+//   f32_tile   tiles of 64 x 64, eight wavefronts, 32-deep k steps through three LDS buffers (global loads four steps
+//     ahead, one barrier per step).  1024 x 1024 x 5504: 98 us = 117 TFLOP/s, 4096^3: 1033 us = 133 (this card's vendor product: 154).
+//     With two buffers, loads two steps ahead behind branches and the reads of a step behind its barrier: 113 and 1157 us.  (128 x 128 tiles:
+//     5 % faster than those at 4096^3, two to four times slower on outputs of up to 1024 rows.  Sixteen wavefronts and 64-deep steps:
+//     93 us at 1024 x 1024 x 5504, but 129 against 112 at 1024 x 5504 x 1024.)
 //   f32_small  tiles of 32 x 32 whose eight wavefronts split the contraction and read their
 //     fragments straight from global memory (L2): for outputs with too few tiles to fill the chip the time is the
 //     latency of the serial k loop, and this cuts the loop and takes the barriers out of it (128 x 256 x 688: 95 -> 8 us).
@@ -91,6 +92,41 @@ struct F32Tile {
   }
 };
 
+// The tiles of an operand along K, for F32Tile::store.  VEC: buffer loads without a branch (what does not exist carries an offset past the
+// buffer and reads as zero), so that the waits for them count exactly; the base moves with the step, offsets stay within one tile.
+constexpr int VEC_MAX_LD = 1 << 22;
+template <bool KC, int ROWS, bool VEC, int NT>
+struct F32Stream {
+  using Tile = F32Tile<KC, ROWS, VEC, NT>;
+  static constexpr int N4 = Tile::N4;
+  const float* p;
+  int ld, row0, n_rows, K;
+  int voff[N4], k_in[N4];                              // byte offset inside a tile (or past it), k inside the step
+  __device__ __forceinline__ F32Stream(const float* p_, int ld_, int row0_, int n_rows_, int K_) : p(p_), ld(ld_), row0(row0_), n_rows(n_rows_), K(K_) {
+#pragma unroll
+    for (int i = 0; i < N4; ++i) {
+      const int q = i * NT + threadIdx.x;
+      const int row = KC ? q / (FK / 4) : q % (ROWS / 4) * 4;
+      k_in[i] = KC ? q % (FK / 4) * 4 : q / (ROWS / 4);
+      voff[i] = row0 + row < n_rows ? (KC ? row * ld + k_in[i] : k_in[i] * ld + row) * 4 : (int)0x80000000;
+    }
+  }
+  __device__ __forceinline__ void load(f32x4v (&r)[N4], int t) const {
+    if constexpr (VEC) {
+      const float* base = KC ? p + (size_t)row0 * ld + t * FK : p + (size_t)t * FK * ld + row0;
+      const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0x7fffffff, 0x00020000);
+      typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+      for (int i = 0; i < N4; ++i) {
+        const int vo = t * FK + k_in[i] < K ? voff[i] : (int)0x80000000;
+        r[i] = __builtin_bit_cast(f32x4v, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(rsrc, vo, 0, 0));
+      }
+    } else {
+      Tile::load(r, p, ld, row0, n_rows, t * FK, K);
+    }
+  }
+};
+
 // Accumulator value r of a 32x32 block: row 8 (r / 4) + 4 (lane >> 5) + r % 4, column lane & 31: a store instruction
 // writes 128 contiguous bytes of two rows.
 __device__ __forceinline__ void put_f32(float v, float* __restrict__ C, const float* __restrict__ R, const float* __restrict__ bias,
@@ -112,46 +148,71 @@ __device__ __forceinline__ void f32_tile(const float* __restrict__ A, const floa
   using TileB = F32Tile<TB, 64, VEC, TILE_THREADS>;
   constexpr int CHUNKS = FK / 8 / KG;                 // 8-deep k chunks of a step per wavefront
   constexpr int BUF = TileA::FLOATS + TileB::FLOATS;
-  static_assert(2 * BUF >= 4 * 1024, "the second group's sums reuse the tile buffers");
-  __shared__ __attribute__((aligned(16))) float pool[2 * BUF];
+  static_assert(3 * BUF >= 4 * 1024, "the second group's sums reuse the tile buffers");
+  __shared__ __attribute__((aligned(16))) float pool[3 * BUF];
   const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) & 3, group = threadIdx.x >> 8;
   const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
   f32x16 acc;
 #pragma unroll
   for (int e = 0; e < 16; ++e) acc[e] = 0.f;
 
-  // Global loads run two steps ahead of their use: step t + 2 is requested when step t starts and goes to LDS at the end
-  // of step t + 1.  One step ahead, a tile on every CU waited for memory a third of its time (N = M = K = 1024: 28 us
-  // with four wavefronts and one step ahead, 24 us this way = 89 TFLOP/s).
+  // Three buffers: while step t is contracted, step t + 2 goes from registers to LDS and step t + 4 is requested from memory, and the first
+  // fragments of step t + 1, complete since the barrier before, are read under the last MFMAs: what the step's one barrier waits for has
+  // MFMAs running beside it, and the MFMAs behind it have their operands.  (1024 x 1024 x 1024: 24 us = 91 TFLOP/s.)
   f32x4v ra[2][TileA::N4], rb[2][TileB::N4];
   const int steps = (K + FK - 1) / FK;
-  auto fetch = [&](int set, int t) {
-    TileA::load(ra[set], A, lda, m0, M, t * FK, K);
-    TileB::load(rb[set], B, ldb, n0, N, t * FK, K);
+  const F32Stream<!TA, 64, VEC, TILE_THREADS> sa(A, lda, m0, M, K);
+  const F32Stream<TB, 64, VEC, TILE_THREADS> sb(B, ldb, n0, N, K);
+  auto fetch = [&](int set, int t) {                   // a step past the end: zeros
+    sa.load(ra[set], t);
+    sb.load(rb[set], t);
   };
   auto put = [&](int set, int buf) {
     TileA::store(ra[set], pool + buf * BUF);
     TileB::store(rb[set], pool + buf * BUF + TileA::FLOATS);
   };
-  auto step = [&](int t, int cur) {                  // cur = t & 1, a constant at every call
-    if (t + 2 < steps) fetch(cur, t + 2);
+  static_assert(CHUNKS == 2, "two chunks of a step per wavefront");
+  f32x4v fa[2], fb[2];
+  auto frags = [&](int c8, int buf) {
+    fa[c8] = TileA::frag(pool + buf * BUF, wm, group * CHUNKS + c8, lane);
+    fb[c8] = TileB::frag(pool + buf * BUF + TileA::FLOATS, wn, group * CHUNKS + c8, lane);
+  };
+  auto multiply = [&](int c8) {
 #pragma unroll
-    for (int c8 = 0; c8 < CHUNKS; ++c8) {
-      const f32x4v fa = TileA::frag(pool + cur * BUF, wm, group * CHUNKS + c8, lane);
-      const f32x4v fb = TileB::frag(pool + cur * BUF + TileA::FLOATS, wn, group * CHUNKS + c8, lane);
-#pragma unroll
-      for (int c = 0; c < 4; ++c) acc = mfma_f32(fa[c], fb[c], acc);
-    }
-    if (t + 1 < steps) put(cur ^ 1, cur ^ 1);
+    for (int c = 0; c < 4; ++c) acc = mfma_f32(fa[c8][c], fb[c8][c], acc);
+  };
+  auto step = [&](int t, int set, int buf) {           // set = t % 2, buf = t % 3: constants at every call
+    frags(1, buf);
+    multiply(0);
+    __builtin_amdgcn_sched_barrier(0);
+    put(set, (buf + 2) % 3);
+    fetch(set, t + 4);
+    frags(0, (buf + 1) % 3);
+    multiply(1);
+    __builtin_amdgcn_sched_barrier(0);                 // the MFMAs stay on this side: they run while the reads and writes land
     __syncthreads();
   };
   fetch(0, 0);
-  if (steps > 1) fetch(1, 1);
+  fetch(1, 1);
   put(0, 0);
+  fetch(0, 2);
+  put(1, 1);
+  fetch(1, 3);
   __syncthreads();
-  for (int t = 0; t < steps; t += 2) {
-    step(t, 0);
-    if (t + 1 < steps) step(t + 1, 1);
+  frags(0, 0);
+  for (int t = 0;; t += 6) {
+    step(t, 0, 0);
+    if (t + 1 >= steps) break;
+    step(t + 1, 1, 1);
+    if (t + 2 >= steps) break;
+    step(t + 2, 0, 2);
+    if (t + 3 >= steps) break;
+    step(t + 3, 1, 0);
+    if (t + 4 >= steps) break;
+    step(t + 4, 0, 1);
+    if (t + 5 >= steps) break;
+    step(t + 5, 1, 2);
+    if (t + 6 >= steps) break;
   }
   if (group > 0)
 #pragma unroll
@@ -350,7 +411,7 @@ hipError_t launch_f32(const GemmArgs& g, hipStream_t s) {
 
 // 16-byte loads need aligned rows and a contiguous extent of whole float4s (M or N when K-strided, K when K-contiguous)
 bool vec_ok(const GemmArgs& g) {
-  return !((g.lda | g.ldb) & 3) && !((uintptr_t)g.A & 15) && !((uintptr_t)g.B & 15) && !((g.transA ? g.M : g.K) & 3) &&
+  return g.lda < VEC_MAX_LD && g.ldb < VEC_MAX_LD && !((g.lda | g.ldb) & 3) && !((uintptr_t)g.A & 15) && !((uintptr_t)g.B & 15) && !((g.transA ? g.M : g.K) & 3) &&
          !((g.transB ? g.K : g.N) & 3);
 }
 template <bool TA, bool TB>

@@ -15,6 +15,9 @@ GEMM_SHAPES = [(1, 1, 1), (31, 33, 7), (32, 64, 8), (63, 65, 33), (70, 45, 31), 
 # kernel) and 99, 97
 TINY_SHAPES = [(15, 17, 15), (16, 16, 16), (17, 31, 129), (33, 47, 513), (8 * 32, 12 * 32, 130), (8 * 32 + 1, 11 * 32, 127), (1, 97 * 32, 20)]
 
+# the tile kernel with 16-byte loads: ragged tiles, K of one to seven steps of 32 (its loop has six), whole and not
+VEC_SHAPES = [(516, 1028, 4), (700, 900, 36), (520, 1044, 64), (512, 1024, 100), (580, 960, 160), (516, 1088, 188), (640, 900, 228)]
+
 
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
 @pytest.mark.parametrize("pad", [0, 3])
@@ -24,7 +27,7 @@ def test_f32_gemm_tile_edges(ta, tb, pad):
     import torch
     import paper_2605_18750_amd as R
     from paper_2605_18750_amd import harness as Hn
-    for M, N, K in GEMM_SHAPES + TINY_SHAPES:
+    for M, N, K in GEMM_SHAPES + TINY_SHAPES + VEC_SHAPES:
         print(f"[f32 gemm] M{M} N{N} K{K} ta{ta} tb{tb} pad{pad}", flush=True)
         shp = [(K, M) if ta else (M, K), (N, K) if tb else (K, N), (M, N)]
         A, B, Rr = [SI.make_tensor(7, f"f32{M}.{N}.{K}{n}", s, 1.0, "fp32") for n, s in zip("ABR", shp)]
