@@ -65,8 +65,8 @@ int rrfp_gemm_plan_ws(int M, int N, int K, int lda, int ldb, int ldc, int trans_
 
 /* How the weight gradients of a W task (paper Section 7.1) are cut: n products (at most 32) of M[i] x N[i], contracted over the
  * same K tokens, in one launch.  Pure host logic.  out[0] = tiles of 256 x 256 contracted whole, out[1] = tiles after them
- * that are cut along K, out[2] = the ranges they are cut into (1: none, 0: the whole list runs in 64 x 64 tiles, out[0] of
- * them).  Each range writes a 256 x 256 fp32 plane per tile into the workspace; ranges that do not fit are not made.
+ * that are cut along K, out[2] = the ranges they are cut into (1: none, 0: the whole list runs in 64 x 64 tiles, -1: in
+ * 128 x 128 tiles, out[0] of them).  Each range writes a 256 x 256 fp32 plane per tile into the workspace; ranges that do not fit are not made.
  * STAGE_EINVAL for NULL or non-positive arguments and for a product the grouped kernel does not take (M or N not a
  * multiple of 8, operands of 2 GiB). */
 int rrfp_wgrad_group_plan(int n, const int32_t* M, const int32_t* N, int K, size_t workspace_bytes, int n_cu, int32_t out[3]);

@@ -417,6 +417,12 @@ __device__ __forceinline__ void colsum_block(const float* __restrict__ partial, 
 __global__ __launch_bounds__(256) void colsum_kernel(const float* __restrict__ partial, int n_partial, int H, float* __restrict__ out) {
   colsum_block(partial, n_partial, H, H, blockIdx.x * 64, out);
 }
+// Entry of a list (at most 64) that workgroup `block` belongs to, from the entries' first workgroups: all are loaded at once, for a walk would be a
+// chain of loads from the arguments in host memory.
+__device__ __forceinline__ int list_index(const int* start, int n, int block) {
+  const int lane = threadIdx.x & 63;
+  return __builtin_amdgcn_readfirstlane(__popcll(__ballot(lane < n && start[lane] <= block)) - 1);
+}
 // The vector gradients of a whole B task: each sum is 2 to 5 us of latency (a few workgroups that walk some hundred rows), so one launch
 // takes up to COLSUM_LIST_MAX of them, workgroup after workgroup.  4 layers with LayerNorm and biases: 32 launches of 4.7 us a task -> 1 (with the
 // chunk sums of the bias gradients below, also one launch).
@@ -426,8 +432,7 @@ struct ColsumList {
   int n;
 };
 __global__ __launch_bounds__(256) void colsum_list_kernel(const ColsumList list) {
-  int i = 0;
-  while (i + 1 < list.n && list.start[i + 1] <= (int)blockIdx.x) ++i;
+  const int i = list_index(list.start, list.n, blockIdx.x);
   const ColsumJob& j = list.job[i];
   colsum_block(j.partial, j.n_partial, j.ld, j.width, ((int)blockIdx.x - list.start[i]) * 64, j.out);
 }
@@ -711,8 +716,7 @@ struct ColsumRowsList {
 };
 template <typename T>
 __global__ __launch_bounds__(256) void colsum_rows_list_kernel(const ColsumRowsList list, int Tn) {
-  int i = 0;
-  while (i + 1 < list.n && list.start[i + 1] <= (int)blockIdx.x) ++i;
+  const int i = list_index(list.start, list.n, blockIdx.x);
   const ColsumRowsJob& j = list.job[i];
   colsum_rows_block<T>((const T*)j.src, j.N, j.partial, Tn, j.N, (int)blockIdx.x - list.start[i]);
 }
@@ -932,8 +936,7 @@ struct HalfCopies {
   int n;
 };
 __global__ __launch_bounds__(256) void bf16_to_f16_kernel(const HalfCopies list) {
-  int t = 0;
-  while (t + 1 < list.n && list.start[t + 1] <= (int)blockIdx.x) ++t;
+  const int t = list_index(list.start, list.n, blockIdx.x);
   const bf16_t* src = (const bf16_t*)list.c[t].src;
   f16_t* dst = (f16_t*)list.c[t].dst;
   const size_t n8 = list.c[t].n / 8, i0 = (size_t)((int)blockIdx.x - list.start[t]) * HALF_COPY_VECS + threadIdx.x;
@@ -1167,7 +1170,9 @@ hipError_t launch_colsum_rows_list(const ColsumRowsJob* jobs, int n, int Tn, int
   list.n = 0;
   list.start[0] = 0;
   auto flush = [&]() -> hipError_t {
-    if (list.n > 0) DISPATCH_T(dtype, hipLaunchKernelGGL(colsum_rows_list_kernel<T>, dim3(list.start[list.n], chunks), dim3(256), 0, s, list, Tn));
+    if (list.n > 0) {
+      DISPATCH_T(dtype, hipLaunchKernelGGL(colsum_rows_list_kernel<T>, dim3(list.start[list.n], chunks), dim3(256), 0, s, list, Tn));
+    }
     list.n = 0;
     return hipGetLastError();
   };

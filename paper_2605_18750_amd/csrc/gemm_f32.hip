@@ -21,6 +21,7 @@
 // Every output element is summed in one fixed order (k chunks ascending inside a wavefront, the ranges of
 // the wavefronts added in order), so a call always gives the same bits.
 #include <algorithm>
+#include <climits>
 
 #include "kernels.h"
 #include "numeric.h"
@@ -367,19 +368,21 @@ constexpr int F32_GROUP_MAX = 32;
 struct F32Problem {
   const float *A, *B;
   float* C;
-  int M, N, lda, ldb, ldc, tiles_n, start;             // start = index of its first tile
+  int M, N, lda, ldb, ldc, tiles_n;
 };
 struct F32Group {
+  int start[F32_GROUP_MAX];                            // index of each product's first tile; INT_MAX past the last product
   F32Problem p[F32_GROUP_MAX];
-  int n, K;
+  int K;
 };
 template <bool VEC, bool SMALL>
 __global__ __launch_bounds__(SMALL ? 64 * SMALL_WAVES : TILE_THREADS) void gemm_f32_group_kernel(const F32Group g) {
   constexpr int EDGE = SMALL ? 32 : 64;
-  int i = 0;
-  while (i + 1 < g.n && g.p[i + 1].start <= (int)blockIdx.x) ++i;
+  int i = -1;                                          // all starts at once: a walk is a chain of loads from host memory
+#pragma unroll
+  for (int k = 0; k < F32_GROUP_MAX; ++k) i += g.start[k] <= (int)blockIdx.x;
   const F32Problem& p = g.p[i];
-  const int t = blockIdx.x - p.start, m0 = t / p.tiles_n * EDGE, n0 = t % p.tiles_n * EDGE;
+  const int t = blockIdx.x - g.start[i], m0 = t / p.tiles_n * EDGE, n0 = t % p.tiles_n * EDGE;
   if constexpr (SMALL) f32_small<true, false, VEC>(p.A, p.B, p.C, nullptr, nullptr, p.M, p.N, g.K, p.lda, p.ldb, p.ldc, 0, m0, n0);
   else f32_tile<true, false, VEC>(p.A, p.B, p.C, nullptr, nullptr, p.M, p.N, g.K, p.lda, p.ldb, p.ldc, 0, m0, n0);
 }
@@ -422,14 +425,15 @@ hipError_t launch_f32_aligned(const GemmArgs& g, hipStream_t s) {
 // The rule of launch_f32 on the tiles of the whole group.
 hipError_t launch_f32_group(const GemmArgs* g, int n, hipStream_t s) {
   F32Group grp{};
-  grp.n = n;
   grp.K = g[0].K;
+  for (int i = n; i < F32_GROUP_MAX; ++i) grp.start[i] = INT_MAX;
   bool vec = true;
   auto tiles = [&](int edge) {
     int t = 0;
     for (int i = 0; i < n; ++i) {
       const int tn = (g[i].N + edge - 1) / edge;
-      grp.p[i] = F32Problem{(const float*)g[i].A, (const float*)g[i].B, (float*)g[i].C, g[i].M, g[i].N, g[i].lda, g[i].ldb, g[i].ldc, tn, t};
+      grp.p[i] = F32Problem{(const float*)g[i].A, (const float*)g[i].B, (float*)g[i].C, g[i].M, g[i].N, g[i].lda, g[i].ldb, g[i].ldc, tn};
+      grp.start[i] = t;
       t += (g[i].M + edge - 1) / edge * tn;
     }
     return t;

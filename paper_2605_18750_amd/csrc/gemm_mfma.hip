@@ -30,6 +30,7 @@
 // the choice of 128-row tiles and the split-K factor depend only on the shape and on the device's CU
 // count, never on what else is running, so a given call always sums in the same order.
 #include <algorithm>
+#include <climits>
 #include <type_traits>
 
 #include "kernels.h"
@@ -1338,19 +1339,23 @@ inline bool wgrad_small(int M, int N, int K, int n_cu) {
 constexpr int GROUP_MAX = WGRAD_GROUP_MAX;             // the list travels in the kernel arguments (1.8 KB of 4)
 struct WgradProblem {
   const bf16_t* A; const bf16_t* B; float* C;
-  int M, N, lda, ldb, ldc, tiles_m, tiles_n, start;    // start = index of its first tile
+  int M, N, lda, ldb, ldc, tiles_m, tiles_n;
 };
 struct WgradGroup {
+  int start[GROUP_MAX];                                // index of each product's first tile; INT_MAX past the last product
   WgradProblem p[GROUP_MAX];
-  int n, K;
+  int K;
   int full, tail, k_split;                             // tiles contracted whole; tiles after them, cut into ranges of k_split
   float* ws;
 };
 
-__device__ __forceinline__ const WgradProblem& group_problem(const WgradGroup& g, int tile) {
-  int i = 0;
-  while (i + 1 < g.n && g.p[i + 1].start <= tile) ++i;
-  return g.p[i];
+// The product a tile belongs to.  No walk along the list: the arguments lie in host memory, and a chain of loads, each the next line, cost a
+// launch of 16 products 5 us before its first tile.  All starts are loaded at once.
+__device__ __forceinline__ int group_index(const WgradGroup& g, int tile) {
+  int i = -1;
+#pragma unroll
+  for (int k = 0; k < GROUP_MAX; ++k) i += g.start[k] <= tile;
+  return i;
 }
 
 // Work item id: tile id for id < full, else range (id - full) / tail of tile full + (id - full) % tail.  Pointers are those of the
@@ -1368,9 +1373,10 @@ __device__ __forceinline__ WgradItem wgrad_item(const WgradGroup& g, int id) {
     k0 = range * g.k_split;
     K = min(g.k_split, K - k0);
   }
-  const WgradProblem& p = group_problem(g, tile);
+  const int i = group_index(g, tile);
+  const WgradProblem& p = g.p[i];
   int tm, tn;
-  tile_coords(tile - p.start, p.tiles_m, p.tiles_n, tm, tn);
+  tile_coords(tile - g.start[i], p.tiles_m, p.tiles_n, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
   WgradItem w;
   w.lda = p.lda; w.ldb = p.ldb;
@@ -1412,9 +1418,6 @@ struct WgradLoader {
   }
 };
 
-// Groups of four steps of an item, at least two (its first and its last).
-__device__ __forceinline__ int wgrad_groups(int nk) { return max(2, (nk + 3) >> 2); }
-
 // A workgroup per CU walks the items blockIdx.x, + gridDim.x, ...  The steps of all its items form one sequence: the first steps of an item
 // are loaded under the last MFMAs of the one before, and its sums go straight from the accumulators to memory, no LDS between, so that
 // the stores drain under the next item's steps.  Four 32 KB buffers hold a group of four steps; an item's steps are padded to whole
@@ -1426,8 +1429,7 @@ __device__ __forceinline__ int wgrad_groups(int nk) { return max(2, (nk + 3) >> 
 // reads behind the L2s, at K of thousands the matrix pipes at the power limit.  A workgroup per tile, its sums through LDS -> this, inside
 // the stage: 4 layers of hidden 4096 at 256 to 512 tokens 1137 -> 979 us a launch, at 4096 tokens 5368 -> 5191; 8 layers of hidden 1280 at
 // 6272 tokens 1540 -> 1519; 2 layers of hidden 2048 at 3704 tokens 652 -> 616.  Waiting for 16 operations instead of 60 behind the stores
-// of an item (so for nearly all of them) gave half of that; stepping one item in two groups at least (K <= 128 is padded to 256) costs nothing
-// there, where the stores set the time.
+// of an item (so for nearly all of them) gave half of that.
 __global__ __launch_bounds__(256) void gemm_mfma_wgrad_group_kernel(const WgradGroup g, int items) {
   __shared__ __attribute__((aligned(1024))) char stage0[DSTAGE];
   __shared__ __attribute__((aligned(1024))) char stage1[DSTAGE];
@@ -1452,13 +1454,16 @@ __global__ __launch_bounds__(256) void gemm_mfma_wgrad_group_kernel(const WgradG
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i], f.b[j], acc[i][j], 0, 0, 0);
   };
+  // An item is contracted in two groups at least, so that its first steps run before the stores of the item before are waited for; where
+  // no workgroup has a second item one will do.
+  const int min_groups = items > (int)gridDim.x ? 2 : 1;
   int id = blockIdx.x;
   WgradItem next = wgrad_item(g, id);                  // the item whose steps are being loaded
   WgradLoader la, lb;
   la.init(next.A, next.a_bytes, next.lda, wave, lane);
   lb.init(next.B, next.b_bytes, next.ldb, wave, lane);
   float* C = next.C;                                   // of the item that is being contracted
-  int ldc = next.ldc, rows = next.rows, cols = next.cols, groups = wgrad_groups(next.nk), t = 0;
+  int ldc = next.ldc, rows = next.rows, cols = next.cols, groups = max(min_groups, (next.nk + 3) >> 2), t = 0;
   la.issue(stage0, 0, true, wave);
   lb.issue(stage0 + DTILE, 0, true, wave);
   la.issue(stage1, 1, 1 < next.nk, wave);
@@ -1489,16 +1494,17 @@ __global__ __launch_bounds__(256) void gemm_mfma_wgrad_group_kernel(const WgradG
   interleave_ds_vm_mfma<16, 16, 4>();                                                                    \
   __builtin_amdgcn_sched_barrier(0);
   for (;;) {
-    // first four steps: the loads of the next two were issued before the 256 stores of the item before
-    t = 4;
-    RRFP_W_FIRST(0, VM_60, stage0, stage1)
-    RRFP_W_SECOND(0, stage0, stage1)
-    RRFP_W_FIRST(1, VM_60, stage1, stage2)
-    RRFP_W_SECOND(1, stage1, stage2)
-    RRFP_W_FIRST(2, VM_16, stage2, stage3)
-    RRFP_W_SECOND(2, stage2, stage3)
-    RRFP_W_FIRST(3, VM_16, stage3, stage0)
-    RRFP_W_SECOND(3, stage3, stage0)
+    if (groups > 1) {   // first four steps: the loads of the next two were issued before the 256 stores of the item before
+      t = 4;
+      RRFP_W_FIRST(0, VM_60, stage0, stage1)
+      RRFP_W_SECOND(0, stage0, stage1)
+      RRFP_W_FIRST(1, VM_60, stage1, stage2)
+      RRFP_W_SECOND(1, stage1, stage2)
+      RRFP_W_FIRST(2, VM_16, stage2, stage3)
+      RRFP_W_SECOND(2, stage2, stage3)
+      RRFP_W_FIRST(3, VM_16, stage3, stage0)
+      RRFP_W_SECOND(3, stage3, stage0)
+    }
     for (; groups > 2; --groups) {
       t += 4;
       RRFP_W_FIRST(0, VM_16, stage0, stage1)
@@ -1552,7 +1558,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_wgrad_group_kernel(const WgradG
     ldc = next.ldc;
     rows = next.rows;
     cols = next.cols;
-    groups = wgrad_groups(next.nk);
+    groups = max(min_groups, (next.nk + 3) >> 2);
     clear();
     RRFP_W_SECOND(3, stage3, stage0)
   }
@@ -1564,9 +1570,10 @@ __global__ __launch_bounds__(256) void gemm_mfma_wgrad_group_kernel(const WgradG
 // Planes of the cut tiles added in range order: 16 workgroups per tile, 16 rows each.
 __global__ __launch_bounds__(256) void wgrad_group_finish_kernel(const WgradGroup g, int ranges) {
   const int t = blockIdx.x >> 4, tile = g.full + t;
-  const WgradProblem& p = group_problem(g, tile);
+  const int i = group_index(g, tile);
+  const WgradProblem& p = g.p[i];
   int tm, tn;
-  tile_coords(tile - p.start, p.tiles_m, p.tiles_n, tm, tn);
+  tile_coords(tile - g.start[i], p.tiles_m, p.tiles_n, tm, tn);
   const int c = (threadIdx.x & 63) * 4, n = tn * BN + c;
   if (n >= p.N) return;                                // N is a multiple of 8
   float4 v[4];
@@ -1589,11 +1596,117 @@ __global__ __launch_bounds__(256) void wgrad_group_finish_kernel(const WgradGrou
   }
 }
 
+// The same list with 128 x 128 tiles, one per workgroup of four wavefronts (64 x 64 each, v_mfma_f32_32x32x16_bf16), two workgroups per CU:
+// for few tokens on a chip the 256-row tiles do not fill.  What bounds it is latency (the first loads, a barrier a step, the store of the
+// tile): four times the workgroups, a quarter of the store each.  32-deep steps through four 16 KB buffers, loads three steps ahead;
+// both operands' tiles as in read_frag, rows of 256 bytes, 64-byte units moved by k & 3 (the k rows one pass of a transposed read meets).
+constexpr int MT = 128, MTILE = 32 * MT * 2;           // tile edge; bytes of one operand of a step
+struct MidLoader {
+  const bf16_t* base;
+  int bytes, k_stride, voff[2];
+  __device__ __forceinline__ void init(const bf16_t* p, int n_bytes, int ld, int wave, int lane) {
+    base = p;
+    bytes = n_bytes;
+    k_stride = DBK * ld * 2;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int k = (i * 4 + wave) * 4 + (lane >> 4), cp = lane & 15;
+      voff[i] = (k * ld + ((((cp >> 2) ^ (k & 3)) << 2) | (cp & 3)) * 8) * 2;
+    }
+  }
+  __device__ __forceinline__ void issue(char* tile, int t, bool exists, int wave) const {
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, exists ? bytes : 0, 0x00020000);
+    const int soff = exists ? t * k_stride : 0;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_ptr)(tile + (i * 4 + wave) * 1024), 16, voff[i], soff, 0, 0);
+  }
+};
+__device__ __forceinline__ bf16x8 mid_frag(const char* tile, int row0, int ks, int lane) {
+  const int kb = ks * 16 + (lane >> 5) * 8 + ((lane & 15) >> 2);
+  const int c = (row0 >> 3) + ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1);
+  const char* p = tile + kb * (MT * 2) + (((((c >> 2) ^ (kb & 3)) << 2) | (c & 3)) << 4) + (lane & 1) * 8;
+  union { short4v h[2]; bf16x8 v; } u;
+  u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)p);
+  u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(p + 4 * MT * 2));
+  return u.v;
+}
+__global__ __launch_bounds__(256, 2) void gemm_mfma_wgrad_group_mid_kernel(const WgradGroup g) {
+  __shared__ __attribute__((aligned(1024))) char stage0[2 * MTILE];
+  __shared__ __attribute__((aligned(1024))) char stage1[2 * MTILE];
+  __shared__ __attribute__((aligned(1024))) char stage2[2 * MTILE];
+  __shared__ __attribute__((aligned(1024))) char stage3[2 * MTILE];
+  const int i = group_index(g, blockIdx.x);
+  const WgradProblem& p = g.p[i];
+  int tm, tn;
+  tile_coords(blockIdx.x - g.start[i], p.tiles_m, p.tiles_n, tm, tn);
+  const int m0 = tm * MT, n0 = tn * MT, K = g.K, nk = (K + DBK - 1) / DBK;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
+  MidLoader la, lb;
+  la.init(p.A + m0, (int)(((size_t)(K - 1) * p.lda + (p.M - m0)) * 2), p.lda, wave, lane);
+  lb.init(p.B + n0, (int)(((size_t)(K - 1) * p.ldb + (p.N - n0)) * 2), p.ldb, wave, lane);
+  auto issue = [&](char* buf, int t) {
+    la.issue(buf, t, t < nk, wave);
+    lb.issue(buf + MTILE, t, t < nk, wave);
+  };
+  issue(stage0, 0);
+  issue(stage1, 1);
+  issue(stage2, 2);
+  floatx16 acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  constexpr int VM_8 = 0x0070 | 8;                     // all but the loads of the two steps after; lgkmcnt(0)
+#define RRFP_MID_STEP(cur, ahead, t)                                                                        \
+  __builtin_amdgcn_s_waitcnt(VM_8);                                                                         \
+  stage_barrier();                                                                                          \
+  issue(ahead, (t) + 3);                                                                                    \
+  _Pragma("unroll") for (int ks = 0; ks < 2; ++ks) {                                                        \
+    bf16x8 fa[2], fb[2];                                                                                    \
+    _Pragma("unroll") for (int i = 0; i < 2; ++i) {                                                         \
+      fa[i] = mid_frag(cur, wm + i * 32, ks, lane);                                                         \
+      fb[i] = mid_frag(cur + MTILE, wn + i * 32, ks, lane);                                                 \
+    }                                                                                                       \
+    _Pragma("unroll") for (int i = 0; i < 2; ++i)                                                           \
+    _Pragma("unroll") for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0); \
+  }
+  for (int t = 0;; t += 4) {
+    RRFP_MID_STEP(stage0, stage3, t)
+    if (t + 1 >= nk) break;
+    RRFP_MID_STEP(stage1, stage0, t + 1)
+    if (t + 2 >= nk) break;
+    RRFP_MID_STEP(stage2, stage1, t + 2)
+    if (t + 3 >= nk) break;
+    RRFP_MID_STEP(stage3, stage2, t + 3)
+    if (t + 4 >= nk) break;
+  }
+#undef RRFP_MID_STEP
+  __builtin_amdgcn_s_waitcnt(0x0070);                  // the zero loads of the steps past the end have landed too
+  const int rows = min(MT, p.M - m0), cols = min(MT, p.N - n0);
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int col = wn + j * 32 + (lane & 31);
+    if (col >= cols) continue;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int row = wm + i * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
+        if (row < rows) p.C[(size_t)(m0 + row) * p.ldc + n0 + col] = acc[i][j][e];
+      }
+  }
+}
+
 // The same list with 64 x 64 tiles (tile counts and starts are those of the small kernel).
 __global__ __launch_bounds__(SMALL_NW * 64) void gemm_mfma_wgrad_group_small_kernel(const WgradGroup g) {
-  const WgradProblem& p = group_problem(g, blockIdx.x);
+  const int i = group_index(g, blockIdx.x);
+  const WgradProblem& p = g.p[i];
   int tm, tn;
-  tile_coords(blockIdx.x - p.start, p.tiles_m, p.tiles_n, tm, tn);
+  tile_coords(blockIdx.x - g.start[i], p.tiles_m, p.tiles_n, tm, tn);
   small_tile<false, false, float, false, ACT_NONE, false, ST>(p.A, p.B, p.C, nullptr, p.M, p.N, g.K, p.lda, p.ldb, p.ldc, 0, tm * ST, tn * ST,
                                                           nullptr, 0, nullptr, nullptr);
 }
@@ -1636,9 +1749,15 @@ hipError_t launch_a_kc(const GemmArgs& g, hipStream_t s) {
 }
 
 // How the group is cut: estimated times as in a_kc_split, 8 us a round of 256-row tiles beyond its k steps.
-// ranges = 0: the small-output kernel.  A pure function of the shapes, the device and the scratch.
+// ranges = 0: the small-output kernel, -1: 128 x 128 tiles.  A pure function of the shapes, the device and the scratch.
+// The 128 x 128 tiles are for short contractions: up to 320 tokens while one round of them (two per CU, 3/4 full) replaces 256-row tiles that
+// leave CUs idle or 64 x 64 ones past a round, and up to 128 tokens where the 256-row tiles would need a second round of up to half the CUs.
+// Measured (us; else -> 128 x 128): 2 layers of hidden 512 at 40 / 128 / 300 tokens 12.3 -> 10.4, 12.8 -> 11.8, 17.4 -> 16.2, at 777 26.5 -> 26.2;
+// 4 of hidden 256 13.6 -> 9.0, 14.5 -> 9.5, 18.1 -> 13.1; 1 of hidden 1536 at 40 / 128 27.8 -> 23.9, 29.3 -> 27.4; but 4 of hidden 512 at 40 (736 tiles)
+// 14.9 -> 16.5, 1 of hidden 256 at 40 (192 tiles of 64 x 64) 5.6 -> 7.5.
 struct GroupCut { int full, tail, ranges; };
-inline GroupCut wgrad_group_cut(long long t256, long long t64, int K, int n_cu, size_t ws_bytes) {
+inline GroupCut wgrad_group_cut(long long t256, long long t128, long long t64, int K, int n_cu, size_t ws_bytes) {
+  if ((K <= 320 && t64 > n_cu && 2 * t128 <= 3 * n_cu) || (K <= 128 && t256 > n_cu && 2 * t256 <= 3 * n_cu)) return GroupCut{(int)t128, 0, -1};
   constexpr float US_STEP = 0.75f, US_ROUND = 8.0f, FINISH_US = 4.0f, PLANE_BYTES_PER_US = 8.0e6f;
   constexpr int MAX_RANGES = 16, MIN_STEPS = 8;
   const int steps = (K + DBK - 1) / DBK, r = (int)(t256 % n_cu);
@@ -1666,15 +1785,19 @@ inline long long group_tiles(const GemmArgs* g, int n, int edge) {
 
 hipError_t launch_wgrad_group_mfma(const GemmArgs* g, int n, hipStream_t s) {
   WgradGroup grp{};
-  grp.n = n;
   grp.K = g[0].K;
   const bool ws = g[0].ws && !((uintptr_t)g[0].ws & 15);
-  const GroupCut cut = wgrad_group_cut(group_tiles(g, n, BM), group_tiles(g, n, ST), grp.K, cu_count(), ws ? g[0].ws_bytes : 0);
-  const int edge = cut.ranges == 0 ? ST : BM;
+  const GroupCut cut = wgrad_group_cut(group_tiles(g, n, BM), group_tiles(g, n, MT), group_tiles(g, n, ST), grp.K, cu_count(), ws ? g[0].ws_bytes : 0);
+  const int edge = cut.ranges == 0 ? ST : cut.ranges < 0 ? MT : BM;
+  for (int i = 0; i < GROUP_MAX; ++i) grp.start[i] = i < n ? (int)group_tiles(g, i, edge) : INT_MAX;
   for (int i = 0; i < n; ++i)
     grp.p[i] = WgradProblem{(const bf16_t*)g[i].A, (const bf16_t*)g[i].B, (float*)g[i].C, g[i].M, g[i].N, g[i].lda, g[i].ldb, g[i].ldc,
-                            (g[i].M + edge - 1) / edge, (g[i].N + edge - 1) / edge, (int)group_tiles(g, i, edge)};
-  if (cut.ranges == 0) {
+                            (g[i].M + edge - 1) / edge, (g[i].N + edge - 1) / edge};
+  if (edge == MT) {
+    hipLaunchKernelGGL(gemm_mfma_wgrad_group_mid_kernel, dim3(cut.full), dim3(256), 0, s, grp);
+    return hipGetLastError();
+  }
+  if (edge == ST) {
     hipLaunchKernelGGL(gemm_mfma_wgrad_group_small_kernel, dim3(cut.full), dim3(SMALL_NW * 64), 0, s, grp);
     return hipGetLastError();
   }
@@ -1871,19 +1994,20 @@ size_t gemm_mfma_plane_bytes(int max_M, int N, int K, int n_cu) {
   return most;
 }
 
-// Of the lengths of one 32-deep step the longest is the last to go to the 64 x 64 tiles; else the cut is that of the step.
+// Of the lengths of one 32-deep step the longest is the last to go to the 64 x 64 or 128 x 128 tiles (whose limits are whole steps); else the cut
+// is that of the step.
 size_t gemm_mfma_wgrad_plane_bytes(const GemmArgs* g, int n, int min_K, int max_K, int n_cu) {
-  const long long t256 = group_tiles(g, n, BM), t64 = group_tiles(g, n, ST);
+  const long long t256 = group_tiles(g, n, BM), t128 = group_tiles(g, n, MT), t64 = group_tiles(g, n, ST);
   size_t most = 0;
   for (int step = (min_K - 1) / DBK; step * DBK < max_K; ++step) {
-    const GroupCut cut = wgrad_group_cut(t256, t64, std::min((step + 1) * DBK, max_K), n_cu, ~(size_t)0);
+    const GroupCut cut = wgrad_group_cut(t256, t128, t64, std::min((step + 1) * DBK, max_K), n_cu, ~(size_t)0);
     if (cut.ranges > 1) most = std::max(most, (size_t)cut.ranges * cut.tail * BM * BN * 4);
   }
   return most;
 }
 
 WgradGroupPlan gemm_mfma_wgrad_group_plan(const GemmArgs* g, int n, int n_cu, size_t ws_bytes) {
-  const GroupCut cut = wgrad_group_cut(group_tiles(g, n, BM), group_tiles(g, n, ST), g[0].K, n_cu, ws_bytes);
+  const GroupCut cut = wgrad_group_cut(group_tiles(g, n, BM), group_tiles(g, n, MT), group_tiles(g, n, ST), g[0].K, n_cu, ws_bytes);
   return WgradGroupPlan{cut.full, cut.tail, cut.ranges, cut.ranges > 1 ? (size_t)cut.ranges * cut.tail * BM * BN * 4 : 0};
 }
 

@@ -70,7 +70,7 @@ size_t gemm_mfma_plane_bytes(int max_M, int N, int K, int n_cu);
 struct GemmPlan { int kernel, wavefronts, main_workgroups, short_workgroups, split_k; };
 GemmPlan gemm_mfma_plan(const GemmArgs& g, int n_cu, size_t ws_bytes);
 // The same for a list of weight gradients that go in one launch: tiles contracted whole, tiles after them that are cut along K
-// and into how many ranges (1 = none; 0: the whole list in 64 x 64 tiles), bytes of their partial planes.
+// and into how many ranges (1 = none; 0: the whole list in 64 x 64 tiles, -1: in 128 x 128 tiles), bytes of their partial planes.
 constexpr int WGRAD_GROUP_MAX = 32;   // products per launch
 struct WgradGroupPlan { int full, tail, ranges; size_t plane_bytes; };
 // The same over every K up to max_K, and over n_counts CU counts, for a list as launch_wgrad_group takes it (K of its products is

@@ -51,6 +51,16 @@ LISTS = [
     (_products(2, 1088, 17, 17, 64, 2880), 1100, 18 * 3, dict(full=512, tail=18, ranges=3)),
     (_products(1, 72, 1, 1, 64, 136), 65, None, dict(full=24, tail=0, ranges=0)),
     ([(1032, 2056)], 4129, None, dict(full=0, tail=45, ranges=5)),
+    # 128 x 128 tiles, ragged: less than a step, one and a bit, five and a bit, the most of the rule for one round; two rounds
+    (_products(2, 504, 8, 2, 64, 1400), 31, None, dict(full=344, tail=0, ranges=-1)),
+    (_products(2, 504, 8, 2, 64, 1400), 33, None, dict(full=344, tail=0, ranges=-1)),
+    (_products(2, 504, 8, 2, 64, 1400), 165, None, dict(full=344, tail=0, ranges=-1)),
+    (_products(2, 504, 8, 2, 64, 1400), 320, None, dict(full=344, tail=0, ranges=-1)),
+    (_products(2, 504, 8, 2, 64, 1400), 321, None, dict(full=88, tail=0, ranges=1)),
+    (_products(2, 504, 8, 2, 64, 1400), 100, None, dict(full=344, tail=0, ranges=-1)),
+    ([(2376, 3176), (3000, 2056), (1032, 6152)], 97, None, dict(full=1324, tail=0, ranges=-1)),
+    # one 256-row tile per workgroup, K of one group of four steps
+    (_products(4, 512, 8, 2, 64, 1536), 97, None, dict(full=184, tail=0, ranges=1)),
     # workgroups that walk two tiles, of 1, 5, 9 and 12 steps (a workgroup takes them in groups of four, at least two of them)
     ([(2376, 3176), (4096, 2056), (1032, 6152)], 31, None, dict(full=399, tail=0, ranges=1)),
     ([(2376, 3176), (4096, 2056), (1032, 6152)], 131, None, dict(full=399, tail=0, ranges=1)),
