@@ -6,8 +6,12 @@
 
 namespace rrfp {
 
+bool gemm_act_supported(const GemmArgs& g) {
+  return g.act == ACT_NONE || (g.in_dtype == F32 ? gemm_f32_act_supported(g) : gemm_mfma_act_supported(g));
+}
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
-  if (g.act != ACT_NONE) return gemm_act_supported(g) ? launch_gemm_mfma(g, s) : hipErrorInvalidValue;
+  if (!gemm_act_supported(g)) return hipErrorInvalidValue;
+  if (g.act != ACT_NONE) return g.in_dtype == F32 ? launch_gemm_f32(g, s) : launch_gemm_mfma(g, s);
   if (g.in_dtype == F32 && g.out_dtype == F32) return launch_gemm_f32(g, s);
   return gemm_mfma_supports(g) ? launch_gemm_mfma(g, s) : launch_gemm_simt(g, s);
 }

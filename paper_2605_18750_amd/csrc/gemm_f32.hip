@@ -103,11 +103,17 @@ struct F32Stream {
   const float* p;
   int ld, row0, n_rows, K;
   int voff[N4], k_in[N4];                              // byte offset inside a tile (or past it), k inside the step
-  __device__ __forceinline__ F32Stream(const float* p_, int ld_, int row0_, int n_rows_, int K_) : p(p_), ld(ld_), row0(row0_), n_rows(n_rows_), K(K_) {
+  // pair_f > 0 (K-strided, VEC): the columns of a SwiGLU forward of pair_f features, as f32_column
+  __device__ __forceinline__ F32Stream(const float* p_, int ld_, int row0_, int n_rows_, int K_, int pair_f = 0)
+      : p(p_), ld(ld_), row0(pair_f > 0 ? 0 : row0_), n_rows(n_rows_), K(K_) {
 #pragma unroll
     for (int i = 0; i < N4; ++i) {
       const int q = i * NT + threadIdx.x;
-      const int row = KC ? q / (FK / 4) : q % (ROWS / 4) * 4;
+      int row = KC ? q / (FK / 4) : q % (ROWS / 4) * 4;
+      if (pair_f > 0) {
+        const int f = (row0_ >> 1) + row % (ROWS / 2);
+        row = f < pair_f ? f + (row >= ROWS / 2 ? pair_f : 0) : n_rows;
+      }
       k_in[i] = KC ? q % (FK / 4) * 4 : q / (ROWS / 4);
       voff[i] = row0 + row < n_rows ? (KC ? row * ld + k_in[i] : k_in[i] * ld + row) * 4 : (int)0x80000000;
     }
@@ -130,21 +136,69 @@ struct F32Stream {
 
 // Accumulator value r of a 32x32 block: row 8 (r / 4) + 4 (lane >> 5) + r % 4, column lane & 31: a store instruction
 // writes 128 contiguous bytes of two rows.
-__device__ __forceinline__ void put_f32(float v, float* __restrict__ C, const float* __restrict__ R, const float* __restrict__ bias,
-                                        int m, int n, int ldc, int ldr) {
-  if (bias) v += bias[n];
-  if (R) v += R[(size_t)m * ldr + n];
-  C[(size_t)m * ldc + n] = v;
+// ACT: the activation of GemmArgs on the sum (SwiGLU forward needs two sums and is put by put_swiglu).  The formulas of the stand-alone kernels
+// of elementwise.hip; what the fusion saves is their launch and the trip of the tensor through memory: an iteration of one layer, hidden 256,
+// ffn 688, four microbatches of 128 tokens 437 -> 420 us; two layers, hidden 1024, ffn 2752, 1541 tokens 2802 -> 2775 us.
+struct F32Out {
+  float* C; const float* R; const float* bias; float* E;
+  int ldc, ldr, lde;
+};
+__device__ __forceinline__ float sigmoid_f32(float z) { return 1.0f / (1.0f + __expf(-z)); }
+// What the sum of row m, column n meets: the residual, or the saved tensor of an activation's backward (x; SwiGLU: gate x, up y).
+template <int ACT>
+__device__ __forceinline__ void get_operands(float& x, float& y, const F32Out& o, int m, int n, int N) {
+  x = y = 0.f;
+  if constexpr (ACT == ACT_GELU_BWD || ACT == ACT_SWIGLU_BWD) {
+    x = o.E[(size_t)m * o.lde + n];
+    if constexpr (ACT == ACT_SWIGLU_BWD) y = o.E[(size_t)m * o.lde + N + n];
+  } else if (o.R) {
+    x = o.R[(size_t)m * o.ldr + n];
+  }
+}
+template <int ACT>
+__device__ __forceinline__ void put_f32(float v, float x, float y, const F32Out& o, int m, int n, int N) {
+  if (o.bias) v += o.bias[n];
+  float* c = o.C + (size_t)m * o.ldc + n;
+  if constexpr (ACT == ACT_GELU_FWD) {
+    o.E[(size_t)m * o.lde + n] = 0.5f * v * (1.0f + erff(v * 0.70710678118654752f));
+  } else if constexpr (ACT == ACT_GELU_BWD) {
+    const float Phi = 0.5f * (1.0f + erff(x * 0.70710678118654752f)), phi = 0.39894228040143268f * __expf(-0.5f * x * x);
+    v *= Phi + x * phi;
+  } else if constexpr (ACT == ACT_SWIGLU_BWD) {
+    const float sg = sigmoid_f32(x);
+    c[N] = v * x * sg;
+    v = v * y * sg * (1.0f + x * (1.0f - sg));
+  } else {
+    v += x;
+  }
+  *c = v;
+}
+// Row m, feature f of a SwiGLU forward of F features: the sums of its gate and up columns.
+__device__ __forceinline__ void put_swiglu(float g, float up, const F32Out& o, int m, int f, int F) {
+  if (o.bias) { g += o.bias[f]; up += o.bias[F + f]; }
+  float* c = o.C + (size_t)m * o.ldc + f;
+  c[0] = g;
+  c[F] = up;
+  o.E[(size_t)m * o.lde + f] = g * sigmoid_f32(g) * up;
+}
+// Column of C that column c of the tile at n0 stands for; SwiGLU forward: the first half of the tile is gate, the second the up columns of
+// the same features (those past the last feature: the last one again).
+template <int ACT, int EDGE>
+__device__ __forceinline__ int f32_column(int n0, int c, int N) {
+  if constexpr (ACT == ACT_SWIGLU_FWD) {
+    const int F = N >> 1;
+    return min((n0 >> 1) + c % (EDGE / 2), F - 1) + (c >= EDGE / 2 ? F : 0);
+  }
+  return min(n0 + c, N - 1);
 }
 
 // Tile of 64 x 64, eight wavefronts: two groups of 2 x 2 (32 x 32 of C each), each group contracting one half of every
 // step's k; the groups' sums are added at the end, group 0 first.  Eight instead of four wavefronts because a grid of
 // about one tile per CU would otherwise leave a single wavefront per SIMD to cover its own LDS reads and barriers.
 constexpr int KG = 2, TILE_THREADS = 256 * KG;
-template <bool TA, bool TB, bool VEC>
-__device__ __forceinline__ void f32_tile(const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ C,
-                                      const float* __restrict__ R, const float* __restrict__ bias, int M, int N, int K, int lda, int ldb,
-                                      int ldc, int ldr, int m0, int n0) {
+template <bool TA, bool TB, bool VEC, int ACT = ACT_NONE>
+__device__ __forceinline__ void f32_tile(const float* __restrict__ A, const float* __restrict__ B, const F32Out& out, int M, int N, int K,
+                                         int lda, int ldb, int m0, int n0) {
   using TileA = F32Tile<!TA, 64, VEC, TILE_THREADS>;
   using TileB = F32Tile<TB, 64, VEC, TILE_THREADS>;
   constexpr int CHUNKS = FK / 8 / KG;                 // 8-deep k chunks of a step per wavefront
@@ -163,7 +217,7 @@ __device__ __forceinline__ void f32_tile(const float* __restrict__ A, const floa
   f32x4v ra[2][TileA::N4], rb[2][TileB::N4];
   const int steps = (K + FK - 1) / FK;
   const F32Stream<!TA, 64, VEC, TILE_THREADS> sa(A, lda, m0, M, K);
-  const F32Stream<TB, 64, VEC, TILE_THREADS> sb(B, ldb, n0, N, K);
+  const F32Stream<TB, 64, VEC, TILE_THREADS> sb(B, ldb, n0, N, K, ACT == ACT_SWIGLU_FWD ? N >> 1 : 0);
   auto fetch = [&](int set, int t) {                   // a step past the end: zeros
     sa.load(ra[set], t);
     sb.load(rb[set], t);
@@ -215,16 +269,37 @@ __device__ __forceinline__ void f32_tile(const float* __restrict__ A, const floa
     step(t + 5, 1, 2);
     if (t + 6 >= steps) break;
   }
+  // operands of the epilogue, requested together before the sums are exchanged (one by one each row would wait for its own)
+  float x[16], y[16];
+  auto row_of = [&](int r) { return m0 + wm + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3); };
+  if (ACT != ACT_SWIGLU_FWD && group == 0)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) get_operands<ACT>(x[r], y[r], out, min(row_of(r), M - 1), min(n0 + wn + (lane & 31), N - 1), N);
   if (group > 0)
 #pragma unroll
     for (int e = 0; e < 16; ++e) pool[wave * 1024 + e * 64 + lane] = acc[e];
   __syncthreads();
+  if (group == 0)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] += pool[wave * 1024 + r * 64 + lane];
+  if constexpr (ACT == ACT_SWIGLU_FWD) {              // the up columns' wavefronts hand their sums to the gate columns'
+    static_assert(3 * BUF >= (4 + 2) * 1024, "room for them");
+    if (group == 0 && wn > 0)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) pool[(4 + (wave >> 1)) * 1024 + e * 64 + lane] = acc[e];
+    __syncthreads();
+    if (wn > 0) return;
+  }
   if (group > 0) return;
-  const int n = n0 + wn + (lane & 31);
+  const int n = ACT == ACT_SWIGLU_FWD ? (n0 >> 1) + (lane & 31) : n0 + wn + (lane & 31);
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
-    const int m = m0 + wm + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-    if (m < M && n < N) put_f32(acc[r] + pool[wave * 1024 + r * 64 + lane], C, R, bias, m, n, ldc, ldr);
+    const int m = row_of(r);
+    if constexpr (ACT == ACT_SWIGLU_FWD) {
+      if (m < M && n < (N >> 1)) put_swiglu(acc[r], pool[(4 + (wave >> 1)) * 1024 + r * 64 + lane], out, m, n, N >> 1);
+    } else {
+      if (m < M && n < N) put_f32<ACT>(acc[r], x[r], y[r], out, m, n, N);
+    }
   }
 }
 
@@ -243,13 +318,39 @@ __device__ __forceinline__ f32x4v small_frag(const float* __restrict__ p, int ld
   return v;
 }
 
-template <bool TA, bool TB, bool VEC>
-__device__ __forceinline__ void f32_small(const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ C,
-                                      const float* __restrict__ R, const float* __restrict__ bias, int M, int N, int K, int lda, int ldb,
-                                      int ldc, int ldr, int m0, int n0) {
+// The wavefronts' sums of a tile, [SMALL_WAVES][EDGE][EDGE], added in order and put.
+template <int ACT, int EDGE>
+__device__ __forceinline__ void put_sums(const float* red, const F32Out& out, int M, int N, int m0, int n0) {
+  constexpr int W = ACT == ACT_SWIGLU_FWD ? EDGE / 2 : EDGE;          // values (features) per row
+  for (int q = threadIdx.x; q < EDGE * W; q += 64 * SMALL_WAVES) {
+    const int at = q / W * EDGE + q % W;
+    float v = red[at], up = ACT == ACT_SWIGLU_FWD ? red[at + EDGE / 2] : 0.f;
+#pragma unroll
+    for (int w = 1; w < SMALL_WAVES; ++w) {
+      v += red[w * EDGE * EDGE + at];
+      if (ACT == ACT_SWIGLU_FWD) up += red[w * EDGE * EDGE + at + EDGE / 2];
+    }
+    const int m = m0 + q / W;
+    if constexpr (ACT == ACT_SWIGLU_FWD) {
+      const int f = (n0 >> 1) + q % W;
+      if (m < M && f < (N >> 1)) put_swiglu(v, up, out, m, f, N >> 1);
+    } else {
+      const int n = n0 + q % W;
+      float x, y;
+      if (m < M && n < N) {
+        get_operands<ACT>(x, y, out, m, n, N);
+        put_f32<ACT>(v, x, y, out, m, n, N);
+      }
+    }
+  }
+}
+
+template <bool TA, bool TB, bool VEC, int ACT = ACT_NONE>
+__device__ __forceinline__ void f32_small(const float* __restrict__ A, const float* __restrict__ B, const F32Out& out, int M, int N, int K,
+                                          int lda, int ldb, int m0, int n0) {
   __shared__ float red[SMALL_WAVES][32 * 32];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int m = min(m0 + (lane & 31), M - 1), n = min(n0 + (lane & 31), N - 1);
+  const int m = min(m0 + (lane & 31), M - 1), n = f32_column<ACT, 32>(n0, lane & 31, N);
   const int chunks = (K + 7) / 8, per = (chunks + SMALL_WAVES - 1) / SMALL_WAVES;
   const int k_end = min(K, (wave + 1) * per * 8);
   f32x16 acc;
@@ -289,26 +390,19 @@ __device__ __forceinline__ void f32_small(const float* __restrict__ A, const flo
 #pragma unroll
   for (int r = 0; r < 16; ++r) red[wave][((r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) * 32 + (lane & 31)] = acc[r];
   __syncthreads();
-  for (int q = threadIdx.x; q < 32 * 32; q += 64 * SMALL_WAVES) {
-    float v = red[0][q];
-#pragma unroll
-    for (int w = 1; w < SMALL_WAVES; ++w) v += red[w][q];
-    const int mo = m0 + (q >> 5), no = n0 + (q & 31);
-    if (mo < M && no < N) put_f32(v, C, R, bias, mo, no, ldc, ldr);
-  }
+  put_sums<ACT, 32>(&red[0][0], out, M, N, m0, n0);
 }
 
 // Tiles of 16 x 16 on v_mfma_f32_16x16x4_f32, otherwise as f32_small: four times the workgroups for the smallest outputs.  In a
 // chunk of 16 k lane l holds row l & 15 and k = 4 (l >> 4) + i for the i-th of four MFMAs.
 constexpr int TINY = 16, TINY_CHUNKS = 4;
 __device__ __forceinline__ f32x4v mfma_f32_16(float a, float b, f32x4v c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-template <bool TA, bool TB, bool VEC>
-__device__ __forceinline__ void f32_tiny(const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ C,
-                                         const float* __restrict__ R, const float* __restrict__ bias, int M, int N, int K, int lda, int ldb,
-                                         int ldc, int ldr, int m0, int n0) {
+template <bool TA, bool TB, bool VEC, int ACT = ACT_NONE>
+__device__ __forceinline__ void f32_tiny(const float* __restrict__ A, const float* __restrict__ B, const F32Out& out, int M, int N, int K,
+                                         int lda, int ldb, int m0, int n0) {
   __shared__ float red[SMALL_WAVES][TINY * TINY];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int m = min(m0 + (lane & 15), M - 1), n = min(n0 + (lane & 15), N - 1);
+  const int m = min(m0 + (lane & 15), M - 1), n = f32_column<ACT, TINY>(n0, lane & 15, N);
   const int chunks = (K + 15) / 16, per = (chunks + SMALL_WAVES - 1) / SMALL_WAVES;
   const int k_end = min(K, (wave + 1) * per * 16);
   f32x4v acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
@@ -343,22 +437,16 @@ __device__ __forceinline__ void f32_tiny(const float* __restrict__ A, const floa
 #pragma unroll
   for (int r = 0; r < 4; ++r) red[wave][((lane >> 4) * 4 + r) * TINY + (lane & 15)] = acc[0][r] + acc[1][r];
   __syncthreads();
-  const int q = threadIdx.x, mo = m0 + (q >> 4), no = n0 + (q & 15);
-  if (q >= TINY * TINY || mo >= M || no >= N) return;
-  float v = red[0][q];
-#pragma unroll
-  for (int w = 1; w < SMALL_WAVES; ++w) v += red[w][q];
-  put_f32(v, C, R, bias, mo, no, ldc, ldr);
+  put_sums<ACT, TINY>(&red[0][0], out, M, N, m0, n0);
 }
 
-template <bool TA, bool TB, bool VEC, int EDGE>
+template <bool TA, bool TB, bool VEC, int EDGE, int ACT>
 __global__ __launch_bounds__(EDGE < 64 ? 64 * SMALL_WAVES : TILE_THREADS) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ B,
-                                                                                         float* __restrict__ C, const float* __restrict__ R,
-                                                                                         const float* __restrict__ bias, int M, int N, int K,
-                                                                                         int lda, int ldb, int ldc, int ldr) {
-  if constexpr (EDGE == TINY) f32_tiny<TA, TB, VEC>(A, B, C, R, bias, M, N, K, lda, ldb, ldc, ldr, blockIdx.y * TINY, blockIdx.x * TINY);
-  else if constexpr (EDGE == 32) f32_small<TA, TB, VEC>(A, B, C, R, bias, M, N, K, lda, ldb, ldc, ldr, blockIdx.y * 32, blockIdx.x * 32);
-  else f32_tile<TA, TB, VEC>(A, B, C, R, bias, M, N, K, lda, ldb, ldc, ldr, blockIdx.y * 64, blockIdx.x * 64);
+                                                                                         const F32Out out, int M, int N, int K, int lda, int ldb) {
+  const int m0 = blockIdx.y * EDGE, n0 = blockIdx.x * EDGE;
+  if constexpr (EDGE == TINY) f32_tiny<TA, TB, VEC, ACT>(A, B, out, M, N, K, lda, ldb, m0, n0);
+  else if constexpr (EDGE == 32) f32_small<TA, TB, VEC, ACT>(A, B, out, M, N, K, lda, ldb, m0, n0);
+  else f32_tile<TA, TB, VEC, ACT>(A, B, out, M, N, K, lda, ldb, m0, n0);
 }
 
 // Weight gradients of a whole task in one launch: the products are independent (A stored [K, M], B [K, N]), and a small
@@ -383,8 +471,9 @@ __global__ __launch_bounds__(SMALL ? 64 * SMALL_WAVES : TILE_THREADS) void gemm_
   for (int k = 0; k < F32_GROUP_MAX; ++k) i += g.start[k] <= (int)blockIdx.x;
   const F32Problem& p = g.p[i];
   const int t = blockIdx.x - g.start[i], m0 = t / p.tiles_n * EDGE, n0 = t % p.tiles_n * EDGE;
-  if constexpr (SMALL) f32_small<true, false, VEC>(p.A, p.B, p.C, nullptr, nullptr, p.M, p.N, g.K, p.lda, p.ldb, p.ldc, 0, m0, n0);
-  else f32_tile<true, false, VEC>(p.A, p.B, p.C, nullptr, nullptr, p.M, p.N, g.K, p.lda, p.ldb, p.ldc, 0, m0, n0);
+  const F32Out out{p.C, nullptr, nullptr, nullptr, p.ldc, 0, 0};
+  if constexpr (SMALL) f32_small<true, false, VEC>(p.A, p.B, out, p.M, p.N, g.K, p.lda, p.ldb, m0, n0);
+  else f32_tile<true, false, VEC>(p.A, p.B, out, p.M, p.N, g.K, p.lda, p.ldb, m0, n0);
 }
 
 // Which kernel: fewer than 128 tiles of 64 x 64 leave over half of the chip idle, and the small kernel's 32 x 32 tiles
@@ -397,14 +486,14 @@ int f32_tile_edge(int M, int N) {
   return tiles(64) >= 128 ? 64 : tiles(32) > 96 ? 32 : TINY;
 }
 
-template <bool TA, bool TB, bool VEC>
+template <bool TA, bool TB, bool VEC, int ACT = ACT_NONE>
 hipError_t launch_f32(const GemmArgs& g, hipStream_t s) {
-  const float *A = (const float*)g.A, *B = (const float*)g.B, *bias = (const float*)g.bias;
-  float* C = (float*)g.C;
+  const F32Out out{(float*)g.C, g.R, (const float*)g.bias, (float*)g.E, g.ldc, g.ldr, g.lde};
   const int t = f32_tile_edge(g.M, g.N);
-  const dim3 grid((g.N + t - 1) / t, (g.M + t - 1) / t);
+  const int columns = ACT == ACT_SWIGLU_FWD ? (g.N / 2 + t / 2 - 1) / (t / 2) : (g.N + t - 1) / t;
+  const dim3 grid(columns, (g.M + t - 1) / t);
 #define RRFP_GO(EDGE, THREADS) \
-  hipLaunchKernelGGL((gemm_f32_kernel<TA, TB, VEC, EDGE>), grid, dim3(THREADS), 0, s, A, B, C, g.R, bias, g.M, g.N, g.K, g.lda, g.ldb, g.ldc, g.ldr)
+  hipLaunchKernelGGL((gemm_f32_kernel<TA, TB, VEC, EDGE, ACT>), grid, dim3(THREADS), 0, s, (const float*)g.A, (const float*)g.B, out, g.M, g.N, g.K, g.lda, g.ldb)
   if (t == 64) RRFP_GO(64, TILE_THREADS);
   else if (t == 32) RRFP_GO(32, 64 * SMALL_WAVES);
   else RRFP_GO(TINY, 64 * SMALL_WAVES);
@@ -453,8 +542,27 @@ hipError_t launch_f32_group(const GemmArgs* g, int n, hipStream_t s) {
 
 }  // namespace
 
+bool gemm_f32_act_supported(const GemmArgs& g) {
+  if (g.in_dtype != F32 || g.out_dtype != F32 || g.transA || g.R || !g.E || !vec_ok(g)) return false;
+  switch (g.act) {
+    case ACT_SWIGLU_FWD: return !g.transB && g.N % 8 == 0;              // the vectors of B's columns lie in one half
+    case ACT_GELU_FWD: return !g.transB;
+    case ACT_SWIGLU_BWD: case ACT_GELU_BWD: return g.transB;
+    default: return false;
+  }
+}
+
 hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.K <= 0 || g.in_dtype != F32 || g.out_dtype != F32) return hipErrorInvalidValue;
+  if (g.act != ACT_NONE) {
+    if (!gemm_f32_act_supported(g)) return hipErrorInvalidValue;
+    switch (g.act) {
+      case ACT_SWIGLU_FWD: return launch_f32<false, false, true, ACT_SWIGLU_FWD>(g, s);
+      case ACT_GELU_FWD: return launch_f32<false, false, true, ACT_GELU_FWD>(g, s);
+      case ACT_SWIGLU_BWD: return launch_f32<false, true, true, ACT_SWIGLU_BWD>(g, s);
+      default: return launch_f32<false, true, true, ACT_GELU_BWD>(g, s);
+    }
+  }
   if (!g.transA && !g.transB) return launch_f32_aligned<false, false>(g, s);
   if (!g.transA) return launch_f32_aligned<false, true>(g, s);
   if (!g.transB) return launch_f32_aligned<true, false>(g, s);

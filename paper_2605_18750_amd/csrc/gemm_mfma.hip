@@ -1887,7 +1887,7 @@ hipError_t launch_act(const GemmArgs& g, hipStream_t s) {
 
 int device_cu_count() { return cu_count(); }
 
-bool gemm_act_supported(const GemmArgs& g) {
+bool gemm_mfma_act_supported(const GemmArgs& g) {
   if (g.act == ACT_NONE) return true;
   if (!gemm_mfma_supports(g) || !direct_ok(g) || g.R || g.out_dtype != BF16 || !g.E || (g.lde & 7) ||
       ((uintptr_t)g.E & 15) || g.transA)
@@ -2020,7 +2020,7 @@ hipError_t launch_gemm_mfma_wgrad_group(const GemmArgs* g, int n, hipStream_t s)
 hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s) {
   if (!gemm_mfma_supports(g)) return hipErrorInvalidValue;
   if (g.act != ACT_NONE) {
-    if (!gemm_act_supported(g)) return hipErrorInvalidValue;
+    if (!gemm_mfma_act_supported(g)) return hipErrorInvalidValue;
     switch (g.act) {
       case ACT_SWIGLU_FWD: return launch_act<false, ACT_SWIGLU_FWD>(g, s);
       case ACT_GELU_FWD: return launch_act<false, ACT_GELU_FWD>(g, s);

@@ -27,7 +27,7 @@ static inline hipError_t set_max_dynamic_lds_once(std::once_flag& flag, hipError
 //   transB == false: B stored [K,N] (ldb), true: stored [N,K] (ldb).
 // in_dtype is the type of A and B; out_dtype the type of C (F32 for weight gradients and for the
 // residual stream).
-// Optional activation fused into the epilogue (bf16 MFMA kernel only; see gemm_act_supported):
+// Optional activation fused into the epilogue (see gemm_act_supported):
 //   ACT_SWIGLU_FWD  N = 2F, B = [K, 2F] (gate columns then up columns).  C [M, 2F] receives gate|up,
 //                   E [M, F] (lde) receives m = silu(gate) * up computed from the fp32 accumulators.
 //   ACT_GELU_FWD    N = F.  C [M, F] receives u, E [M, F] receives gelu(u).
@@ -50,7 +50,9 @@ struct GemmArgs {
   const void* bias; // optional [N] vector of the storage type added to every row before residual / activation
   const float* out_scale;  // optional device scalar (a power of two) multiplied into a plain 16-bit output before rounding
 };
-bool gemm_act_supported(const GemmArgs& g);   // true if launch_gemm can run g.act fused for this shape
+bool gemm_act_supported(const GemmArgs& g);   // true if launch_gemm can run g.act fused for this shape and type
+bool gemm_mfma_act_supported(const GemmArgs& g);
+bool gemm_f32_act_supported(const GemmArgs& g);
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);       // picks the kernel family
 hipError_t launch_gemm_simt(const GemmArgs& g, hipStream_t s);  // fp32-FMA tiles, any shape and type
 hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t s);   // fp32 MFMA tiles, any fp32 shape
