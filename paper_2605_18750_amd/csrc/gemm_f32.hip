@@ -476,8 +476,9 @@ __global__ __launch_bounds__(SMALL ? 64 * SMALL_WAVES : TILE_THREADS) void gemm_
   else f32_tile<true, false, VEC>(p.A, p.B, out, p.M, p.N, g.K, p.lda, p.ldb, m0, n0);
 }
 
-// Which kernel: fewer than 128 tiles of 64 x 64 leave over half of the chip idle, and the small kernel's 32 x 32 tiles
-// then win (128 x 256 x 1376: 15 against 30 us; at 144 tiles, 517 x 1024 x 1024, it is 29 against 24 us).
+// Which kernel (us, 32 x 32 against 64 x 64 tiles): up to 64 tiles of 64 x 64 the small kernel's fill one round and win clearly (256 x 1024 x 1024
+// 12.7 / 21.6, x 4096 37.6 / 74.7); from there to 127 they win where K is short (448 x 1024 x 256 7.0 / 8.6), tie at K = 1024 (22.0 / 21.6) and lose
+// at longer K over a K-strided B (x 2752 57 / 50); from 128 they need three rounds.
 // Sixteen k ranges instead of eight change nothing: the operand rows then bound it through the L1.
 // So below 97 tiles of 32 x 32 the tiles are 16 x 16, which spreads those rows over four times the CUs (us, 32 -> 16): 128 x 256 x 1376 15.3 ->
 // 7.5, x 256 4.4 -> 3.2, 32 x 1024 x 2752 28.9 -> 12.7, 128 x 768 x 256 (96 tiles) 4.5 -> 4.4; but 128 x 1376 x 256 (172 tiles) 4.9 -> 6.5.
