@@ -466,9 +466,9 @@ struct F32Group {
 template <bool VEC, bool SMALL>
 __global__ __launch_bounds__(SMALL ? 64 * SMALL_WAVES : TILE_THREADS) void gemm_f32_group_kernel(const F32Group g) {
   constexpr int EDGE = SMALL ? 32 : 64;
-  int i = -1;                                          // all starts at once: a walk is a chain of loads from host memory
-#pragma unroll
-  for (int k = 0; k < F32_GROUP_MAX; ++k) i += g.start[k] <= (int)blockIdx.x;
+  static_assert(F32_GROUP_MAX <= 64, "a lane per product");
+  const int lane = threadIdx.x & 63;                   // all starts at once: a walk is a chain of loads from host memory
+  const int i = __builtin_amdgcn_readfirstlane(__popcll(__ballot(lane < F32_GROUP_MAX && g.start[lane] <= (int)blockIdx.x)) - 1);
   const F32Problem& p = g.p[i];
   const int t = blockIdx.x - g.start[i], m0 = t / p.tiles_n * EDGE, n0 = t % p.tiles_n * EDGE;
   const F32Out out{p.C, nullptr, nullptr, nullptr, p.ldc, 0, 0};

@@ -1350,13 +1350,15 @@ struct WgradGroup {
 };
 
 // The product a tile belongs to.  No walk along the list: the arguments lie in host memory, and a chain of loads, each the next line, cost a
-// launch of 16 products 5 us before its first tile.  All starts are loaded at once.
-__device__ __forceinline__ int group_index(const WgradGroup& g, int tile) {
-  int i = -1;
-#pragma unroll
-  for (int k = 0; k < GROUP_MAX; ++k) i += g.start[k] <= tile;
-  return i;
+// launch of 16 products 5 us before its first tile.  Lane l of a wavefront keeps the start of product l, and a tile is a compare and a count
+// of bits.  (All starts compared in scalar registers were some 250 instructions a tile, more than a short walk: one layer of hidden 512 at 512 tokens,
+// 688 tiles of 64 x 64, walk 18.5 us, scalar 19.8, lanes 18.2; one of hidden 2048 at 32 tokens, 688 tiles of 256 x 256, 36.1, 42.4, 40.6.)
+static_assert(GROUP_MAX <= 64, "a lane per product");
+__device__ __forceinline__ int group_starts(const WgradGroup& g) {
+  const int lane = threadIdx.x & 63;
+  return lane < GROUP_MAX ? g.start[lane] : INT_MAX;
 }
+__device__ __forceinline__ int group_index(int starts, int tile) { return __builtin_amdgcn_readfirstlane(__popcll(__ballot(starts <= tile)) - 1); }
 
 // Work item id: tile id for id < full, else range (id - full) / tail of tile full + (id - full) % tail.  Pointers are those of the
 // item's first element; rows, cols: how much of the 256 x 256 tile the output has.
@@ -1365,7 +1367,7 @@ struct WgradItem {
   float* C;
   int a_bytes, b_bytes, lda, ldb, ldc, rows, cols, nk;
 };
-__device__ __forceinline__ WgradItem wgrad_item(const WgradGroup& g, int id) {
+__device__ __forceinline__ WgradItem wgrad_item(const WgradGroup& g, int starts, int id) {
   int tile = id, range = -1, k0 = 0, K = g.K;
   if (id >= g.full) {
     range = (id - g.full) / g.tail;
@@ -1373,7 +1375,7 @@ __device__ __forceinline__ WgradItem wgrad_item(const WgradGroup& g, int id) {
     k0 = range * g.k_split;
     K = min(g.k_split, K - k0);
   }
-  const int i = group_index(g, tile);
+  const int i = group_index(starts, tile);
   const WgradProblem& p = g.p[i];
   int tm, tn;
   tile_coords(tile - g.start[i], p.tiles_m, p.tiles_n, tm, tn);
@@ -1458,7 +1460,8 @@ __global__ __launch_bounds__(256) void gemm_mfma_wgrad_group_kernel(const WgradG
   // no workgroup has a second item one will do.
   const int min_groups = items > (int)gridDim.x ? 2 : 1;
   int id = blockIdx.x;
-  WgradItem next = wgrad_item(g, id);                  // the item whose steps are being loaded
+  const int starts = group_starts(g);
+  WgradItem next = wgrad_item(g, starts, id);                  // the item whose steps are being loaded
   WgradLoader la, lb;
   la.init(next.A, next.a_bytes, next.lda, wave, lane);
   lb.init(next.B, next.b_bytes, next.ldb, wave, lane);
@@ -1521,7 +1524,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_wgrad_group_kernel(const WgradG
     t = 0;
     next.nk = 0;
     if (id < items) {
-      next = wgrad_item(g, id);
+      next = wgrad_item(g, starts, id);
       la.init(next.A, next.a_bytes, next.lda, wave, lane);
       lb.init(next.B, next.b_bytes, next.ldb, wave, lane);
     }
@@ -1570,7 +1573,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_wgrad_group_kernel(const WgradG
 // Planes of the cut tiles added in range order: 16 workgroups per tile, 16 rows each.
 __global__ __launch_bounds__(256) void wgrad_group_finish_kernel(const WgradGroup g, int ranges) {
   const int t = blockIdx.x >> 4, tile = g.full + t;
-  const int i = group_index(g, tile);
+  const int i = group_index(group_starts(g), tile);
   const WgradProblem& p = g.p[i];
   int tm, tn;
   tile_coords(tile - g.start[i], p.tiles_m, p.tiles_n, tm, tn);
@@ -1636,7 +1639,7 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma_wgrad_group_mid_kernel(const
   __shared__ __attribute__((aligned(1024))) char stage1[2 * MTILE];
   __shared__ __attribute__((aligned(1024))) char stage2[2 * MTILE];
   __shared__ __attribute__((aligned(1024))) char stage3[2 * MTILE];
-  const int i = group_index(g, blockIdx.x);
+  const int i = group_index(group_starts(g), blockIdx.x);
   const WgradProblem& p = g.p[i];
   int tm, tn;
   tile_coords(blockIdx.x - g.start[i], p.tiles_m, p.tiles_n, tm, tn);
@@ -1703,7 +1706,7 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma_wgrad_group_mid_kernel(const
 
 // The same list with 64 x 64 tiles (tile counts and starts are those of the small kernel).
 __global__ __launch_bounds__(SMALL_NW * 64) void gemm_mfma_wgrad_group_small_kernel(const WgradGroup g) {
-  const int i = group_index(g, blockIdx.x);
+  const int i = group_index(group_starts(g), blockIdx.x);
   const WgradProblem& p = g.p[i];
   int tm, tn;
   tile_coords(blockIdx.x - g.start[i], p.tiles_m, p.tiles_n, tm, tn);

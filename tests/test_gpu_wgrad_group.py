@@ -66,6 +66,10 @@ LISTS = [
     ([(2376, 3176), (4096, 2056), (1032, 6152)], 131, None, dict(full=399, tail=0, ranges=1)),
     ([(2376, 3176), (4096, 2056), (1032, 6152)], 257, None, dict(full=399, tail=0, ranges=1)),
     ([(2376, 3176), (4096, 2056), (1032, 6152)], 384, None, dict(full=399, tail=0, ranges=1)),
+    # the most products a launch takes, of unequal tile counts, in each tile size
+    ([(72, 136), (136, 72)] * 16, 97, None, dict(full=192, tail=0, ranges=0)),
+    ([(136, 264), (264, 8)] * 16, 300, None, dict(full=144, tail=0, ranges=-1)),
+    ([(520, 776), (8, 264)] * 16, 97, None, dict(full=224, tail=0, ranges=1)),
 ]
 
 
