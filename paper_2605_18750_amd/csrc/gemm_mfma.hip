@@ -1421,17 +1421,20 @@ struct WgradLoader {
 };
 
 // A workgroup per CU walks the items blockIdx.x, + gridDim.x, ...  The steps of all its items form one sequence: the first steps of an item
-// are loaded under the last MFMAs of the one before, and its sums go straight from the accumulators to memory, no LDS between, so that
-// the stores drain under the next item's steps.  Four 32 KB buffers hold a group of four steps; an item's steps are padded to whole
-// groups with steps of zeros.  While step s is contracted the loads of step s + 4 go to its own buffer: A's after the barrier in the
+// are loaded under the last MFMAs of the one before, and its sums go straight from the accumulators to memory, no LDS between.  Four
+// 32 KB buffers hold a group of four steps; an item's steps are padded to whole groups with steps of zeros (1.3 us for three of them).
+// While step s is contracted the loads of step s + 4 go to its own buffer: A's after the barrier in the
 // middle of the step (when nobody reads that buffer any more), B's in the first half of step s + 1.  They are waited for in the
 // middle of step s + 3: everything but the 16 loads of the two steps after it that were issued later.
+// The stores of an item overlap little of the next one: the counter holds 63 and retires in order, so behind the 256 stores of a wavefront the
+// first two steps' waits leave at most 56 of them in flight, and the third, whose B was requested after them, none.
 // A is the first operand of the MFMA here: a lane holds one column, and a store instruction writes 128 contiguous bytes of two rows.
 // What bounds it: at K of a few hundred the fp32 output (a CU alone stores a tile in 3.4 us, 256 at once in 11: 6 TB/s) and the operand
 // reads behind the L2s, at K of thousands the matrix pipes at the power limit.  A workgroup per tile, its sums through LDS -> this, inside
 // the stage: 4 layers of hidden 4096 at 256 to 512 tokens 1137 -> 979 us a launch, at 4096 tokens 5368 -> 5191; 8 layers of hidden 1280 at
-// 6272 tokens 1540 -> 1519; 2 layers of hidden 2048 at 3704 tokens 652 -> 616.  Waiting for 16 operations instead of 60 behind the stores
-// of an item (so for nearly all of them) gave half of that.
+// 6272 tokens 1540 -> 1519; 2 layers of hidden 2048 at 3704 tokens 652 -> 616.  Waiting for all but 16 of the loads and stores at every step gave half
+// of that.  Few tokens (us, a workgroup per tile -> two groups an item -> this): hidden 2048 at 32 tokens 36.1 -> 40.6 -> 34.1, 1536 at 64
+// 25.7 -> 29.0 -> 24.5, 4096 at 128 184 -> 165 -> 153; one round of tiles at one step, hidden 1024 at 32, 14.9 -> 15.5 -> 15.7 (the zeros).
 __global__ __launch_bounds__(256) void gemm_mfma_wgrad_group_kernel(const WgradGroup g, int items) {
   __shared__ __attribute__((aligned(1024))) char stage0[DSTAGE];
   __shared__ __attribute__((aligned(1024))) char stage1[DSTAGE];
@@ -1439,8 +1442,6 @@ __global__ __launch_bounds__(256) void gemm_mfma_wgrad_group_kernel(const WgradG
   __shared__ __attribute__((aligned(1024))) char stage3[DSTAGE];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = (wave >> 1) * 128, wn = (wave & 1) * 128;
-  // lgkmcnt(0) and at most 16 (60) loads and stores of the wavefront in flight
-  constexpr int VM_16 = 0x0070 | (16 & 15) | ((16 >> 4) << 14), VM_60 = 0x0070 | (60 & 15) | ((60 >> 4) << 14);
   floatx16 acc[4][4];
   auto clear = [&] {
 #pragma unroll
@@ -1456,17 +1457,20 @@ __global__ __launch_bounds__(256) void gemm_mfma_wgrad_group_kernel(const WgradG
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i], f.b[j], acc[i][j], 0, 0, 0);
   };
-  // An item is contracted in two groups at least, so that its first steps run before the stores of the item before are waited for; where
-  // no workgroup has a second item one will do.
-  const int min_groups = items > (int)gridDim.x ? 2 : 1;
+  // LDS reads, and all but the 16 loads issued last; over_stores: but the 60 loads and stores issued last, for the first two steps of an item,
+  // whose loads precede the stores of the item before
+  auto wait_loads = [](bool over_stores) {
+    if (over_stores) __builtin_amdgcn_s_waitcnt(0x0070 | (60 & 15) | ((60 >> 4) << 14));
+    else __builtin_amdgcn_s_waitcnt(0x0070 | (16 & 15) | ((16 >> 4) << 14));
+  };
   int id = blockIdx.x;
   const int starts = group_starts(g);
-  WgradItem next = wgrad_item(g, starts, id);                  // the item whose steps are being loaded
+  WgradItem next = wgrad_item(g, starts, id);          // the item whose steps are being loaded
   WgradLoader la, lb;
   la.init(next.A, next.a_bytes, next.lda, wave, lane);
   lb.init(next.B, next.b_bytes, next.ldb, wave, lane);
   float* C = next.C;                                   // of the item that is being contracted
-  int ldc = next.ldc, rows = next.rows, cols = next.cols, groups = max(min_groups, (next.nk + 3) >> 2), t = 0;
+  int ldc = next.ldc, rows = next.rows, cols = next.cols, groups = (next.nk + 3) >> 2, t = 0;
   la.issue(stage0, 0, true, wave);
   lb.issue(stage0 + DTILE, 0, true, wave);
   la.issue(stage1, 1, 1 < next.nk, wave);
@@ -1482,8 +1486,8 @@ __global__ __launch_bounds__(256) void gemm_mfma_wgrad_group_kernel(const WgradG
   load_frags32<4, 4>(fx, stage0, 0, wm, wn, lane);
   load_frags32<4, 4>(fy, stage0, 1, wm, wn, lane);
   multiply(fx);
-#define RRFP_W_FIRST(P, VM, b0, b1)                                                                      \
-  __builtin_amdgcn_s_waitcnt(VM);                                                                        \
+#define RRFP_W_FIRST(P, over_stores, b0, b1)                                                             \
+  wait_loads(over_stores);                                                                               \
   stage_barrier();                                                                                       \
   la.issue(b0, t + (P), t + (P) < next.nk, wave);                                                        \
   load_frags32<4, 4>(fx, b1, 0, wm, wn, lane);                                                           \
@@ -1497,26 +1501,27 @@ __global__ __launch_bounds__(256) void gemm_mfma_wgrad_group_kernel(const WgradG
   interleave_ds_vm_mfma<16, 16, 4>();                                                                    \
   __builtin_amdgcn_sched_barrier(0);
   for (;;) {
+    const bool only = groups == 1;
     if (groups > 1) {   // first four steps: the loads of the next two were issued before the 256 stores of the item before
       t = 4;
-      RRFP_W_FIRST(0, VM_60, stage0, stage1)
+      RRFP_W_FIRST(0, true, stage0, stage1)
       RRFP_W_SECOND(0, stage0, stage1)
-      RRFP_W_FIRST(1, VM_60, stage1, stage2)
+      RRFP_W_FIRST(1, true, stage1, stage2)
       RRFP_W_SECOND(1, stage1, stage2)
-      RRFP_W_FIRST(2, VM_16, stage2, stage3)
+      RRFP_W_FIRST(2, false, stage2, stage3)
       RRFP_W_SECOND(2, stage2, stage3)
-      RRFP_W_FIRST(3, VM_16, stage3, stage0)
+      RRFP_W_FIRST(3, false, stage3, stage0)
       RRFP_W_SECOND(3, stage3, stage0)
     }
     for (; groups > 2; --groups) {
       t += 4;
-      RRFP_W_FIRST(0, VM_16, stage0, stage1)
+      RRFP_W_FIRST(0, false, stage0, stage1)
       RRFP_W_SECOND(0, stage0, stage1)
-      RRFP_W_FIRST(1, VM_16, stage1, stage2)
+      RRFP_W_FIRST(1, false, stage1, stage2)
       RRFP_W_SECOND(1, stage1, stage2)
-      RRFP_W_FIRST(2, VM_16, stage2, stage3)
+      RRFP_W_FIRST(2, false, stage2, stage3)
       RRFP_W_SECOND(2, stage2, stage3)
-      RRFP_W_FIRST(3, VM_16, stage3, stage0)
+      RRFP_W_FIRST(3, false, stage3, stage0)
       RRFP_W_SECOND(3, stage3, stage0)
     }
     // last four steps of the item: their loads are the next item's
@@ -1528,13 +1533,13 @@ __global__ __launch_bounds__(256) void gemm_mfma_wgrad_group_kernel(const WgradG
       la.init(next.A, next.a_bytes, next.lda, wave, lane);
       lb.init(next.B, next.b_bytes, next.ldb, wave, lane);
     }
-    RRFP_W_FIRST(0, VM_16, stage0, stage1)
+    RRFP_W_FIRST(0, only, stage0, stage1)
     RRFP_W_SECOND(0, stage0, stage1)
-    RRFP_W_FIRST(1, VM_16, stage1, stage2)
+    RRFP_W_FIRST(1, only, stage1, stage2)
     RRFP_W_SECOND(1, stage1, stage2)
-    RRFP_W_FIRST(2, VM_16, stage2, stage3)
+    RRFP_W_FIRST(2, false, stage2, stage3)
     RRFP_W_SECOND(2, stage2, stage3)
-    RRFP_W_FIRST(3, VM_16, stage3, stage0)
+    RRFP_W_FIRST(3, false, stage3, stage0)
     int voff[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -1561,7 +1566,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_wgrad_group_kernel(const WgradG
     ldc = next.ldc;
     rows = next.rows;
     cols = next.cols;
-    groups = max(min_groups, (next.nk + 3) >> 2);
+    groups = (next.nk + 3) >> 2;
     clear();
     RRFP_W_SECOND(3, stage3, stage0)
   }

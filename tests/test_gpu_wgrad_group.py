@@ -61,11 +61,15 @@ LISTS = [
     ([(2376, 3176), (3000, 2056), (1032, 6152)], 97, None, dict(full=1324, tail=0, ranges=-1)),
     # one 256-row tile per workgroup, K of one group of four steps
     (_products(4, 512, 8, 2, 64, 1536), 97, None, dict(full=184, tail=0, ranges=1)),
-    # workgroups that walk two tiles, of 1, 5, 9 and 12 steps (a workgroup takes them in groups of four, at least two of them)
+    # workgroups that walk two tiles, of 1, 5, 9 and 12 steps (a workgroup takes them in groups of four)
     ([(2376, 3176), (4096, 2056), (1032, 6152)], 31, None, dict(full=399, tail=0, ranges=1)),
     ([(2376, 3176), (4096, 2056), (1032, 6152)], 131, None, dict(full=399, tail=0, ranges=1)),
     ([(2376, 3176), (4096, 2056), (1032, 6152)], 257, None, dict(full=399, tail=0, ranges=1)),
     ([(2376, 3176), (4096, 2056), (1032, 6152)], 384, None, dict(full=399, tail=0, ranges=1)),
+    # workgroups that walk two and three tiles of a single group: 1, 3 and 4 steps
+    ([(2376, 3176), (4096, 2056), (1032, 6152), (2000, 3384), (3176, 2000)], 32, None, dict(full=615, tail=0, ranges=1)),
+    ([(2376, 3176), (4096, 2056), (1032, 6152), (2000, 3384), (3176, 2000)], 65, None, dict(full=615, tail=0, ranges=1)),
+    ([(2376, 3176), (4096, 2056), (1032, 6152), (2000, 3384), (3176, 2000)], 128, None, dict(full=615, tail=0, ranges=1)),
     # the most products a launch takes, of unequal tile counts, in each tile size
     ([(72, 136), (136, 72)] * 16, 97, None, dict(full=192, tail=0, ranges=0)),
     ([(136, 264), (264, 8)] * 16, 300, None, dict(full=144, tail=0, ranges=-1)),
