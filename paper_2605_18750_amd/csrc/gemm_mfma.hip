@@ -1758,14 +1758,16 @@ hipError_t launch_a_kc(const GemmArgs& g, hipStream_t s) {
 
 // How the group is cut: estimated times as in a_kc_split, 8 us a round of 256-row tiles beyond its k steps.
 // ranges = 0: the small-output kernel, -1: 128 x 128 tiles.  A pure function of the shapes, the device and the scratch.
-// The 128 x 128 tiles are for short contractions: up to 320 tokens while one round of them (two per CU, 3/4 full) replaces 256-row tiles that
-// leave CUs idle or 64 x 64 ones past a round, and up to 128 tokens where the 256-row tiles would need a second round of up to half the CUs.
-// Measured (us; else -> 128 x 128): 2 layers of hidden 512 at 40 / 128 / 300 tokens 12.3 -> 10.4, 12.8 -> 11.8, 17.4 -> 16.2, at 777 26.5 -> 26.2;
-// 4 of hidden 256 13.6 -> 9.0, 14.5 -> 9.5, 18.1 -> 13.1; 1 of hidden 1536 at 40 / 128 27.8 -> 23.9, 29.3 -> 27.4; but 4 of hidden 512 at 40 (736 tiles)
-// 14.9 -> 16.5, 1 of hidden 256 at 40 (192 tiles of 64 x 64) 5.6 -> 7.5.
+// The 128 x 128 tiles are for short contractions.  Up to 320 tokens while one round of them (two per CU, 3/4 full) replaces 256-row tiles that
+// leave CUs idle or 64 x 64 ones past a round.  Measured (us, else -> 128 x 128): 2 layers of hidden 512 at 32 / 128 / 300 tokens 11.6 -> 9.7,
+// 11.9 -> 11.3, 16.2 -> 15.5, 4 of hidden 256 12.3 -> 8.3, 13.3 -> 9.4, 16.8 -> 12.8.  Past 320 it depends on the list: 172 tiles of 128 x 128 still
+// win at 640 (22.0 -> 19.9), 88 lose from 512 on (12.8 -> 13.8), 344 tie.  But 4 of hidden 512 at 40 (736 tiles) 14.9 -> 16.5, 1 of hidden 256
+// at 40 (192 tiles of 64 x 64) 5.6 -> 7.5.  Up to 64 tokens also where the 256-row tiles would need a second round of up to half the CUs: 2 of
+// hidden 1024 at 32 / 64 22.2 -> 21.3, 22.8 -> 23.0, with GELU 24.2 -> 22.2, 24.5 -> 23.1; 8 of hidden 512 24.1 -> 23.4, 24.8 -> 26.7.  From there it loses:
+// at 128 23.6 -> 27.2, 25.0 -> 26.8, 25.9 -> 33.0.
 struct GroupCut { int full, tail, ranges; };
 inline GroupCut wgrad_group_cut(long long t256, long long t128, long long t64, int K, int n_cu, size_t ws_bytes) {
-  if ((K <= 320 && t64 > n_cu && 2 * t128 <= 3 * n_cu) || (K <= 128 && t256 > n_cu && 2 * t256 <= 3 * n_cu)) return GroupCut{(int)t128, 0, -1};
+  if ((K <= 320 && t64 > n_cu && 2 * t128 <= 3 * n_cu) || (K <= 64 && t256 > n_cu && 2 * t256 <= 3 * n_cu)) return GroupCut{(int)t128, 0, -1};
   constexpr float US_STEP = 0.75f, US_ROUND = 8.0f, FINISH_US = 4.0f, PLANE_BYTES_PER_US = 8.0e6f;
   constexpr int MAX_RANGES = 16, MIN_STEPS = 8;
   const int steps = (K + DBK - 1) / DBK, r = (int)(t256 % n_cu);

@@ -58,7 +58,9 @@ LISTS = [
     (_products(2, 504, 8, 2, 64, 1400), 320, None, dict(full=344, tail=0, ranges=-1)),
     (_products(2, 504, 8, 2, 64, 1400), 321, None, dict(full=88, tail=0, ranges=1)),
     (_products(2, 504, 8, 2, 64, 1400), 100, None, dict(full=344, tail=0, ranges=-1)),
-    ([(2376, 3176), (3000, 2056), (1032, 6152)], 97, None, dict(full=1324, tail=0, ranges=-1)),
+    ([(2376, 3176), (3000, 2056), (1032, 6152)], 64, None, dict(full=1324, tail=0, ranges=-1)),
+    ([(2376, 3176), (3000, 2056), (1032, 6152)], 65, None, dict(full=363, tail=0, ranges=1)),
+    ([(2376, 3176), (3000, 2056), (1032, 6152)], 97, None, dict(full=363, tail=0, ranges=1)),
     # one 256-row tile per workgroup, K of one group of four steps
     (_products(4, 512, 8, 2, 64, 1536), 97, None, dict(full=184, tail=0, ranges=1)),
     # workgroups that walk two tiles, of 1, 5, 9 and 12 steps (a workgroup takes them in groups of four)
