@@ -88,6 +88,13 @@ int rrfp_wgrad_group(int n, const void* const* A, const void* const* B, void* co
  * n_kv_heads. */
 int rrfp_attn_dkv_subsets(int n_q_heads, int n_kv_heads, int n_kv_tiles, int n_cu);
 
+/* Which attention kernels a microbatch of the segments cu_seqlens_host [n_segments + 1] takes (as stage_F; causal 0 or 1, dtype =
+ * STAGE_DTYPE_*).  Pure host logic.  out[0] forward, out[1] dK/dV, out[2] dQ: 0 = tiles whose wavefronts walk the whole other side,
+ * 1 = small tiles with the other side dealt to the wavefronts.  The two add in another order, each always in the same one; the
+ * choice depends on the segments, the sizes and n_cu alone.  STAGE_EINVAL for NULL, non-positive or unsupported arguments. */
+int rrfp_attn_plan(const int32_t* cu_seqlens_host, int n_segments, int n_q_heads, int n_kv_heads, int head_dim, int causal, int dtype,
+                   int n_cu, int32_t out[3]);
+
 /* ---- HBM-bound kernels of the tasks, one by one (steps a1, a10 and a13 of the F and B tasks and of the
  * gradient reduction; paper Section 3.1 for the tasks, Section 7.1 for the requirement that the result must
  * not depend on the order tasks ran in, which is why every sum here has one fixed order). ---------------- */

@@ -71,6 +71,8 @@ def lib() -> C.CDLL:
         L.stage_scratch_bytes.restype = C.c_int
         L.rrfp_attn_dkv_subsets.argtypes = [C.c_int] * 4
         L.rrfp_attn_dkv_subsets.restype = C.c_int
+        L.rrfp_attn_plan.argtypes = [C.POINTER(C.c_int32)] + [C.c_int] * 7 + [C.POINTER(C.c_int32)]
+        L.rrfp_attn_plan.restype = C.c_int
         L.rrfp_rmsnorm_fwd.argtypes = [vp, vp, vp, vp, C.c_int, C.c_int, C.c_float, C.c_int, vp]
         L.rrfp_rmsnorm_fwd.restype = C.c_int
         L.rrfp_rmsnorm_bwd_rows.argtypes = [C.c_int] * 4
@@ -208,6 +210,16 @@ def rrfp_attn_dkv_subsets(n_q_heads, n_kv_heads, n_kv_tiles, n_cu=256):
     if rc < 1:
         raise StageError(rc, "rrfp_attn_dkv_subsets rejected its arguments")
     return rc
+
+
+def rrfp_attn_plan(cu_seqlens, n_q_heads, n_kv_heads, head_dim, causal, dtype, n_cu=256):
+    """Which of the forward, dK/dV and dQ kernels deal the other side's rows to the wavefronts of a small tile (pure host logic)."""
+    cu = (C.c_int32 * len(cu_seqlens))(*cu_seqlens)
+    out = (C.c_int32 * 3)()
+    rc = lib().rrfp_attn_plan(cu, len(cu_seqlens) - 1, n_q_heads, n_kv_heads, head_dim, causal, dtype, n_cu, out)
+    if rc != STAGE_OK:
+        raise StageError(rc, "rrfp_attn_plan rejected its arguments")
+    return dict(zip(("forward", "dkv", "dq"), (bool(v) for v in out)))
 
 
 def rrfp_gemm_plan(M, N, K, trans_a, trans_b, out_dtype, n_cu=256, have_scratch=False, lda=None, ldb=None, ldc=None, workspace_bytes=None):

@@ -15,10 +15,12 @@
 // still spread over the chip: heads in grid x (sub-tiles there and heads in y were 2.5 % slower on an iteration of a 16-head
 // stage at 1024 tokens), sub-tiles in y and, past 65535 of them (many segments of a few tokens), in z.  Bound by the fp32 matrix rate (157
 // TFLOP/s) once the sequences are long enough, by the
-// latency of the key loop before that, where the split kernels below take over (see split_streams for both at each size).  16 query
+// latency of the key loop before that, where the split kernels below take over (see attn_f32_plan for both at each size).  16 query
 // heads of 64, T = 2048: forward 155 us, dQ 189, dK/dV 248.
 // No atomics: sums run over ascending steps; with grouped heads every query head leaves its own dK, dV plane and the
 // planes are added in head order.
+#include <algorithm>
+
 #include "kernels.h"
 #include "numeric.h"
 
@@ -102,13 +104,13 @@ __device__ __forceinline__ void cols_times_scores(f32x4v (&out)[F32Cfg<D>::NS], 
 }
 
 struct SubTile { int r0, r1, s0, s1; };
-// Sub-tile of `rows` rows; r0 >= r1: nothing to do.
-__device__ __forceinline__ SubTile sub_tile(const AttnTile* __restrict__ tiles, int n_tiles, int per_tile, int rows = SUB) {
+// Sub-tile of SUB rows; r0 >= r1: nothing to do.
+__device__ __forceinline__ SubTile sub_tile(const AttnTile* __restrict__ tiles, int n_tiles, int per_tile) {
   const int i = (int)(blockIdx.z * gridDim.y + blockIdx.y);
   if (i >= n_tiles * per_tile) return SubTile{0, 0, 0, 0};
   const AttnTile t = tiles[i / per_tile];
-  const int r0 = t.r0 + i % per_tile * rows;
-  return SubTile{r0, min(r0 + rows, t.r1), t.s0, t.s1};
+  const int r0 = t.r0 + i % per_tile * SUB;
+  return SubTile{r0, min(r0 + SUB, t.r1), t.s0, t.s1};
 }
 
 // ------------------------------------------------------------------------- forward
@@ -366,6 +368,17 @@ __global__ __launch_bounds__(256) void attn_dkv_f32_kernel(const float* __restri
 // memory (no LDS, no barrier in the walk); their sums meet in LDS and are added in wavefront order.
 constexpr int SPLIT = 8, ROWS = 16;                     // wavefronts of a workgroup; rows it owns
 
+// Sub-tile of ROWS rows; per_tile of them are launched for each tile: as many as the longest segment has (r0 >= r1: nothing to do).  Every
+// tile starts at another one: with few heads a sub-tile's place in its tile would decide its XCD, and segments that end early would
+// leave some of them without work.
+__device__ __forceinline__ SubTile split_tile(const AttnTile* __restrict__ tiles, int n_tiles, int per_tile) {
+  const int i = (int)(blockIdx.z * gridDim.y + blockIdx.y), tile = i / per_tile;
+  if (tile >= n_tiles) return SubTile{0, 0, 0, 0};
+  const AttnTile t = tiles[tile];
+  const int r0 = t.r0 + (i + tile) % per_tile * ROWS;
+  return SubTile{r0, min(r0 + ROWS, t.r1), t.s0, t.s1};
+}
+
 // Block of 16 rows at row0 of a [*, ld] tensor, rows at or past row_end repeat row_end - 1.  Rows: lane l has row l & 15, the values
 // 16 s + 4 (l >> 4) .. + 3 of slice s.  Columns: lane l has value 16 db + (l & 15) of row 4 (l >> 4) + r.
 template <int D>
@@ -422,12 +435,12 @@ __device__ __forceinline__ f32x4v get_sum(const float* area, int row, int c, con
 
 template <int D>
 __global__ __launch_bounds__(64 * SPLIT) void attn_fwd_f32_split_kernel(const float* __restrict__ qkv, float* __restrict__ o, float* __restrict__ lse,
-                                                                        const AttnTile* __restrict__ tiles, int n_tiles, int Tn, int nq, int nkv,
+                                                                        const AttnTile* __restrict__ tiles, int n_tiles, int per_tile, int Tn, int nq, int nkv,
                                                                         int causal) {
   constexpr int NS = F32Cfg<D>::NS;
   __shared__ __attribute__((aligned(16))) float area[SPLIT * ROWS * F32Cfg<D>::PITCH];
   __shared__ float ms[SPLIT * ROWS], ls[SPLIT * ROWS];
-  const SubTile tl = sub_tile(tiles, n_tiles, ATTN_TILE_Q / ROWS, ROWS);
+  const SubTile tl = split_tile(tiles, n_tiles, per_tile);
   if (tl.r0 >= tl.r1) return;
   const int a = blockIdx.x, b = a / (nq / nkv);
   const int ld = (nq + 2 * nkv) * D;
@@ -502,11 +515,11 @@ __global__ __launch_bounds__(64 * SPLIT) void attn_fwd_f32_split_kernel(const fl
 template <int D>
 __global__ __launch_bounds__(64 * SPLIT) void attn_dq_f32_split_kernel(const float* __restrict__ qkv, const float* __restrict__ d_o,
                                                                        const float* __restrict__ lse, const float* __restrict__ delta,
-                                                                       float* __restrict__ dqkv, const AttnTile* __restrict__ tiles, int n_tiles,
+                                                                       float* __restrict__ dqkv, const AttnTile* __restrict__ tiles, int n_tiles, int per_tile,
                                                                        int Tn, int nq, int nkv, int causal) {
   constexpr int NS = F32Cfg<D>::NS;
   __shared__ __attribute__((aligned(16))) float area[SPLIT * ROWS * F32Cfg<D>::PITCH];
-  const SubTile tl = sub_tile(tiles, n_tiles, ATTN_TILE_Q / ROWS, ROWS);
+  const SubTile tl = split_tile(tiles, n_tiles, per_tile);
   if (tl.r0 >= tl.r1) return;
   const int a = blockIdx.x, b = a / (nq / nkv);
   const int ld = (nq + 2 * nkv) * D;
@@ -548,11 +561,11 @@ __global__ __launch_bounds__(64 * SPLIT) void attn_dq_f32_split_kernel(const flo
 template <int D>
 __global__ __launch_bounds__(64 * SPLIT) void attn_dkv_f32_split_kernel(const float* __restrict__ qkv, const float* __restrict__ d_o,
                                                                         const float* __restrict__ lse, const float* __restrict__ delta,
-                                                                        float* __restrict__ dqkv, const AttnTile* __restrict__ tiles, int n_tiles,
+                                                                        float* __restrict__ dqkv, const AttnTile* __restrict__ tiles, int n_tiles, int per_tile,
                                                                         int Tn, int nq, int nkv, int causal, float* __restrict__ part) {
   constexpr int NS = F32Cfg<D>::NS;
   __shared__ __attribute__((aligned(16))) float area[SPLIT * ROWS * F32Cfg<D>::PITCH];
-  const SubTile tl = sub_tile(tiles, n_tiles, ATTN_TILE_KV / ROWS, ROWS);
+  const SubTile tl = split_tile(tiles, n_tiles, per_tile);
   if (tl.r0 >= tl.r1) return;
   const int a = blockIdx.x, G = nq / nkv, b = a / G;
   const int ld = (nq + 2 * nkv) * D;
@@ -618,43 +631,50 @@ __global__ __launch_bounds__(256) void dkv_combine_f32_kernel(const float* __res
   }
 }
 
+int split_per_tile(const AttnArgs& a, int tile_rows) { return (std::min(a.longest, tile_rows) + ROWS - 1) / ROWS; }
 dim3 sub_tile_grid(int nq, int n) {
   const int z = (n + 65534) / 65535;
   return dim3(nq, (n + z - 1) / z, z);
 }
 
-// Which kernels: below two 64-row sub-tiles of a query head per CU the split ones.  us, 64-row sub-tiles -> split, forward, dK/dV, dQ:
-// 128 rows x 4 heads 12.4 -> 6.7, 15.7 -> 8.2, 12.1 -> 7.0; 517 x 16 35 -> 18, 54 -> 29, 40 -> 21; 1024 x 16 (two segments) 53 -> 31, 75 -> 56,
-// 62 -> 42; 1024 x 8 of 128 105 -> 49, 172 -> 75, 131 -> 62; 2048 x 16 155 -> 121, 248 -> 258, 189 -> 187; 4096 x 16 421 -> 425, 721 -> 935,
-// 543 -> 682 (every block of the other side is read by four times as many workgroups).  32 rows a workgroup: slower up to 1024 x 16.
-bool split_streams(const AttnArgs& a) { return (long long)a.T * a.nq < 2LL * SUB * device_cu_count(); }
-
 template <int D>
 hipError_t fwd_launch(const AttnArgs& a, hipStream_t s) {
-  const bool split = split_streams(a);
-  const auto kernel = split ? attn_fwd_f32_split_kernel<D> : attn_fwd_f32_kernel<D>;
-  hipLaunchKernelGGL(kernel, sub_tile_grid(a.nq, a.n_q_tiles * (ATTN_TILE_Q / (split ? ROWS : SUB))), dim3(split ? 64 * SPLIT : 256), 0, s,
-                     (const float*)a.qkv, (float*)a.o, a.lse, a.q_tiles, a.n_q_tiles, a.T, a.nq, a.nkv, a.causal);
+  if (attn_f32_plan(a, device_cu_count()).fwd) {
+    const int per_tile = split_per_tile(a, ATTN_TILE_Q);
+    hipLaunchKernelGGL(attn_fwd_f32_split_kernel<D>, sub_tile_grid(a.nq, a.n_q_tiles * per_tile), dim3(64 * SPLIT), 0, s, (const float*)a.qkv,
+                       (float*)a.o, a.lse, a.q_tiles, a.n_q_tiles, per_tile, a.T, a.nq, a.nkv, a.causal);
+  } else {
+    hipLaunchKernelGGL(attn_fwd_f32_kernel<D>, sub_tile_grid(a.nq, a.n_q_tiles * (ATTN_TILE_Q / SUB)), dim3(256), 0, s, (const float*)a.qkv,
+                       (float*)a.o, a.lse, a.q_tiles, a.n_q_tiles, a.T, a.nq, a.nkv, a.causal);
+  }
   return hipGetLastError();
 }
 
 template <int D>
 hipError_t bwd_launch(const AttnArgs& a, hipStream_t s) {
   float* part = a.nq > a.nkv ? a.dkv_part : nullptr;
-  const bool split = split_streams(a);
-  const dim3 threads(split ? 64 * SPLIT : 256);
-  const int rows = split ? ROWS : SUB;
+  const AttnPlan plan = attn_f32_plan(a, device_cu_count());
   hipLaunchKernelGGL(attn_delta_f32_kernel, dim3((a.T * a.nq + 15) / 16), dim3(256), 0, s, (const float*)a.o, (const float*)a.d_o, a.delta, a.T,
                      a.nq, a.d);
-  const auto dkv = split ? attn_dkv_f32_split_kernel<D> : attn_dkv_f32_kernel<D>;
-  hipLaunchKernelGGL(dkv, sub_tile_grid(a.nq, a.n_kv_tiles * (ATTN_TILE_KV / rows)), threads, 0, s, (const float*)a.qkv,
-                     (const float*)a.d_o, a.lse, a.delta, (float*)a.dqkv, a.kv_tiles, a.n_kv_tiles, a.T, a.nq, a.nkv, a.causal, part);
+  if (plan.dkv) {
+    const int per_tile = split_per_tile(a, ATTN_TILE_KV);
+    hipLaunchKernelGGL(attn_dkv_f32_split_kernel<D>, sub_tile_grid(a.nq, a.n_kv_tiles * per_tile), dim3(64 * SPLIT), 0, s, (const float*)a.qkv,
+                       (const float*)a.d_o, a.lse, a.delta, (float*)a.dqkv, a.kv_tiles, a.n_kv_tiles, per_tile, a.T, a.nq, a.nkv, a.causal, part);
+  } else {
+    hipLaunchKernelGGL(attn_dkv_f32_kernel<D>, sub_tile_grid(a.nq, a.n_kv_tiles * (ATTN_TILE_KV / SUB)), dim3(256), 0, s, (const float*)a.qkv,
+                       (const float*)a.d_o, a.lse, a.delta, (float*)a.dqkv, a.kv_tiles, a.n_kv_tiles, a.T, a.nq, a.nkv, a.causal, part);
+  }
   if (part)
     hipLaunchKernelGGL(dkv_combine_f32_kernel, dim3((unsigned)(((size_t)a.T * a.nkv * D / 4 + 255) / 256)), dim3(256), 0, s, part,
                        (float*)a.dqkv, a.T, a.nq, a.nkv, D, 1.0f / sqrtf((float)D));
-  const auto dq = split ? attn_dq_f32_split_kernel<D> : attn_dq_f32_kernel<D>;
-  hipLaunchKernelGGL(dq, sub_tile_grid(a.nq, a.n_q_tiles * (ATTN_TILE_Q / rows)), threads, 0, s, (const float*)a.qkv,
-                     (const float*)a.d_o, a.lse, a.delta, (float*)a.dqkv, a.q_tiles, a.n_q_tiles, a.T, a.nq, a.nkv, a.causal);
+  if (plan.dq) {
+    const int per_tile = split_per_tile(a, ATTN_TILE_Q);
+    hipLaunchKernelGGL(attn_dq_f32_split_kernel<D>, sub_tile_grid(a.nq, a.n_q_tiles * per_tile), dim3(64 * SPLIT), 0, s, (const float*)a.qkv,
+                       (const float*)a.d_o, a.lse, a.delta, (float*)a.dqkv, a.q_tiles, a.n_q_tiles, per_tile, a.T, a.nq, a.nkv, a.causal);
+  } else {
+    hipLaunchKernelGGL(attn_dq_f32_kernel<D>, sub_tile_grid(a.nq, a.n_q_tiles * (ATTN_TILE_Q / SUB)), dim3(256), 0, s, (const float*)a.qkv,
+                       (const float*)a.d_o, a.lse, a.delta, (float*)a.dqkv, a.q_tiles, a.n_q_tiles, a.T, a.nq, a.nkv, a.causal);
+  }
   return hipGetLastError();
 }
 
@@ -672,6 +692,21 @@ hipError_t bwd_launch(const AttnArgs& a, hipStream_t s) {
     case 128: return CALL<128>(a, s); \
     default: return hipErrorInvalidValue; \
   }
+
+// Where the split kernels are launched (attn_deal; measured below two 64-row sub-tiles of a query head per CU, and kept from there on
+// where the tiled ones win: 2048 x 16 heads 248 -> 258 us in dK/dV, 4096 x 16 543 -> 682 in dQ).  A bidirectional row counts twice,
+// in the forward also a row of more than 64 columns, whose sums leave a CU two workgroups instead of four.  us, tiled -> split, forward, dK/dV,
+// dQ, in brackets where it is not launched; 16 heads of 64, causal, rows in segments of one length: 1269 of 1024 69.6 -> 42.4, 102.4 -> 84.4, 82.6 -> 57.2;
+// 1024 of 512 34.5 -> 25.7, 51.6 -> 49.1, 39.6 -> 35.0; of 256 19.4 -> 20.3, (28.8 -> 34.9), (21.5 -> 25.2); of 128 16.5 -> 14.6, (17.9 -> 25.5), (18.9 -> 17.1);
+// 614 of 128 15.1 -> 10.5, (16.7 -> 18.8), 18.8 -> 12.3; 409 of 32 7.1 -> 6.4, 9.2 -> 9.6, 8.5 -> 6.1; 1986 of 512 41.6 -> 42.6, (66.6 -> 88.6), (49.8 -> 60.1).
+// 4 heads of 128, bidirectional: 983 of 128 17.6 -> 12.0, 28.2 -> 16.5, 20.7 -> 11.3; 3276 of 512 (56.5 -> 69.4), (93.5 -> 117.5), (70.4 -> 89.1); 7946 of 32
+// 54 -> 38, (75 -> 59), 71 -> 47.  32 rows a workgroup: slower up to 1024 x 16.
+AttnPlan attn_f32_plan(const AttnArgs& a, int n_cu) {
+  if ((long long)a.T * a.nq >= 2LL * SUB * n_cu) return AttnPlan{false, false, false};
+  const float both = a.causal ? 1.0f : 2.0f, wide = a.d > 64 ? 2.0f : 1.0f;
+  return AttnPlan{attn_deal(a, n_cu, AttnLine{64.f, 4.0f, 64}, both * wide, ROWS), attn_deal(a, n_cu, AttnLine{28.f, 2.5f, 16}, both, ROWS),
+                  attn_deal(a, n_cu, AttnLine{48.f, 1.5f, 64}, both, ROWS)};
+}
 
 hipError_t launch_attn_fwd_f32(const AttnArgs& a, hipStream_t s) {
   if (a.dtype != F32 || a.n_q_tiles < 1) return hipErrorInvalidValue;

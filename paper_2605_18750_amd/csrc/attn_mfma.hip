@@ -724,13 +724,6 @@ inline int attn_cu_count() {
   return cached[dev];
 }
 
-// Which kernels: up to 64 rows of a query head per CU the ones of attn_mfma_split.hip, dK/dV only for heads of 64 (wider ones need
-// so many registers that a CU holds four wavefronts) and with the query heads of a group dealt as far as the partial planes allow.  us, the
-// kernels here -> split, forward, dK/dV, dQ: 100 rows x 8 heads of 64 7.3 -> 5.4, 9.8 -> 7.0, 4.9 -> 3.6; 777 x 8 15.6 -> 9.2, 18.4 -> 13.4,
-// 11.5 -> 4.6; 2048 x 8 41 -> 30, 47 -> 38, 33 -> 16; 512 x 32 of 128 23.5 -> 19.8, (26.5 -> 30.6), 14.4 -> 9.6; 784 x 16 of 80, bidirectional
-// 25.8 -> 25.7, (40 -> 39), 19.8 -> 13.4; but 1024 x 32 of 128 38 -> 45, 26.4 -> 23.8 and 2352 x 16 of 80 30 -> 61, 23 -> 32.
-bool split_streams(const AttnArgs& a) { return (long long)a.T * a.nq <= 64LL * attn_cu_count(); }
-
 template <int D>
 hipError_t bwd_launch(const AttnArgs& a, hipStream_t s) {
   auto kkv = attn_dkv_mfma_kernel<D>;
@@ -740,9 +733,9 @@ hipError_t bwd_launch(const AttnArgs& a, hipStream_t s) {
   const float scale = 1.0f / sqrtf((float)D);
   hipLaunchKernelGGL(attn_delta_mfma_kernel<D>, dim3((a.T * a.nq + 15) / 16), dim3(256), 0, s, (const bf16_t*)a.o,
                      a.o32, (const el_t*)a.d_o, a.delta, a.T, a.nq);
-  const bool split = split_streams(a), split_dkv = split && D == 64;
-  const int n_sub = a.dkv_part ? attn_dkv_subsets(a.nq, a.nkv, split_dkv ? 1 : a.n_kv_tiles, split_dkv ? 1 << 30 : attn_cu_count()) : 1;
-  if (split_dkv) {
+  const AttnPlan plan = attn_mfma_plan(a, attn_cu_count());
+  const int n_sub = a.dkv_part ? attn_dkv_subsets(a.nq, a.nkv, plan.dkv ? 1 : a.n_kv_tiles, plan.dkv ? 1 << 30 : attn_cu_count()) : 1;
+  if (plan.dkv) {
     if (hipError_t e = launch_attn_dkv_split(a, n_sub, s); e != hipSuccess) return e;
   } else hipLaunchKernelGGL(kkv, dim3(a.nkv * n_sub, a.n_kv_tiles), dim3(256), DkvCfg<D>::SMEM, s, (const el_t*)a.qkv,
                      (const el_t*)a.d_o, a.lse, a.delta, (bf16_t*)a.dqkv, a.kv_tiles, a.T, a.nq, a.nkv, a.causal, scale, a.grad_scale,
@@ -754,7 +747,7 @@ hipError_t bwd_launch(const AttnArgs& a, hipStream_t s) {
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return split ? launch_attn_dq_split(a, s) : launch_attn_dq_mfma(a, s);
+  return plan.dq ? launch_attn_dq_split(a, s) : launch_attn_dq_mfma(a, s);
 }
 
 template <int D>
@@ -773,13 +766,32 @@ hipError_t fwd_launch(const AttnArgs& a, hipStream_t s) {
 
 }  // namespace
 
+// Where the kernels of attn_mfma_split.hip are launched (attn_deal; measured up to 64 rows of a query head per CU: 1024 x 32 heads of 128 38 -> 45 us
+// in the forward; dQ still wins there, 26.4 -> 23.8, and loses at 2352 x 16 of 80, 23 -> 32).  dK/dV only for heads of 64 (wider ones need so
+// many registers that a CU holds four wavefronts: 26.5 -> 30.6 for 512 x 32 of 128), where dQ is split too, since the tiled dQ reads blocks of dS
+// that only the tiled dK/dV writes, and with the query heads of a group dealt as far as the partial planes allow.  A bidirectional row
+// counts half as much again; heads of 80, of which the LDS holds one workgroup a CU, as well, in dQ twice.  us, kernels here -> split,
+// forward, dK/dV, dQ, in brackets where not launched; 8 heads of 64, causal, rows in segments of one length: 1024 of 1024 23.5 -> 13.7, 26.5 -> 19.2, 17.2 -> 7.4; 1986 of 1024 24.1 -> 17.9, 28.2 -> 26.1, 17.9 -> 9.3;
+// 1986 of 512 15.6 -> 13.0, (18.6 -> 20.4), 11.9 -> 5.9; 1536 of 128 (7.3 -> 7.8), (11.1 -> 14.4), 4.6 -> 5.0; 819 of 128 6.6 -> 6.4, 10.4 -> 8.1, 5.0 -> 4.1;
+// 245 of 32 5.2 -> 4.8, 6.9 -> 7.2, 3.9 -> 3.4.  8 of 80, bidirectional, forward and dQ: 1024 of 1024 27.9 -> 15.8, 22.4 -> 10.2; 1536 of 256 (13.1 -> 14.8),
+// (8.3 -> 8.3); 1986 of 32 12.6 -> 11.6, 8.0 -> 6.2.  32 of 128: 496 of 256 (17.2 -> 15.6), 8.3 -> 7.6; 384 of 128, bidirectional, (9.8 -> 12.7), 5.9 -> 5.6; 384 of
+// 32 14.6 -> 7.2, 8.6 -> 4.4.
+AttnPlan attn_mfma_plan(const AttnArgs& a, int n_cu) {
+  if ((long long)a.T * a.nq > 64LL * n_cu) return AttnPlan{false, false, false};
+  const float both = a.causal ? 1.0f : 1.5f;
+  const bool alone = a.d == 80;                         // one workgroup a CU
+  const bool dq = attn_deal(a, n_cu, AttnLine{64.f, 3.0f, 32}, alone ? 2.0f : 1.0f, 32);
+  return AttnPlan{attn_deal(a, n_cu, AttnLine{28.f, 2.5f, 32}, both * (alone ? 1.5f : 1.0f), 32),
+                  a.d == 64 && dq && attn_deal(a, n_cu, AttnLine{28.f, 1.5f, 0}, both, 32), dq};
+}
+
 bool attn_mfma_supports(const AttnArgs& a) {
   return a.dtype == BF16 && (a.d == 64 || a.d == 80 || a.d == 128) && a.n_q_tiles >= 1;
 }
 
 hipError_t launch_attn_fwd_mfma(const AttnArgs& a, hipStream_t s) {
   if (!attn_mfma_supports(a)) return hipErrorInvalidValue;
-  if (split_streams(a)) return launch_attn_fwd_split(a, s);
+  if (attn_mfma_plan(a, attn_cu_count()).fwd) return launch_attn_fwd_split(a, s);
   if (a.d == 64) return fwd_launch<64>(a, s);
   if (a.d == 80) return fwd_launch<80>(a, s);
   return fwd_launch<128>(a, s);

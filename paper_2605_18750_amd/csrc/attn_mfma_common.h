@@ -12,6 +12,7 @@
 #include "kernels.h"
 #include "numeric.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace rrfp {

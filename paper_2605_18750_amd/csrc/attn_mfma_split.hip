@@ -1,4 +1,4 @@
-// MFMA attention for grids that leave CUs idle (the rule and both sides' times: split_streams in attn_mfma.hip): the same products, types and roundings as
+// MFMA attention for grids that leave CUs idle (the rule and both sides' times: attn_mfma_plan): the same products, types and roundings as
 // attn_mfma.hip and attn_mfma_dq.hip, but a workgroup owns 32 rows and its wavefronts take the 32-row blocks of the other side in turn,
 // without a barrier in the walk; their sums meet in LDS and are added in wavefront order.  With few rows and heads the time of
 // the other kernels is one wavefront's serial walk over the whole other side behind a barrier per step (2 us per 64 keys in the
@@ -69,18 +69,22 @@ __device__ __forceinline__ float4 sums_get(const char* smem, int row, int c, con
 }
 __device__ __forceinline__ uint2 pack_bf16x4(float4 v) { return make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w)); }
 
-// Sub-tile of 32 rows, the last rows of a tile first (under a causal mask they have the longest walk).
+// Sub-tile of 32 rows; per_tile of them are launched for each tile: as many as the longest segment has (r0 >= r1: nothing to do).  The last
+// rows of a tile first (under a causal mask they have the longest walk), from another start in every tile: with few heads a
+// sub-tile's place in its tile would decide its XCD, and segments that end early would leave some of them without work.
 __device__ __forceinline__ AttnTile split_tile(const AttnTile* __restrict__ tiles, int i, int per_tile) {
-  AttnTile t = tiles[i / per_tile];
-  t.r0 += (per_tile - 1 - i % per_tile) * 32;
+  const int tile = i / per_tile;
+  AttnTile t = tiles[tile];
+  t.r0 += (per_tile - 1 - i % per_tile + tile) % per_tile * 32;
   t.r1 = min(t.r1, t.r0 + 32);
   return t;
 }
+int split_per_tile(const AttnArgs& a, int tile_rows) { return (std::min(a.longest, tile_rows) + 31) / 32; }
 
 template <int D>
 __global__ __launch_bounds__(64 * SplitCfg<D>::NW, 2) void attn_fwd_split_kernel(const el_t* __restrict__ qkv, bf16_t* __restrict__ o,
                                                                              float* __restrict__ o32, el_t* __restrict__ o16,
-                                                                             float* __restrict__ lse, const AttnTile* __restrict__ tiles, int Tn,
+                                                                             float* __restrict__ lse, const AttnTile* __restrict__ tiles, int per_tile, int Tn,
                                                                              int nq, int nkv, int causal, float scale_log2e) {
   using C = SplitCfg<D>;
   constexpr int NDS = C::NDS, NDB = C::NDB, NW = C::NW, AREA = C::area(C::TILE);
@@ -88,7 +92,7 @@ __global__ __launch_bounds__(64 * SplitCfg<D>::NW, 2) void attn_fwd_split_kernel
   float* const ms = reinterpret_cast<float*>(smem + NW * AREA);
   float* const ls = ms + NW * 32;
   const int a = blockIdx.x % nq, b = a / (nq / nkv);
-  const AttnTile tl = split_tile(tiles, blockIdx.x / nq, ATTN_TILE_Q / 32);
+  const AttnTile tl = split_tile(tiles, blockIdx.x / nq, per_tile);
   if (tl.r0 >= tl.r1) return;
   const int ld = (nq + 2 * nkv) * D;
   const el_t *kp = qkv + (nq + b) * D, *vp = qkv + (nq + nkv + b) * D;
@@ -192,7 +196,7 @@ __global__ __launch_bounds__(64 * SplitCfg<D>::NW, 2) void attn_fwd_split_kernel
 template <int D>
 __global__ __launch_bounds__(64 * SplitCfg<D>::NW) void attn_dkv_split_kernel(const el_t* __restrict__ qkv, const el_t* __restrict__ d_o,
                                                                              const float* __restrict__ lse, const float* __restrict__ delta,
-                                                                             bf16_t* __restrict__ dqkv, const AttnTile* __restrict__ tiles, int Tn,
+                                                                             bf16_t* __restrict__ dqkv, const AttnTile* __restrict__ tiles, int per_tile, int Tn,
                                                                              int nq, int nkv, int causal, float scale,
                                                                              const float* __restrict__ grad_scale, el_t* __restrict__ ds,
                                                                              int ds_rows, int ds_nqs, int n_sub, float* __restrict__ part) {
@@ -202,7 +206,7 @@ __global__ __launch_bounds__(64 * SplitCfg<D>::NW) void attn_dkv_split_kernel(co
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int heads = nkv * n_sub, b = blockIdx.x % heads / n_sub, sub = blockIdx.x % heads % n_sub;
   const int G = nq / nkv / n_sub, a0 = b * (nq / nkv) + sub * G;
-  const AttnTile tl = split_tile(tiles, blockIdx.x / heads, ATTN_TILE_KV / 32);
+  const AttnTile tl = split_tile(tiles, blockIdx.x / heads, per_tile);
   if (tl.r0 >= tl.r1) return;
   const int ld = (nq + 2 * nkv) * D;
   const int lane = threadIdx.x & 63, h = lane >> 5, li = lane & 31;
@@ -296,7 +300,7 @@ __global__ __launch_bounds__(64 * SplitCfg<D>::NW) void attn_dkv_split_kernel(co
 
 template <int D>
 __global__ __launch_bounds__(64 * SplitCfg<D>::NW) void attn_dq_split_kernel(const el_t* __restrict__ qkv, const el_t* __restrict__ ds,
-                                                                            bf16_t* __restrict__ dqkv, const AttnTile* __restrict__ tiles, int nq,
+                                                                            bf16_t* __restrict__ dqkv, const AttnTile* __restrict__ tiles, int per_tile, int nq,
                                                                             int nkv, int causal, float scale, const float* __restrict__ grad_scale,
                                                                             int ds_rows, int ds_nqs) {
   using C = SplitCfg<D>;
@@ -305,7 +309,7 @@ __global__ __launch_bounds__(64 * SplitCfg<D>::NW) void attn_dq_split_kernel(con
   constexpr int NDS = C::NDS, NDB = C::NDB, NW = C::NW, AREA = C::area(C::TILE + 2 * DS_PAIR);
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int a = blockIdx.x % nq, b = a / (nq / nkv);
-  const AttnTile tl = split_tile(tiles, blockIdx.x / nq, ATTN_TILE_Q / 32);
+  const AttnTile tl = split_tile(tiles, blockIdx.x / nq, per_tile);
   if (tl.r0 >= tl.r1) return;
   const int ld = (nq + 2 * nkv) * D;
   const el_t* kp = qkv + (nq + b) * D;
@@ -368,8 +372,9 @@ hipError_t fwd_launch(const AttnArgs& a, hipStream_t s) {
   static std::once_flag once;
   static hipError_t once_status = hipSuccess;
   if (hipError_t e = set_max_dynamic_lds_once(once, once_status, (const void*)attn_fwd_split_kernel<D>, smem); e != hipSuccess) return e;
-  hipLaunchKernelGGL(attn_fwd_split_kernel<D>, dim3(a.n_q_tiles * (ATTN_TILE_Q / 32) * a.nq), dim3(64 * C::NW), smem, s, (const el_t*)a.qkv,
-                     (bf16_t*)a.o, a.o32, (el_t*)a.o16, a.lse, a.q_tiles, a.T, a.nq, a.nkv, a.causal, 1.4426950408889634f / sqrtf((float)D));
+  const int per_tile = split_per_tile(a, ATTN_TILE_Q);
+  hipLaunchKernelGGL(attn_fwd_split_kernel<D>, dim3(a.n_q_tiles * per_tile * a.nq), dim3(64 * C::NW), smem, s, (const el_t*)a.qkv,
+                     (bf16_t*)a.o, a.o32, (el_t*)a.o16, a.lse, a.q_tiles, per_tile, a.T, a.nq, a.nkv, a.causal, 1.4426950408889634f / sqrtf((float)D));
   return hipGetLastError();
 }
 
@@ -380,8 +385,9 @@ hipError_t dkv_launch(const AttnArgs& a, int n_sub, hipStream_t s) {
   static std::once_flag once;
   static hipError_t once_status = hipSuccess;
   if (hipError_t e = set_max_dynamic_lds_once(once, once_status, (const void*)attn_dkv_split_kernel<D>, smem); e != hipSuccess) return e;
-  hipLaunchKernelGGL(attn_dkv_split_kernel<D>, dim3(a.n_kv_tiles * (ATTN_TILE_KV / 32) * a.nkv * n_sub), dim3(64 * C::NW), smem, s,
-                     (const el_t*)a.qkv, (const el_t*)a.d_o, a.lse, a.delta, (bf16_t*)a.dqkv, a.kv_tiles, a.T, a.nq, a.nkv, a.causal,
+  const int per_tile = split_per_tile(a, ATTN_TILE_KV);
+  hipLaunchKernelGGL(attn_dkv_split_kernel<D>, dim3(a.n_kv_tiles * per_tile * a.nkv * n_sub), dim3(64 * C::NW), smem, s,
+                     (const el_t*)a.qkv, (const el_t*)a.d_o, a.lse, a.delta, (bf16_t*)a.dqkv, a.kv_tiles, per_tile, a.T, a.nq, a.nkv, a.causal,
                      1.0f / sqrtf((float)D), a.grad_scale, (el_t*)a.ds, a.ds_rows, a.ds_nqs, n_sub, a.dkv_part);
   return hipGetLastError();
 }
@@ -393,8 +399,9 @@ hipError_t dq_launch(const AttnArgs& a, hipStream_t s) {
   static std::once_flag once;
   static hipError_t once_status = hipSuccess;
   if (hipError_t e = set_max_dynamic_lds_once(once, once_status, (const void*)attn_dq_split_kernel<D>, smem); e != hipSuccess) return e;
-  hipLaunchKernelGGL(attn_dq_split_kernel<D>, dim3(a.n_q_tiles * (ATTN_TILE_Q / 32) * a.nq), dim3(64 * C::NW), smem, s, (const el_t*)a.qkv,
-                     (const el_t*)a.ds, (bf16_t*)a.dqkv, a.q_tiles, a.nq, a.nkv, a.causal, 1.0f / sqrtf((float)D), a.grad_scale, a.ds_rows, a.ds_nqs);
+  const int per_tile = split_per_tile(a, ATTN_TILE_Q);
+  hipLaunchKernelGGL(attn_dq_split_kernel<D>, dim3(a.n_q_tiles * per_tile * a.nq), dim3(64 * C::NW), smem, s, (const el_t*)a.qkv,
+                     (const el_t*)a.ds, (bf16_t*)a.dqkv, a.q_tiles, per_tile, a.nq, a.nkv, a.causal, 1.0f / sqrtf((float)D), a.grad_scale, a.ds_rows, a.ds_nqs);
   return hipGetLastError();
 }
 

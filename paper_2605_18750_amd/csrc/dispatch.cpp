@@ -64,6 +64,7 @@ size_t wgrad_group_plane_bytes(GemmArgs* g, int n, int max_K, const int* n_cu, i
   }
   return most;
 }
+AttnPlan attn_plan(const AttnArgs& a, int n_cu) { return attn_mfma_supports(a) ? attn_mfma_plan(a, n_cu) : attn_f32_plan(a, n_cu); }
 hipError_t launch_attn_fwd(const AttnArgs& a, hipStream_t s) {
   return attn_mfma_supports(a) ? launch_attn_fwd_mfma(a, s) : launch_attn_fwd_f32(a, s);
 }

@@ -1,5 +1,7 @@
 // Kernel-level C entry points (include/rrfp_kernels.h): thin argument checks around the
 // launchers the stage tasks use.
+#include <algorithm>
+
 #include "../../include/rrfp_kernels.h"
 #include "../../include/rrfp_stage.h"
 #include "kernels.h"
@@ -91,6 +93,24 @@ extern "C" int rrfp_rmsnorm_fwd(const float* x, const void* g, void* h, float* r
 extern "C" int rrfp_attn_dkv_subsets(int n_q_heads, int n_kv_heads, int n_kv_tiles, int n_cu) {
   if (n_q_heads < 1 || n_kv_heads < 1 || n_kv_tiles < 1 || n_cu < 1 || n_q_heads % n_kv_heads) return STAGE_EINVAL;
   return attn_dkv_subsets(n_q_heads, n_kv_heads, n_kv_tiles, n_cu);
+}
+
+extern "C" int rrfp_attn_plan(const int32_t* cu, int n_seg, int n_q_heads, int n_kv_heads, int head_dim, int causal, int dtype, int n_cu,
+                              int32_t out[3]) {
+  if (!cu || !out || n_seg < 1 || n_q_heads < 1 || n_kv_heads < 1 || n_q_heads % n_kv_heads || n_cu < 1 || cu[0] != 0) return STAGE_EINVAL;
+  if ((causal != 0 && causal != 1) || (dtype != F32 && dtype != BF16)) return STAGE_EINVAL;
+  if (dtype == BF16 ? head_dim != 64 && head_dim != 80 && head_dim != 128 : head_dim < 16 || head_dim > 128 || head_dim % 16) return STAGE_EINVAL;
+  AttnArgs a{};
+  for (int s = 0; s < n_seg; ++s) {
+    const int n = cu[s + 1] - cu[s];
+    if (n < 1) return STAGE_EINVAL;
+    a.n_q_tiles += (n - 1) / ATTN_TILE_Q + 1;
+    a.longest = std::max(a.longest, n);
+  }
+  a.T = cu[n_seg]; a.nq = n_q_heads; a.nkv = n_kv_heads; a.d = head_dim; a.causal = causal; a.dtype = dtype;
+  const AttnPlan p = attn_plan(a, n_cu);
+  out[0] = p.fwd; out[1] = p.dkv; out[2] = p.dq;
+  return STAGE_OK;
 }
 
 extern "C" int rrfp_rmsnorm_bwd_rows(int T, int H, int dtype, int n_cu) {

@@ -99,6 +99,7 @@ struct AttnArgs {
   const AttnTile* q_tiles; int n_q_tiles;     // device pointers to the tile lists
   const AttnTile* kv_tiles; int n_kv_tiles;
   int T, nq, nkv, d, causal, dtype;
+  int longest;          // rows of the longest segment
   // backward only
   const void* d_o;      // [T, nq d]
   void* dqkv;           // [T, (nq + 2 nkv) d]
@@ -137,6 +138,22 @@ inline int attn_dkv_subsets(int nq, int nkv, int n_kv_tiles, int n_cu) {
 inline size_t attn_dkv_part_bytes(int T, int nq, int nkv, int d, int dtype) {
   if (nq == nkv) return 0;
   return (size_t)2 * (dtype == F32 ? nq / nkv : attn_dkv_subsets(nq, nkv, 1, 1 << 30)) * T * nkv * d * 4;
+}
+// Which of a microbatch's kernels deal the other side's rows to the wavefronts of a small tile (else: tiles that walk it).  A pure function
+// of the sizes (T, nq, d, causal, dtype, n_q_tiles, longest) and the CU count.
+struct AttnPlan { bool fwd, dkv, dq; };
+AttnPlan attn_plan(const AttnArgs& a, int n_cu);
+AttnPlan attn_f32_plan(const AttnArgs& a, int n_cu);
+AttnPlan attn_mfma_plan(const AttnArgs& a, int n_cu);
+// The line between the two.  What dealing saves is the serial walk over the longest segment; what it costs is read and exchanged per row of every head
+// (weight: how much more a row does than under a causal mask at the smallest head dimension): up to base + slope per 32 rows of the longest segment,
+// in rows of a head per CU.  Segments of at most `always` rows are one block for the tiled kernels too, and the dealt ones launch fewer
+// workgroups for them.  A sub-tile that does not exist, beside a longer segment, costs a workgroup: three times the line of them at most.
+struct AttnLine { float base, slope; int always; };
+inline bool attn_deal(const AttnArgs& a, int n_cu, const AttnLine& line, float weight, int rows) {
+  const float most = n_cu * (line.base + line.slope * a.longest / 32.0f);
+  const int launched = ((a.longest < ATTN_TILE_Q ? a.longest : ATTN_TILE_Q) + rows - 1) / rows * rows;      // rows per tile
+  return a.longest <= line.always || ((float)a.T * a.nq * weight <= most && (float)a.n_q_tiles * launched * a.nq <= 3.0f * most);
 }
 hipError_t launch_attn_fwd(const AttnArgs& a, hipStream_t s);
 hipError_t launch_attn_bwd(const AttnArgs& a, hipStream_t s);

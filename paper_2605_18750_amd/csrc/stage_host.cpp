@@ -246,6 +246,7 @@ enum MbState { MB_FREE = 0, MB_F = 1, MB_B = 2, MB_W = 3, MB_POISONED = 4 };
 struct MbSlot {
   int state = MB_FREE;
   int T = 0, n_seg = 0, n_q_tiles = 0, n_kv_tiles = 0;
+  int longest = 0;               // rows of the longest segment
   hipEvent_t ev_F = nullptr, ev_B = nullptr, ev_W = nullptr, ev_copy = nullptr;
   bool copy_pending = false;
   AttnTile* staging = nullptr;   // pinned host, 2 * max_tiles entries
@@ -288,6 +289,12 @@ void set_error(stage_t* st, const char* fmt, ...) {
       return STAGE_EHIP;                                                               \
     }                                                                                  \
   } while (0)
+
+int longest_segment(const int32_t* cu, int n_seg) {
+  int longest = 0;
+  for (int s = 0; s < n_seg; ++s) longest = std::max(longest, cu[s + 1] - cu[s]);
+  return longest;
+}
 
 int refuse_poisoned(stage_t* st, int mb, const char* task);
 
@@ -493,6 +500,7 @@ int stage_F(stage_t* st, int mb, const void* x_dev, const int32_t* cu, int n_seg
   AttnTile* qt = m.staging;
   m.n_q_tiles = build_tiles(cu, n_seg, ATTN_TILE_Q, c.causal != 0, false, qt);
   m.n_kv_tiles = build_tiles(cu, n_seg, ATTN_TILE_KV, c.causal != 0, true, qt + m.n_q_tiles);
+  m.longest = longest_segment(cu, n_seg);
 
   char* base = mb_base(st, mb);
   if (st->reduce_recorded) HIP_TRY(st, hipStreamWaitEvent(s, st->ev_reduce, 0));
@@ -554,7 +562,7 @@ int stage_F(stage_t* st, int mb, const void* x_dev, const int32_t* cu, int n_seg
     a.o16 = half_path ? base + L.o16 : nullptr;
     a.q_tiles = (const AttnTile*)(base + P.t_tiles); a.n_q_tiles = m.n_q_tiles;
     a.kv_tiles = (const AttnTile*)(base + P.t_tiles) + m.n_q_tiles; a.n_kv_tiles = m.n_kv_tiles;
-    a.T = T; a.nq = c.n_q_heads; a.nkv = c.n_kv_heads; a.d = c.head_dim; a.causal = c.causal; a.dtype = dt;
+    a.T = T; a.longest = m.longest; a.nq = c.n_q_heads; a.nkv = c.n_kv_heads; a.d = c.head_dim; a.causal = c.causal; a.dtype = dt;
     HIP_TRY(st, launch_attn_fwd(a, s));
     g.A = base + L.o; g.lda = nqd; g.B = param_ptr(st, l, STAGE_P_WO); g.ldb = H;
     if (half_path) { g.in_dtype = F16; g.A = base + L.o16; g.B = st->arena + P.w16o_off[l]; }
@@ -692,7 +700,7 @@ int stage_B(stage_t* st, int mb, const void* dy_dev, void* dx_dev, void* stream)
     a.o32 = dt == BF16 ? (float*)(base + L.o32) : nullptr;
     a.q_tiles = (const AttnTile*)(base + P.t_tiles); a.n_q_tiles = m.n_q_tiles;
     a.kv_tiles = (const AttnTile*)(base + P.t_tiles) + m.n_q_tiles; a.n_kv_tiles = m.n_kv_tiles;
-    a.T = T; a.nq = c.n_q_heads; a.nkv = c.n_kv_heads; a.d = c.head_dim; a.causal = c.causal; a.dtype = dt;
+    a.T = T; a.longest = m.longest; a.nq = c.n_q_heads; a.nkv = c.n_kv_heads; a.d = c.head_dim; a.causal = c.causal; a.dtype = dt;
     a.d_o = base + P.t_do; a.dqkv = base + L.dqkv; a.delta = (float*)(base + P.t_delta);
     a.grad_scale = gscale;
     a.ds = P.t_ds ? base + P.t_ds : nullptr; a.ds_rows = P.ds_rows; a.ds_nqs = P.ds_nqs;

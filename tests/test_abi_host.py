@@ -206,6 +206,39 @@ def test_dkv_head_subsets_are_a_pure_function_of_shape():
     _expect(R.STAGE_EINVAL, R.rrfp_attn_dkv_subsets, 6, 4, 1)
 
 
+def test_attention_plan_looks_at_the_segments():
+    """Dealing the other side to the wavefronts saves the walk over the longest segment and costs rows: few rows or long segments, not many
+    rows in segments of a tile or two, whatever their product with the heads."""
+    def plan(lengths, nq, d, causal, dtype, **kw):
+        cu = [0]
+        for n in lengths:
+            cu.append(cu[-1] + n)
+        return tuple(R.rrfp_attn_plan(cu, nq, nq, d, causal, dtype, **kw).values())
+    F32, BF = R.STAGE_DTYPE_FP32, R.STAGE_DTYPE_BF16
+    # few rows: dealt (bf16 dK/dV only for heads of 64); the caps on rows of a head per CU: 128 and 64
+    assert plan([128], 4, 64, 1, F32) == plan([777], 8, 64, 1, BF) == (True, True, True)
+    assert plan([512], 32, 128, 1, BF) == (True, False, True) and plan([513], 32, 128, 1, BF) == (False, False, False)
+    assert plan([2047], 16, 64, 1, F32) == (True, True, True) and plan([2048], 16, 64, 1, F32) == (False, False, False)
+    # the same rows in shorter segments, down to those of a block
+    assert [plan([n] * (1024 // n), 16, 64, 1, F32) for n in (512, 256, 128, 16)] == [(True, True, True), (True, False, False), (True, False, False), (True, True, True)]
+    assert [plan([n] * (1536 // n), 8, 64, 1, BF) for n in (768, 512, 128, 32)] == [(True, True, True), (True, True, True), (False, False, True), (True, False, True)]
+    # bidirectional rows and wide heads weigh more
+    assert plan([512] * 6, 4, 128, 1, F32) == (True, True, True) and plan([512] * 6, 4, 128, 0, F32) == (False, False, False)
+    assert plan([256] * 6, 8, 80, 0, BF) == (False, False, False) and plan([256] * 6, 8, 64, 0, BF) == (False, False, True)
+    # one long segment among many of a token: sub-tiles that do not exist would be most of the grid
+    assert plan([1000] + [1] * 2000, 4, 64, 1, F32) == (False, False, False) and plan([1000] + [500] * 4, 4, 64, 1, F32) == (True, True, True)
+    assert plan([1024], 16, 64, 1, F32, n_cu=64) == (False, False, False)
+    # dQ reads what its own dK/dV kernel writes of dS: never a dealt dK/dV with a tiled dQ
+    rng = random.Random(3)
+    for _ in range(3000):
+        top = rng.choice((8, 40, 200, 1000, 4000))
+        p = plan([rng.randint(1, top) for _ in range(rng.randint(1, 60))], rng.choice((1, 2, 4, 8, 32)), 64, rng.randint(0, 1), BF)
+        assert p[2] or not p[1]
+    for bad in (([0, 0], 2, 2, 64, 1, BF), ([1, 2], 2, 2, 64, 1, BF), ([0, 4], 3, 2, 64, 1, BF), ([0, 4], 2, 2, 96, 1, BF), ([0, 4], 2, 2, 24, 1, F32),
+                ([0, 4], 2, 2, 64, 2, F32), ([0, 4], 2, 2, 64, 1, 5), ([0], 2, 2, 64, 1, F32)):
+        _expect(R.STAGE_EINVAL, R.rrfp_attn_plan, *bad)
+
+
 def _task_products(H, nq, nkv, d, F, layers, swiglu=True):
     """(M, N) of the weight gradients of a W task, in the order the stage lists them."""
     return [(H, (nq + 2 * nkv) * d), (nq * d, H), (H, (2 if swiglu else 1) * F), (F, H)] * layers

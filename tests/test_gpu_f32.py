@@ -63,11 +63,11 @@ def test_f32_attention_tile_edges(d, causal, nq, nkv):
 @pytest.mark.parametrize("d,causal,nkv", [(16, True, 64), (32, False, 8), (48, True, 16), (64, True, 4), (80, False, 16), (96, True, 32),
                                           (112, False, 16), (128, True, 4)])
 def test_f32_attention_choice_of_kernels(d, causal, nkv):
-    """64 query heads: at 512 tokens (2 x 64 rows a CU on 256 CUs) the 64-row kernels run, at 511 the ones that deal the other side to the
-    wavefronts.  Segments around 16 and 128 rows (one and all blocks of eight wavefronts)."""
+    """64 query heads: from 512 tokens on (2 x 64 rows a CU on 256 CUs) the 64-row kernels run, at 87 the ones that deal the other side to the
+    wavefronts, at 511 the one or the other.  Segments around 16 and 128 rows (one and all blocks of eight wavefronts)."""
     shape = SI.StageShape(f"f32choice{d}", 1, 32, 64, nkv, d, 32, 2, dtype="fp32", x_std=1.0, dy_std=1.0, w_std=0.15, causal=causal)
-    lengths = [[1, 17, 127, 129, 15, 223], [16, 144, 128, 223]]
-    assert [sum(n) for n in lengths] == [512, 511]
+    lengths = [[1, 17, 127, 129, 15, 223], [16, 144, 128, 223], [17, 15, 55]]
+    assert [sum(n) for n in lengths] == [512, 511, 87]
     w = Hp.Workload(shape, [[0] + [int(v) for v in np.cumsum(n)] for n in lengths])
     print(f"[f32 attention] d{d} causal{causal} heads 64/{nkv}", flush=True)
     got = Hp.run_gpu(w, keep_raw=True)
@@ -84,3 +84,15 @@ def test_f32_attention_many_segments():
     print(f"[f32 attention] {len(w.cus[0]) - 1} segments, {w.cus[0][-1]} tokens", flush=True)
     worst = Hp.compare(Hp.run_gpu(w), Hp.run_oracle(w), Hp.TOL["fp32"], "many segments")
     print(f"[f32 attention] many segments: worst {worst:.2e}", flush=True)
+
+
+def test_f32_attention_many_segments_of_one_head():
+    """16 400 segments of a token and one of 64: the kernels that deal the other side to the wavefronts, four sub-tiles a segment, 65 604 of them
+    in the forward and dQ kernels."""
+    import paper_2605_18750_amd as R
+    shape = SI.StageShape("f32manysegments1", 1, 32, 1, 1, 16, 32, 1, dtype="fp32", x_std=1.0, dy_std=1.0, w_std=0.15)
+    w = Hp.Workload(shape, [[0] + [int(v) for v in np.cumsum([1] * 9000 + [64] + [1] * 7400)]])
+    assert R.rrfp_attn_plan(w.cus[0], 1, 1, 16, 1, R.STAGE_DTYPE_FP32) == dict(forward=True, dkv=False, dq=True)
+    print(f"[f32 attention] {len(w.cus[0]) - 1} segments of one head", flush=True)
+    worst = Hp.compare(Hp.run_gpu(w), Hp.run_oracle(w), Hp.TOL["fp32"], "many segments, one head")
+    print(f"[f32 attention] many segments of one head: worst {worst:.2e}", flush=True)
