@@ -149,6 +149,9 @@ AttnPlan attn_mfma_plan(const AttnArgs& a, int n_cu);
 // (weight: how much more a row does than under a causal mask at the smallest head dimension): up to base + slope per 32 rows of the longest segment,
 // in rows of a head per CU.  Segments of at most `always` rows are one block for the tiled kernels too, and the dealt ones launch fewer
 // workgroups for them.  A sub-tile that does not exist, beside a longer segment, costs a workgroup: three times the line of them at most.
+// Forward + dK/dV + dQ in us, tiled -> dealt by rows alone, every sub-tile of a tile launched -> this: fp32, 1 head of 64, 31784 rows in segments of 64
+// 91 -> 219 -> 73; 2 heads of 128, 8028 rows of 1 2502 -> 9381 -> 833; 16 of 64, 1986 of 256, bidirectional 119 -> 185 -> 120; bf16, 4 of 80,
+// 3973 of 32 41 -> 117 -> 37; 32 of 128, 496 of 32 44 -> 39 -> 34.
 struct AttnLine { float base, slope; int always; };
 inline bool attn_deal(const AttnArgs& a, int n_cu, const AttnLine& line, float weight, int rows) {
   const float most = n_cu * (line.base + line.slope * a.longest / 32.0f);
