@@ -898,9 +898,13 @@ __global__ __launch_bounds__(256) void headnorm_bwd_kernel(T* __restrict__ dy, i
 // ---------------------------------------------------------------- rotary embedding
 // The angle is formed in double precision and reduced to [0, 2 pi) before the single-precision sine and cosine, so that the
 // fp32 path keeps its 1e-4 budget at positions in the thousands.  A thread turns one vector of pairs of one row in up to ROPE_HEADS
-// heads: the angles, which bound the kernel when every head formed its own (2048 tokens x 40 heads of 128: 27 -> 10 us), are formed once for
-// all of them.  Workgroup: 256 / (half / V) rows of a query tile.
-constexpr int ROPE_HEADS = 8;
+// heads, which share its angles.  Workgroup: 256 / (half / V) rows of a query tile, blocks_per_tile of them launched for each: as many as the longest
+// segment has.  What bounds it: memory at some thousand rows, before that the serial work of a thread, 0.4 us a head (with all loads in flight the same;
+// the angles, formed in double, cost nothing beside it), so two heads and not eight.  us, a lane per pair and a workgroup per head and tile -> eight heads a
+// thread -> this: bf16, 40 heads of 128, 2048 rows 25 -> 9.0 -> 8.1, 512 rows 23 -> 7.2 -> 4.4, 300 in three segments 11.3 -> 6.8 -> 4.1; 40 of 64, 61 rows in
+// segments of 4 3.0 -> 7.2 -> 4.1; 8 of 128, 3973 segments of a row 16 -> 58 -> 17 (four heads: 15.7); 72 of 128, 4096 rows 54 -> 31 -> 26.6; fp32,
+// 8 of 128, 983 rows in segments of 16 4.4 -> 10.1 -> 4.0; 2 of 64, 8000 in segments of 2 6.6 -> 22.5 -> 5.2.
+constexpr int ROPE_HEADS = 2;
 template <typename T>
 __global__ __launch_bounds__(256) void rope_kernel(T* __restrict__ x, const AttnTile* __restrict__ tiles, int blocks_per_tile, int n_heads, int d,
                                                    int ld, double log2_base, float sign) {
@@ -908,8 +912,9 @@ __global__ __launch_bounds__(256) void rope_kernel(T* __restrict__ x, const Attn
   __shared__ double theta[64];
   const AttnTile tl = tiles[blockIdx.x / blocks_per_tile];
   const int half = d >> 1, chunks = half / V, rows = 256 / chunks;
-  const int row = tl.r0 + (int)(blockIdx.x % blocks_per_tile) * rows + (int)threadIdx.x / chunks;
+  const int row0 = tl.r0 + (int)(blockIdx.x % blocks_per_tile) * rows, row = row0 + (int)threadIdx.x / chunks;
   const int c = threadIdx.x % chunks * V;
+  if (row0 >= tl.r1) return;
   if ((int)threadIdx.x < half) theta[threadIdx.x] = exp2(-2.0 * (double)threadIdx.x / (double)d * log2_base);
   __syncthreads();
   if (row >= tl.r1 || (int)threadIdx.x >= rows * chunks) return;
@@ -921,10 +926,11 @@ __global__ __launch_bounds__(256) void rope_kernel(T* __restrict__ x, const Attn
     __sincosf((float)ang, &sn[i], &cs[i]);
     sn[i] *= sign;
   }
-  const int h0 = blockIdx.y * ROPE_HEADS, h1 = min(n_heads, h0 + ROPE_HEADS);
   T* p = x + (size_t)row * ld + c;
-#pragma unroll 4
-  for (int h = h0; h < h1; ++h) {
+#pragma unroll
+  for (int u = 0; u < ROPE_HEADS; ++u) {
+    const int h = blockIdx.y * ROPE_HEADS + u;
+    if (h >= n_heads) break;
     float a[V], b[V], ra[V], rb[V];
     load_vec<T>(p + h * d, a);
     load_vec<T>(p + h * d + half, b);
@@ -1003,10 +1009,10 @@ hipError_t launch_widen(const void* src, float* dst, size_t n, int dtype, hipStr
   return hipGetLastError();
 }
 
-hipError_t launch_rope(void* x, const AttnTile* q_tiles, int n_q_tiles, int n_heads, int d, int ld, float base,
+hipError_t launch_rope(void* x, const AttnTile* q_tiles, int n_q_tiles, int longest, int n_heads, int d, int ld, float base,
                        float sign, int dtype, hipStream_t s) {
   if (n_q_tiles < 1 || n_heads < 1 || d % 16 || d < 16 || d > 128 || !(base > 1.0f)) return hipErrorInvalidValue;
-  const int rows = 256 / (d / 2 / (dtype == F32 ? 4 : 8)), per_tile = (ATTN_TILE_Q + rows - 1) / rows;
+  const int rows = 256 / (d / 2 / (dtype == F32 ? 4 : 8)), per_tile = (std::min(longest, ATTN_TILE_Q) + rows - 1) / rows;
   const dim3 grid(n_q_tiles * per_tile, (n_heads + ROPE_HEADS - 1) / ROPE_HEADS);
   if (dtype == F16) {
     hipLaunchKernelGGL(rope_kernel<f16_t>, grid, dim3(256), 0, s, (f16_t*)x, q_tiles, per_tile, n_heads, d, ld, log2((double)base), sign);

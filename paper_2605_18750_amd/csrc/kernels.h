@@ -176,8 +176,8 @@ hipError_t launch_widen(const void* src, float* dst, size_t n, int dtype, hipStr
                         float* partial = nullptr, const void* host = nullptr, void* device = nullptr, size_t bytes = 0);
 // Rotary embedding, in place, on the first n_heads heads (head_dim d, even) of every row of a [T, ld]
 // tensor: pair (x_i, x_{i+d/2}) turns by sign * pos * base^(-2i/d), pos = row - segment start, rows and
-// segment starts taken from the query tile list (the tiles partition the rows).
-hipError_t launch_rope(void* x, const AttnTile* q_tiles, int n_q_tiles, int n_heads, int d, int ld, float base,
+// segment starts taken from the query tile list (the tiles partition the rows; longest: rows of the longest segment).
+hipError_t launch_rope(void* x, const AttnTile* q_tiles, int n_q_tiles, int longest, int n_heads, int d, int ld, float base,
                        float sign, int dtype, hipStream_t s);
 
 // h = x * r * g, r = rsqrt(mean(x^2) + eps); x fp32, r_out [T] fp32, g and h storage type.

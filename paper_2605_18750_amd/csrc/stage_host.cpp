@@ -554,7 +554,7 @@ int stage_F(stage_t* st, int mb, const void* x_dev, const int32_t* cu, int n_seg
                                       param_ptr(st, l, STAGE_P_GQ), param_ptr(st, l, STAGE_P_GK), base + L.qk_hat,
                                       (float*)(base + L.qk_r), T, c.norm_eps, qdt, s));
     if (c.rope)   // rotate q and k in place: the stash then holds what the attention (and its backward) reads
-      HIP_TRY(st, launch_rope(base + L.qkv, (const AttnTile*)(base + P.t_tiles), m.n_q_tiles, c.n_q_heads + c.n_kv_heads,
+      HIP_TRY(st, launch_rope(base + L.qkv, (const AttnTile*)(base + P.t_tiles), m.n_q_tiles, m.longest, c.n_q_heads + c.n_kv_heads,
                               c.head_dim, P.n_qkv, c.rope_base, 1.0f, qdt, s));
     AttnArgs a{};
     a.qkv = base + L.qkv; a.o = base + L.o; a.lse = (float*)(base + L.lse);
@@ -707,7 +707,7 @@ int stage_B(stage_t* st, int mb, const void* dy_dev, void* dx_dev, void* stream)
     a.dkv_part = P.t_dkvp ? (float*)(base + P.t_dkvp) : nullptr;
     HIP_TRY(st, launch_attn_bwd(a, s));
     if (c.rope)   // gradients w.r.t. the rotated q, k -> w.r.t. the projection outputs (inverse rotation)
-      HIP_TRY(st, launch_rope(base + L.dqkv, (const AttnTile*)(base + P.t_tiles), m.n_q_tiles, c.n_q_heads + c.n_kv_heads,
+      HIP_TRY(st, launch_rope(base + L.dqkv, (const AttnTile*)(base + P.t_tiles), m.n_q_tiles, m.longest, c.n_q_heads + c.n_kv_heads,
                               c.head_dim, P.n_qkv, c.rope_base, -1.0f, dt, s));
     if (c.qk_norm) {   // gradients w.r.t. the normalised heads -> w.r.t. the projection outputs, gain gradients to the slot
       HIP_TRY(st, launch_headnorm_bwd(base + L.dqkv, P.n_qkv, c.n_q_heads, c.n_q_heads + c.n_kv_heads, c.head_dim,
