@@ -47,6 +47,12 @@ class StageShape:
     x_std: float = 1.0
     dy_std: float = 1.0
 
+    def __post_init__(self):
+        # a value that only resembles a variant would be taken for the other one
+        for field, allowed in (("dtype", ("fp32", "bf16")), ("mlp_kind", ("swiglu", "gelu")), ("norm_kind", ("rms", "layer"))):
+            if getattr(self, field) not in allowed:
+                raise ValueError(f"{field} must be one of {allowed}, not {getattr(self, field)!r}")
+
     def replace(self, **kw) -> "StageShape":
         d = asdict(self)
         d.update(kw)

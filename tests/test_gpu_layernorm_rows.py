@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 def test_layernorm_and_bias_gradients(hidden, ffn, dtype, tokens):
     """The storage type's tolerance; a row, chunk or column block missed moves a gradient by 1 / sqrt(129) of itself or more."""
     shape = SI.StageShape(f"lnrows{hidden}", 1, hidden, 1, 1, 64, ffn, 2, dtype=dtype, mlp_kind="gelu", causal=False, x_std=1.0, dy_std=1.0,
-                          w_std=0.02, norm_kind=1, bias=True)
+                          w_std=0.02, norm_kind="layer", bias=True)
     w = Hp.Workload(shape, [[0, (tokens + 1) // 2, tokens]] if tokens > 1 else [[0, 1]])
     print(f"[layernorm rows] {hidden} {ffn} {dtype} {tokens}", flush=True)
     worst = Hp.compare(Hp.run_gpu(w), Hp.run_oracle(w), Hp.TOL[dtype], shape.name)

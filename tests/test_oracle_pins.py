@@ -548,3 +548,12 @@ def test_generator_is_counter_based_and_normal():
     order = SI.ready_order(8, 5)
     pos = {kj: i for i, kj in enumerate(order)}
     assert len(order) == 24 and all(pos[("F", j)] < pos[("B", j)] < pos[("W", j)] for j in range(8))
+
+
+@pytest.mark.parametrize("field,value", [("norm_kind", 1), ("norm_kind", "layernorm"), ("mlp_kind", 0), ("dtype", "f32")])
+def test_stage_shape_refuses_a_variant_it_does_not_know(field, value):
+    """Anything but the named variants would run as the other one, on the GPU and in the oracle alike."""
+    with pytest.raises(ValueError, match=field):
+        SI.StageShape("x", 1, 64, 1, 1, 64, 64, 1, **{field: value})
+    with pytest.raises(ValueError, match=field):
+        SI.TINY.replace(**{field: value})
