@@ -57,7 +57,7 @@ struct Plan {
   size_t param_elems;
   std::vector<LayerStash> layer;
   size_t t_dh, t_do, t_delta, t_tiles;   // per-microbatch temporaries; t_tiles: query tiles, then key tiles
-  // GEMM scratch of a microbatch (split-K planes of F, B and W, partial gain rows of B): t_dm, B's fp32 temporary of an unfused
+  // GEMM scratch of a microbatch (split-K planes of F, B and W): t_dm, B's fp32 temporary of an unfused
   // activation backward, directly behind it t_ds, both idle outside the one kernel or the two attention kernels of B that use
   // them, and as much more as scratch_need asks for.
   size_t t_dm, ws_bytes;
@@ -124,11 +124,11 @@ int check_config(const stage_config* c) {
 }
 
 // Scratch with which every cut of every microbatch of up to max_tokens tokens is the one its own shape asks for: the planes
-// of the products of F, B and W (and as much as the partial rows of the RMSNorm backward take).  Without it the cut, and so the summation
+// of the products of F, B and W.  Without it the cut, and so the summation
 // order, of a microbatch would hang on max_tokens and max_segments.  The chip whole and in its equal partitions.
 size_t scratch_need(const stage_config* c, const Plan* p) {
   const int T = c->max_tokens, H = c->hidden, F = c->ffn, nqd = c->n_q_heads * c->head_dim;
-  size_t need = c->norm_kind == 0 ? norm_bwd_few_rows_bytes(T, H, c->dtype) : 0;
+  size_t need = 0;
   if (c->dtype != STAGE_DTYPE_BF16) return need;
   std::pair<int, int> forms[8] = {{p->n_qkv, H}, {H, nqd}, {p->n_up, H}, {H, F}, {F, H}, {H, p->n_up}, {nqd, H}, {H, p->n_qkv}};   // N, K
   std::sort(forms, forms + 8);

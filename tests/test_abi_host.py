@@ -291,10 +291,8 @@ def test_stage_scratch_never_limits_a_cut(H, nq, nkv, d, F, layers, swiglu, max_
             for first in range(0, layers, 8):
                 products = _task_products(H, nq, nkv, d, F, min(8, layers - first), swiglu)
                 assert R.rrfp_wgrad_group_plan(products, T, workspace_bytes=ws, n_cu=n_cu) == R.rrfp_wgrad_group_plan(products, T, n_cu=n_cu), T
-            for dtype in (BF, F32):
-                rows = R.rrfp_rmsnorm_bwd_rows(T, H, dtype, n_cu)
-                need = 0 if rows == 8 else -(-T // rows) * H * 4
-                assert need <= (ws if dtype == BF else R.stage_scratch_bytes(cfg(dtype=0)))
+    # fp32 products are never cut: the scratch is B's temporary alone (the partial rows of the vector gradients have arrays of their own)
+    assert R.stage_scratch_bytes(cfg(dtype=0)) == -(-max_tokens * F * 4 // 256) * 256
 
 
 def test_rmsnorm_backward_rows():
