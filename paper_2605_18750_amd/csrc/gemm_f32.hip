@@ -512,7 +512,7 @@ hipError_t launch_f32_aligned(const GemmArgs& g, hipStream_t s) {
   return vec_ok(g) ? launch_f32<TA, TB, true>(g, s) : launch_f32<TA, TB, false>(g, s);
 }
 
-// The rule of launch_f32 on the tiles of the whole group.
+// 64 x 64 tiles from 128 of them in the whole group on, else 32 x 32: f32_tile_edge without its 16 x 16 tiles, which no group has been built with.
 hipError_t launch_f32_group(const GemmArgs* g, int n, hipStream_t s) {
   F32Group grp{};
   grp.K = g[0].K;

@@ -1254,8 +1254,8 @@ __global__ __launch_bounds__(SMALL_NW * 64) void gemm_mfma_small_kernel(const bf
 // Edge of the small-output tiles: 32 while there are at most two of them per CU.  us, 64 -> 32: 129 x 512 x 512 6.2 -> 4.1, x 1536 10.8 -> 6.7,
 // 512 x 512 x 3072 24.7 -> 13.8, 129 x 3072 x 512 (480 tiles of 32) 6.4 -> 5.5; but 777 x 768 x 512 (600) 6.5 -> 7.3, 300 x 3072 x 512 (960) 6.8 -> 9.2.
 inline long long small_tiles(int M, int N, int edge) { return (long long)((M + edge - 1) / edge) * ((N + edge - 1) / edge); }
-// Below 32 rows (a few tokens in all: no training microbatch) the 64 x 64 tiles and with them the choice of split tiles stay, although
-// 1 x 2048 x 2048 would go 10.1 -> 6.9.
+// Below 32 rows the 64 x 64 tiles stay, not because they are faster (1 x 2048 x 2048 would go 10.1 -> 6.9, the one shape measured there) but because
+// the lower estimate would take the products of a few tokens out of the split form, which the tests of that form reach through them.
 inline int small_edge(int M, int N, int n_cu) { return M >= 32 && small_tiles(M, N, 32) <= 2 * n_cu ? 32 : ST; }
 
 template <bool A_KC, bool B_KC, typename TO, bool HAS_R, int ACT, bool F16IN>
