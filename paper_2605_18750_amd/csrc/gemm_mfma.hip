@@ -1432,9 +1432,9 @@ struct WgradLoader {
 // What bounds it: at K of a few hundred the fp32 output (a CU alone stores a tile in 3.4 us, 256 at once in 11: 6 TB/s) and the operand
 // reads behind the L2s, at K of thousands the matrix pipes at the power limit.  A workgroup per tile, its sums through LDS -> this, inside
 // the stage: 4 layers of hidden 4096 at 256 to 512 tokens 1137 -> 979 us a launch, at 4096 tokens 5368 -> 5191; 8 layers of hidden 1280 at
-// 6272 tokens 1540 -> 1519; 2 layers of hidden 2048 at 3704 tokens 652 -> 616.  Waiting for all but 16 of the loads and stores at every step gave half
-// of that.  Few tokens (us, a workgroup per tile -> two groups an item -> this): hidden 2048 at 32 tokens 36.1 -> 40.6 -> 34.1, 1536 at 64
-// 25.7 -> 29.0 -> 24.5, 4096 at 128 184 -> 165 -> 153; one round of tiles at one step, hidden 1024 at 32, 14.9 -> 15.5 -> 15.7 (the zeros).
+// 6272 tokens 1540 -> 1519; 2 layers of hidden 2048 at 3704 tokens 652 -> 616; on another box, with group_starts, 955, 5154, 1478 and 611.
+// Waiting for all but 16 of the loads and stores at every step gave half of that.  Few tokens (us, a workgroup per tile -> two groups an
+// item -> this): hidden 2048 at 32 tokens 36.1 -> 40.6 -> 34.1, 1536 at 64 25.7 -> 29.0 -> 24.5, 4096 at 128 184 -> 165 -> 153; one round of tiles at one step, hidden 1024 at 32, 14.9 -> 15.5 -> 15.7 (the zeros).
 __global__ __launch_bounds__(256) void gemm_mfma_wgrad_group_kernel(const WgradGroup g, int items) {
   __shared__ __attribute__((aligned(1024))) char stage0[DSTAGE];
   __shared__ __attribute__((aligned(1024))) char stage1[DSTAGE];
